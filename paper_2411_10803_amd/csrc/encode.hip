@@ -2,9 +2,9 @@
 // Merging (Eq. 5), followed by stable compaction of the survivors.
 //
 // Launch plan (all on the caller's stream, no host synchronisation):
-//   encode_scores_kernel one launch, two kinds of waves:
+//   encode_scores_kernel one launch, two kinds of waves (two launches for many tokens, see ScoreBlocks):
 //       window waves     one wave per window: Gram matrix in registers -> S    (HBM: reads x once)
-//       key-row waves    one wave per four key rows: q_cls . k_j per head      (HBM: reads k_cls once)
+//       key-row waves    one wave per eight key rows: q_cls . k_j per head     (HBM: reads k_cls once)
 //   encode_decide_kernel one block per sample: softmax + head mean, radix top-k -> O, merge
 //                        decisions, prefix sum of survivors, small outputs    (tiny)
 //   encode_emit_kernel  one wave per window: row copies / mass-weighted means (re-reads x, writes out_x)
@@ -29,33 +29,29 @@ struct EncodeDims {
     int kt, kh, kw;
     int M, W, ws, nwx, nwy, nwt;
     int clipped;      // the window does not divide the grid: windows at the far border hold fewer tokens
-    int moff[16];     // member_offset(m), m < ws: filled by the host so that kernels get them as scalars
+    // members m < ws, filled by the host so that kernels get them as scalars: token = window_base + moff[m], and the
+    // place inside the window, mpos[m] = dt << 16 | dy << 8 | dx
+    int moff[16], mpos[16];
+    FastDiv by_W, by_nwx, by_nwy, by_kw, by_kh;
 };
 
-// Token of member m of window w; -1 for a member that a clipped border window does not have.
-__device__ __forceinline__ int member_token(const EncodeDims& p, int w, int m) {
-    const int wx = w % p.nwx, wy = (w / p.nwx) % p.nwy, wt = w / (p.nwx * p.nwy);
-    const int dx = m % p.kw, dy = (m / p.kw) % p.kh, dt = m / (p.kw * p.kh);
-    const int t = wt * p.kt + dt, y = wy * p.kh + dy, x = wx * p.kw + dx;
-    if (p.clipped && (t >= p.T || y >= p.Hg || x >= p.Wg)) return -1;
-    return (t * p.Hg + y) * p.Wg + x;
+// A window on the grid: its first token and how far it reaches (clipped windows hold fewer tokens).
+struct WindowAt { int base, rt, ry, rx; };
+__device__ __forceinline__ WindowAt window_at(const EncodeDims& p, int w) {
+    const int row = p.by_nwx.div(w), wx = w - row * p.nwx, wt = p.by_nwy.div(row), wy = row - wt * p.nwy;
+    const int t = wt * p.kt, y = wy * p.kh, x = wx * p.kw;
+    return WindowAt{(t * p.Hg + y) * p.Wg + x, p.T - t, p.Hg - y, p.Wg - x};
 }
-__device__ __forceinline__ bool member_in_grid(const EncodeDims& p, int w, int m) {
-    return !p.clipped || member_token(p, w, m) >= 0;
+__device__ __forceinline__ bool member_exists(const EncodeDims& p, const WindowAt& a, int m) {
+    return !p.clipped || ((p.mpos[m] >> 16) < a.rt && ((p.mpos[m] >> 8) & 0xFF) < a.ry && (p.mpos[m] & 0xFF) < a.rx);
 }
-// member_token(p, w, m) = window_base(p, w) + member_offset(p, m)
-__device__ __forceinline__ int window_base(const EncodeDims& p, int w) {
-    const int wx = w % p.nwx, wy = (w / p.nwx) % p.nwy, wt = w / (p.nwx * p.nwy);
-    return (wt * p.kt * p.Hg + wy * p.kh) * p.Wg + wx * p.kw;
-}
-__host__ __device__ __forceinline__ int member_offset(const EncodeDims& p, int m) {
-    const int dx = m % p.kw, dy = (m / p.kw) % p.kh, dt = m / (p.kw * p.kh);
-    return (dt * p.Hg + dy) * p.Wg + dx;
-}
-// A wave that works on one window: lane m < ws computes member m's token (one division sequence
-// for all members instead of one per member); read back with wave_member().
+// A wave that works on one window: lane m < ws computes member m's token (-1 where a clipped window does not have
+// it); read back with wave_member().
 __device__ __forceinline__ int lane_member_token(const EncodeDims& p, int w, int lane) {
-    return lane < p.ws ? member_token(p, w, lane) : 0;
+    const WindowAt a = window_at(p, w);
+    const int row = p.by_kw.div(lane), dx = lane - row * p.kw, dt = p.by_kh.div(row), dy = row - dt * p.kh;
+    if (lane >= p.ws) return 0;
+    return dt < a.rt && dy < a.ry && dx < a.rx ? a.base + (dt * p.Hg + dy) * p.Wg + dx : -1;
 }
 __device__ __forceinline__ int wave_member(int per_lane, int m) { return __builtin_amdgcn_readlane(per_lane, m); }
 
@@ -142,15 +138,13 @@ __host__ __device__ __forceinline__ int cls_groups(int M) { return (M + 1 + kCls
 
 template <bool BF>
 __device__ __forceinline__ void cls_logits_rows(
-    long item, const void* __restrict__ q_cls, const void* __restrict__ k_cls, const uint8_t* __restrict__ valid,
-    const EncodeDims& p, float* __restrict__ logits, float2* __restrict__ part)
+    int b, int g, const void* __restrict__ q_cls, const void* __restrict__ k_cls, const uint8_t* __restrict__ valid,
+    const EncodeDims& p, float* __restrict__ logits, float2* __restrict__ part, float2* s_stat)
 {
     constexpr int VEC = Vec<BF>::N;
     constexpr int R = kClsRows;
     const int lane = lane_id();
-    const int gps = cls_groups(p.M);
-    if (item >= (long)p.B * gps) return;
-    const int b = (int)(item / gps), g = (int)(item % gps), j0 = g * R;
+    const int gps = cls_groups(p.M), j0 = g * R;
     // wave-uniform.  Loads are never guarded one by one (a guarded load waits for the one before it):
     // addresses are clamped into the sample instead and what was read for an inactive row is ignored.
     bool act[R];
@@ -193,49 +187,58 @@ __device__ __forceinline__ void cls_logits_rows(
     float acc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = 0.f;
+    // slices of the rows per round: fp32 rows are twice as long, and a lone image waits half as often with two in
+    // flight (scores of 1 x 576 tokens 10.6 -> 9.8 us); bf16 with two is slower (8 x 2880 tokens 18.1 -> 20.0 us)
+    constexpr int UNR = BF ? 1 : 2;
     const int iters = (nvec + kWave - 1) / kWave;
-    for (int it = 0; it < iters; ++it) {
-        const int idx = it * kWave + lane;
-        float part_r[R];
+    for (int it0 = 0; it0 < iters; it0 += UNR) {
+        typename Vec<BF>::Raw kv[UNR][R], qv[UNR];
 #pragma unroll
-        for (int r = 0; r < R; ++r) part_r[r] = 0.f;
-        {
-            const int ic = min(idx, nvec - 1);       // lanes beyond the row repeat its last vector and drop it
-            typename Vec<BF>::Raw kv[R];
-            const typename Vec<BF>::Raw qv = Vec<BF>::load_raw(qrow, ic * VEC);
-#pragma unroll
+        for (int u = 0; u < UNR; ++u) {
+            const int ic = min((it0 + u) * kWave + lane, nvec - 1);  // lanes beyond the row repeat its last vector and drop it
+            qv[u] = Vec<BF>::load_raw(qrow, ic * VEC);
             // the key rows are read exactly once: streaming loads, so that they do not push x (read again by
             // the emit kernel) out of the Infinity Cache
-            for (int r = 0; r < R; ++r) kv[r] = Vec<BF>::load_raw_once(krow[r], ic * VEC);
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-                if (act[r] && idx < nvec) part_r[r] = Vec<BF>::dot(qv, kv[r], part_r[r]);
+            for (int r = 0; r < R; ++r) kv[u][r] = Vec<BF>::load_raw_once(krow[r], ic * VEC);
         }
-        if (vph < kWave) {
-            float lg[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r) lg[r] = group_sum_rt(part_r[r], vph) * scale;
-            if (idx < nvec && (lane & (vph - 1)) == 0) {
-                const int h = idx / vph;
-                pout[(size_t)h * gps] = finish(lg);
+        for (int u = 0; u < UNR; ++u) {
+            const int it = it0 + u, idx = it * kWave + lane;
+            if (it >= iters) break;
+            float part_r[R];
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (act[r]) out[(size_t)r * p.Hc + h] = lg[r];
-            }
-        } else {
-            const int per_head = vph / kWave;                 // iterations per head
-#pragma unroll
-            for (int r = 0; r < R; ++r) acc[r] += part_r[r];
-            if ((it + 1) % per_head == 0) {
+            for (int r = 0; r < R; ++r) part_r[r] = act[r] && idx < nvec ? Vec<BF>::dot(qv[u], kv[u][r], 0.f) : 0.f;
+            if (vph < kWave) {
                 float lg[R];
 #pragma unroll
-                for (int r = 0; r < R; ++r) { lg[r] = wave_sum(acc[r]) * scale; acc[r] = 0.f; }
-                if (lane == 0) {
-                    const int h = it / per_head;
-                    pout[(size_t)h * gps] = finish(lg);
+                for (int r = 0; r < R; ++r) lg[r] = group_sum_rt(part_r[r], vph) * scale;
+                if (idx < nvec && (lane & (vph - 1)) == 0) {
+                    const int h = idx / vph;
+                    const float2 st = finish(lg);
+                    pout[(size_t)h * gps] = st;
+                    if (s_stat) s_stat[h] = st;
 #pragma unroll
                     for (int r = 0; r < R; ++r)
                         if (act[r]) out[(size_t)r * p.Hc + h] = lg[r];
+                }
+            } else {
+                const int per_head = vph / kWave;                 // iterations per head
+#pragma unroll
+                for (int r = 0; r < R; ++r) acc[r] += part_r[r];
+                if ((it + 1) % per_head == 0) {
+                    float lg[R];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) { lg[r] = wave_sum(acc[r]) * scale; acc[r] = 0.f; }
+                    if (lane == 0) {
+                        const int h = it / per_head;
+                        const float2 st = finish(lg);
+                        pout[(size_t)h * gps] = st;
+                        if (s_stat) s_stat[h] = st;
+#pragma unroll
+                        for (int r = 0; r < R; ++r)
+                            if (act[r]) out[(size_t)r * p.Hc + h] = lg[r];
+                    }
                 }
             }
         }
@@ -245,15 +248,18 @@ __device__ __forceinline__ void cls_logits_rows(
 // ---------------------------------------------------------------------------------------------
 // Eq. 5: S_w = mean over unordered pairs of valid members of cos(x_m, x_n).  One wave per window;
 // each lane owns a strided slice of the feature dimension and keeps the upper triangle of the
-// Gram matrix (norms on the diagonal) in registers; one butterfly per entry at the end.
+// Gram matrix (norms on the diagonal) in registers.  What follows the loads is a chain on one wave, so it is kept
+// short: all sums in one butterfly that halves its list as it goes, then a lane per pair for the cosines (against 36
+// separate wave sums and 28 divisions on one lane: 4 x 4608 tokens, 2x2x2 windows, 22.4 -> 15.6 us = 4.8 TB/s).
 template <int WSM, bool BF>
 __device__ __forceinline__ void window_sim_item(
-    long item, const void* __restrict__ x, const uint8_t* __restrict__ valid, const EncodeDims& p, float* __restrict__ sim)
+    int item, const void* __restrict__ x, const uint8_t* __restrict__ valid, const EncodeDims& p, float* __restrict__ sim,
+    float* s_gram)
 {
     constexpr int VEC = Vec<BF>::N;
     const int lane = lane_id();
-    if (item >= (long)p.B * p.W) return;
-    const int b = (int)(item / p.W), w = (int)(item % p.W);
+    if (item >= p.B * p.W) return;
+    const int b = p.by_W.div(item), w = item - b * p.W;
     const size_t esz = BF ? 2 : 4;
 
     const char* rows[WSM];
@@ -268,12 +274,14 @@ __device__ __forceinline__ void window_sim_item(
         ok[m] = m < p.ws && wave_member(ok_l, mm) != 0;
         rows[m] = static_cast<const char*>(x) + ((size_t)b * p.M + max(wave_member(tok_l, mm), 0)) * p.D * esz;
     }
-    float G[WSM * (WSM + 1) / 2];
+    constexpr int NG = WSM * (WSM + 1) / 2;
+    float G[NG];
 #pragma unroll
-    for (int i = 0; i < WSM * (WSM + 1) / 2; ++i) G[i] = 0.f;
+    for (int i = 0; i < NG; ++i) G[i] = 0.f;
 
-    // small windows take two slices of the feature dimension per round (2*WSM loads in flight)
-    constexpr int NS = WSM <= 4 ? 2 : 1;
+    // slices of the feature dimension per round: a small window has the whole 1024 elements in flight (fp32: 16
+    // loads; 16 x 576 tokens 19.7 -> 17.7 us, 8 x 2880 tokens 41 -> 37 us against two slices)
+    constexpr int NS = WSM <= 4 ? (BF ? 2 : 4) : 1;
     for (int c0 = lane * VEC; c0 < p.D; c0 += NS * kWave * VEC) {
         typename Vec<BF>::Raw v[NS][WSM];
         bool in[NS];
@@ -301,46 +309,163 @@ __device__ __forceinline__ void window_sim_item(
                 }
         }
     }
+    wave_sums(G, lane);
+    // the sums change hands through LDS: lane q takes the pairs q, q + 64, ...
+    constexpr int NP = WSM * (WSM - 1) / 2;
 #pragma unroll
-    for (int i = 0; i < WSM * (WSM + 1) / 2; ++i) G[i] = wave_sum(G[i]);
-
-    if (lane == 0) {
-        float S = 0.f;
-        int npairs = 0;
-        float diag[WSM];
-        {
-            int idx = 0;
-#pragma unroll
-            for (int m = 0; m < WSM; ++m) { diag[m] = G[idx]; idx += WSM - m; }
-        }
-        int idx = 0;
-#pragma unroll
-        for (int m = 0; m < WSM; ++m)
-#pragma unroll
-            for (int n = m; n < WSM; ++n) {
-                if (n > m && ok[m] && ok[n]) {
-                    const float den = sqrtf(diag[m]) * sqrtf(diag[n]);
-                    S += (diag[m] > 0.f && diag[n] > 0.f) ? G[idx] / den : 0.f;
-                    ++npairs;
-                }
-                ++idx;
-            }
-        sim[(size_t)b * p.W + w] = npairs > 0 ? S / (float)npairs : 0.f;
+    for (int r = 0; r < WaveSums<NG>::H3; ++r) {
+        const int i = wave_sums_index<NG>(lane, r);
+        if (lane < 16 && i >= 0) s_gram[i] = G[r];
     }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint64_t okmask = __ballot(ok_l);
+    float S = 0.f;
+    int npairs = 0;
+#pragma unroll
+    for (int q0 = 0; q0 < NP; q0 += kWave) {
+        int m = 0, left = q0 + lane;                 // pair q -> members m < n: WSM-1 pairs with member 0, then WSM-2, ...
+#pragma unroll
+        for (int mm = 0; mm < WSM - 1; ++mm)
+            if (m == mm && left >= WSM - 1 - mm) { left -= WSM - 1 - mm; ++m; }
+        const bool in = q0 + lane < NP;
+        const int n = in ? m + 1 + left : 0;
+        m = in ? m : 0;
+        const int at = m * WSM - m * (m - 1) / 2;    // the triangle's row m: (m, m) first
+        const float dm = s_gram[at], dn = s_gram[n * WSM - n * (n - 1) / 2], g = s_gram[at + n - m];
+        const bool both = in && ((okmask >> m) & (okmask >> n) & 1ull);
+        if (both && dm > 0.f && dn > 0.f) S += g / (sqrtf(dm) * sqrtf(dn));
+        npairs += __popcll(__ballot(both));
+    }
+    S = wave_sum(S);
+    if (lane == 0) sim[(size_t)b * p.W + w] = npairs > 0 ? S / (float)npairs : 0.f;
 }
 
-// One launch for both bandwidth-bound score passes: waves [0, B*W) take a window each (Eq. 5), the
-// following waves a few key rows each (Eq. 6 logits; none when no key set is asked for).
+// Key scores a_cls of kKeyTokens tokens per block, for samples whose decision takes them ready-made
+// (encode_decide_large_kernel).  The block merges the per-block statistics of the whole sample (a pair per head and
+// kClsRows * kEncWaves key rows), turns its own groups' maxima into factors and adds up num * factor over the heads.
+// All of a round's loads are in flight together.
+constexpr int kMaxMergedHeads = 64;
+constexpr int kKeyTokens = 256;
+constexpr int kKeyGroups = kKeyTokens / kClsRows + 1;
+__host__ __device__ __forceinline__ int cls_blocks(int M) { return (cls_groups(M) + kEncWaves - 1) / kEncWaves; }
+struct KeyScoreLds {
+    float f[kKeyGroups * kMaxMergedHeads];           // [group][head]
+    float2 st[256];
+    float m[kMaxMergedHeads], inv[kMaxMergedHeads];
+};
+__device__ __forceinline__ void key_scores(
+    int b, int chunk, const EncodeDims& p, const uint8_t* __restrict__ valid, const float* __restrict__ logits,
+    const float2* __restrict__ cls_part, const float2* __restrict__ block_stat, float* __restrict__ acls,
+    float* __restrict__ a_cls_out, KeyScoreLds& s)
+{
+    const int tid = threadIdx.x, M = p.M, Hc = p.Hc;
+    const int j = chunk * kKeyTokens + tid, jc = min(j, M - 1);      // this thread's token
+    const int gps = cls_groups(M), cb = cls_blocks(M), g0 = (chunk * kKeyTokens + 1) / kClsRows;
+    const int ng = min(kKeyGroups, gps - g0);
+    // the token's first 16 numerators, its validity and the first group maximum depend on nothing
+    const f32x4* x = reinterpret_cast<const f32x4*>(logits + ((size_t)b * (M + 1) + 1 + jc) * Hc);
+    f32x4 xv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) xv[q] = x[min(q, Hc / 4 - 1)];
+    const bool ok = !valid || valid[(size_t)b * M + jc];
+    // statistics: thread = (slice, head), eight pairs per round
+    const int nsl = 256 / Hc, h = tid % Hc, sl = tid / Hc;
+    {
+        const float2* bs = block_stat + (size_t)b * cb * Hc + h;
+        float mx = -INFINITY, z = 0.f;
+        if (sl < nsl)
+            for (int c0 = sl; c0 < cb; c0 += 8 * nsl) {
+                float2 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = bs[(size_t)min(c0 + u * nsl, cb - 1) * Hc];
+                float m2 = mx;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (c0 + u * nsl >= cb) v[u] = make_float2(-INFINITY, 0.f);
+                    m2 = fmaxf(m2, v[u].x);
+                }
+                if (m2 > -INFINITY) {
+                    z *= fast_exp2(mx - m2);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) z = fmaf(v[u].y, fast_exp2(v[u].x - m2), z);
+                }
+                mx = m2;
+            }
+        s.st[tid] = make_float2(mx, z);
+    }
+    __syncthreads();
+    if (tid < Hc) {
+        float mx = -INFINITY, z = 0.f;
+        for (int q = 0; q < nsl; ++q) mx = fmaxf(mx, s.st[q * Hc + tid].x);
+        for (int q = 0; q < nsl; ++q) z = fmaf(s.st[q * Hc + tid].y, fast_exp2(s.st[q * Hc + tid].x - mx), z);
+        s.m[tid] = mx;                               // finite: the CLS row always counts
+        s.inv[tid] = 1.0f / (z * (float)Hc);
+    }
+    __syncthreads();
+    for (int e = tid; e < ng * Hc; e += 256) {
+        const int hh = e / ng, g = e - hh * ng;      // groups contiguous in cls_part
+        s.f[g * Hc + hh] = fast_exp2(cls_part[((size_t)b * Hc + hh) * gps + g0 + g].x - s.m[hh]) * s.inv[hh];
+    }
+    __syncthreads();
+    if (j >= M) return;
+    const f32x4* f = reinterpret_cast<const f32x4*>(s.f + ((j + 1) / kClsRows - g0) * Hc);
+    float a = 0.f;
+    auto add = [&](const f32x4& v, const f32x4& w) {
+        a = fmaf(v.x, w.x, a); a = fmaf(v.y, w.y, a); a = fmaf(v.z, w.z, a); a = fmaf(v.w, w.w, a);
+    };
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (q < Hc / 4) add(xv[q], f[q]);
+    for (int q = 4; q < Hc / 4; ++q) add(x[q], f[q]);
+    if (!ok) a = -INFINITY;                          // (its numerators were never written)
+    acls[(size_t)b * M + j] = a;
+    if (a_cls_out) a_cls_out[(size_t)b * M + j] = a;
+}
+
+// Both bandwidth-bound score passes: waves that take a window each (Eq. 5) and waves that take a few key rows each
+// (Eq. 6 logits; none when no key set is asked for).  A block does one of the three things below; the launch says
+// where in the grid each begins.
+//   windows, then key rows      one launch
+//   key rows alone,             then windows with the key-score blocks ahead of them: two launches for samples whose
+//                               decision wants the scores ready-made; the key scores hide behind the windows.
+//                               The key-row blocks (each within one sample) then also leave their groups' statistics
+//                               merged: block_stat[b][block of the sample][h].
+struct ScoreBlocks { int keyscore, windows, rows; };                 // blocks of each kind, in grid order
 template <int WSM, bool XBF, bool QKBF>
 __global__ __launch_bounds__(256) void encode_scores_kernel(
     const void* __restrict__ x, const void* __restrict__ q_cls, const void* __restrict__ k_cls,
-    const uint8_t* __restrict__ valid, EncodeDims p, int with_cls, float* __restrict__ sim, float* __restrict__ logits,
-    float2* __restrict__ cls_part)
+    const uint8_t* __restrict__ valid, EncodeDims p, ScoreBlocks nb, float* __restrict__ sim, float* __restrict__ logits,
+    float2* __restrict__ cls_part, float2* __restrict__ block_stat, float* __restrict__ acls, float* __restrict__ a_cls_out)
 {
-    const long item = (long)blockIdx.x * (blockDim.x >> 6) + wave_id();
-    const long n_win = (long)p.B * p.W;
-    if (item < n_win) window_sim_item<WSM, XBF>(item, x, valid, p, sim);
-    else if (with_cls) cls_logits_rows<QKBF>(item - n_win, q_cls, k_cls, valid, p, logits, cls_part);
+    union Lds { KeyScoreLds k; float2 stat[kEncWaves][kMaxMergedHeads]; float gram[kEncWaves][WSM * (WSM + 1) / 2]; };
+    __shared__ Lds s;
+    int blk = blockIdx.x;
+    if (blk < nb.keyscore) {
+        const int chunks = (p.M + kKeyTokens - 1) / kKeyTokens;
+        key_scores(blk / chunks, blk % chunks, p, valid, logits, cls_part, block_stat, acls, a_cls_out, s.k);
+        return;
+    }
+    blk -= nb.keyscore;
+    if (blk < nb.windows) {
+        window_sim_item<WSM, XBF>(blk * kEncWaves + wave_id(), x, valid, p, sim, s.gram[wave_id()]);
+        return;
+    }
+    blk -= nb.windows;
+    const int cb = cls_blocks(p.M), b = blk / cb, wb = blk % cb, g = wb * kEncWaves + wave_id();
+    if (g < cls_groups(p.M))
+        cls_logits_rows<QKBF>(b, g, q_cls, k_cls, valid, p, logits, cls_part, block_stat ? s.stat[wave_id()] : nullptr);
+    if (!block_stat) return;
+    __syncthreads();
+    const int nw = min(kEncWaves, cls_groups(p.M) - wb * kEncWaves);
+    for (int h = threadIdx.x; h < p.Hc; h += blockDim.x) {
+        float mx = -INFINITY, z = 0.f;
+        for (int w = 0; w < nw; ++w) mx = fmaxf(mx, s.stat[w][h].x);
+        for (int w = 0; w < nw; ++w)
+            if (s.stat[w][h].x > -INFINITY) z = fmaf(s.stat[w][h].y, fast_exp2(s.stat[w][h].x - mx), z);
+        block_stat[((size_t)b * cb + wb) * p.Hc + h] = make_float2(mx, z);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -447,9 +572,10 @@ __global__ __launch_bounds__(1024) void encode_decide_kernel(
     for (int w = tid; w < W; w += blockDim.x) {
         int n = 0;
         bool has_key = false;
+        const WindowAt at = window_at(p, w);
         for (int m = 0; m < p.ws; ++m) {
-            const int tok = member_token(p, w, m);
-            if (tok < 0 || (vb && !vb[tok])) continue;
+            const int tok = at.base + p.moff[m];
+            if (!member_exists(p, at, m) || (vb && !vb[tok])) continue;
             ++n;
             has_key |= iskey_b[tok] != 0;
         }
@@ -473,9 +599,10 @@ __global__ __launch_bounds__(1024) void encode_decide_kernel(
                 mass = mb ? mb[j] : 1.0f;
             } else {
                 int first = -1;
+                const WindowAt at = window_at(p, w);
                 for (int m = 0; m < p.ws; ++m) {
-                    const int tok = member_token(p, w, m);
-                    if (tok < 0 || (vb && !vb[tok])) continue;
+                    const int tok = at.base + p.moff[m];
+                    if (!member_exists(p, at, m) || (vb && !vb[tok])) continue;
                     if (first < 0) first = tok;
                     mass += mb ? mb[tok] : 1.0f;
                 }
@@ -499,7 +626,7 @@ __global__ __launch_bounds__(1024) void encode_decide_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same decisions for M <= 1024*IPT with a sample's tokens in registers (thread t owns the IPT
+// The same decisions for M <= 1024*IPT <= 5120 with a sample's tokens in registers (thread t owns the IPT
 // consecutive tokens t*IPT ..): the kernel is a chain of dependent steps on one CU per sample, so it
 // is built to be short rather than wide.
 //   - the softmax denominators come from the per-wave statistics the score kernel left (a few
@@ -599,7 +726,8 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
     struct WinInfo { int base, first, n; uint32_t vmask; float total; };
     auto analyse = [&](int w) -> WinInfo {
         WinInfo wi;
-        wi.base = window_base(p, w); wi.first = -1; wi.n = 0; wi.vmask = 0u; wi.total = 0.f;
+        const WindowAt at = window_at(p, w);
+        wi.base = at.base; wi.first = -1; wi.n = 0; wi.vmask = 0u; wi.total = 0.f;
 #pragma unroll
         for (int m0 = 0; m0 < WS; m0 += 4) {         // four members' flags and masses in flight (WS >= ws)
             if (m0 >= p.ws) break;
@@ -609,7 +737,7 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
             bool inb[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                inb[u] = m0 + u < p.ws && member_in_grid(p, w, m0 + u);
+                inb[u] = m0 + u < p.ws && member_exists(p, at, m0 + u);
                 tk[u] = inb[u] ? wi.base + p.moff[m0 + u] : wi.base;     // the window's first token is always there
             }
 #pragma unroll
@@ -808,6 +936,198 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
+// The decisions for samples of many tokens.  Bound by the latency of one CU's chain of steps.  In the kernel above that
+// CU also fetches 64 bytes of numerators per token, at about 40 GB/s; here the scores a_cls come ready-made (4 bytes
+// per token, see key_scores): 2 x 9216 tokens 14.3 us (the memory-resident kernel 95.9), 4 x 8064 12.1 (26.9).  A thread holds the scores of
+// the tokens tid + 1024*t in registers for the selection; token flags (and the mass of a merged window at its first
+// member) pass through LDS.  The final scan goes by waves: a wave owns a contiguous stretch of tokens and takes 64
+// of them at a time, so that the outputs are written coalesced.
+constexpr int kLargeTokens = 28672;                  // 5 bytes of LDS each: 140 of the CU's 160 KiB
+enum : uint8_t { kTokValid = 1, kTokKey = 2, kTokFirst = 4, kTokGone = 8 };
+template <int IPT, int WS>
+__global__ __launch_bounds__(1024) void encode_decide_large_kernel(
+    EncodeDims p, const uint8_t* __restrict__ valid, const float* __restrict__ mass_in,
+    const float* __restrict__ acls, const float* __restrict__ sim, float tau,
+    int key_budget, int key_adaptive, float key_lambda, int32_t* __restrict__ key_count,
+    uint8_t* __restrict__ wmerged, int32_t* __restrict__ dstpos,
+    int32_t* __restrict__ out_index, float* __restrict__ out_mass, uint8_t* __restrict__ out_is_key,
+    uint8_t* __restrict__ out_valid, int32_t* __restrict__ out_count, int32_t* __restrict__ key_index,
+    float* __restrict__ a_cls_out, float* __restrict__ window_sim_out)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
+    __shared__ int s_hist[kSelectHistInts];
+    __shared__ int s_red[16];
+    __shared__ float s_redf[16];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+    const int M = p.M, W = p.W;
+    float* s_tmass = reinterpret_cast<float*>(s_dyn);
+    uint8_t* s_flag = s_dyn + 4 * (size_t)M;
+    const uint8_t* vb = valid ? valid + (size_t)b * M : nullptr;
+    const float* mb = mass_in ? mass_in + (size_t)b * M : nullptr;
+    const bool with_keys = key_budget > 0 || key_adaptive;
+    if (tid < 256) s_hist[tid] = 0;                  // for block_select_keys, after later barriers
+    // the first rounds of windows: where they lie and their similarities, on the way while the keys are selected
+    constexpr int PRE = 2;
+    WindowAt wat[PRE];
+    float wsim[PRE];
+#pragma unroll
+    for (int r = 0; r < PRE; ++r) {
+        const int w = min(tid + 1024 * r, W - 1);
+        wsim[r] = sim[(size_t)b * W + w];
+        wat[r] = window_at(p, w);
+    }
+    uint32_t okmask = 0, keymask = 0;                // bit t: the token tid + 1024*t
+    {
+        float av[IPT];
+        uint32_t vv[IPT];
+#pragma unroll
+        for (int t = 0; t < IPT; ++t) av[t] = with_keys ? acls[(size_t)b * M + min(tid + 1024 * t, M - 1)] : 0.f;
+#pragma unroll
+        for (int t = 0; t < IPT; ++t) vv[t] = vb ? vb[min(tid + 1024 * t, M - 1)] : 1u;
+#pragma unroll
+        for (int t = 0; t < IPT; ++t) okmask |= (tid + 1024 * t < M && vv[t] != 0 ? 1u : 0u) << t;
+        if (with_keys) {
+            __syncthreads();                         // s_hist is clear
+            if (!key_adaptive) {                     // Eq. 7, budget form
+                const SelectBound sb = block_select_keys([&](auto f) {
+#pragma unroll
+                    for (int t = 0; t < IPT; ++t) f((okmask >> t) & 1u ? rank_key(av[t], tid + 1024 * t) : 0ull);
+                }, key_budget, s_hist);
+#pragma unroll
+                for (int t = 0; t < IPT; ++t)
+                    keymask |= ((rank_key(av[t], tid + 1024 * t) >> sb.shift) >= sb.bound ? 1u : 0u) << t;
+            } else {                                 // Eq. 7 as printed: a_cls > mu, mu = mean + lambda * std
+                float s1 = 0.f;
+#pragma unroll
+                for (int t = 0; t < IPT; ++t)
+                    if ((okmask >> t) & 1u) s1 += av[t];
+                s1 = block_sum(s1, s_redf);
+                const int cnt = block_sum_i(__popc(okmask), s_red);
+                const float mean = cnt > 0 ? s1 / (float)cnt : 0.f;
+                float s2 = 0.f;
+#pragma unroll
+                for (int t = 0; t < IPT; ++t)
+                    if ((okmask >> t) & 1u) { const float dlt = av[t] - mean; s2 = fmaf(dlt, dlt, s2); }
+                s2 = block_sum(s2, s_redf);
+                const float mu = mean + key_lambda * sqrtf(cnt > 0 ? s2 / (float)cnt : 0.f);
+#pragma unroll
+                for (int t = 0; t < IPT; ++t) keymask |= (av[t] > mu ? 1u : 0u) << t;
+            }
+            keymask &= okmask;
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < IPT; ++t) {
+        const int j = tid + 1024 * t;
+        if (j >= M) continue;
+        s_flag[j] = ((okmask >> t) & 1u ? kTokValid : 0) | ((keymask >> t) & 1u ? kTokKey : 0);
+        if (!with_keys && a_cls_out) a_cls_out[(size_t)b * M + j] = 0.f;
+    }
+    __syncthreads();
+
+    // ---- merge decision per window: S > tau, >= 2 valid members, no key member
+    auto decide = [&](int w, const WindowAt& at, float S) {
+        uint8_t fl[WS];
+#pragma unroll
+        for (int m = 0; m < WS; ++m)                 // every flag in flight; members that do not exist read as absent
+            fl[m] = s_flag[m < p.ws && member_exists(p, at, m) ? at.base + p.moff[m] : at.base];
+        int n = 0, first = -1;
+        bool has_key = false;
+        float total = 0.f;
+#pragma unroll
+        for (int m = 0; m < WS; ++m) {
+            if (m >= p.ws || !member_exists(p, at, m)) fl[m] = 0;
+            if (!fl[m]) continue;
+            const int tok = at.base + p.moff[m];
+            ++n;
+            has_key |= (fl[m] & kTokKey) != 0;
+            if (first < 0) first = tok;
+            total += mb ? mb[tok] : 1.0f;
+        }
+        const bool mg = n >= 2 && !has_key && S > tau;
+        if (mg) {
+#pragma unroll
+            for (int m = 0; m < WS; ++m) {
+                const int tok = at.base + p.moff[m];
+                if (fl[m]) s_flag[tok] = kTokValid | (tok == first ? kTokFirst : kTokGone);
+            }
+            s_tmass[first] = total;
+        }
+        wmerged[(size_t)b * W + w] = mg;
+        if (window_sim_out) window_sim_out[(size_t)b * W + w] = S;
+    };
+#pragma unroll
+    for (int r = 0; r < PRE; ++r)
+        if (tid + 1024 * r < W) decide(tid + 1024 * r, wat[r], wsim[r]);
+    for (int w = tid + 1024 * PRE; w < W; w += 1024) decide(w, window_at(p, w), sim[(size_t)b * W + w]);
+    __syncthreads();
+
+    // ---- keys and survivors in ascending token index (a stretch is at most 64 * IPT tokens)
+    const int stretch = ((M + 1023) / 1024) * kWave;
+    const int t0 = wv * stretch, t1 = min(t0 + stretch, M);
+    uint8_t fl[IPT];
+    int packed = 0;                                  // keys in the high half, survivors in the low half
+#pragma unroll
+    for (int t = 0; t < IPT; ++t) {
+        const int j = t0 + t * kWave + lane;
+        fl[t] = s_flag[min(j, M - 1)];
+        if (j >= t1) fl[t] = 0;
+        packed += ((fl[t] & kTokKey) ? 0x10000 : 0) + ((fl[t] && !(fl[t] & kTokGone)) ? 1 : 0);
+    }
+    packed = wave_sum_i(packed);
+    if (lane == 0) s_red[wv] = packed;
+    __syncthreads();
+    int total;
+    const int before = wave_prefix_of_totals(s_red, total);
+    int kpos = before >> 16, spos = before & 0xFFFF;
+    const int nkeys = total >> 16, nsurv = total & 0xFFFF;
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int t = 0; t < IPT; ++t) {
+        const int j = t0 + t * kWave + lane;
+        const bool key = (fl[t] & kTokKey) != 0, surv = fl[t] && !(fl[t] & kTokGone);
+        const uint64_t kmask = __ballot(key), smask = __ballot(surv);
+        if (key) {
+            const int r = kpos + __popcll(kmask & below);
+            if (r < key_budget) key_index[(size_t)b * key_budget + r] = j;
+        }
+        const int so = spos + __popcll(smask & below);
+        if (j < t1) dstpos[(size_t)b * M + j] = surv ? so : -1;
+        if (surv) {
+            const size_t o = (size_t)b * M + so;
+            out_index[o] = j;
+            out_mass[o] = (fl[t] & kTokFirst) ? s_tmass[j] : (mb ? mb[j] : 1.0f);
+            s_flag[so] = key ? 1 : 0;                // every flag is in a register: its place holds the output's byte
+        }
+        kpos += __popcll(kmask);
+        spos += __popcll(smask);
+    }
+    if (with_keys) {
+        for (int r = nkeys + tid; r < key_budget; r += 1024) key_index[(size_t)b * key_budget + r] = -1;
+        if (key_count && tid == 0) key_count[b] = nkeys;
+    }
+    if (tid == 0) out_count[b] = nsurv;
+    __syncthreads();
+    // the byte outputs, four at a time where the rows of the batch allow it
+    uint8_t* kb = out_is_key + (size_t)b * M;
+    uint8_t* vo = out_valid ? out_valid + (size_t)b * M : nullptr;
+    const bool words = (M & 3) == 0 && ((reinterpret_cast<uintptr_t>(kb) | reinterpret_cast<uintptr_t>(vo)) & 3) == 0;
+    const int n4 = words ? M / 4 : 0;
+    for (int q = tid; q < n4; q += 1024) {
+        const int s4 = 4 * q;
+        if (s4 + 4 <= nsurv) *reinterpret_cast<uint32_t*>(kb + s4) = *reinterpret_cast<const uint32_t*>(s_flag + s4);
+        else
+            for (int s2 = s4; s2 < nsurv; ++s2) kb[s2] = s_flag[s2];
+        const int live = min(max(nsurv - s4, 0), 4);
+        if (vo) *reinterpret_cast<uint32_t*>(vo + s4) = live == 4 ? 0x01010101u : 0x01010101u & ((1u << (8 * live)) - 1u);
+    }
+    for (int s2 = 4 * n4 + tid; s2 < M; s2 += 1024) {
+        if (s2 < nsurv) kb[s2] = s_flag[s2];
+        if (vo) vo[s2] = s2 < nsurv;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Writes the surviving rows.  One wave per window.
 template <bool BF>
 __global__ __launch_bounds__(256) void encode_emit_kernel(
@@ -817,9 +1137,9 @@ __global__ __launch_bounds__(256) void encode_emit_kernel(
 {
     constexpr int VEC = Vec<BF>::N;
     const int lane = lane_id();
-    const long item = (long)blockIdx.x * (blockDim.x >> 6) + wave_id();
-    if (item >= (long)p.B * p.W) return;
-    const int b = (int)(item / p.W), w = (int)(item % p.W);
+    const int item = blockIdx.x * kEncWaves + wave_id();
+    if (item >= p.B * p.W) return;
+    const int b = p.by_W.div(item), w = item - b * p.W;
     const size_t esz = BF ? 2 : 4;
     const size_t rowb = (size_t)p.D * esz;
     const char* xb = static_cast<const char*>(x) + (size_t)b * p.M * rowb;
@@ -896,7 +1216,8 @@ __global__ __launch_bounds__(256) void encode_emit_kernel(
 }
 
 struct EncodeWorkspace {
-    float* logits; float2* cls_part; float* acls; float* sim; uint8_t* iskey; uint8_t* wmerged; int32_t* dstpos;
+    float* logits; float2* cls_part; float2* block_stat; float* acls; float* sim; uint8_t* iskey; uint8_t* wmerged;
+    int32_t* dstpos;
     size_t bytes;
 };
 
@@ -905,6 +1226,7 @@ EncodeWorkspace carve_encode(void* base, int B, int M, int W, int Hc) {
     EncodeWorkspace ws;
     ws.logits = c.take<float>((size_t)B * (Hc > 0 ? Hc : 1) * (M + 1));
     ws.cls_part = c.take<float2>((size_t)B * (Hc > 0 ? Hc : 1) * cls_groups(M));
+    ws.block_stat = c.take<float2>((size_t)B * (Hc > 0 ? Hc : 1) * cls_blocks(M));
     ws.acls = c.take<float>((size_t)B * M);
     ws.sim = c.take<float>((size_t)B * W);
     ws.iskey = c.take<uint8_t>((size_t)B * M);
@@ -921,24 +1243,27 @@ size_t decide_fast_lds_bytes(int M) {
     const size_t factors = (size_t)cls_groups(M) * 16 * 4, flags = 2 * (size_t)M + 16;
     return head + (factors > flags ? factors : flags);
 }
-// More than 64 KiB of dynamic LDS has to be asked for (only the 8-tokens-per-thread form needs it).
-bool decide_fast_lds_ready(int M, size_t bytes) {
-    if (bytes <= 64 * 1024) return true;
-    if (M <= 4096) return false;
-    bool ok = true;
-    ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_decide_fast_kernel<8, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
-    ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_decide_fast_kernel<8, 8>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
-    ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_decide_fast_kernel<8, 16>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
-    return ok;
-}
-
+struct ScoreArgs {
+    const void* x; const void* q_cls; const void* k_cls; const uint8_t* valid; float* sim; float* logits; float2* cls_part;
+    float2* block_stat; float* acls; float* a_cls_out;
+};
 template <int WSM>
-void launch_scores(dim3 grid, hipStream_t st, bool xbf, bool qkbf, const void* x, const void* q_cls, const void* k_cls,
-                   const uint8_t* valid, const EncodeDims& p, int with_cls, float* sim, float* logits, float2* cls_part) {
-    if (xbf && qkbf) MD_LAUNCH("encode_scores", st, (encode_scores_kernel<WSM, true, true>), grid, 64 * kEncWaves, 0, x, q_cls, k_cls, valid, p, with_cls, sim, logits, cls_part);
-    else if (xbf) MD_LAUNCH("encode_scores", st, (encode_scores_kernel<WSM, true, false>), grid, 64 * kEncWaves, 0, x, q_cls, k_cls, valid, p, with_cls, sim, logits, cls_part);
-    else if (qkbf) MD_LAUNCH("encode_scores", st, (encode_scores_kernel<WSM, false, true>), grid, 64 * kEncWaves, 0, x, q_cls, k_cls, valid, p, with_cls, sim, logits, cls_part);
-    else MD_LAUNCH("encode_scores", st, (encode_scores_kernel<WSM, false, false>), grid, 64 * kEncWaves, 0, x, q_cls, k_cls, valid, p, with_cls, sim, logits, cls_part);
+void launch_scores(ScoreBlocks nb, hipStream_t st, bool xbf, bool qkbf, const EncodeDims& p, const ScoreArgs& a) {
+    const unsigned grid = (unsigned)(nb.keyscore + nb.windows + nb.rows);
+#define MD_ENC_SCORES(X_, K_)                                                                                  \
+    MD_LAUNCH("encode_scores", st, (encode_scores_kernel<WSM, X_, K_>), grid, 64 * kEncWaves, 0, a.x, a.q_cls, a.k_cls, a.valid, p, nb, \
+        a.sim, a.logits, a.cls_part, a.block_stat, a.acls, a.a_cls_out)
+    if (xbf && qkbf) MD_ENC_SCORES(true, true);
+    else if (xbf) MD_ENC_SCORES(true, false);
+    else if (qkbf) MD_ENC_SCORES(false, true);
+    else MD_ENC_SCORES(false, false);
+#undef MD_ENC_SCORES
+}
+void launch_scores(int ws, ScoreBlocks nb, hipStream_t st, bool xbf, bool qkbf, const EncodeDims& p, const ScoreArgs& a) {
+    if (ws <= 2) launch_scores<2>(nb, st, xbf, qkbf, p, a);
+    else if (ws <= 4) launch_scores<4>(nb, st, xbf, qkbf, p, a);
+    else if (ws <= 8) launch_scores<8>(nb, st, xbf, qkbf, p, a);
+    else launch_scores<16>(nb, st, xbf, qkbf, p, a);
 }
 
 }  // namespace
@@ -1015,20 +1340,33 @@ int encode_merge_impl(
     p.kt = kt; p.kh = kh; p.kw = kw; p.M = M; p.W = W; p.ws = ws;
     p.nwx = nwx; p.nwy = nwy; p.nwt = nwt;
     p.clipped = (T % kt || Hg % kh || Wg % kw) ? 1 : 0;
-    for (int m = 0; m < kMaxWindow; ++m) p.moff[m] = m < ws ? member_offset(p, m) : 0;
+    p.by_W = FastDiv::make(W); p.by_nwx = FastDiv::make(nwx); p.by_nwy = FastDiv::make(nwy);
+    p.by_kw = FastDiv::make(kw); p.by_kh = FastDiv::make(kh);
+    for (int m = 0; m < kMaxWindow; ++m) {
+        const int mm = m < ws ? m : 0, dx = mm % kw, dy = mm / kw % kh, dt = mm / (kw * kh);
+        p.moff[m] = (dt * Hg + dy) * Wg + dx;
+        p.mpos[m] = dt << 16 | dy << 8 | dx;
+    }
     hipStream_t st = static_cast<hipStream_t>(stream);
 
-    const long items = (long)B * W + (with_keys ? (long)B * cls_groups(M) : 0);
-    dim3 sgrid((unsigned)((items + kEncWaves - 1) / kEncWaves));
+    const int win_blocks = (int)(((long)B * W + kEncWaves - 1) / kEncWaves);
+    const int row_blocks = with_keys ? B * cls_blocks(M) : 0;
+    // Up to 5120 tokens the decision kernel fetches the numerators itself; beyond that the scores are made beforehand
+    // (two score launches, about 5 us more, against a decision 8 to 15 us shorter).  Measured, us per call, numerators /
+    // ready-made: 4 x 4608 tokens 41.1 / 41.7, 4 x 5760 48.5 / 49.6, 4 x 6144 51.3 / 47.9, 16 x 5760 135.5 / 131.5,
+    // 4 x 8064 66.8 / 56.5.  (The LDS of the former stays below 64 KiB.)
+    const size_t dlds = decide_fast_lds_bytes(M), llds = 5 * (size_t)M;
+    const bool fast_ok = M <= 5120 && (!with_keys || (Hc <= 16 && Hc % 4 == 0));
+    const bool large_ok = !fast_ok && M <= kLargeTokens && (!with_keys || (Hc <= kMaxMergedHeads && Hc % 4 == 0));
     const bool xbf = x_dtype == MD_BF16, qkbf = qk_dtype == MD_BF16;
-    const int with_cls = with_keys;
-    if (ws <= 2) launch_scores<2>(sgrid, st, xbf, qkbf, x, q_cls, k_cls, valid, p, with_cls, wsp.sim, wsp.logits, wsp.cls_part);
-    else if (ws <= 4) launch_scores<4>(sgrid, st, xbf, qkbf, x, q_cls, k_cls, valid, p, with_cls, wsp.sim, wsp.logits, wsp.cls_part);
-    else if (ws <= 8) launch_scores<8>(sgrid, st, xbf, qkbf, x, q_cls, k_cls, valid, p, with_cls, wsp.sim, wsp.logits, wsp.cls_part);
-    else launch_scores<16>(sgrid, st, xbf, qkbf, x, q_cls, k_cls, valid, p, with_cls, wsp.sim, wsp.logits, wsp.cls_part);
-    dim3 wgrid((unsigned)(((long)B * W + kEncWaves - 1) / kEncWaves));
-    const size_t dlds = decide_fast_lds_bytes(M);
-    const bool fast_ok = M <= 8192 && (!with_keys || (Hc <= 16 && Hc % 4 == 0)) && decide_fast_lds_ready(M, dlds);
+    const ScoreArgs sa{x, q_cls, k_cls, valid, wsp.sim, wsp.logits, wsp.cls_part, large_ok ? wsp.block_stat : nullptr, wsp.acls, a_cls_out};
+    if (large_ok && with_keys) {
+        launch_scores(ws, ScoreBlocks{0, 0, row_blocks}, st, xbf, qkbf, p, sa);
+        launch_scores(ws, ScoreBlocks{B * ((M + kKeyTokens - 1) / kKeyTokens), win_blocks, 0}, st, xbf, qkbf, p, sa);
+    } else {
+        launch_scores(ws, ScoreBlocks{0, win_blocks, row_blocks}, st, xbf, qkbf, p, sa);
+    }
+    dim3 wgrid((unsigned)win_blocks);
 #define MD_DECIDE_FAST(IPT_, WS_)                                                                             \
     MD_LAUNCH("encode_decide", st, (encode_decide_fast_kernel<IPT_, WS_>), B, 1024, dlds,                  \
         p, valid, mass_in, wsp.logits, wsp.cls_part, wsp.sim, tau, key_budget, key_adaptive, key_lambda, key_count,  \
@@ -1040,10 +1378,28 @@ int encode_merge_impl(
     else if (fast_ok && M <= 2048) MD_DECIDE_FAST_WS(2);
     else if (fast_ok && M <= 3072) MD_DECIDE_FAST_WS(3);     // e.g. five tiles of 24 x 24 tokens
     else if (fast_ok && M <= 4096) MD_DECIDE_FAST_WS(4);
-    else if (fast_ok && M <= 5120) MD_DECIDE_FAST_WS(5);     // e.g. eight frames of 24 x 24 tokens
-    else if (fast_ok && M <= 6144) MD_DECIDE_FAST_WS(6);
-    else if (fast_ok) MD_DECIDE_FAST_WS(8);
-    else
+    else if (fast_ok) MD_DECIDE_FAST_WS(5);                  // e.g. eight frames of 24 x 24 tokens
+    else if (large_ok) {
+#define MD_DECIDE_LARGE(IPT_, WS_)                                                                             \
+    do {                                                                                                       \
+        if (llds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_decide_large_kernel<IPT_, WS_>), \
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)llds) != hipSuccess) \
+            return fail(MD_EHIP, "encode_merge: %zu bytes of LDS refused", llds);                              \
+        MD_LAUNCH("encode_decide", st, (encode_decide_large_kernel<IPT_, WS_>), B, 1024, llds,                \
+            p, valid, mass_in, wsp.acls, wsp.sim, tau, key_budget, key_adaptive, key_lambda, key_count, wsp.wmerged, wsp.dstpos, \
+            out_index, out_mass, out_is_key, out_valid, out_count, key_index, a_cls_out, window_sim_out);      \
+    } while (0)
+#define MD_DECIDE_LARGE_WS(IPT_)                                                                              \
+    do { if (ws <= 4) MD_DECIDE_LARGE(IPT_, 4); else if (ws <= 8) MD_DECIDE_LARGE(IPT_, 8); else MD_DECIDE_LARGE(IPT_, 16); } while (0)
+        if (M <= 6144) MD_DECIDE_LARGE_WS(6);
+        else if (M <= 8192) MD_DECIDE_LARGE_WS(8);
+        else if (M <= 10240) MD_DECIDE_LARGE_WS(10);
+        else if (M <= 12288) MD_DECIDE_LARGE_WS(12);
+        else if (M <= 16384) MD_DECIDE_LARGE_WS(16);
+        else MD_DECIDE_LARGE_WS(28);
+#undef MD_DECIDE_LARGE_WS
+#undef MD_DECIDE_LARGE
+    } else
         MD_LAUNCH("encode_decide", st, (encode_decide_kernel), B, 1024, 0,
             p, valid, mass_in, wsp.logits, wsp.cls_part, wsp.sim, tau, key_budget, key_adaptive, key_lambda, key_count,
             wsp.acls, wsp.iskey, wsp.wmerged, wsp.dstpos,

@@ -25,6 +25,21 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
     return u >> 16;
 }
 
+// Division by a number that the host knows: n / d for 0 <= n < 2^31 as one wide multiplication and a shift
+// (mul = ceil(2^(31+l) / d), l = ceil(log2 d), which is exact for 31-bit n).  A division by a run-time number is some
+// thirty dependent instructions, and an index takes several of them before a wave can ask for its first byte.
+struct FastDiv {
+    uint32_t mul, shift;
+    int d;
+    __host__ static FastDiv make(int d) {
+        uint32_t l = 0;
+        while ((1ll << l) < d) ++l;
+        return FastDiv{(uint32_t)(((1ull << (31 + l)) + d - 1) / d), 31 + l, d};
+    }
+    __device__ __forceinline__ int div(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
+    __device__ __forceinline__ int mod(int n) const { return n - div(n) * d; }
+};
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 // wave index within the block, as a scalar (the compiler cannot see that threadIdx.x / 64 is wave-uniform)
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
@@ -89,6 +104,42 @@ __device__ __forceinline__ float group_sum_rt(float v, int g) {
     if (g >= 32) v += __shfl_xor(v, 16, kWave);
     if (g >= 64) v += __shfl_xor(v, 32, kWave);
     return v;
+}
+
+// Sums of N values over the wave, each left in one lane of every 16: a value costs about three instructions instead
+// of the twelve of wave_sum, since every exchange also halves the number of values a lane carries on.  Step by step
+// (partners l^15, l^7, l^3, l^1) the upper half of the list goes to the lane whose bit 3, 2, 1, 0 is set; the four
+// rows of 16 lanes are added last.  v[r] of a lane is then the sum of value wave_sums_index<N>(lane, r) (-1: none).
+template <int N> struct WaveSums { static constexpr int H0 = (N + 1) / 2, H1 = (H0 + 1) / 2, H2 = (H1 + 1) / 2, H3 = (H2 + 1) / 2; };
+template <int N>
+__device__ __forceinline__ int wave_sums_index(int lane, int r) {
+    using W = WaveSums<N>;
+    const int i3 = r + (lane & 1 ? W::H3 : 0), i2 = i3 + (lane & 2 ? W::H2 : 0);
+    const int i1 = i2 + (lane & 4 ? W::H1 : 0), i0 = i1 + (lane & 8 ? W::H0 : 0);
+    return i3 < W::H2 && i2 < W::H1 && i1 < W::H0 && i0 < N ? i0 : -1;
+}
+template <int CTRL, int N, int LEN>
+__device__ __forceinline__ void wave_sums_step(float (&v)[LEN], bool upper) {
+    constexpr int H = (N + 1) / 2;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+        const float hi = k + H < N ? v[k + H] : 0.f;
+        const float keep = upper ? hi : v[k], give = upper ? v[k] : hi;
+        v[k] = keep + dpp_f<CTRL>(give);
+    }
+}
+template <int N>
+__device__ __forceinline__ void wave_sums(float (&v)[N], int lane) {
+    using W = WaveSums<N>;
+    wave_sums_step<0x140, N>(v, lane & 8);           // row_mirror: l^15
+    wave_sums_step<0x141, W::H0>(v, lane & 4);       // row_half_mirror: l^7
+    wave_sums_step<0x1B, W::H1>(v, lane & 2);        // quad_perm [3,2,1,0]: l^3
+    wave_sums_step<0xB1, W::H2>(v, lane & 1);        // quad_perm [1,0,3,2]: l^1
+#pragma unroll
+    for (int r = 0; r < W::H3; ++r) {
+        v[r] += __shfl_xor(v[r], 16, kWave);
+        v[r] += __shfl_xor(v[r], 32, kWave);
+    }
 }
 
 // 64-bit minimum: first the high words, then the low words of the lanes that hold the winning high word
@@ -218,8 +269,8 @@ __device__ __forceinline__ SelectBound block_radix_select(KeyFn key, int n, int 
     return SelectBound{prefix, shift};
 }
 
-// Same selection with the keys held in registers (IPT per thread, 0 = absent; real keys are never 0
-// as long as the tie value is below 2^31 - 1), built for a short chain of dependent steps:
+// Same selection for keys that a thread has at hand (0 = absent; real keys are never 0 as long as the
+// tie value is below 2^31 - 1), built for a short chain of dependent steps:
 //   - the scores of one sample share their leading bits (sign, most of the exponent): the block's
 //     smallest and largest score are found first and the passes start below the bits they share, so
 //     the first histogram is spread over its bins instead of piling onto two or three of them;
@@ -229,15 +280,16 @@ __device__ __forceinline__ SelectBound block_radix_select(KeyFn key, int n, int 
 // `hist`: 768 ints of shared memory whose first 256 the caller has zeroed, with a block barrier
 // between the zeroing and this call.  All threads of the block (at most 16 waves) must call it.
 constexpr int kSelectHistInts = 768;
-template <int IPT>
-__device__ __forceinline__ SelectBound block_select_topk(const uint64_t (&key)[IPT], int k, int* hist) {
+// `each(f)` calls f(key) for every key this thread holds (registers, or computed again on each pass).
+template <class ForEach>
+__device__ __forceinline__ SelectBound block_select_keys(ForEach each, int k, int* hist) {
     if (k <= 0) return SelectBound{~0ull, 0};               // nothing selected
     const int lane = lane_id(), wv = wave_id(), nw = blockDim.x >> 6;
     // leading bits common to every present key's score
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-#pragma unroll
-    for (int t = 0; t < IPT; ++t)
-        if (key[t] != 0) { lo = min(lo, (uint32_t)(key[t] >> 32)); hi = max(hi, (uint32_t)(key[t] >> 32)); }
+    each([&](uint64_t kv) {
+        if (kv != 0) { lo = min(lo, (uint32_t)(kv >> 32)); hi = max(hi, (uint32_t)(kv >> 32)); }
+    });
     lo = wave_min_u32(lo);
     hi = ~wave_min_u32(~hi);
     if (lane == 0) { hist[512 + wv] = (int)lo; hist[528 + wv] = (int)hi; }     // hist[2] is not in use before pass 1
@@ -253,11 +305,9 @@ __device__ __forceinline__ SelectBound block_select_topk(const uint64_t (&key)[I
     for (int pass = 0;; ++pass) {
         int* h = hist + (pass % 3) * 256;
         int* hn = hist + ((pass + 1) % 3) * 256;
-#pragma unroll
-        for (int t = 0; t < IPT; ++t) {
-            const uint64_t kv = key[t];
+        each([&](uint64_t kv) {
             if (kv != 0 && (first || (kv >> shift) == prefix)) atomicAdd(&h[(kv >> sh) & 0xFF], 1);
-        }
+        });
         if (threadIdx.x < 256) hn[threadIdx.x] = 0;
         __syncthreads();
         // digits 255..0, four per lane, high digits in low lanes; every wave does the same scan
@@ -288,6 +338,14 @@ __device__ __forceinline__ SelectBound block_select_topk(const uint64_t (&key)[I
         sh = max(sh - 8, 0);
     }
     return SelectBound{prefix, shift};
+}
+// The keys held in registers, IPT per thread.
+template <int IPT>
+__device__ __forceinline__ SelectBound block_select_topk(const uint64_t (&key)[IPT], int k, int* hist) {
+    return block_select_keys([&](auto f) {
+#pragma unroll
+        for (int t = 0; t < IPT; ++t) f(key[t]);
+    }, k, hist);
 }
 
 // Block-wide minimum of 64-bit values (same result on every thread).  `red` holds >= blockDim.x/64 entries.
