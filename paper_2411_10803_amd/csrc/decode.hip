@@ -2,7 +2,8 @@
 // (attention of Eq. 4), keep a running score per entry, evict down to a budget and compact the
 // cache by hole filling.
 //
-//   decode_logits_kernel  one wave per cache entry at a time: an entry's K row (H heads x d, all
+//   decode_logits_stream_kernel / decode_logits_kernel
+//                         one wave per cache entry at a time: an entry's K row (H heads x d, all
 //                         contiguous) is read once with 16-byte loads, 16 lanes per head slice;
 //                         segmented butterflies give the H logits.  Pure streaming: a GEMV at about
 //                         1 flop per byte, so plain ALUs, not MFMA.
@@ -85,17 +86,23 @@ __device__ __forceinline__ float dot8(const u32x4& a, const float (&qv)[8]) {
     return s;
 }
 
-// Streaming shape: an entry's row is NIT KiB (H*d*2 = NIT*1024 bytes).  A wave keeps the whole query
+// Streaming shape: an entry's row is at most NIT KiB (H*d*2 bytes, d = 64 or 128).  A wave keeps the whole query
 // in registers and reads each entry's row in one go: NIT independent 16-byte loads per lane, every
 // load instruction covering 1 KiB of consecutive addresses.  Waves stride over the sample's entries.
+// Where the row ends inside a piece the lanes behind it read its last vector again against a zero query.
 // Each wave also keeps online softmax statistics (max, sum of exp2) of every head over the entries
 // it has seen; the block's four waves are merged and written as one partial per (sample, block, head),
 // so the selection kernel does not have to sweep the logits for them.
-// STRIDED: the cache has another layout; a load instruction then covers kWave/LPH head slices of
-// d*2 contiguous bytes each instead of 1 KiB of one row.
+// Bound by the read of K: 64 caches of 1025 entries, 32 heads of 128, 90 us = 6.0 TB/s; 60 of 748 entries, 40 heads,
+// head-major, 81 us = 5.7 TB/s (93 through the generic form).  A second register set with the next row in flight did
+// not help (89 us at half the waves), nor did one store per entry with the statistics spread over the lanes of a
+// group (91 and 89 us).
+// LAYOUT 0: dense rows of exactly NIT KiB (a load's offset is then a constant of the instruction: 0.6 us of 90 on 64
+// caches of 1025 entries).  1: dense rows that end inside a piece.  2: any other layout; a load instruction then
+// covers kWave/LPH head slices of d*2 contiguous bytes each instead of 1 KiB of one row.
 // STREAM_ONCE: the cache is larger than what the L2 / Infinity Cache can hold until the row moves, so
 // the K rows are read with streaming loads (they would only evict each other and everything else).
-template <int LPH, int NIT, bool STRIDED, bool STREAM_ONCE>
+template <int LPH, int NIT, int LAYOUT, bool STREAM_ONCE>
 __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache, const int32_t* __restrict__ len,
     DecodeDims p, KvLayout lay, float scale, float* __restrict__ logits, float2* __restrict__ stat_partial)
@@ -106,34 +113,33 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
     const int b = blockIdx.y;
     const int wave_global = blockIdx.x * 4 + wv;
     const int nwaves = gridDim.x * 4;
-    const int row = p.H * p.d;
+    const int row = p.H * p.d, nvec = row / 8;
     const u32x4* qb = reinterpret_cast<const u32x4*>(q + (long)b * row);
     const u32x4* kb = reinterpret_cast<const u32x4*>(k_cache + (long)b * p.Lcap * row);
     const uint16_t* ks = k_cache + (long)b * lay.batch;
-    long off[NIT];                                   // STRIDED: element offset of this lane's vectors within an entry
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int idx = it * kWave + lane;
-        off[it] = (long)(idx / LPH) * lay.head + (idx % LPH) * 8;
-    }
-    float* lb = logits + (long)b * p.Lcap * p.H;
-    const float scale_l2 = scale * kLog2eD;
-
+    int vec[NIT];                                    // this lane's vectors within a row
+    long off[NIT];                                   // LAYOUT 2: their element offsets within an entry
     float qv[NIT][8];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const u32x4 w = qb[it * kWave + lane];
+        const int idx = it * kWave + lane;
+        vec[it] = LAYOUT == 0 ? idx : min(idx, nvec - 1);
+        off[it] = (long)(vec[it] / LPH) * lay.head + (vec[it] % LPH) * 8;
+        u32x4 w = qb[vec[it]];
+        if (LAYOUT != 0 && idx >= nvec) w = u32x4{0, 0, 0, 0};
         qv[it][0] = bf16_lo(w.x); qv[it][1] = bf16_hi(w.x); qv[it][2] = bf16_lo(w.y); qv[it][3] = bf16_hi(w.y);
         qv[it][4] = bf16_lo(w.z); qv[it][5] = bf16_hi(w.z); qv[it][6] = bf16_lo(w.w); qv[it][7] = bf16_hi(w.w);
     }
-    float m[NIT], z[NIT];                            // log2 domain; every lane of a head's group holds the same values
+    float* lb = logits + (long)b * p.Lcap * p.H;
+    const float scale_l2 = scale * kLog2eD;
+    float m[NIT], z[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) { m[it] = -INFINITY; z[it] = 0.f; }
 
     const int n = min(max(len[b], 0), p.Lcap);
     for (int j = wave_global; j < n; j += nwaves) {
         u32x4 kv[NIT];
-        if constexpr (STRIDED) {
+        if constexpr (LAYOUT == 2) {
             const uint16_t* kr = ks + (long)j * lay.token;
 #pragma unroll
             for (int it = 0; it < NIT; ++it) {
@@ -141,10 +147,10 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
                 kv[it] = STREAM_ONCE ? __builtin_nontemporal_load(src) : *src;
             }
         } else {
-            const u32x4* kr = kb + (long)j * (row / 8);
+            const u32x4* kr = kb + (long)j * (LAYOUT == 0 ? NIT * kWave : nvec);
 #pragma unroll
             for (int it = 0; it < NIT; ++it)
-                kv[it] = STREAM_ONCE ? __builtin_nontemporal_load(kr + it * kWave + lane) : kr[it * kWave + lane];
+                kv[it] = STREAM_ONCE ? __builtin_nontemporal_load(kr + vec[it]) : kr[vec[it]];
         }
         float part[NIT];
 #pragma unroll
@@ -161,7 +167,8 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
         }
         if ((lane & (LPH - 1)) == 0) {
 #pragma unroll
-            for (int it = 0; it < NIT; ++it) lb[(long)j * p.H + it * HPI + lane / LPH] = part[it] * scale;
+            for (int it = 0; it < NIT; ++it)
+                if (LAYOUT == 0 || it * HPI + lane / LPH < p.H) lb[(long)j * p.H + it * HPI + lane / LPH] = part[it] * scale;
         }
     }
     if ((lane & (LPH - 1)) == 0) {
@@ -169,7 +176,7 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
         for (int it = 0; it < NIT; ++it) { s_m[wv][it * HPI + lane / LPH] = m[it]; s_z[wv][it * HPI + lane / LPH] = z[it]; }
     }
     __syncthreads();
-    for (int h = threadIdx.x; h < NIT * HPI; h += blockDim.x) {
+    for (int h = threadIdx.x; h < p.H; h += blockDim.x) {
         float mn = -INFINITY;
 #pragma unroll
         for (int w = 0; w < 4; ++w) mn = fmaxf(mn, s_m[w][h]);
@@ -186,6 +193,7 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
 // t, t+1024, ... (coalesced loads; the first one does not depend on the live length, so it is
 // requested before the length arrives).  IPT >= ceil(Lcap / 1024).  One round of global loads for
 // the common case, then block-level phases only.
+// LPE = lanes per entry = H / 4 where that is a power of two up to 8; 0: any other H that is a multiple of four.
 template <int IPT, int LPE>
 __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     DecodeDims p, const float* __restrict__ logits, const float2* __restrict__ stat_partial, int n_part,
@@ -194,9 +202,11 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     int32_t* __restrict__ holes, int32_t* __restrict__ movers, int32_t* __restrict__ n_move,
     int32_t* __restrict__ evicted_ids, int32_t* __restrict__ evicted_count)
 {
-    extern __shared__ int s_holes[];                 // [Lcap] evicted slots below the new length, then [Lcap] a_t
-    float* s_at = reinterpret_cast<float*>(s_holes + p.Lcap);
-    __shared__ float s_cm[1024], s_cz[1024];         // per head: max (log2 domain), 1 / (Z * H)
+    // [Lcap] a_t (and behind it, for LPE = 0, the waves' shares); once every thread has taken its a_t the same
+    // memory holds the list of evicted slots below the new length
+    extern __shared__ __attribute__((aligned(16))) int s_holes[];
+    float* s_at = reinterpret_cast<float*>(s_holes);
+    __shared__ __attribute__((aligned(16))) float s_cm[1024], s_cz[1024];    // per head: max (log2 domain), 1 / (Z * H)
     __shared__ int s_red[16];
     __shared__ int s_hist[kSelectHistInts];
     __shared__ uint64_t s_red64[16];
@@ -218,8 +228,9 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     // with LPE = H/4 fully coalesced 16-byte loads per lane; lane l then holds heads 4*(l%LPE)..+3 of
     // the entries u*(64/LPE) + l/LPE, u = 0..LPE-1.
     constexpr int PFR = IPT < 2 ? IPT : 2;           // rounds requested before the length is known
-    constexpr int EPI = kWave / LPE;                 // entries per load instruction
-    f32x4 lpf[PFR][LPE];
+    constexpr int LPE1 = LPE ? LPE : 1;
+    constexpr int EPI = kWave / LPE1;                // entries per load instruction
+    f32x4 lpf[PFR][LPE1];
 #pragma unroll
     for (int t = 0; t < PFR; ++t) {
         const int j = tid + t * 1024;
@@ -230,13 +241,13 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
         const int base = t * 1024 + wv * kWave;
 #pragma unroll
         for (int u = 0; u < LPE; ++u) {
-            const int e = base + u * EPI + lane / LPE;
+            const int e = base + u * EPI + lane / LPE1;
             lpf[t][u] = e < p.Lcap ? reinterpret_cast<const f32x4*>(lb + (long)base * H)[u * kWave + lane]
                                    : f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
-    // the logits kernel's partial statistics: `parts` consecutive lanes share a head, each takes a slice
-    const int parts = min(1024 / H, kWave), sh = tid / parts, sq = tid % parts;
+    // the logits kernel's partial statistics: `parts` consecutive lanes (a power of two) share a head, each takes a slice
+    const int parts = min(1 << (31 - __clz(1024 / H)), kWave), sh = tid / parts, sq = tid % parts;
     float mn = -INFINITY, zn = 0.f;
     if (sh < H) {
         const float2* sp = stat_partial + (long)b * n_part * H + sh;
@@ -282,7 +293,49 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     // so their statistics sit in registers; LPE lanes add up an entry's heads and one of them drops
     // the result in LDS, from where the entry's owner picks it up (same wave: LDS keeps program order).
     float a_new[IPT];
-    {
+    if constexpr (LPE == 0) {
+        // H / 4 = `vpe` vectors of 16 bytes per entry, not a power of two: a wave takes 32 entries at a time, 32 * vpe
+        // consecutive vectors.  A lane's vectors belong to changing heads, so it takes their statistics from LDS, and
+        // a vector's share goes through LDS to the lane that adds up the entry's shares, in head order.
+        const int vpe = H >> 2;
+        const uint32_t vmul = 65536u / (uint32_t)vpe + 1u;               // x / vpe = x * vmul >> 16 for x < 32 * vpe <= 1024
+        float* s_share = s_at + p.Lcap + wv * (32 * vpe);
+        for (int e0 = wv * kWave; e0 < n; e0 += (e0 & 32) ? 1024 - 32 : 32) {
+            const f32x4* lv = reinterpret_cast<const f32x4*>(lb + (long)e0 * H);
+            const int ne = min(n - e0, 32), nv = ne * vpe;               // live entries of this round, their vectors
+            for (int u0 = 0; u0 < nv; u0 += 5 * kWave) {
+                f32x4 v[5];
+#pragma unroll
+                for (int u = 0; u < 5; ++u) v[u] = lv[min(u0 + u * kWave + lane, nv - 1)];
+#pragma unroll
+                for (int u = 0; u < 5; ++u) {
+                    const int x = u0 + u * kWave + lane;
+                    if (x < nv) {
+                        const int g = x - (int)(((uint32_t)x * vmul) >> 16) * vpe;
+                        const f32x4 cm = reinterpret_cast<const f32x4*>(s_cm)[g], cz = reinterpret_cast<const f32x4*>(s_cz)[g];
+                        float part = fast_exp2(fmaf(v[u].x, kLog2eD, -cm.x)) * cz.x;
+                        part = fmaf(fast_exp2(fmaf(v[u].y, kLog2eD, -cm.y)), cz.y, part);
+                        part = fmaf(fast_exp2(fmaf(v[u].z, kLog2eD, -cm.z)), cz.z, part);
+                        part = fmaf(fast_exp2(fmaf(v[u].w, kLog2eD, -cm.w)), cz.w, part);
+                        s_share[x] = part;
+                    }
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (lane < ne) {
+                float sum = 0.f;
+                for (int c = 0; c < vpe; ++c) sum += s_share[lane * vpe + c];
+                s_at[e0 + lane] = sum;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+#pragma unroll
+        for (int t = 0; t < IPT; ++t) a_new[t] = live[t] ? fmaf(decay, a_old[t], s_at[tid + t * 1024]) : 0.f;
+    } else {
         float cm[4], cz[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) { cm[c] = s_cm[4 * (lane % LPE) + c]; cz[c] = s_cz[4 * (lane % LPE) + c]; }
@@ -792,9 +845,11 @@ int decode_evict_impl(
     const uint16_t* qp = static_cast<const uint16_t*>(q);
     const uint16_t* kp = static_cast<const uint16_t*>(k_cache);
     const int row_bytes = H * d * 2;
-    const int nit = row_bytes % 1024 == 0 ? row_bytes / 1024 : 0;
+    // 1 KiB pieces of a row, rounded up to a form that is compiled (a piece behind the row's end costs a cached load)
+    const int pieces = (row_bytes + 1023) / 1024;
+    const int nit = pieces <= 2 ? pieces : (pieces <= 4 ? 4 : (pieces <= 5 ? 5 : (pieces <= 8 ? 8 : (pieces <= 10 ? 10 : 16))));
     int n_part = 0;                                   // > 0: the logits kernel left per-block softmax statistics
-    if (d == 128 && (nit == 1 || nit == 2 || nit == 4 || nit == 8)) {
+    if ((d == 128 || d == 64) && pieces <= 16) {
         // streaming shape: about 16 waves per CU in flight, each striding over its sample's entries
         int blocks_x = (MD_DEC_BLOCKS + B - 1) / B;
         const int max_x = (Lcap + 3) / 4;
@@ -802,29 +857,30 @@ int decode_evict_impl(
         if (blocks_x > kMaxStatParts) blocks_x = kMaxStatParts;
         if (blocks_x < 1) blocks_x = 1;
         dim3 g1(blocks_x, B);
-#define MD_STREAM2(NIT_, S_, O_)                                                                                   \
-        MD_LAUNCH("decode_logits", st, (decode_logits_stream_kernel<16, NIT_, S_, O_>), g1, 256, 0,                \
-            qp, kp, len, p, lay, softmax_scale, w.logits, w.stat_partial)
-#define MD_STREAM(NIT_, S_) do { if (stream_once) MD_STREAM2(NIT_, S_, true); else MD_STREAM2(NIT_, S_, false); } while (0)
         // a cache beyond half of the 256 MB Infinity Cache is streamed; a smaller one is kept cached for
         // the row moves that follow
         const bool stream_once = cache_bytes > (size_t)128 << 20;
-        if (dense) {
-            switch (nit) {
-                case 1: MD_STREAM(1, false); break;
-                case 2: MD_STREAM(2, false); break;
-                case 4: MD_STREAM(4, false); break;
-                default: MD_STREAM(8, false); break;
-            }
-        } else {
-            switch (nit) {
-                case 1: MD_STREAM(1, true); break;
-                case 2: MD_STREAM(2, true); break;
-                case 4: MD_STREAM(4, true); break;
-                default: MD_STREAM(8, true); break;
-            }
+#define MD_STREAM2(LPH_, NIT_, Y_, O_)                                                                             \
+        MD_LAUNCH("decode_logits", st, (decode_logits_stream_kernel<LPH_, NIT_, Y_, O_>), g1, 256, 0,              \
+            qp, kp, len, p, lay, softmax_scale, w.logits, w.stat_partial)
+#define MD_STREAM1(LPH_, NIT_)                                                                                     \
+        do {                                                                                                       \
+            if (!dense) { if (stream_once) MD_STREAM2(LPH_, NIT_, 2, true); else MD_STREAM2(LPH_, NIT_, 2, false); }                 \
+            else if (row_bytes == NIT_ * 1024) { if (stream_once) MD_STREAM2(LPH_, NIT_, 0, true); else MD_STREAM2(LPH_, NIT_, 0, false); } \
+            else { if (stream_once) MD_STREAM2(LPH_, NIT_, 1, true); else MD_STREAM2(LPH_, NIT_, 1, false); }                        \
+        } while (0)
+#define MD_STREAM(NIT_) do { if (d == 128) MD_STREAM1(16, NIT_); else MD_STREAM1(8, NIT_); } while (0)
+        switch (nit) {
+            case 1: MD_STREAM(1); break;
+            case 2: MD_STREAM(2); break;
+            case 4: MD_STREAM(4); break;
+            case 5: MD_STREAM(5); break;
+            case 8: MD_STREAM(8); break;
+            case 10: MD_STREAM(10); break;
+            default: MD_STREAM(16); break;
         }
 #undef MD_STREAM2
+#undef MD_STREAM1
 #undef MD_STREAM
         n_part = blocks_x;
     } else {
@@ -841,9 +897,11 @@ int decode_evict_impl(
             default: MD_LAUNCH("decode_logits", st, (decode_logits_kernel<64>), g1, 256, 0, qp, kp, len, p, lay, softmax_scale, tpb, w.logits); break;
         }
     }
-    const bool fast_h = H == 4 || H == 8 || H == 16 || H == 32 || H == 64;
-    if (n_part > 0 && Lcap <= 8192 && fast_h) {
-        const size_t lds = 2 * sizeof(int) * (size_t)Lcap;
+    // selection in registers: up to 8192 slots, and heads in fours (a power of two up to 32: sums over lanes; any other
+    // number, where a wave's shares still fit the 64 KB a launch gets: sums through LDS)
+    const bool lane_sums = H == 4 || H == 8 || H == 16 || H == 32;
+    const size_t lds = sizeof(int) * ((size_t)Lcap + (lane_sums ? 0 : 16 * 32 * ((size_t)H / 4)));
+    if (n_part > 0 && Lcap <= 8192 && H % 4 == 0 && H <= 128 && lds <= 64 * 1024) {
         const int ipt = (Lcap + 1023) / 1024;
 #define MD_SELECT_FAST(I, E)                                                                                       \
     MD_LAUNCH("decode_select", st, (decode_select_fast_kernel<I, E>), B, 1024, lds,                          \
@@ -855,7 +913,7 @@ int decode_evict_impl(
         case 8: MD_SELECT_FAST(I, 2); break;                                                                       \
         case 16: MD_SELECT_FAST(I, 4); break;                                                                      \
         case 32: MD_SELECT_FAST(I, 8); break;                                                                      \
-        default: MD_SELECT_FAST(I, 16); break;                                                                     \
+        default: MD_SELECT_FAST(I, 0); break;                                                                      \
     }
         if (ipt <= 1) { MD_SELECT_FAST_H(1) }
         else if (ipt <= 2) { MD_SELECT_FAST_H(2) }
