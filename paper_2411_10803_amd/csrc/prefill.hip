@@ -27,13 +27,13 @@ namespace md {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kMaxChunks = 8;                        // key chunks per (sample, head) in the row-statistics sweep, at most
+constexpr int kMaxChunks = 16;                       // key chunks per (sample, head) in the row-statistics sweep, at most
 
 struct PrefillDims {
     int B, Mv, N, H, d, C, L;
     int nch;          // key chunks per (sample, head) in the row-statistics sweep
-    int chunk;        // keys per chunk (multiple of 128)
     int Npad;         // 32 * (number of 32-row text blocks)
+    int ng;           // text groups a sample of N text rows has (see text_group)
     int Rcap;
     KvLayout q, kv;   // element strides of q_txt and of k (v shares them)
 };
@@ -72,11 +72,12 @@ struct LdsRows {
     // One wave instruction: rows slot_row .. slot_row+RPL-1 of the LDS block at `lds_base` (wave-uniform)
     // receive the global rows grow0+slot_row.. of the matrix behind `rs` (rows row_bytes apart).
     // `live` (wave-uniform) false: nothing is fetched.
+    template <bool STREAM = false>
     __device__ static __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, uint32_t row_bytes, int grow0, int slot_row,
                                                  char* lds_base, int lane, bool live) {
         const int row = slot_row + lane / CH, pos = lane % CH;
         const uint32_t off = live ? (uint32_t)(grow0 + row) * row_bytes + (uint32_t)((pos ^ swz(row)) << 4) : 0xFFFFFF00u;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(lds_base + slot_row * ROWB), 16, off, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(lds_base + slot_row * ROWB), 16, off, 0, 0, STREAM ? 2 : 0);
     }
     // LDS byte address of this lane's fragment row in the 32-row tile at `tile` (aligned to 32*ROWB),
     // with the swizzle and the lane half folded in; chunk index ks is applied with XOR.
@@ -136,6 +137,21 @@ __device__ __forceinline__ int wave_max_int(int v) {
 }
 __device__ __forceinline__ int effective_rows(int last, int Mv) { return last < 0 ? 0 : min(Mv, (last + 32) & ~31); }
 
+// What the kernels that follow need to know of a sample, written by the first one of a call.
+struct SampleRows { int vision; int text_blocks; };   // effective vision rows; 32-row blocks with text rows below txt_len
+// A block of a sweep holds up to `nbw` 32-row text blocks, one per wave column.  More of them (longer prompts) are
+// cut into groups that share them out evenly, counted over the blocks that hold rows of the sample at hand: a sample
+// with a short prompt has fewer groups than the longest one, or none, and columns without a block only help to move K.
+struct TextGroup { int first, count; };
+__device__ __forceinline__ int text_blocks_of(int tl) { return (tl + 31) >> 5; }
+__device__ __forceinline__ int text_groups_of(int blocks, int nbw) { return (blocks + nbw - 1) / nbw; }
+__device__ __forceinline__ TextGroup text_group(int g, int blocks, int groups) {
+    if (groups <= 1) return TextGroup{0, blocks};
+    // blocks / groups for at most 32 blocks: (blocks + 1/2) / groups stays 1/16 away from the next whole number
+    const int base = (int)(((float)blocks + 0.5f) * __builtin_amdgcn_rcpf((float)groups)), extra = blocks - base * groups;
+    return TextGroup{g * base + min(g, extra), base + (g < extra ? 1 : 0)};
+}
+
 // Row statistics folded into one constant: a probability of the head mean is
 // exp2(s*scale*log2e + c) with c = -m - log2(Z) - log2(H); text rows beyond txt_len get -inf (-> 0).
 __device__ __forceinline__ float fold_stats(float m, float z, bool row_ok, int H) {
@@ -169,9 +185,9 @@ __device__ __forceinline__ void load_query_frags(const uint16_t* qb, long tok_st
 }
 
 // ---------------------------------------------------------------------------------------------
-// Sweep 1: row statistics.  Block = (key chunk x text group, head, sample), 4 waves.  The waves of a
+// Sweep 1: row statistics.  Block = (key chunk, text group, head, sample), 4 or 8 waves.  The waves of a
 // block share every K tile through LDS: wave w works on text block w % NBW of the group and on key
-// tile w / NBW of the TW = 4/NBW tiles in flight per step, so a wave keeps the fragments of ONE
+// tile w / NBW of the TW tiles in flight per step, so a wave keeps the fragments of ONE
 // 32-row text block in registers and K is read once per block.  K tiles stream through S LDS slots
 // (filled S-1 steps ahead, no staging registers); one block barrier per step.  Inside a step the
 // MFMA chain of the current tile is issued before the softmax arithmetic of the previous one (two
@@ -240,11 +256,11 @@ __device__ __forceinline__ void interleave_mfma_valu() {
     }
 }
 
-template <int NBW, int TW, int KS>
+template <int NBW, int TW, int KS, bool STREAM>
 __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     const uint16_t* __restrict__ q_txt, const uint16_t* __restrict__ k,
     const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ txt_len, PrefillDims p, float scale_log2e,
-    float2* __restrict__ partial, float* __restrict__ cstat, bf16x8* __restrict__ qfrag, int32_t* __restrict__ mv_eff)
+    float2* __restrict__ partial, float* __restrict__ cstat, bf16x8* __restrict__ qfrag, SampleRows* __restrict__ rows)
 {
     using T = LdsRows<KS>;
     // NBW wave columns (one 32-row text block each) x TW tile lanes (one 32-key tile of a step each): four waves,
@@ -252,8 +268,9 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     // in LDS instead of in a separate kernel
     constexpr int NW = NBW * TW;
     // LDS slots.  The eight-wave form runs with two (one step in flight while one is worked on): with more
-    // requests outstanding per CU the sweep gets slower, not faster, when K comes from HBM (46.3 against 47.9 us)
-    constexpr int S = TW == 1 ? 4 : (NW == 8 ? 2 : 3);
+    // requests outstanding per CU the sweep gets slower, not faster, when K comes from HBM (46.3 against 47.9 us);
+    // four tile lanes too: three slots of 128 rows would leave room for one block per CU instead of two
+    constexpr int S = TW == 1 ? 4 : (NBW == 1 || NBW == 4 ? 2 : 3);
     constexpr int SLOT_ROWS = 32 * TW, SLOT_BYTES = SLOT_ROWS * T::ROWB;
     constexpr int NLW = SLOT_ROWS / T::RPL / NW;      // load instructions per wave and step
     constexpr int QBYTES = NBW * 32 * T::ROWB;        // the block's query tiles during the prologue (one per wave column)
@@ -263,10 +280,24 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     __shared__ int s_last[NW];
     const int lane = lane_id(), wv = wave_id();
     const int nbw = wv % NBW, tw = wv / NBW;
-    const int ch = blockIdx.x % p.nch, tg = blockIdx.x / p.nch, h = blockIdx.y, b = blockIdx.z;
-    const int nbg = tg * NBW + nbw;                   // 32-row text block of this wave
-    const int i0 = 32 * nbg;
+    // one text group: grid (chunk, head, sample).  Several: the blocks of one (chunk, head, sample) read the same K at the
+    // same time, so they follow each other on one XCD (blocks go round-robin over the 8 XCDs, each with its own L2)
+    int ch = blockIdx.x, tg = 0, h = blockIdx.y, b = blockIdx.z;
+    if (p.ng > 1) {
+        const int q = (int)blockIdx.x >> 3;
+        tg = q % p.ng;
+        int item = (q / p.ng) * 8 + ((int)blockIdx.x & 7);
+        if (item >= p.B * p.H * p.nch) return;
+        ch = item % p.nch; item /= p.nch;
+        h = item % p.H; b = item / p.H;
+    }
     const int tl = txt_len ? min(max(txt_len[b], 0), p.N) : p.N;
+    const int nbl = text_blocks_of(tl), ngl = text_groups_of(nbl, NBW);
+    if (tg > 0 && tg >= ngl) return;                  // (group 0 stays: it says how many rows matter)
+    const TextGroup grp = ngl > 0 ? text_group(tg, nbl, ngl) : TextGroup{0, 0};
+    const int nbg = grp.first + nbw;                  // 32-row text block of this wave
+    const bool live = nbw < grp.count;
+    const int i0 = 32 * nbg;
     const uint16_t* kb = k + (long)b * p.kv.batch + (long)h * p.kv.head;
     const uint16_t* qb = q_txt + (long)b * p.q.batch + (long)h * p.q.head;
     const uint8_t* vb = vis_valid ? vis_valid + (long)b * p.Mv : nullptr;
@@ -293,7 +324,7 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
 #pragma unroll
         for (int t = 0; t < NLW; ++t) {
             const int sr = (t * NW + wv) * T::RPL;
-            T::issue(rk, krow, row0 + (row0 + sr >= Me ? jump : 0), sr, slot, lane, true);
+            T::template issue<STREAM>(rk, krow, row0 + (row0 + sr >= Me ? jump : 0), sr, slot, lane, true);
         }
     };
     // Validity of the 32 keys of this wave's tile in the steps g0 .. g0+63: lane l fetches the 32 mask bytes of
@@ -353,15 +384,15 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
         for (int w2 = 1; w2 < NW; ++w2) last = max(last, s_last[w2]);
         Me = effective_rows(last, p.Mv);
         plan();
-        if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0) mv_eff[b] = Me;   // for the second sweep
+        if (ch == 0 && tg == 0 && h == 0 && threadIdx.x == 0) rows[b] = SampleRows{Me, nbl};   // for the second sweep
         const int ahead = min(S - 1, max(nit, nit_guess));
         if (ahead > 0 && step_row0(ahead - 1) + SLOT_ROWS > Me) {            // a requested step reaches beyond Me: again, with the jump
 #pragma unroll
             for (int g = 0; g < S - 1; ++g)
                 if (g < nit) issue_step(g);
         }
-    } else if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0) {
-        mv_eff[b] = p.Mv;
+    } else if (ch == 0 && tg == 0 && h == 0 && threadIdx.x == 0) {
+        rows[b] = SampleRows{p.Mv, nbl};
     }
 
     float m = -INFINITY, z = 0.f;
@@ -389,10 +420,13 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
         return pd;
     };
     // Step g: wait for its tiles, refill the slot of step g-1, fragments of this wave's tile.
-    auto fetch = [&](int g, bf16x8 (&kf)[KS]) {
+    auto advance = [&](int g) {
         if (g + S - 2 < nit) { MD_VM_WAIT((S - 2) * NLW); } else { MD_VM_WAIT(0); }   // this wave's part of step g has landed
         block_sync_lds();                             // ... and everyone else's; step g-1's slot is free
         if (g + S - 1 < nit) issue_step(g + S - 1);
+    };
+    auto fetch = [&](int g, bf16x8 (&kf)[KS]) {
+        advance(g);
         T::frags(T::frag_base(s_k + (g % S) * SLOT_BYTES + tw * 32 * T::ROWB, lane), kf);
     };
     // The MFMA chain of step g is issued together with the arithmetic on the tile of step g-1.
@@ -412,6 +446,10 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     };
     f32x16 accA, accB;
     Pending pend{true, 0xFFFFu};
+    if (!live) {                                      // wave-uniform: no text rows here, K still comes in through every wave
+        for (int g = 0; g < nit; ++g) advance(g);
+        nit = 0;
+    }
     if (nit > 0) {
         bf16x8 kf[KS];
         fetch(0, kf);
@@ -431,7 +469,7 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     }
     MD_VM_WAIT(0);
     // the fragment-major copy of the text queries for the second sweep (here, where no load waits behind the stores)
-    if (ch == 0 && tw == 0 && nbg < p.Npad / 32) {
+    if (ch == 0 && tw == 0 && live) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
             qfrag[((((long)b * p.H + h) * (p.Npad / 32) + nbg) * KS + ks) * kWave + lane] = qf[ks];
@@ -455,8 +493,8 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
 #pragma unroll
             for (int t = 0; t < TW; ++t) zn += s_z[t * NBW + nb][r] * fast_exp2(s_m[t * NBW + nb][r] - mn);
         }
-        const int ii = 32 * (tg * NBW + nb) + r;
-        if (ii < p.Npad) {
+        const int ii = 32 * (grp.first + nb) + r;
+        if (nb < grp.count) {
             if (p.nch == 1)     // the only chunk: fold the statistics right away (see fold_stats)
                 cstat[((long)b * p.H + h) * p.Npad + ii] = fold_stats(mn, zn, ii < tl, p.H);
             else
@@ -477,7 +515,7 @@ __global__ __launch_bounds__(256) void prefill_cstat_kernel(
     const int tl = txt_len ? min(max(txt_len[b], 0), p.N) : p.N;
     const float2* pp = partial + bh * p.nch * p.Npad + i;
     float mn = -INFINITY, zn = 0.f;
-    for (int c = 0; c < p.nch; ++c) {
+    for (int c = 0; c < (i < tl ? p.nch : 0); ++c) {   // (nothing was written for text blocks beyond txt_len)
         const float2 v = pp[(long)c * p.Npad];
         const float m2 = fmaxf(mn, v.x);
         if (m2 > -INFINITY) zn = zn * fast_exp2(mn - m2) + v.y * fast_exp2(v.x - m2);
@@ -492,7 +530,7 @@ template <int KS>
 __global__ __launch_bounds__(256) void prefill_qpack_kernel(
     const uint16_t* __restrict__ q_txt, const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ txt_len,
     const float* __restrict__ row_lse, PrefillDims p, bf16x8* __restrict__ qfrag, float* __restrict__ cstat,
-    int32_t* __restrict__ mv_eff)
+    SampleRows* __restrict__ rows)
 {
     using T = LdsRows<KS>;
     __shared__ __attribute__((aligned(1024))) char s_q[4 * 32 * T::ROWB];
@@ -510,7 +548,8 @@ __global__ __launch_bounds__(256) void prefill_qpack_kernel(
             __syncthreads();
             last = max(max(s_last[0], s_last[1]), max(s_last[2], s_last[3]));
         }
-        if (threadIdx.x == 0) mv_eff[b] = effective_rows(last, p.Mv);
+        if (threadIdx.x == 0)
+            rows[b] = SampleRows{effective_rows(last, p.Mv), text_blocks_of(txt_len ? min(max(txt_len[b], 0), p.N) : p.N)};
         return;
     }
     const long item = (long)blockIdx.x * 4 + wv;
@@ -540,7 +579,9 @@ __global__ __launch_bounds__(256) void prefill_qpack_kernel(
 // [p*U/P, (p+1)*U/P), ordered (sample, key group, head), whatever the shape: no block count has to
 // match the chip.  A block of 4 waves holds a [kb keys x 32*NBW text rows] tile of a[i][j] in
 // registers (wave w: text block w % NBW, the KT key tiles of tile lane w / NBW) and adds one head's
-// probabilities per unit.  Per unit the kb K rows go global -> registers -> LDS (two slots; the rows
+// probabilities per unit.  With more than 128 text rows the text groups are units of their own in the same launch, next to
+// each other: 3 x 4608 keys, 100 to 300 text rows, 84 us with one launch per group and all of them full, 47 us now;
+// key groups of 128 there: 47 and 2 us more for the pieces.  Per unit the kb K rows go global -> registers -> LDS (two slots; the rows
 // of unit u+2 are requested while unit u is worked on), the wave's text-query fragments come from
 // qfrag (coalesced).  The row statistics are folded into one constant per (head, text row):
 // p = exp2(s*scale*log2e + c), c = -m - log2(Z*H) (cstat: from sweep 1, or from the caller's
@@ -549,39 +590,69 @@ __global__ __launch_bounds__(256) void prefill_qpack_kernel(
 // "piece" (fp32, key-major); prefill_colfix_kernel adds a key group's pieces in a fixed order and
 // reduces over the text rows (Eq. 8 / Eq. 10).  Which block holds which piece is a function of the
 // shapes alone, so the result does not depend on timing.
-struct ColPlan { int P; long U; int nkg; int Gmax; int kb; };   // kb: vision keys per unit (a power of two)
+struct ColPlan { int P; long U; int nkg; int Gmax; int kb; int nbw; };   // kb: vision keys per unit (a power of two); nbw: text blocks
 
-__host__ __device__ __forceinline__ int unit_block(long u, int P, long U) { return (int)(((u + 1) * P - 1) / U); }
+// n / d; the index arithmetic of the sweeps fits 32 bits at all but the largest sizes, and a 64-bit division is four
+// times the instructions
+__device__ __forceinline__ long index_div(long n, long d) {
+    return ((n | d) >> 32) == 0 ? (long)((uint32_t)n / (uint32_t)d) : n / d;
+}
+__device__ __forceinline__ int unit_block(long u, int P, long U) { return (int)index_div((u + 1) * P - 1, U); }
 
-// The same decomposition over the key groups that matter (mv_eff, one entry per sample; written by the
-// kernel before this sweep): sample b owns the tiles [tile0(b), tile0(b) + ceil(mv_eff[b] / 128)).
-// Fewer units than the host planned for means fewer blocks at work only where a key group would
+// The same decomposition over what matters (SampleRows, one entry per sample; written by the kernel before this
+// sweep): a sample has key_groups(vision) x text_groups(text_blocks) tiles, the text groups of a key group next to
+// each other, so that the blocks that read the same K rows run side by side on one XCD.
+// Fewer units than the host planned for means fewer blocks at work only where a tile would
 // otherwise be cut into more pieces than the workspace holds (Gmax).
-struct ColRun { long U; int P; int tile0; int nk; };
 __device__ __forceinline__ int key_groups(int rows, int kb) { return (rows + kb - 1) / kb; }
-__device__ __forceinline__ ColRun effective_run(const int32_t* __restrict__ mv_eff, int B, int H, ColPlan cp, int bq) {
-    int tiles = 0, tile0 = 0, nk = 0;
-    for (int b = 0; b < B; ++b) {
-        const int n = key_groups(mv_eff[b], cp.kb);
-        if (b == bq) { tile0 = tiles; nk = n; }
-        tiles += n;
+struct SampleTiles { int b, tile0, nk, nbl, nt; };                // a sample: first tile, key groups, text blocks and groups
+// All samples at once, one per lane (64 at a time): the number of tiles, and in `s` the sample that holds tile `t`
+// (find_tile) or sample `t` itself.  One vector load and a lane scan; a loop over scalar loads is a dependent chain.
+__device__ __forceinline__ int find_sample(const SampleRows* __restrict__ rows, int B, ColPlan cp, bool find_tile, int t, SampleTiles& s) {
+    if (B == 1) {
+        const SampleRows r = rows[0];
+        s = SampleTiles{0, 0, key_groups(r.vision, cp.kb), r.text_blocks, text_groups_of(r.text_blocks, cp.nbw)};
+        return s.nk * s.nt;
     }
+    const int lane = lane_id();
+    int tiles = 0;
+    s = SampleTiles{0, 0, 0, 0, 0};
+    for (int b0 = 0; b0 < B; b0 += kWave) {
+        const int b = b0 + lane;
+        const SampleRows r = rows[min(b, B - 1)];
+        const int nk = key_groups(r.vision, cp.kb), nt = text_groups_of(r.text_blocks, cp.nbw);
+        const int n = b < B ? nk * nt : 0;
+        const int incl = wave_incl_scan_i(n) + tiles;
+        const unsigned long long hit = __ballot(find_tile ? incl > t && n > 0 && incl - n <= t : b == t);
+        if (hit) {
+            const int l = __builtin_ctzll(hit);
+            s.b = b0 + l;
+            s.tile0 = __builtin_amdgcn_readlane(incl - n, l);
+            s.nk = __builtin_amdgcn_readlane(nk, l);
+            s.nbl = __builtin_amdgcn_readlane(r.text_blocks, l);
+            s.nt = __builtin_amdgcn_readlane(nt, l);
+        }
+        tiles = __builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+    return tiles;
+}
+struct ColRun { long U; int P; };
+__device__ __forceinline__ ColRun effective_run(int tiles, int H, ColPlan cp) {
     ColRun r;
     r.U = (long)tiles * H;
-    long P = (long)(cp.Gmax - 1) * tiles;             // pieces per key group <= ceil(H*P/U) + 1 <= Gmax
+    long P = (long)(cp.Gmax - 1) * tiles;             // pieces per tile <= ceil(H*P/U) + 1 <= Gmax
     if (cp.Gmax >= H || P > cp.P) P = cp.P;
     if (P >= 8) P &= ~7L;                             // whole rounds over the 8 XCDs
     if (P < 1) P = 1;
     r.P = (int)P;
-    r.tile0 = tile0;
-    r.nk = nk;
     return r;
 }
 
-template <int NBW, int KT, int KS>
+// MULTI: samples may have several text groups.
+template <int NBW, int KT, int KS, bool MULTI>
 __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
     const bf16x8* __restrict__ qfrag, const uint16_t* __restrict__ k, const float* __restrict__ cstat,
-    const int32_t* __restrict__ mv_eff, PrefillDims p, ColPlan cp, float scale_log2e, int tgrp, float* __restrict__ apart)
+    const SampleRows* __restrict__ rows, PrefillDims p, ColPlan cp, float scale_log2e, float* __restrict__ apart)
 {
     constexpr int TW = 4 / NBW;
     constexpr int KB = 32 * TW * KT;                  // keys per unit (= cp.kb)
@@ -595,46 +666,56 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
     const int nbw = wv % NBW, tw = wv / NBW;
     // Blocks go round-robin over the 8 XCDs (each with its own L2): the blocks of one XCD take neighbouring
     // runs, so a sample's query fragments are fetched into one or two L2s, not all eight.
-    const ColRun run = effective_run(mv_eff, p.B, p.H, cp, -1);
+    SampleTiles st0;
+    const ColRun run = effective_run(find_sample(rows, p.B, cp, false, 0, st0), p.H, cp);
     const int P = run.P;
     const long U = run.U;
     if ((int)blockIdx.x >= P) return;
     const int pb = (P % 8 == 0) ? (int)(blockIdx.x % 8) * (P / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
-    const long u0 = (long)pb * U / P, u1 = (long)(pb + 1) * U / P;
+    const long u0 = index_div((long)pb * U, P), u1 = index_div((long)(pb + 1) * U, P);
     if (u0 >= u1) return;
     const int nbt = p.Npad / 32;
-    const int nbg = tgrp * NBW + nbw;                 // 32-row text block of this wave (may lie beyond the prompt)
-    const bool has_rows = nbg < nbt;
-    const int nbc = has_rows ? nbg : 0;
-    const int i = 32 * nbc + (lane & 31);
     const long tok_stride = p.kv.token;
 
-    // unit u = (tile, head); tile = (sample, key group), counted over the key groups that matter.  The
+    // unit u = (tile, head); tile = (sample, key group, text group), counted over the ones that matter.  The
     // block walks its run with three cursors (the unit being worked on, the one whose fragments are
     // requested, the one whose K rows are requested), each advanced without divisions.
-    struct Unit { int b, kg, h, nk, t; };             // nk: key groups of sample b; t: tile index
+    struct Unit { int b, kg, tg, h, nk, nt, nbl, t; };   // nk, nt, nbl: key groups, text groups, text blocks of sample b; t: tile
+    auto at_sample = [&](Unit& x) {
+        const SampleRows r = rows[x.b];
+        x.nk = key_groups(r.vision, KB); x.nbl = r.text_blocks; x.nt = MULTI ? text_groups_of(x.nbl, NBW) : min(x.nbl, 1);
+    };
     auto unit_at = [&](long u) -> Unit {
         Unit x;
-        x.t = (int)(u / p.H);
+        x.t = (int)index_div(u, p.H);
         x.h = (int)(u - (long)x.t * p.H);
-        int first = 0;
-        x.b = 0; x.kg = 0; x.nk = 1;
-        for (int b = 0; b < p.B; ++b) {
-            const int n = key_groups(mv_eff[b], KB);
-            if (x.t >= first && x.t < first + n) { x.b = b; x.kg = x.t - first; x.nk = n; }
-            first += n;
-        }
+        SampleTiles st;
+        find_sample(rows, p.B, cp, true, x.t, st);
+        x.b = st.b; x.nk = st.nk; x.nt = st.nt; x.nbl = st.nbl;
+        x.kg = MULTI ? (x.t - st.tile0) / st.nt : x.t - st.tile0;
+        x.tg = MULTI ? x.t - st.tile0 - x.kg * st.nt : 0;
         return x;
     };
     auto advance = [&](Unit& x) {
         if (++x.h == p.H) {
             x.h = 0;
             ++x.t;
-            if (++x.kg == x.nk) {
-                x.kg = 0;
-                do { ++x.b; x.nk = x.b < p.B ? key_groups(mv_eff[x.b], KB) : 1; } while (x.nk == 0);
+            if (!MULTI || ++x.tg == x.nt) {
+                x.tg = 0;
+                if (++x.kg == x.nk) {
+                    x.kg = 0;
+                    do {
+                        if (++x.b == p.B) break;      // behind the last unit
+                        at_sample(x);
+                    } while (x.nk * x.nt == 0);
+                }
             }
         }
+    };
+    // this wave's 32-row text block in a unit's group; -1: the group has none for it
+    auto text_block = [&](const Unit& x) {
+        const TextGroup g = MULTI ? text_group(x.tg, x.nbl, x.nt) : TextGroup{0, x.nbl};
+        return nbw < g.count ? g.first + nbw : -1;
     };
     // This wave's share of a unit's K rows: NLW x 1 KiB; rows beyond the last vision key repeat it.
     // (`live` false, past the end of the run: every lane reads the same 16 bytes -- the loads stay
@@ -654,15 +735,14 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
 #pragma unroll
         for (int t = 0; t < NLW; ++t) *reinterpret_cast<u32x4*>(base + (t * 4 + wv) * RPL * PITCH) = st[t];
     };
-    auto load_q = [&](const Unit& x, bool live, bf16x8 (&qf)[KS]) {
-        const bf16x8* qh = qfrag + (((long)x.b * p.H + x.h) * nbt + nbc) * KS * kWave + (live ? lane : 0);
+    auto load_q = [&](const Unit& x, int nb, bool live, bf16x8 (&qf)[KS]) {
+        const bf16x8* qh = qfrag + (((long)x.b * p.H + x.h) * nbt + max(nb, 0)) * KS * kWave + (live ? lane : 0);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[ks] = qh[live ? ks * kWave : 0];
     };
     // folded row statistic of this lane's text row for the unit's head (-inf beyond txt_len)
-    auto load_c = [&](const Unit& x) -> float {
-        const float c = cstat[((long)x.b * p.H + x.h) * p.Npad + i];
-        return has_rows ? c : -INFINITY;
+    auto load_c = [&](const Unit& x, int nb) -> float {
+        return cstat[((long)x.b * p.H + x.h) * p.Npad + 32 * max(nb, 0) + (lane & 31)];
     };
     auto frags = [&](int slot, int kt, bf16x8 (&f)[KS]) {
         const char* q = s_k + slot * SLOT_BYTES + ((tw * KT + kt) * 32 + (lane & 31)) * PITCH + (lane >> 5) * 16;
@@ -681,11 +761,11 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
 #pragma unroll
             for (int r = 0; r < 16; ++r) a_acc[kt][r] = 0.f;
     };
-    // the piece of key group (x.b, x.kg) this block holds: apart[piece][b][j][i], text rows contiguous
-    auto flush = [&](const Unit& x) {
+    // the piece of the unit's tile that this block holds: apart[piece][b][j][i], text rows contiguous
+    auto flush = [&](const Unit& x, int nb) {
         const int piece = pb - unit_block((long)x.t * p.H, P, U);
-        if (has_rows) {
-            float* ap = apart + (((long)piece * p.B + x.b) * p.Mv) * p.Npad + i;
+        if (nb >= 0) {
+            float* ap = apart + (((long)piece * p.B + x.b) * p.Mv) * p.Npad + 32 * nb + (lane & 31);
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
@@ -701,8 +781,9 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
     bf16x8 qf[KS];
     Unit xc = unit_at(u0), xq = xc, xk = xc;         // cursors: current unit, fragments, K rows
     load_k(xk, true, st);
-    load_q(xq, true, qf);
-    float c_cur = load_c(xq), c_nxt = 0.f;
+    int nbc = text_block(xc), nbq = nbc;             // text blocks of the current unit and of the one whose fragments are requested
+    load_q(xq, nbq, true, qf);
+    float c_cur = load_c(xq, nbq), c_nxt = 0.f;
     store_k(0, st);
     if (u0 + 1 < u1) advance(xk);
     load_k(xk, u0 + 1 < u1, st);
@@ -716,8 +797,9 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
         store_k(slot ^ 1, st);                        // unit u+1
         if (u + 2 < u1) advance(xk);
         load_k(xk, u + 2 < u1, st);                   // unit u+2
-        if (u + 1 < u1) advance(xq);
-        c_nxt = load_c(xq);
+        if (u + 1 < u1) { advance(xq); nbq = text_block(xq); }
+        c_nxt = load_c(xq, nbq);
+        if (nbc >= 0) {                               // wave-uniform
         bf16x8 kfA[KS], kfB[KS];
         f32x16 accA, accB;
         frags(slot, 0, kfA);
@@ -736,14 +818,18 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
                 add_probs(a_acc[kt - 1], accB, c_cur);
             }
         }
-        load_q(xq, u + 1 < u1, qf);                   // unit u+1
+        load_q(xq, nbq, u + 1 < u1, qf);              // unit u+1
         add_probs(a_acc[KT - 1], ((KT - 1) & 1) ? accB : accA, c_cur);
+        } else {
+            load_q(xq, nbq, u + 1 < u1, qf);
+        }
         c_cur = c_nxt;
-        if (xc.h == p.H - 1 || u + 1 == u1) {         // the run leaves this key group
-            flush(xc);
+        if (xc.h == p.H - 1 || u + 1 == u1) {         // the run leaves this tile
+            flush(xc, nbc);
             clear_acc();
         }
         advance(xc);
+        nbc = nbq;
     };
     long u = u0;
     for (; u + 1 < u1; u += 2) {
@@ -758,26 +844,28 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
 // key group, same pieces), lanes over text rows; all loads of a piece are in flight together.
 constexpr int kFixKeys = 4;
 __global__ __launch_bounds__(256) void prefill_colfix_kernel(
-    const float* __restrict__ apart, const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ mv_eff,
+    const float* __restrict__ apart, const uint8_t* __restrict__ vis_valid, const SampleRows* __restrict__ rows,
     PrefillDims p, ColPlan cp, float* __restrict__ Vout, float* __restrict__ Iout)
 {
     const int lane = lane_id(), wv = wave_id(), b = blockIdx.y;
     const long gstride = (long)p.B * p.Mv * p.Npad;
     const int j0 = (blockIdx.x * 4 + wv) * kFixKeys;
     if (j0 >= p.Mv) return;
-    const ColRun run = effective_run(mv_eff, p.B, p.H, cp, b);
+    SampleTiles sm;
+    const ColRun run = effective_run(find_sample(rows, p.B, cp, false, b, sm), p.H, cp);
     // keys behind the rows that matter: no pieces were written, their scores are zero
-    const bool skipped = j0 / cp.kb >= run.nk;
-    const long tile = run.tile0 + j0 / cp.kb;
-    const int npieces = skipped ? 0 : unit_block(tile * p.H + p.H - 1, run.P, run.U) - unit_block(tile * p.H, run.P, run.U) + 1;
+    const int kg = j0 / cp.kb;
     float s[kFixKeys], mx[kFixKeys];
 #pragma unroll
     for (int q = 0; q < kFixKeys; ++q) { s[q] = 0.f; mx[q] = 0.f; }
-    for (int i0 = 0; i0 < p.Npad; i0 += 2 * kWave) {
-        // two text rows per lane and round (lanes beyond Npad read a valid row and drop it)
-        const int ia = i0 + lane, ib = i0 + kWave + lane;
-        const bool oka = ia < p.Npad, okb = ib < p.Npad;
-        const int ca = oka ? ia : 0, cb = okb ? ib : 0;
+    for (int tg = 0; tg < (kg < sm.nk ? sm.nt : 0); ++tg) {
+        const long tile = sm.tile0 + (long)kg * sm.nt + tg;
+        const int npieces = unit_block(tile * p.H + p.H - 1, run.P, run.U) - unit_block(tile * p.H, run.P, run.U) + 1;
+        const TextGroup grp = text_group(tg, sm.nbl, sm.nt);
+        // two text rows per lane: a group has at most 2 * kWave of them (lanes beyond read a valid row and drop it)
+        const int n = 32 * grp.count;
+        const bool oka = lane < n, okb = kWave + lane < n;
+        const int ca = 32 * grp.first + (oka ? lane : 0), cb = 32 * grp.first + (okb ? kWave + lane : 0);
         float a0[kFixKeys], a1[kFixKeys];
 #pragma unroll
         for (int q = 0; q < kFixKeys; ++q) { a0[q] = 0.f; a1[q] = 0.f; }
@@ -1126,56 +1214,63 @@ __global__ __launch_bounds__(256) void prefill_compact_strided_kernel(
     for (int c = threadIdx.x; c < kvn; c += blockDim.x) {
         const int h = c / lph, w = c - h * lph;
         const long so = sbase + (long)h * p.kv.head + w * 8, d_o = dbase + (long)h * out.head + w * 8;
-        const u32x4 a = *reinterpret_cast<const u32x4*>(k + so);
-        const u32x4 c2 = *reinterpret_cast<const u32x4*>(v + so);
+        const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k + so));
+        const u32x4 c2 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v + so));
         *reinterpret_cast<u32x4*>(k_out + d_o) = a;
-        *reinterpret_cast<u32x4*>(v_out + d_o) = c2;
+        __builtin_nontemporal_store(c2, reinterpret_cast<u32x4*>(v_out + d_o));
     }
     const int hv = p.C / 8;
     const u32x4* hs = hidden + ((long)b * p.L + src) * hv;
     u32x4* hd = hidden_out + ((long)b * rows_cap + o) * hv;
-    for (int c = threadIdx.x; c < hv; c += blockDim.x) hd[c] = hs[c];
+    for (int c = threadIdx.x; c < hv; c += blockDim.x) __builtin_nontemporal_store(__builtin_nontemporal_load(hs + c), hd + c);
 }
 
 struct PrefillWorkspace {
     float2* partial; float* cstat; bf16x8* qfrag; float* apart; float* V; float* I; float* score; int32_t* src_row;
-    int32_t* mv_eff;
+    SampleRows* rows;
     size_t bytes;
 };
 
-#ifndef MD_RS_BLOCKS
-#define MD_RS_BLOCKS 512   // target number of blocks of the row-statistics sweep (two per CU)
-#endif
-
-
 // Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, chunk, rs_waves; ColPlan col; int occ; };
+struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream; ColPlan col; int occ; };
 constexpr int kNumCU = 256;                          // MI355X
 
-ScorePlan plan_scores(int B, int Mv, int N, int H) {
+ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     ScorePlan s;
     s.nbt = (N + 31) / 32;                            // 32-row text blocks
-    s.nbw = s.nbt == 1 ? 1 : (s.nbt == 2 ? 2 : 4);    // text blocks per block (one per wave or wave pair)
-    s.ng = (s.nbt + s.nbw - 1) / s.nbw;               // text groups: K is read once per group
-    // sweep 1: chunks of whole 128-key units, enough blocks to fill the chip a few times, at least
-    // four units per chunk
+    s.nbw = s.nbt == 1 ? 1 : (s.nbt == 2 ? 2 : 4);    // text blocks per block, one per wave column
+    s.ng = (s.nbt + s.nbw - 1) / s.nbw;               // text groups: each goes over K, side by side
+    // sweep 1: blocks of four waves (two per CU) or of eight (one per CU; the chunks two small blocks would take meet in
+    // LDS), and the number of key chunks per (sample, head, text group), at least four 128-key units each.  Whole rounds
+    // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start
+    // (5), the keys it takes (ns per key, from alone on the chip to every place taken), the merge kernel for several chunks.
+    // Measured to within 20 % at 17 shapes; before -> after e.g. 13 x 1039 keys, 32 heads, 10 text rows: 36.6 -> 23.1,
+    // 6 x 1152 keys, 384 text rows: 250 -> 69, 5 x 774 keys, 16 heads, 60 text rows: 14.5 -> 13.1.
     const int units = (Mv + N + 127) / 128;
-    int nch = (MD_RS_BLOCKS + B * H * s.ng - 1) / (B * H * s.ng);
-    // four text blocks and two chunks per (sample, head): one block of eight waves takes both halves instead
-    // (same number of waves on the chip, the halves' statistics meet in LDS, no merge kernel)
-    s.rs_waves = 4;
-    if (s.nbw == 4 && nch == 2) { s.rs_waves = 8; nch = 1; }
-    if (nch > units / 4) nch = units / 4;
-    if (nch < 1) nch = 1;
-    if (nch > kMaxChunks) nch = kMaxChunks;
-    const int upc = (units + nch - 1) / nch;
-    s.chunk = upc * 128;
-    s.nch = (units + upc - 1) / upc;
+    const long n = (long)B * H * s.ng;
+    double best = 0;
+    for (int waves = 4; waves <= 8; waves += 4)
+        for (int nch = 1; nch <= kMaxChunks && (nch == 1 || nch <= units / 4); ++nch) {
+            const long blocks = n * nch, places = waves == 4 ? 2 * kNumCU : kNumCU;
+            const double fill = blocks < places ? (double)blocks / places : 1.0;
+            const double alone = s.nbw == 1 ? 7.5 : (s.nbw == 2 ? (waves == 8 ? 8.0 : 9.0) : (waves == 8 ? 11.0 : 14.0));
+            const double full = waves == 8 ? (s.nbw < 4 ? 11.5 : (s.ng > 1 ? 15.0 : 16.0)) : (s.nbw < 4 ? 21.0 : (s.ng > 1 ? 26.0 : 34.0));
+            const double per_key = alone + (full - alone) * fill;
+            const double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? 5.0 : 0.0);
+            if (best == 0 || t < 0.97 * best) { best = t; s.rs_waves = waves; s.nch = nch; }
+        }
+    // a vision K that outgrows the Infinity Cache before the second sweep comes to it is read with streaming loads: what
+    // the first sweep leaves in the cache then only has to be pushed out again (6 x 6009 keys, 32 heads: both sweeps 147 ->
+    // 136 us, 16 x 2880: 201 -> 188); where a good part of it survives, plain loads (8 x 2880 with 3/4 of the slots
+    // valid: 85 against 88).  Up to 64 text rows the line lies lower (3 x 5523, 40 heads, 170 MB: 81 -> 73; 13 x 1029, 110 MB: 49 -> 52)
+    const double k_mb = (double)B * Mv * H * d * 2 / 1e6;
+    s.rs_stream = k_mb > (s.nbw <= 2 ? 160.0 : 230.0);
     // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
     ColPlan& c = s.col;
     c.kb = s.nbw == 1 ? 128 : 64;
     c.nkg = (Mv + c.kb - 1) / c.kb;
-    c.U = (long)B * c.nkg * H;
+    c.nbw = s.nbw;
+    c.U = (long)B * c.nkg * H * s.ng;
     // blocks per CU: two where a block holds four text blocks (the second block covers the first one's waits),
     // and with two text blocks when the runs stay long enough (20 units per CU); otherwise one (fewer, longer
     // runs: fewer pieces, fewer prologues; measured faster there)
@@ -1194,7 +1289,7 @@ ScorePlan plan_scores(int B, int Mv, int N, int H) {
 PrefillWorkspace carve_prefill(void* base, int B, int Mv, int N, int H, int Rcap) {
     Carver c(base);
     PrefillWorkspace w;
-    const ScorePlan s = plan_scores(B, Mv, N, H);
+    const ScorePlan s = plan_scores(B, Mv, N, H, 128);     // (the sizes do not depend on d)
     const int Npad = s.nbt * 32;
     w.partial = c.take<float2>((size_t)B * H * s.nch * Npad);
     w.cstat = c.take<float>((size_t)B * H * Npad);
@@ -1204,7 +1299,7 @@ PrefillWorkspace carve_prefill(void* base, int B, int Mv, int N, int H, int Rcap
     w.I = c.take<float>((size_t)B * Mv);
     w.score = c.take<float>((size_t)B * Mv);
     w.src_row = c.take<int32_t>((size_t)B * (Rcap + N));
-    w.mv_eff = c.take<int32_t>((size_t)B);
+    w.rows = c.take<SampleRows>((size_t)B);
     w.bytes = c.off;
     return w;
 }
@@ -1215,14 +1310,20 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
     const uint16_t* qp = static_cast<const uint16_t*>(q_txt);
     const uint16_t* kp = static_cast<const uint16_t*>(k);
     if (!row_lse) {
-        dim3 g1(p.nch * s.ng, p.H, p.B);
+        const dim3 g1 = s.ng == 1 ? dim3(p.nch, p.H, p.B) : dim3((unsigned)(((long)p.nch * p.H * p.B + 7) / 8 * 8 * s.ng));
 #define MD_ROWSTATS(NBW_, TW_)                                                                                 \
-        MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_kernel<NBW_, TW_, KS>), g1, 64 * NBW_ * TW_, 0,   \
-            qp, kp, vis_valid, txt_len, p, scale_log2e, w.partial, w.cstat, w.qfrag, w.mv_eff)
-        if (s.nbw == 1) MD_ROWSTATS(1, 4);
-        else if (s.nbw == 2) MD_ROWSTATS(2, 2);
-        else if (s.rs_waves == 8) MD_ROWSTATS(4, 2);
-        else MD_ROWSTATS(4, 1);
+        do {                                                                                                   \
+            if (s.rs_stream)                                                                                   \
+                MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_kernel<NBW_, TW_, KS, true>), g1, 64 * NBW_ * TW_, 0, \
+                    qp, kp, vis_valid, txt_len, p, scale_log2e, w.partial, w.cstat, w.qfrag, w.rows);          \
+            else                                                                                               \
+                MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_kernel<NBW_, TW_, KS, false>), g1, 64 * NBW_ * TW_, 0, \
+                    qp, kp, vis_valid, txt_len, p, scale_log2e, w.partial, w.cstat, w.qfrag, w.rows);          \
+        } while (0)
+        const bool big = s.rs_waves == 8;
+        if (s.nbw == 1) { if (big) MD_ROWSTATS(1, 8); else MD_ROWSTATS(1, 4); }
+        else if (s.nbw == 2) { if (big) MD_ROWSTATS(2, 4); else MD_ROWSTATS(2, 2); }
+        else { if (big) MD_ROWSTATS(4, 2); else MD_ROWSTATS(4, 1); }
 #undef MD_ROWSTATS
         if (p.nch > 1) {
             const long n = (long)p.B * p.H * p.Npad;
@@ -1231,20 +1332,19 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
     } else {
         const long items = (long)p.B * p.H * s.nbt;
         MD_LAUNCH("prefill_qpack", st, (prefill_qpack_kernel<KS>), (unsigned)((items + 3) / 4 + p.B), 256, 0, qp, vis_valid, txt_len,
-                  row_lse, p, w.qfrag, w.cstat, w.mv_eff);
+                  row_lse, p, w.qfrag, w.cstat, w.rows);
     }
-    for (int tg = 0; tg < s.ng; ++tg) {
-#define MD_COLSCORE(NBW_, KT_)                                                                                 \
-        MD_LAUNCH("prefill_colscore", st, (prefill_colscore_kernel<NBW_, KT_, KS>), s.col.P, 256, 0,           \
-            w.qfrag, kp, w.cstat, w.mv_eff, p, s.col, scale_log2e, tg, w.apart)
-        // 32 * (4 / NBW) * KT keys per unit = s.col.kb
-        if (s.nbw == 1) MD_COLSCORE(1, 1);
-        else if (s.nbw == 2) MD_COLSCORE(2, 1);
-        else MD_COLSCORE(4, 2);
+#define MD_COLSCORE(NBW_, KT_, M_)                                                                             \
+    MD_LAUNCH("prefill_colscore", st, (prefill_colscore_kernel<NBW_, KT_, KS, M_>), s.col.P, 256, 0,               \
+        w.qfrag, kp, w.cstat, w.rows, p, s.col, scale_log2e, w.apart)
+    // 32 * (4 / NBW) * KT keys per unit = s.col.kb
+    if (s.nbw == 1) MD_COLSCORE(1, 1, false);
+    else if (s.nbw == 2) MD_COLSCORE(2, 1, false);
+    else if (s.ng == 1) MD_COLSCORE(4, 2, false);
+    else MD_COLSCORE(4, 2, true);
 #undef MD_COLSCORE
-    }
     const int fx = (p.Mv + 4 * kFixKeys - 1) / (4 * kFixKeys);          // four waves of kFixKeys keys per block
-    MD_LAUNCH("prefill_colfix", st, (prefill_colfix_kernel), dim3(fx, p.B), 256, 0, w.apart, vis_valid, w.mv_eff, p, s.col, w.V, w.I);
+    MD_LAUNCH("prefill_colfix", st, (prefill_colfix_kernel), dim3(fx, p.B), 256, 0, w.apart, vis_valid, w.rows, p, s.col, w.V, w.I);
     return MD_OK;
 }
 
@@ -1323,9 +1423,9 @@ int prefill_filter_impl(
     PrefillDims p;
     p.B = B; p.Mv = Mv; p.N = N; p.H = H; p.d = d; p.C = C; p.L = Mv + N; p.Rcap = Rcap;
     p.q = lq; p.kv = lkv;
-    const ScorePlan sp = plan_scores(B, Mv, N, H);
+    const ScorePlan sp = plan_scores(B, Mv, N, H, d);
     p.Npad = sp.nbt * 32;
-    p.nch = sp.nch; p.chunk = sp.chunk;
+    p.nch = sp.nch; p.ng = sp.ng;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const float sl2 = softmax_scale * kLog2e;
 
