@@ -7,10 +7,11 @@
 //                         contiguous) is read once with 16-byte loads, 16 lanes per head slice;
 //                         segmented butterflies give the H logits.  Pure streaming: a GEMV at about
 //                         1 flop per byte, so plain ALUs, not MFMA.
-//   decode_select_kernel  one block per sample: softmax statistics per head, head mean, running
-//                         score update, radix top-k among unprotected entries, hole/mover lists,
-//                         moves of the small per-entry arrays
-//   decode_move_kernel    copies the K and V rows of the movers into the holes
+//   decode_select_fast_kernel / decode_select_kernel
+//                         softmax statistics per head, head mean, running score update, radix top-k among
+//                         unprotected entries, hole/mover lists, moves of the small per-entry arrays; for
+//                         short or few caches also the row moves (several blocks per sample, the same selection in each)
+//   decode_move_kernel    copies the K and V rows of the movers into the holes, where many may move
 #include "md_device.hpp"
 #include "md_host.hpp"
 
@@ -21,6 +22,9 @@ constexpr float kLog2eD = 1.4426950408889634f;
 
 struct DecodeDims { int B, Lcap, H, d; };
 constexpr int kMaxStatParts = 256;               // blocks per sample of the streaming logits kernel
+
+// The small per-entry state of a cache, [B, Lcap] each and len [B].
+struct StateArrays { float* acc; int32_t* ids; uint8_t* protect; int32_t* len; };
 
 // logits[b][j][h] = scale * q[b][h] . k[b][j][h]      (token-major so an entry's H logits are contiguous)
 // LPH = lanes per head slice = d / 8.  Generic shape: walks an entry's row in 1 KiB pieces.
@@ -105,7 +109,8 @@ __device__ __forceinline__ float dot8(const u32x4& a, const float (&qv)[8]) {
 template <int LPH, int NIT, int LAYOUT, bool STREAM_ONCE>
 __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache, const int32_t* __restrict__ len,
-    DecodeDims p, KvLayout lay, float scale, float* __restrict__ logits, float2* __restrict__ stat_partial)
+    DecodeDims p, KvLayout lay, float scale, float* __restrict__ logits, float2* __restrict__ stat_partial,
+    StateArrays state, StateArrays copy)
 {
     constexpr int HPI = kWave / LPH;                 // heads per load instruction
     __shared__ float s_m[4][NIT * HPI], s_z[4][NIT * HPI];
@@ -137,6 +142,14 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
     for (int it = 0; it < NIT; ++it) { m[it] = -INFINITY; z[it] = 0.f; }
 
     const int n = min(max(len[b], 0), p.Lcap);
+    // the state as it is before the selection changes it, for the other selection blocks of the sample
+    if (copy.acc) {
+        for (int j = blockIdx.x * 256 + threadIdx.x; j < n; j += gridDim.x * 256) {
+            const long i = (long)b * p.Lcap + j;
+            copy.acc[i] = state.acc[i]; copy.ids[i] = state.ids[i]; copy.protect[i] = state.protect[i];
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) copy.len[b] = n;
+    }
     for (int j = wave_global; j < n; j += nwaves) {
         u32x4 kv[NIT];
         if constexpr (LAYOUT == 2) {
@@ -189,7 +202,41 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
     }
 }
 
-// Selection with everything in registers.  Entries are dealt round-robin: thread t owns the entries
+// Rows movers[t] -> holes[t] for t = first, first + step, ... < m of one sample's caches, by a team of 256 threads.
+// Source rows (beyond the new length) and destination rows (holes below it) never coincide, but
+// the compiler cannot know: the vectors of a round are read into registers before any is written.
+// The V rows are not read on this path at all (only moved): always streamed; the K rows where the caches are too large
+// to stay in the Infinity Cache until the next step reads them.
+template <bool STREAM_ONCE>
+__device__ __forceinline__ void move_rows(const DecodeDims& p, const KvLayout& lay, const int* holes, const int* movers, int m,
+                                          int first, int step, int tid, uint16_t* k, uint16_t* v) {
+    const int lph = p.d / 8, sh = __builtin_ctz(lph), rv = p.H << sh;        // 16-byte vectors per head slice (a power of two), per row
+    for (int t = first; t < m; t += step) {
+        const long src = (long)movers[t] * lay.token, dst = (long)holes[t] * lay.token;
+        for (int c = tid; c < rv; c += 512) {
+            const int c2 = c + 256;
+            const bool two = c2 < rv;
+            const long o = (long)(c >> sh) * lay.head + (c & (lph - 1)) * 8, o2 = (long)(c2 >> sh) * lay.head + (c2 & (lph - 1)) * 8;
+            auto at = [](uint16_t* q, long e) { return reinterpret_cast<u32x4*>(q + e); };
+            auto ld = [](const u32x4* q) { return STREAM_ONCE ? __builtin_nontemporal_load(q) : *q; };
+            auto st = [](u32x4* q, const u32x4& x) { if (STREAM_ONCE) __builtin_nontemporal_store(x, q); else *q = x; };
+            const u32x4 k0 = ld(at(k, src + o)), v0 = __builtin_nontemporal_load(at(v, src + o));
+            u32x4 k1 = k0, v1 = v0;
+            if (two) { k1 = ld(at(k, src + o2)); v1 = __builtin_nontemporal_load(at(v, src + o2)); }
+            st(at(k, dst + o), k0);
+            __builtin_nontemporal_store(v0, at(v, dst + o));
+            if (two) { st(at(k, dst + o2), k1); __builtin_nontemporal_store(v1, at(v, dst + o2)); }
+        }
+    }
+}
+
+// Selection with everything in registers.  Two forms:
+//   moves in the same launch (n_move null): gridDim.x blocks per sample work out the same selection, each from the
+//     logits and an unchanged copy of the state (`in`; with one block per sample the state itself), the first one writes
+//     the new state, and they share the rows to move.  The selection is a chain of latencies on a chip that is idle
+//     beside it, and a launch of its own for the moves costs 4 us more.
+//   lists (one block per sample): holes, movers and their number go to decode_move_kernel.
+// Entries are dealt round-robin: thread t owns the entries
 // t, t+1024, ... (coalesced loads; the first one does not depend on the live length, so it is
 // requested before the length arrives).  IPT >= ceil(Lcap / 1024).  One round of global loads for
 // the common case, then block-level phases only.
@@ -197,28 +244,44 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
 template <int IPT, int LPE>
 __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     DecodeDims p, const float* __restrict__ logits, const float2* __restrict__ stat_partial, int n_part,
-    float decay, int budget,
-    float* __restrict__ acc, int32_t* __restrict__ ids, uint8_t* __restrict__ protect, int32_t* __restrict__ len,
+    float decay, int budget, StateArrays in, StateArrays out, KvLayout lay, uint16_t* k_cache, uint16_t* v_cache, int stream_once,
     int32_t* __restrict__ holes, int32_t* __restrict__ movers, int32_t* __restrict__ n_move,
     int32_t* __restrict__ evicted_ids, int32_t* __restrict__ evicted_count)
 {
     // [Lcap] a_t (and behind it, for LPE = 0, the waves' shares); once every thread has taken its a_t the same
-    // memory holds the list of evicted slots below the new length
+    // memory holds the list of evicted slots below the new length and, in its second half, that of the kept ones behind it
     extern __shared__ __attribute__((aligned(16))) int s_holes[];
     float* s_at = reinterpret_cast<float*>(s_holes);
     __shared__ __attribute__((aligned(16))) float s_cm[1024], s_cz[1024];    // per head: max (log2 domain), 1 / (Z * H)
     __shared__ int s_red[16];
     __shared__ int s_hist[kSelectHistInts];
     __shared__ uint64_t s_red64[16];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+    __shared__ int s_rounds[16 * IPT];
+    const int b = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+    const bool writer = blockIdx.x == 0;
     if (tid < 256) s_hist[tid] = 0;                  // for block_select_topk, after later barriers
     const int H = p.H;
     const float* lb = logits + (long)b * p.Lcap * H;
-    float* ab = acc + (long)b * p.Lcap;
-    int32_t* ib = ids + (long)b * p.Lcap;
-    uint8_t* pb = protect + (long)b * p.Lcap;
-    int32_t* hb = holes + (long)b * p.Lcap;
-    int32_t* mvb = movers + (long)b * p.Lcap;
+    const float* ai = in.acc + (long)b * p.Lcap;
+    const int32_t* ii = in.ids + (long)b * p.Lcap;
+    const uint8_t* pi = in.protect + (long)b * p.Lcap;
+    float* ab = out.acc + (long)b * p.Lcap;
+    int32_t* ib = out.ids + (long)b * p.Lcap;
+    uint8_t* pb = out.protect + (long)b * p.Lcap;
+    k_cache += (long)b * lay.batch;
+    v_cache += (long)b * lay.batch;
+    auto move = [&](const int* from, const int* to, int m) {             // `from`, `to` in LDS
+        if (n_move) {                                // up to four rows, one for each team, are moved here all the same
+            if (tid == 0) n_move[b] = m > 4 ? m : 0;
+            if (m > 4) {
+                for (int t = tid; t < m; t += 1024) { movers[(long)b * p.Lcap + t] = from[t]; holes[(long)b * p.Lcap + t] = to[t]; }
+                return;
+            }
+        }
+        const int first = blockIdx.x * 4 + (tid >> 8), step = gridDim.x * 4;
+        if (stream_once) move_rows<true>(p, lay, to, from, m, first, step, tid & 255, k_cache, v_cache);
+        else move_rows<false>(p, lay, to, from, m, first, step, tid & 255, k_cache, v_cache);
+    };
 
     // ---- requests that do not depend on the live length
     float a_old[IPT];
@@ -234,10 +297,10 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
 #pragma unroll
     for (int t = 0; t < PFR; ++t) {
         const int j = tid + t * 1024;
-        const bool in = j < p.Lcap;                  // readable whatever the live length is
-        a_old[t] = in ? ab[j] : 0.f;
-        id[t] = in ? ib[j] : 0;
-        prot[t] = in ? pb[j] != 0 : false;
+        const bool there = j < p.Lcap;               // readable whatever the live length is
+        a_old[t] = there ? ai[j] : 0.f;
+        id[t] = there ? ii[j] : 0;
+        prot[t] = there ? pi[j] != 0 : false;
         const int base = t * 1024 + wv * kWave;
 #pragma unroll
         for (int u = 0; u < LPE; ++u) {
@@ -258,9 +321,10 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
             mn = m2;
         }
     }
-    const int n = min(max(len[b], 0), p.Lcap);
+    const int n = min(max(in.len[b], 0), p.Lcap);
     if (n == 0) {
-        if (tid == 0) { n_move[b] = 0; if (evicted_count) evicted_count[b] = 0; }
+        if (writer && tid == 0 && evicted_count) evicted_count[b] = 0;
+        if (n_move && tid == 0) n_move[b] = 0;
         return;
     }
 #pragma unroll
@@ -272,9 +336,9 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     for (int t = PFR; t < IPT; ++t) {                // further rounds only for long caches
         const int j = tid + t * 1024;
         live[t] = j < n;
-        a_old[t] = live[t] ? ab[j] : 0.f;
-        id[t] = live[t] ? ib[j] : 0;
-        prot[t] = live[t] ? pb[j] != 0 : false;
+        a_old[t] = live[t] ? ai[j] : 0.f;
+        id[t] = live[t] ? ii[j] : 0;
+        prot[t] = live[t] ? pi[j] != 0 : false;
     }
     // the lanes of a head finish the merge: group maximum, then the group sum of the rescaled sums
     {
@@ -370,9 +434,11 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     np = block_sum_i(np, s_red);
 
     if (n <= budget) {                               // nothing leaves: only the scores change
+        if (!writer) return;
 #pragma unroll
         for (int t = 0; t < IPT; ++t) if (live[t]) ab[tid + t * 1024] = a_new[t];
-        if (tid == 0) { n_move[b] = 0; if (evicted_count) evicted_count[b] = 0; }
+        if (tid == 0 && evicted_count) evicted_count[b] = 0;
+        if (n_move && tid == 0) n_move[b] = 0;
         return;
     }
     const int nu = n - np;
@@ -385,15 +451,18 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     if (nu - extra == 1) {
         // Steady state of a decode loop: exactly one entry leaves -- the smallest key.  If it is not
         // the last live slot, the last entry (a survivor) moves into its place.
+        if (!writer) return;
         uint64_t mine = ~0ull;
         int mine_slot = 0;
 #pragma unroll
         for (int t = 0; t < IPT; ++t) if (key[t] != 0 && key[t] < mine) { mine = key[t]; mine_slot = tid + t * 1024; }
         const uint64_t victim = block_min_u64(mine, s_red64);
-        __shared__ int s_vslot;
-        if (mine == victim) s_vslot = mine_slot;     // keys are unique: one writer
+        __shared__ int s_pair[2];
+        if (mine == victim) s_pair[0] = mine_slot;   // keys are unique: one writer
+        if (tid == 0) s_pair[1] = n - 1;
         __syncthreads();
-        const int vslot = s_vslot, last = n - 1;
+        const int vslot = s_pair[0], last = n - 1;
+        move(s_pair + 1, s_pair, vslot != last ? 1 : 0);
 #pragma unroll
         for (int t = 0; t < IPT; ++t) {
             const int j = tid + t * 1024;
@@ -401,17 +470,13 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
             if (j == vslot) {
                 if (evicted_ids) evicted_ids[(long)b * p.Lcap] = id[t];
                 if (j == last) ab[j] = a_new[t];     // stays behind the new end, as the oracle leaves it
-            } else if (j == last && vslot != last) {
-                ab[vslot] = a_new[t]; ib[vslot] = id[t]; pb[vslot] = prot[t] ? 1 : 0;
-                ab[j] = a_new[t];
-                hb[0] = vslot; mvb[0] = last;
             } else {
+                if (j == last) { ab[vslot] = a_new[t]; ib[vslot] = id[t]; pb[vslot] = prot[t] ? 1 : 0; }
                 ab[j] = a_new[t];
             }
         }
         if (tid == 0) {
-            n_move[b] = vslot != last ? 1 : 0;
-            len[b] = new_len;
+            out.len[b] = new_len;
             if (evicted_count) evicted_count[b] = 1;
         }
         return;
@@ -422,46 +487,56 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
 #pragma unroll
     for (int t = 0; t < IPT; ++t)
         keep[t] = live[t] && (prot[t] || (extra > 0 && (key[t] >> sb.shift) >= sb.bound));
-    // hole / mover / evicted lists in ascending slot order: one pass of block scans per round of entries
-    int run_h = 0, run_m = 0, run_e = 0;
+    // hole / mover / evicted lists in ascending slot order.  Holes are counted in the low half of a word, movers in the
+    // high half; an evicted slot's rank is its hole rank below the new length, and behind it what the kept ones leave.
+    int cnt[IPT], pre[IPT];
+#pragma unroll
+    for (int t = 0; t < IPT; ++t) {
+        const int j = tid + t * 1024;
+        const unsigned long long h = __ballot(live[t] && !keep[t] && j < new_len), mv = __ballot(live[t] && keep[t] && j >= new_len);
+        cnt[t] = __popcll(h) | (__popcll(mv) << 16);
+        pre[t] = lanes_below(h) | (lanes_below(mv) << 16);
+    }
+    int wave_pre[IPT];
+    const int m = block_round_prefixes<IPT>(cnt, wave_pre, s_rounds) & 0xFFFF;      // as many movers as holes
+    int* s_movers = s_holes + p.Lcap / 2;
     int mrank[IPT];
 #pragma unroll
     for (int t = 0; t < IPT; ++t) {
         mrank[t] = -1;
-        if (t * 1024 >= n) continue;                 // block-uniform
-        const int j = tid + t * 1024;
-        const bool is_hole = live[t] && !keep[t] && j < new_len;
-        const bool is_mover = live[t] && keep[t] && j >= new_len;
-        const bool is_ev = live[t] && !keep[t];
-        int tot_hm, tot_e;
-        const int pre_hm = block_exscan_i((is_hole ? 1 : 0) | (is_mover ? 1 << 16 : 0), s_red, tot_hm);
-        const int pre_e = block_exscan_i(is_ev ? 1 : 0, s_red, tot_e);
-        if (is_hole) { const int r = run_h + (pre_hm & 0xFFFF); s_holes[r] = j; hb[r] = j; }
-        if (is_mover) { mrank[t] = run_m + (pre_hm >> 16); mvb[mrank[t]] = j; }
-        if (is_ev && evicted_ids) evicted_ids[(long)b * p.Lcap + run_e + pre_e] = id[t];
-        run_h += tot_hm & 0xFFFF; run_m += tot_hm >> 16; run_e += tot_e;
-    }
-    __syncthreads();
-    // write the scores back; a mover's state goes straight to its hole (no overlap: holes < new_len <= movers)
-#pragma unroll
-    for (int t = 0; t < IPT; ++t) {
         const int j = tid + t * 1024;
         if (!live[t]) continue;
-        if (mrank[t] >= 0) {
-            const int dst = s_holes[mrank[t]];
-            ab[dst] = a_new[t];
-            ib[dst] = id[t];
-            pb[dst] = prot[t] ? 1 : 0;
-            ab[j] = a_new[t];
-        } else if (keep[t] || j >= new_len) {
-            ab[j] = a_new[t];
+        const int hr = (pre[t] + wave_pre[t]) & 0xFFFF, mr = (pre[t] + wave_pre[t]) >> 16;
+        if (keep[t]) {
+            if (j >= new_len) { mrank[t] = mr; s_movers[mr] = j; }
+        } else {
+            if (j < new_len) s_holes[hr] = j;
+            if (writer && evicted_ids) evicted_ids[(long)b * p.Lcap + (j < new_len ? hr : j - (new_len - m) - mr)] = id[t];
         }
     }
-    if (tid == 0) {
-        n_move[b] = run_m;
-        len[b] = new_len;
-        if (evicted_count) evicted_count[b] = run_e;
+    __syncthreads();
+    if (writer) {
+        // write the scores back; a mover's state goes straight to its hole (no overlap: holes < new_len <= movers)
+#pragma unroll
+        for (int t = 0; t < IPT; ++t) {
+            const int j = tid + t * 1024;
+            if (!live[t]) continue;
+            if (mrank[t] >= 0) {
+                const int dst = s_holes[mrank[t]];
+                ab[dst] = a_new[t];
+                ib[dst] = id[t];
+                pb[dst] = prot[t] ? 1 : 0;
+                ab[j] = a_new[t];
+            } else if (keep[t] || j >= new_len) {
+                ab[j] = a_new[t];
+            }
+        }
+        if (tid == 0) {
+            out.len[b] = new_len;
+            if (evicted_count) evicted_count[b] = n - new_len;
+        }
     }
+    move(s_movers, s_holes, m);
 }
 
 __global__ __launch_bounds__(1024) void decode_select_kernel(
@@ -757,6 +832,7 @@ __global__ __launch_bounds__(256) void decode_append_strided_kernel(
 
 struct DecodeWorkspace {
     float* logits; float2* stat_partial; uint8_t* keep; int32_t* holes; int32_t* movers; int32_t* n_move;
+    StateArrays copy;
     size_t bytes;
 };
 
@@ -769,6 +845,8 @@ DecodeWorkspace carve_decode(void* base, int B, int Lcap, int H) {
     w.holes = c.take<int32_t>((size_t)B * Lcap);
     w.movers = c.take<int32_t>((size_t)B * Lcap);
     w.n_move = c.take<int32_t>((size_t)B);
+    // (the general selection's keep flags and lists and the streaming one's copy of the state are never in use together)
+    w.copy = StateArrays{reinterpret_cast<float*>(w.holes), w.movers, w.keep, w.n_move};
     w.bytes = c.off;
     return w;
 }
@@ -849,6 +927,28 @@ int decode_evict_impl(
     const int pieces = (row_bytes + 1023) / 1024;
     const int nit = pieces <= 2 ? pieces : (pieces <= 4 ? 4 : (pieces <= 5 ? 5 : (pieces <= 8 ? 8 : (pieces <= 10 ? 10 : 16))));
     int n_part = 0;                                   // > 0: the logits kernel left per-block softmax statistics
+    // selection in registers: up to 8192 slots, and heads in fours (a power of two up to 32: sums over lanes; any other
+    // number, where a wave's shares still fit the 64 KB a launch gets: sums through LDS)
+    const bool lane_sums = H == 4 || H == 8 || H == 16 || H == 32;
+    const size_t select_lds = sizeof(int) * ((size_t)Lcap + (lane_sums ? 0 : 16 * 32 * ((size_t)H / 4)));
+    const bool select_fast = (d == 128 || d == 64) && pieces <= 16 && Lcap <= 8192 && H % 4 == 0 && H <= 128 && select_lds <= 64 * 1024;
+    // Moves in the selection's launch: blocks per sample that together cover the CUs, with no more teams than rows that
+    // can leave, and reading no more than 32 MB of logits between them.  Where that leaves neither half the chip nor all
+    // the teams, the caches are long or many, and a launch for the moves is the smaller price (us, one launch / two:
+    // 4 x 778 entries of 40 heads 13.1 / 15.7, 1 x 1724 of 16 heads 8.7 / 12.8, 60 x 748 of 40 heads 14.4 / 16.7;
+    // 64 x 1025 of 4352 slots 18.4 / 16.2, 18 x 4036 40.4 / 25.8, 64 x 4096 cut to 1024 407 / 387)
+    int select_x = (256 + B - 1) / B;
+    const long leave_x = Lcap > budget ? (Lcap - budget + 3l) / 4 : 1, read_x = (32l << 20) / ((long)B * Lcap * H * 4);
+    if (select_x > leave_x) select_x = (int)leave_x;
+    if (select_x > 32) select_x = 32;
+    if (select_x > read_x) select_x = (int)read_x;
+    const bool one_launch = select_fast && select_x >= 1 && (select_x * (long)B >= 128 || select_x == leave_x || select_x == 32);
+    if (!one_launch) select_x = 1;
+    const StateArrays state{acc, ids, protect, len};
+    const StateArrays copy = one_launch && select_x > 1 ? w.copy : StateArrays{nullptr, nullptr, nullptr, nullptr};
+    // a cache beyond half of the 256 MB Infinity Cache is streamed; a smaller one is kept cached for
+    // the row moves and the steps that follow
+    const bool stream_once = cache_bytes > (size_t)128 << 20;
     if ((d == 128 || d == 64) && pieces <= 16) {
         // streaming shape: about 16 waves per CU in flight, each striding over its sample's entries
         int blocks_x = (MD_DEC_BLOCKS + B - 1) / B;
@@ -857,12 +957,9 @@ int decode_evict_impl(
         if (blocks_x > kMaxStatParts) blocks_x = kMaxStatParts;
         if (blocks_x < 1) blocks_x = 1;
         dim3 g1(blocks_x, B);
-        // a cache beyond half of the 256 MB Infinity Cache is streamed; a smaller one is kept cached for
-        // the row moves that follow
-        const bool stream_once = cache_bytes > (size_t)128 << 20;
 #define MD_STREAM2(LPH_, NIT_, Y_, O_)                                                                             \
         MD_LAUNCH("decode_logits", st, (decode_logits_stream_kernel<LPH_, NIT_, Y_, O_>), g1, 256, 0,              \
-            qp, kp, len, p, lay, softmax_scale, w.logits, w.stat_partial)
+            qp, kp, len, p, lay, softmax_scale, w.logits, w.stat_partial, state, copy)
 #define MD_STREAM1(LPH_, NIT_)                                                                                     \
         do {                                                                                                       \
             if (!dense) { if (stream_once) MD_STREAM2(LPH_, NIT_, 2, true); else MD_STREAM2(LPH_, NIT_, 2, false); }                 \
@@ -897,16 +994,13 @@ int decode_evict_impl(
             default: MD_LAUNCH("decode_logits", st, (decode_logits_kernel<64>), g1, 256, 0, qp, kp, len, p, lay, softmax_scale, tpb, w.logits); break;
         }
     }
-    // selection in registers: up to 8192 slots, and heads in fours (a power of two up to 32: sums over lanes; any other
-    // number, where a wave's shares still fit the 64 KB a launch gets: sums through LDS)
-    const bool lane_sums = H == 4 || H == 8 || H == 16 || H == 32;
-    const size_t lds = sizeof(int) * ((size_t)Lcap + (lane_sums ? 0 : 16 * 32 * ((size_t)H / 4)));
-    if (n_part > 0 && Lcap <= 8192 && H % 4 == 0 && H <= 128 && lds <= 64 * 1024) {
+    if (select_fast) {
         const int ipt = (Lcap + 1023) / 1024;
 #define MD_SELECT_FAST(I, E)                                                                                       \
-    MD_LAUNCH("decode_select", st, (decode_select_fast_kernel<I, E>), B, 1024, lds,                          \
-        p, w.logits, w.stat_partial, n_part, decay, budget, acc, ids, protect, len, w.holes, w.movers, w.n_move,   \
-        evicted_ids, evicted_count)
+    MD_LAUNCH("decode_select", st, (decode_select_fast_kernel<I, E>), dim3(select_x, B), 1024, select_lds,         \
+        p, w.logits, w.stat_partial, n_part, decay, budget, copy.acc ? copy : state, state, lay,                   \
+        static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache), stream_once ? 1 : 0,               \
+        w.holes, w.movers, one_launch ? nullptr : w.n_move, evicted_ids, evicted_count)
 #define MD_SELECT_FAST_H(I)                                                                                        \
     switch (H) {                                                                                                   \
         case 4: MD_SELECT_FAST(I, 1); break;                                                                       \
@@ -924,6 +1018,7 @@ int decode_evict_impl(
         else { MD_SELECT_FAST_H(8) }
 #undef MD_SELECT_FAST_H
 #undef MD_SELECT_FAST
+        if (one_launch) return check_launch("decode_evict");
     } else {
         const size_t lds = sizeof(float) * ((size_t)2 * H + 1024);
         MD_LAUNCH("decode_select", st, (decode_select_kernel), B, 1024, lds,

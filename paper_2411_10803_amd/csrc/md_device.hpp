@@ -206,6 +206,35 @@ __device__ __forceinline__ int block_rank(bool flag, int* red, int& total) {
     return wave_prefix_of_totals(red, total) + below;
 }
 
+// Exclusive prefixes of IPT rounds of items dealt round-robin over a block of 16 waves (round t, wave w, lane l holds
+// item t*1024 + w*64 + l): cnt[t] is this wave's count in round t (wave-uniform; several small counters can share the
+// word), pre[t] the sum of all counts before it.  One barrier for all rounds.  `red`: 16*IPT ints that nobody else uses.
+template <int IPT>
+__device__ __forceinline__ int block_round_prefixes(const int (&cnt)[IPT], int (&pre)[IPT], int* red) {
+    static_assert(IPT <= 8, "two lanes' worth of (round, wave) pairs");
+    const int lane = lane_id(), wv = wave_id();
+    if (lane == 0) {
+#pragma unroll
+        for (int t = 0; t < IPT; ++t) red[t * 16 + wv] = cnt[t];
+    }
+    __syncthreads();
+    const int v0 = lane < 16 * IPT ? red[lane] : 0;
+    const int i0 = wave_incl_scan_i(v0);
+    int total = __builtin_amdgcn_readlane(i0, kWave - 1);
+    int v1 = 0, i1 = 0;
+    if (IPT > 4) {
+        v1 = lane + kWave < 16 * IPT ? red[lane + kWave] : 0;
+        i1 = wave_incl_scan_i(v1) + total;
+        total = __builtin_amdgcn_readlane(i1, kWave - 1);
+    }
+#pragma unroll
+    for (int t = 0; t < IPT; ++t) pre[t] = __builtin_amdgcn_readlane(t < 4 ? i0 - v0 : i1 - v1, (t * 16 + wv) & (kWave - 1));
+    return total;
+}
+__device__ __forceinline__ int lanes_below(unsigned long long ballot) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, 0u));
+}
+
 // Order-preserving composite key: larger score first, then smaller tie value first.
 // `score` must be >= 0 (its bit pattern is then monotone); `tie` in [0, 2^31).
 __device__ __forceinline__ uint64_t rank_key(float score, int tie) {

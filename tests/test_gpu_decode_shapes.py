@@ -1,5 +1,6 @@
 """GPU parity of the streaming scoring and in-register selection kernels at head shapes off the powers of two: rows that
-end inside a 1 KiB piece, heads in fours, both cache layouts, the steady state (one entry leaves) and large cuts."""
+end inside a 1 KiB piece, heads in fours, both cache layouts, the steady state (one entry leaves) and large cuts, with the row
+moves in the selection's launch or in their own."""
 import numpy as np
 import pytest
 
@@ -15,12 +16,22 @@ pytestmark = pytest.mark.gpu
                                         (3, 128, 200, 50), (40, 128, 4100, 3000)])
 @pytest.mark.parametrize("head_major", [False, True])
 def test_head_shapes(H, d, L0, cut, head_major):
+    check(H, d, L0, cut, head_major, None)
+
+
+# a few live entries of many slots: the moves have a launch of their own, unless four rows or fewer move
+@pytest.mark.parametrize("cut", [1, 4, 5, 600])
+def test_long_caches_with_few_entries(cut):
+    check(32, 64, 1000, cut, False, 8000)
+
+
+def check(H, d, L0, cut, head_major, slots):
     import torch
     import paper_2411_10803_amd as md
     from paper_2411_10803_amd import harness
     budget = L0 - cut
     cfg = wl.tiny(wl.CONFIGS[5], B=2, L0=L0, steps=1, decode_budget=budget, n_protect=min(20, budget), H=H, d=d)
-    t = wl.decode_inputs(cfg)
+    t = wl.decode_inputs(cfg, Lcap=slots)
     B, Lcap = cfg.B, t["Lcap"]
     rng = np.random.default_rng(H * L0)
     s0 = {"k": t["k_cache"], "v": t["v_cache"], "acc": rng.random((B, Lcap)).astype(np.float32) * np.float32(1.0 / L0),
