@@ -1058,6 +1058,7 @@ __global__ __launch_bounds__(1024) void prefill_select_fast_kernel(
     __shared__ float s_redf[16];
     __shared__ int s_red[16];
     __shared__ int s_hist[kSelectHistInts];
+    __shared__ int s_rounds[16 * IPT];
     if ((int)blockIdx.x >= p.B) {                    // block-uniform: the blocks that copy the text rows
         copy_text_rows<IPT>(p, tr, vis_valid, txt_len, is_key, budget, s_red);
         return;
@@ -1123,19 +1124,23 @@ __global__ __launch_bounds__(1024) void prefill_select_fast_kernel(
 #pragma unroll
         for (int t = 0; t < IPT; ++t) keep[t] = ok[t] && !((v[t] <= thrV) && (iv[t] < alpha) && !key[t]);
     }
-    int running = 0;
+    // ranks of the kept tokens: one barrier for all rounds (two a round before: 5697 tokens 12.8 -> 11.4 us)
+    int below[IPT], cnts[IPT], wave_pre[IPT];
 #pragma unroll
     for (int t = 0; t < IPT; ++t) {
-        if (t * 1024 >= Mv) continue;                // block-uniform
-        const int j = tid + t * 1024;
-        int total;
-        const int o = running + block_rank(keep[t], s_red, total);
+        const unsigned long long kept = __ballot(keep[t]);
+        cnts[t] = __popcll(kept);
+        below[t] = lanes_below(kept);
+    }
+    const int running = block_round_prefixes<IPT>(cnts, wave_pre, s_rounds);
+#pragma unroll
+    for (int t = 0; t < IPT; ++t) {
+        const int j = tid + t * 1024, o = wave_pre[t] + below[t];
         if (keep[t] && o < p.Rcap) {
             kept_index[(long)b * p.Rcap + o] = j;
             src_row[(long)b * rows_cap + o] = j;
             if (out_protect) out_protect[(long)b * rows_cap + o] = key[t] ? 1 : 0;
         }
-        running += total;
     }
     const int nkept = min(running, p.Rcap);
     for (int i = tid; i < rows_cap - nkept; i += blockDim.x) {
