@@ -23,6 +23,8 @@
 #include "md_device.hpp"
 #include "md_host.hpp"
 
+#include <type_traits>
+
 namespace md {
 namespace {
 
@@ -843,6 +845,8 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
 // V_j = sum_i a[i][j], I_j = max_i a[i][j].  A wave takes four neighbouring vision keys at a time (same
 // key group, same pieces), lanes over text rows; all loads of a piece are in flight together.
 constexpr int kFixKeys = 4;
+// NP: pieces whose loads go out together.
+template <int NP>
 __global__ __launch_bounds__(256) void prefill_colfix_kernel(
     const float* __restrict__ apart, const uint8_t* __restrict__ vis_valid, const SampleRows* __restrict__ rows,
     PrefillDims p, ColPlan cp, float* __restrict__ Vout, float* __restrict__ Iout)
@@ -863,23 +867,31 @@ __global__ __launch_bounds__(256) void prefill_colfix_kernel(
         const int npieces = unit_block(tile * p.H + p.H - 1, run.P, run.U) - unit_block(tile * p.H, run.P, run.U) + 1;
         const TextGroup grp = text_group(tg, sm.nbl, sm.nt);
         // two text rows per lane: a group has at most 2 * kWave of them (lanes beyond read a valid row and drop it)
-        const int n = 32 * grp.count;
-        const bool oka = lane < n, okb = kWave + lane < n;
+        const int nrows = 32 * grp.count;
+        const bool oka = lane < nrows, okb = kWave + lane < nrows;
         const int ca = 32 * grp.first + (oka ? lane : 0), cb = 32 * grp.first + (okb ? kWave + lane : 0);
         float a0[kFixKeys], a1[kFixKeys];
 #pragma unroll
         for (int q = 0; q < kFixKeys; ++q) { a0[q] = 0.f; a1[q] = 0.f; }
-        for (int g = 0; g < npieces; ++g) {
-            float x0[kFixKeys], x1[kFixKeys];
+        auto add_pieces = [&](int g, auto count) {
+            constexpr int n = decltype(count)::value;
+            float x0[n][kFixKeys], x1[n][kFixKeys];
 #pragma unroll
-            for (int q = 0; q < kFixKeys; ++q) {
-                const float* ap = apart + g * gstride + ((long)b * p.Mv + min(j0 + q, p.Mv - 1)) * p.Npad;
-                x0[q] = __builtin_nontemporal_load(ap + ca);       // a piece is read once
-                x1[q] = __builtin_nontemporal_load(ap + cb);
-            }
+            for (int u = 0; u < n; ++u)
 #pragma unroll
-            for (int q = 0; q < kFixKeys; ++q) { a0[q] += x0[q]; a1[q] += x1[q]; }
-        }
+                for (int q = 0; q < kFixKeys; ++q) {
+                    const float* ap = apart + (g + u) * gstride + ((long)b * p.Mv + min(j0 + q, p.Mv - 1)) * p.Npad;
+                    x0[u][q] = __builtin_nontemporal_load(ap + ca);       // a piece is read once
+                    x1[u][q] = __builtin_nontemporal_load(ap + cb);
+                }
+#pragma unroll
+            for (int u = 0; u < n; ++u)
+#pragma unroll
+                for (int q = 0; q < kFixKeys; ++q) { a0[q] += x0[u][q]; a1[q] += x1[u][q]; }
+        };
+        int g = 0;
+        for (; g + NP <= npieces; g += NP) add_pieces(g, std::integral_constant<int, NP>());
+        for (; g < npieces; ++g) add_pieces(g, std::integral_constant<int, 1>());
 #pragma unroll
         for (int q = 0; q < kFixKeys; ++q) {
             const float v0 = oka ? a0[q] : 0.f, v1 = okb ? a1[q] : 0.f;
@@ -1280,7 +1292,10 @@ ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     // and with two text blocks when the runs stay long enough (20 units per CU); otherwise one (fewer, longer
     // runs: fewer pieces, fewer prologues; measured faster there)
     s.occ = s.nbw == 4 || (s.nbw == 2 && c.U >= 20L * kNumCU) ? 2 : 1;
-    long P = (c.U + 3) / 4;
+    // (two of them with a single text block: 1 x 576 keys 9.2 us for the sweep + 5.9 for its pieces with four, 7.2 + 6.6
+    // with two; 4 x 576 with 100 text rows 12.9 + 5.6 with four, 13.4 + 7.1 with two)
+    const long least = s.nbw == 1 ? 2 : 4;
+    long P = (c.U + least - 1) / least;
     if (P > kNumCU * s.occ) P = kNumCU * s.occ;
     if (P < 1) P = 1;
     c.P = (int)P;
@@ -1349,7 +1364,12 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
     else MD_COLSCORE(4, 2, true);
 #undef MD_COLSCORE
     const int fx = (p.Mv + 4 * kFixKeys - 1) / (4 * kFixKeys);          // four waves of kFixKeys keys per block
-    MD_LAUNCH("prefill_colfix", st, (prefill_colfix_kernel), dim3(fx, p.B), 256, 0, w.apart, vis_valid, w.rows, p, s.col, w.V, w.I);
+    // small calls cut a tile into many pieces, a chain of round trips unless four are requested at a time (14 pieces
+    // 8.2 -> 6.7 us); the two or three of a large one are bound by their bytes, and by occupancy (8.1 -> 11.3)
+    if ((long)p.H * s.col.P >= 4 * s.col.U)
+        MD_LAUNCH("prefill_colfix", st, (prefill_colfix_kernel<4>), dim3(fx, p.B), 256, 0, w.apart, vis_valid, w.rows, p, s.col, w.V, w.I);
+    else
+        MD_LAUNCH("prefill_colfix", st, (prefill_colfix_kernel<1>), dim3(fx, p.B), 256, 0, w.apart, vis_valid, w.rows, p, s.col, w.V, w.I);
     return MD_OK;
 }
 
