@@ -136,9 +136,10 @@ template <> struct Vec<true> {
 constexpr int kClsRows = 8;
 __host__ __device__ __forceinline__ int cls_groups(int M) { return (M + 1 + kClsRows - 1) / kClsRows; }
 
-template <bool BF>
+// it_first, it_end: the rows' 64-vector slices to work on (all of them, or with SLICED the one of this wave).
+template <bool BF, bool SLICED>
 __device__ __forceinline__ void cls_logits_rows(
-    int b, int g, const void* __restrict__ q_cls, const void* __restrict__ k_cls, const uint8_t* __restrict__ valid,
+    int b, int g, int it_first, int it_end, const void* __restrict__ q_cls, const void* __restrict__ k_cls, const uint8_t* __restrict__ valid,
     const EncodeDims& p, float* __restrict__ logits, float2* __restrict__ part, float2* s_stat)
 {
     constexpr int VEC = Vec<BF>::N;
@@ -189,9 +190,8 @@ __device__ __forceinline__ void cls_logits_rows(
     for (int r = 0; r < R; ++r) acc[r] = 0.f;
     // slices of the rows per round: fp32 rows are twice as long, and a lone image waits half as often with two in
     // flight (scores of 1 x 576 tokens 10.6 -> 9.8 us); bf16 with two is slower (8 x 2880 tokens 18.1 -> 20.0 us)
-    constexpr int UNR = BF ? 1 : 2;
-    const int iters = (nvec + kWave - 1) / kWave;
-    for (int it0 = 0; it0 < iters; it0 += UNR) {
+    constexpr int UNR = BF || SLICED ? 1 : 2;
+    for (int it0 = it_first; it0 < it_end; it0 += UNR) {
         typename Vec<BF>::Raw kv[UNR][R], qv[UNR];
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
@@ -205,11 +205,11 @@ __device__ __forceinline__ void cls_logits_rows(
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const int it = it0 + u, idx = it * kWave + lane;
-            if (it >= iters) break;
+            if (it >= it_end) break;
             float part_r[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) part_r[r] = act[r] && idx < nvec ? Vec<BF>::dot(qv[u], kv[u][r], 0.f) : 0.f;
-            if (vph < kWave) {
+            if (SLICED || vph < kWave) {
                 float lg[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) lg[r] = group_sum_rt(part_r[r], vph) * scale;
@@ -432,7 +432,7 @@ __device__ __forceinline__ void key_scores(
 //                               decision wants the scores ready-made; the key scores hide behind the windows.
 //                               The key-row blocks (each within one sample) then also leave their groups' statistics
 //                               merged: block_stat[b][block of the sample][h].
-struct ScoreBlocks { int keyscore, windows, rows; };                 // blocks of each kind, in grid order
+struct ScoreBlocks { int keyscore, windows, rows, slices; };         // blocks of each kind, in grid order; waves per key-row group
 template <int WSM, bool XBF, bool QKBF>
 __global__ __launch_bounds__(256) void encode_scores_kernel(
     const void* __restrict__ x, const void* __restrict__ q_cls, const void* __restrict__ k_cls,
@@ -453,12 +453,19 @@ __global__ __launch_bounds__(256) void encode_scores_kernel(
         return;
     }
     blk -= nb.windows;
+    const int gps = cls_groups(p.M);
+    if (nb.slices > 1) {                             // a wave per (group of key rows, slice of the feature dimension)
+        const int item = blk * kEncWaves + wave_id(), gs = item / nb.slices, sl = item - gs * nb.slices, b = gs / gps;
+        if (b < p.B) cls_logits_rows<QKBF, true>(b, gs - b * gps, sl, sl + 1, q_cls, k_cls, valid, p, logits, cls_part, nullptr);
+        return;
+    }
     const int cb = cls_blocks(p.M), b = blk / cb, wb = blk % cb, g = wb * kEncWaves + wave_id();
-    if (g < cls_groups(p.M))
-        cls_logits_rows<QKBF>(b, g, q_cls, k_cls, valid, p, logits, cls_part, block_stat ? s.stat[wave_id()] : nullptr);
+    const int iters = (p.D / Vec<QKBF>::N + kWave - 1) / kWave;
+    if (g < gps)
+        cls_logits_rows<QKBF, false>(b, g, 0, iters, q_cls, k_cls, valid, p, logits, cls_part, block_stat ? s.stat[wave_id()] : nullptr);
     if (!block_stat) return;
     __syncthreads();
-    const int nw = min(kEncWaves, cls_groups(p.M) - wb * kEncWaves);
+    const int nw = min(kEncWaves, gps - wb * kEncWaves);
     for (int h = threadIdx.x; h < p.Hc; h += blockDim.x) {
         float mx = -INFINITY, z = 0.f;
         for (int w = 0; w < nw; ++w) mx = fmaxf(mx, s.stat[w][h].x);
@@ -1263,6 +1270,7 @@ void launch_scores(int ws, ScoreBlocks nb, hipStream_t st, bool xbf, bool qkbf, 
     if (ws <= 2) launch_scores<2>(nb, st, xbf, qkbf, p, a);
     else if (ws <= 4) launch_scores<4>(nb, st, xbf, qkbf, p, a);
     else if (ws <= 8) launch_scores<8>(nb, st, xbf, qkbf, p, a);
+    else if (ws == 9) launch_scores<9>(nb, st, xbf, qkbf, p, a);     // 3 x 3: a third of the pairs of 16 members
     else launch_scores<16>(nb, st, xbf, qkbf, p, a);
 }
 
@@ -1361,10 +1369,16 @@ int encode_merge_impl(
     const bool xbf = x_dtype == MD_BF16, qkbf = qk_dtype == MD_BF16;
     const ScoreArgs sa{x, q_cls, k_cls, valid, wsp.sim, wsp.logits, wsp.cls_part, large_ok ? wsp.block_stat : nullptr, wsp.acls, a_cls_out};
     if (large_ok && with_keys) {
-        launch_scores(ws, ScoreBlocks{0, 0, row_blocks}, st, xbf, qkbf, p, sa);
-        launch_scores(ws, ScoreBlocks{B * ((M + kKeyTokens - 1) / kKeyTokens), win_blocks, 0}, st, xbf, qkbf, p, sa);
+        launch_scores(ws, ScoreBlocks{0, 0, row_blocks, 1}, st, xbf, qkbf, p, sa);
+        launch_scores(ws, ScoreBlocks{B * ((M + kKeyTokens - 1) / kKeyTokens), win_blocks, 0, 1}, st, xbf, qkbf, p, sa);
     } else {
-        launch_scores(ws, ScoreBlocks{0, win_blocks, row_blocks}, st, xbf, qkbf, p, sa);
+        const int vec = qkbf ? 8 : 4, iters = (D / vec + kWave - 1) / kWave;
+        // A wave per 64-vector slice of its key rows, where a head lies inside a slice: the slices were a chain of round
+        // trips (scores of 1 x 576 tokens fp32 10.5 -> 5.2 us, 16 x 576 11.2 -> 10.4, 75 x 400 fp32 46.7 -> 41.0).  Not
+        // for many tokens in windows of more than nine members, whose registers leave room for few waves.
+        const bool sliced = with_keys && iters > 1 && dc / vec < kWave && (ws <= 9 || (long)B * M <= 8192);
+        const int rb = sliced ? (int)(((long)B * cls_groups(M) * iters + kEncWaves - 1) / kEncWaves) : row_blocks;
+        launch_scores(ws, ScoreBlocks{0, win_blocks, rb, sliced ? iters : 1}, st, xbf, qkbf, p, sa);
     }
     dim3 wgrid((unsigned)win_blocks);
 #define MD_DECIDE_FAST(IPT_, WS_)                                                                             \
