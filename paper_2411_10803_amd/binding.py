@@ -61,25 +61,62 @@ def library() -> C.CDLL:
     return _lib
 
 
+# Argument types of the calls, one letter each: p pointer, i int, l int64, f float, z size_t.  The conversion then
+# happens inside ctypes: an object per argument made in Python cost 10 of the 20 us that the host spent on a call.
+_TYPES = {"p": C.c_void_p, "i": C.c_int, "l": C.c_int64, "f": C.c_float, "z": C.c_size_t}
+_ENCODE = "pippipp" + "i" * 10 + "f"
+_PREFILL = "p" * 8 + "i" * 6 + "fiiff" + "i" + "p" * 10
+_EVICT = "p" * 7 + "i" * 4 + "ffi" + "pp"
+_APPEND = "p" * 8 + "i" * 6
+_KEEP = "p" * 7 + "i" * 5 + "pp"
+_SIGNATURES = {
+    "mustdrop_encode_merge": _ENCODE + "i" + "p" * 9 + "pzp",
+    "mustdrop_encode_merge_noalloc": _ENCODE + "i" + "p" * 9 + "p",
+    "mustdrop_encode_merge_adaptive": _ENCODE + "fi" + "p" * 10 + "pzp",
+    "mustdrop_prefill_filter": _PREFILL + "pzp",
+    "mustdrop_prefill_filter_strided": _PREFILL + "ppp" + "pzp",
+    "mustdrop_decode_evict": _EVICT + "pzp",
+    "mustdrop_decode_evict_strided": _EVICT + "p" + "pzp",
+    "mustdrop_decode_append": _APPEND + "p",
+    "mustdrop_decode_append_strided": _APPEND + "p" + "p",
+    "mustdrop_decode_keep": _KEEP + "pzp",
+    "mustdrop_decode_keep_strided": _KEEP + "pl" + "pzp",
+}
+_functions: Dict[str, object] = {}
+
+
+def _call(name: str, *args):
+    """Calls an entry point with plain Python values and device pointers, and raises on an error code."""
+    fn = _functions.get(name)
+    if fn is None:
+        fn = library()[name]                               # a function object of its own: library().<name> stays untyped
+        fn.restype = C.c_int
+        fn.argtypes = [_TYPES[t] for t in _SIGNATURES[name]]
+        _functions[name] = fn
+    try:
+        rc = fn(*args)
+    except C.ArgumentError as e:
+        raise TypeError(f"{name}: {e}") from None
+    _check(rc)
+
+
 def _check(rc: int):
     if rc != 0:
         raise MustDropError(rc, library().mustdrop_last_error().decode())
 
 
-def _ptr(t) -> C.c_void_p:
+def _ptr(t) -> Optional[int]:
     """Device pointer of a torch tensor (None -> NULL)."""
-    if t is None:
-        return C.c_void_p(0)
-    if isinstance(t, int):
-        return C.c_void_p(t)
+    if t is None or isinstance(t, int):
+        return t
     assert t.is_contiguous(), "tensors handed to the C ABI must be contiguous"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _view_ptr(t) -> C.c_void_p:
+def _view_ptr(t) -> int:
     """Device pointer of a [.., tokens, H, d] view whose last axis is contiguous (any other strides)."""
     assert t.stride(-1) == 1, "the head dimension must be contiguous"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _layout(t):
@@ -88,10 +125,12 @@ def _layout(t):
     return KvLayout(st[-4], st[-3], st[-2])
 
 
-def _stream(stream=None) -> C.c_void_p:
+def _stream(stream=None) -> int:
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    # the handle alone; torch.cuda.current_stream() wraps it in an object first
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dtype_code(t) -> int:
@@ -150,14 +189,14 @@ def mustdrop_encode_merge(x, q_cls, k_cls, mass_in, valid, T, Hg, Wg, kt, kh, kw
     if workspace is None:
         workspace = encode_workspace(B, T, Hg, Wg, Hc, kt, kh, kw, dev)
     out["workspace"] = workspace
-    _check(library().mustdrop_encode_merge(
-        _ptr(x), C.c_int(_dtype_code(x)), _ptr(q_cls), _ptr(k_cls), C.c_int(qk_dtype), _ptr(mass_in), _ptr(valid),
-        C.c_int(B), C.c_int(T), C.c_int(Hg), C.c_int(Wg), C.c_int(D), C.c_int(Hc), C.c_int(dc),
-        C.c_int(kt), C.c_int(kh), C.c_int(kw), C.c_float(tau), C.c_int(key_budget),
+    _call("mustdrop_encode_merge",
+        _ptr(x), _dtype_code(x), _ptr(q_cls), _ptr(k_cls), qk_dtype, _ptr(mass_in), _ptr(valid),
+        B, T, Hg, Wg, D, Hc, dc,
+        kt, kh, kw, tau, key_budget,
         _ptr(out["out_x"]), _ptr(out["out_index"]), _ptr(out["out_mass"]), _ptr(out["out_is_key"]),
         _ptr(out["out_valid"]), _ptr(out["out_count"]), _ptr(out["key_index"]),
         _ptr(out.get("a_cls")), _ptr(out.get("window_sim")),
-        _ptr(workspace), C.c_size_t(workspace.numel()), _stream(stream)))
+        _ptr(workspace), workspace.numel(), _stream(stream))
     return out
 
 
@@ -171,13 +210,13 @@ def mustdrop_encode_merge_noalloc(x, q_cls, k_cls, mass_in, valid, T, Hg, Wg, kt
         qk_dtype = _dtype_code(q_cls)
     else:
         Hc, dc, qk_dtype = 1, D, _dtype_code(x)
-    _check(library().mustdrop_encode_merge_noalloc(
-        _ptr(x), C.c_int(_dtype_code(x)), _ptr(q_cls), _ptr(k_cls), C.c_int(qk_dtype), _ptr(mass_in), _ptr(valid),
-        C.c_int(B), C.c_int(T), C.c_int(Hg), C.c_int(Wg), C.c_int(D), C.c_int(Hc), C.c_int(dc),
-        C.c_int(kt), C.c_int(kh), C.c_int(kw), C.c_float(tau), C.c_int(key_budget),
+    _call("mustdrop_encode_merge_noalloc",
+        _ptr(x), _dtype_code(x), _ptr(q_cls), _ptr(k_cls), qk_dtype, _ptr(mass_in), _ptr(valid),
+        B, T, Hg, Wg, D, Hc, dc,
+        kt, kh, kw, tau, key_budget,
         _ptr(out["out_x"]), _ptr(out["out_index"]), _ptr(out["out_mass"]), _ptr(out["out_is_key"]),
         _ptr(out["out_valid"]), _ptr(out["out_count"]), _ptr(out["key_index"]),
-        _ptr(out.get("a_cls")), _ptr(out.get("window_sim")), _stream(stream)))
+        _ptr(out.get("a_cls")), _ptr(out.get("window_sim")), _stream(stream))
     return out
 
 
@@ -206,14 +245,14 @@ def mustdrop_encode_merge_adaptive(x, q_cls, k_cls, mass_in, valid, T, Hg, Wg, k
     if workspace is None:
         workspace = encode_workspace(B, T, Hg, Wg, Hc, kt, kh, kw, dev)
     out["workspace"] = workspace
-    _check(library().mustdrop_encode_merge_adaptive(
-        _ptr(x), C.c_int(_dtype_code(x)), _ptr(q_cls), _ptr(k_cls), C.c_int(_dtype_code(q_cls)), _ptr(mass_in), _ptr(valid),
-        C.c_int(B), C.c_int(T), C.c_int(Hg), C.c_int(Wg), C.c_int(D), C.c_int(Hc), C.c_int(dc),
-        C.c_int(kt), C.c_int(kh), C.c_int(kw), C.c_float(tau), C.c_float(key_lambda), C.c_int(key_cap),
+    _call("mustdrop_encode_merge_adaptive",
+        _ptr(x), _dtype_code(x), _ptr(q_cls), _ptr(k_cls), _dtype_code(q_cls), _ptr(mass_in), _ptr(valid),
+        B, T, Hg, Wg, D, Hc, dc,
+        kt, kh, kw, tau, key_lambda, key_cap,
         _ptr(out["out_x"]), _ptr(out["out_index"]), _ptr(out["out_mass"]), _ptr(out["out_is_key"]),
         _ptr(out["out_valid"]), _ptr(out["out_count"]), _ptr(out["key_index"]), _ptr(out["key_count"]),
         _ptr(out.get("a_cls")), _ptr(out.get("window_sim")),
-        _ptr(workspace), C.c_size_t(workspace.numel()), _stream(stream)))
+        _ptr(workspace), workspace.numel(), _stream(stream))
     return out
 
 
@@ -243,15 +282,15 @@ def mustdrop_prefill_filter(q_txt, k, v, hidden, vis_valid, txt_len, is_key, Mv,
     if workspace is None:
         workspace = prefill_workspace(B, Mv, N, H, Rcap, dev)
     out["workspace"] = workspace
-    _check(library().mustdrop_prefill_filter(
+    _call("mustdrop_prefill_filter",
         _ptr(q_txt), _ptr(k), _ptr(v), _ptr(hidden), _ptr(vis_valid), _ptr(txt_len), _ptr(is_key), _ptr(row_lse),
-        C.c_int(B), C.c_int(Mv), C.c_int(N), C.c_int(H), C.c_int(d), C.c_int(Cdim),
-        C.c_float(softmax_scale), C.c_int(mode), C.c_int(budget), C.c_float(gamma), C.c_float(alpha),
-        C.c_int(Rcap),
+        B, Mv, N, H, d, Cdim,
+        softmax_scale, mode, budget, gamma, alpha,
+        Rcap,
         _ptr(out["hidden_out"]), _ptr(out["k_out"]), _ptr(out["v_out"]),
         _ptr(out["kept_index"]), _ptr(out["kept_count"]), _ptr(out.get("out_len")), _ptr(out.get("out_protect")), _ptr(out.get("out_ids")),
         _ptr(out.get("score_global")), _ptr(out.get("score_indiv")),
-        _ptr(workspace), C.c_size_t(workspace.numel()), _stream(stream)))
+        _ptr(workspace), workspace.numel(), _stream(stream))
     return out
 
 
@@ -261,12 +300,12 @@ def mustdrop_decode_evict(q, k_cache, v_cache, acc, ids, protect, length, softma
     B, Lcap, H, d = k_cache.shape
     if workspace is None:
         workspace = decode_workspace(B, Lcap, H, k_cache.device)
-    _check(library().mustdrop_decode_evict(
+    _call("mustdrop_decode_evict",
         _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(acc), _ptr(ids), _ptr(protect), _ptr(length),
-        C.c_int(B), C.c_int(Lcap), C.c_int(H), C.c_int(d),
-        C.c_float(softmax_scale), C.c_float(decay), C.c_int(budget),
+        B, Lcap, H, d,
+        softmax_scale, decay, budget,
         _ptr(evicted_ids), _ptr(evicted_count),
-        _ptr(workspace), C.c_size_t(workspace.numel()), _stream(stream)))
+        _ptr(workspace), workspace.numel(), _stream(stream))
     return workspace
 
 
@@ -274,10 +313,10 @@ def mustdrop_decode_append(k_new, v_new, k_cache, v_cache, acc, ids, protect, le
                            stream=None):
     """Eq. 3: appends one entry per sample at slot len[b] (device-side, asynchronous)."""
     B, Lcap, H, d = k_cache.shape
-    _check(library().mustdrop_decode_append(
+    _call("mustdrop_decode_append",
         _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache), _ptr(acc), _ptr(ids), _ptr(protect), _ptr(length),
-        C.c_int(B), C.c_int(Lcap), C.c_int(H), C.c_int(d), C.c_int(int(new_id)), C.c_int(int(protect_new)),
-        _stream(stream)))
+        B, Lcap, H, d, int(new_id), int(protect_new),
+        _stream(stream))
 
 
 def mustdrop_decode_keep(k_caches, v_caches, keep, acc, ids, protect, length, evicted_ids=None, evicted_count=None,
@@ -287,11 +326,11 @@ def mustdrop_decode_keep(k_caches, v_caches, keep, acc, ids, protect, length, ev
     n_layers, B, Lcap, H, d = k_caches.shape
     if workspace is None:
         workspace = decode_workspace(B, Lcap, H, k_caches.device)
-    _check(library().mustdrop_decode_keep(
+    _call("mustdrop_decode_keep",
         _ptr(k_caches), _ptr(v_caches), _ptr(keep), _ptr(acc), _ptr(ids), _ptr(protect), _ptr(length),
-        C.c_int(n_layers), C.c_int(B), C.c_int(Lcap), C.c_int(H), C.c_int(d),
+        n_layers, B, Lcap, H, d,
         _ptr(evicted_ids), _ptr(evicted_count),
-        _ptr(workspace), C.c_size_t(workspace.numel()), _stream(stream)))
+        _ptr(workspace), workspace.numel(), _stream(stream))
     return workspace
 
 
@@ -310,16 +349,16 @@ def mustdrop_prefill_filter_strided(q_txt, k, v, hidden, vis_valid, txt_len, is_
         workspace = prefill_workspace(B, Mv, N, H, Rcap, q_txt.device)
     out["workspace"] = workspace
     lq, lkv, lo = _layout(q_txt), _layout(k), _layout(out["k_out"])
-    _check(library().mustdrop_prefill_filter_strided(
+    _call("mustdrop_prefill_filter_strided",
         _view_ptr(q_txt), _view_ptr(k), _view_ptr(v), _ptr(hidden), _ptr(vis_valid), _ptr(txt_len), _ptr(is_key), _ptr(row_lse),
-        C.c_int(B), C.c_int(Mv), C.c_int(N), C.c_int(H), C.c_int(d), C.c_int(Cdim),
-        C.c_float(softmax_scale), C.c_int(mode), C.c_int(budget), C.c_float(gamma), C.c_float(alpha),
-        C.c_int(Rcap),
+        B, Mv, N, H, d, Cdim,
+        softmax_scale, mode, budget, gamma, alpha,
+        Rcap,
         _ptr(out["hidden_out"]), _view_ptr(out["k_out"]), _view_ptr(out["v_out"]),
         _ptr(out["kept_index"]), _ptr(out["kept_count"]), _ptr(out.get("out_len")), _ptr(out.get("out_protect")), _ptr(out.get("out_ids")),
         _ptr(out.get("score_global")), _ptr(out.get("score_indiv")),
         C.byref(lq), C.byref(lkv), C.byref(lo),
-        _ptr(workspace), C.c_size_t(workspace.numel()), _stream(stream)))
+        _ptr(workspace), workspace.numel(), _stream(stream))
     return out
 
 
@@ -331,12 +370,12 @@ def mustdrop_decode_evict_strided(q, k_cache, v_cache, acc, ids, protect, length
     if workspace is None:
         workspace = decode_workspace(B, Lcap, H, k_cache.device)
     lay = _layout(k_cache)
-    _check(library().mustdrop_decode_evict_strided(
+    _call("mustdrop_decode_evict_strided",
         _ptr(q), _view_ptr(k_cache), _view_ptr(v_cache), _ptr(acc), _ptr(ids), _ptr(protect), _ptr(length),
-        C.c_int(B), C.c_int(Lcap), C.c_int(H), C.c_int(d),
-        C.c_float(softmax_scale), C.c_float(decay), C.c_int(budget),
+        B, Lcap, H, d,
+        softmax_scale, decay, budget,
         _ptr(evicted_ids), _ptr(evicted_count), C.byref(lay),
-        _ptr(workspace), C.c_size_t(workspace.numel()), _stream(stream)))
+        _ptr(workspace), workspace.numel(), _stream(stream))
     return workspace
 
 
@@ -346,10 +385,10 @@ def mustdrop_decode_append_strided(k_new, v_new, k_cache, v_cache, acc, ids, pro
     B, Lcap, H, d = k_cache.shape
     assert k_cache.stride() == v_cache.stride()
     lay = _layout(k_cache)
-    _check(library().mustdrop_decode_append_strided(
+    _call("mustdrop_decode_append_strided",
         _ptr(k_new), _ptr(v_new), _view_ptr(k_cache), _view_ptr(v_cache), _ptr(acc), _ptr(ids), _ptr(protect),
-        _ptr(length), C.c_int(B), C.c_int(Lcap), C.c_int(H), C.c_int(d), C.c_int(int(new_id)),
-        C.c_int(int(protect_new)), C.byref(lay), _stream(stream)))
+        _ptr(length), B, Lcap, H, d, int(new_id),
+        int(protect_new), C.byref(lay), _stream(stream))
 
 
 def mustdrop_decode_keep_strided(k_caches, v_caches, keep, acc, ids, protect, length, evicted_ids=None,
@@ -360,11 +399,11 @@ def mustdrop_decode_keep_strided(k_caches, v_caches, keep, acc, ids, protect, le
     if workspace is None:
         workspace = decode_workspace(B, Lcap, H, k_caches.device)
     lay = _layout(k_caches)
-    _check(library().mustdrop_decode_keep_strided(
+    _call("mustdrop_decode_keep_strided",
         _view_ptr(k_caches), _view_ptr(v_caches), _ptr(keep), _ptr(acc), _ptr(ids), _ptr(protect), _ptr(length),
-        C.c_int(n_layers), C.c_int(B), C.c_int(Lcap), C.c_int(H), C.c_int(d),
-        _ptr(evicted_ids), _ptr(evicted_count), C.byref(lay), C.c_int64(k_caches.stride(0)),
-        _ptr(workspace), C.c_size_t(workspace.numel()), _stream(stream)))
+        n_layers, B, Lcap, H, d,
+        _ptr(evicted_ids), _ptr(evicted_count), C.byref(lay), k_caches.stride(0),
+        _ptr(workspace), workspace.numel(), _stream(stream))
     return workspace
 
 
