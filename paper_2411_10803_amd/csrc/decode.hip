@@ -294,6 +294,9 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     constexpr int LPE1 = LPE ? LPE : 1;
     constexpr int EPI = kWave / LPE1;                // entries per load instruction
     f32x4 lpf[PFR][LPE1];
+    // Logits are requested ahead only up to where a steady decode loop has entries: behind them a cache with room to
+    // spare holds nothing but old logits, which come from far away (33 x 168 of 949 slots, 8 blocks each: 35.6 -> 32.7 us)
+    const int ahead = budget < p.Lcap - 64 ? budget + 64 : p.Lcap;
 #pragma unroll
     for (int t = 0; t < PFR; ++t) {
         const int j = tid + t * 1024;
@@ -305,8 +308,8 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
 #pragma unroll
         for (int u = 0; u < LPE; ++u) {
             const int e = base + u * EPI + lane / LPE1;
-            lpf[t][u] = e < p.Lcap ? reinterpret_cast<const f32x4*>(lb + (long)base * H)[u * kWave + lane]
-                                   : f32x4{0.f, 0.f, 0.f, 0.f};
+            lpf[t][u] = e < ahead ? reinterpret_cast<const f32x4*>(lb + (long)base * H)[u * kWave + lane]
+                                  : f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
     // the logits kernel's partial statistics: `parts` consecutive lanes (a power of two) share a head, each takes a slice
@@ -339,6 +342,15 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
         a_old[t] = live[t] ? ai[j] : 0.f;
         id[t] = live[t] ? ii[j] : 0;
         prot[t] = live[t] ? pi[j] != 0 : false;
+    }
+    if (LPE > 0 && n > ahead) {                      // block-uniform
+#pragma unroll
+        for (int t = 0; t < PFR; ++t)
+#pragma unroll
+            for (int u = 0; u < LPE; ++u) {
+                const int base = t * 1024 + wv * kWave, e = base + u * EPI + lane / LPE1;
+                if (e >= ahead && e < n) lpf[t][u] = reinterpret_cast<const f32x4*>(lb + (long)base * H)[u * kWave + lane];
+            }
     }
     // the lanes of a head finish the merge: group maximum, then the group sum of the rescaled sums
     {
@@ -932,12 +944,12 @@ int decode_evict_impl(
     const bool lane_sums = H == 4 || H == 8 || H == 16 || H == 32;
     const size_t select_lds = sizeof(int) * ((size_t)Lcap + (lane_sums ? 0 : 16 * 32 * ((size_t)H / 4)));
     const bool select_fast = (d == 128 || d == 64) && pieces <= 16 && Lcap <= 8192 && H % 4 == 0 && H <= 128 && select_lds <= 64 * 1024;
-    // Moves in the selection's launch: blocks per sample that together cover the CUs, with no more teams than rows that
-    // can leave, and reading no more than 32 MB of logits between them.  Where that leaves neither half the chip nor all
+    // Moves in the selection's launch: blocks per sample that together cover the CUs but do not share one (33 x 168
+    // entries: 264 blocks 16.7 us, 231 10.0, 132 9.4; as two launches 8.3 + 4.3), with no more teams than rows that can leave, and reading no more than 32 MB of logits between them.  Where that leaves neither half the chip nor all
     // the teams, the caches are long or many, and a launch for the moves is the smaller price (us, one launch / two:
     // 4 x 778 entries of 40 heads 13.1 / 15.7, 1 x 1724 of 16 heads 8.7 / 12.8, 60 x 748 of 40 heads 14.4 / 16.7;
     // 64 x 1025 of 4352 slots 18.4 / 16.2, 18 x 4036 40.4 / 25.8, 64 x 4096 cut to 1024 407 / 387)
-    int select_x = (256 + B - 1) / B;
+    int select_x = B <= 256 ? 256 / B : 1;
     const long leave_x = Lcap > budget ? (Lcap - budget + 3l) / 4 : 1, read_x = (32l << 20) / ((long)B * Lcap * H * 4);
     if (select_x > leave_x) select_x = (int)leave_x;
     if (select_x > 32) select_x = 32;
