@@ -295,8 +295,9 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     constexpr int EPI = kWave / LPE1;                // entries per load instruction
     f32x4 lpf[PFR][LPE1];
     // Logits are requested ahead only up to where a steady decode loop has entries: behind them a cache with room to
-    // spare holds nothing but old logits, which come from far away (33 x 168 of 949 slots, 8 blocks each: 35.6 -> 32.7 us)
-    const int ahead = budget < p.Lcap - 64 ? budget + 64 : p.Lcap;
+    // spare holds nothing but old logits, which come from far away (33 x 168 of 949 slots, 8 blocks each: 35.6 -> 32.7 us).
+    // One block per sample takes all at once: a cut to a quarter would wait twice (6 x 1838 entries: 15 us, 18.6 so)
+    const int ahead = gridDim.x > 1 && budget < p.Lcap - 64 ? budget + 64 : p.Lcap;
 #pragma unroll
     for (int t = 0; t < PFR; ++t) {
         const int j = tid + t * 1024;
