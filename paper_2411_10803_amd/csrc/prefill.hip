@@ -22,6 +22,7 @@
 // so the row-softmax reductions over keys stay inside a lane (+ one exchange with lane^32).
 #include "md_device.hpp"
 #include "md_host.hpp"
+#include "prefill_plan.hpp"
 
 #include <type_traits>
 
@@ -29,7 +30,6 @@ namespace md {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kMaxChunks = 16;                       // key chunks per (sample, head) in the row-statistics sweep, at most
 
 struct PrefillDims {
     int B, Mv, N, H, d, C, L;
@@ -145,8 +145,6 @@ struct SampleRows { int vision; int text_blocks; };   // effective vision rows; 
 // cut into groups that share them out evenly, counted over the blocks that hold rows of the sample at hand: a sample
 // with a short prompt has fewer groups than the longest one, or none, and columns without a block only help to move K.
 struct TextGroup { int first, count; };
-__device__ __forceinline__ int text_blocks_of(int tl) { return (tl + 31) >> 5; }
-__device__ __forceinline__ int text_groups_of(int blocks, int nbw) { return (blocks + nbw - 1) / nbw; }
 __device__ __forceinline__ TextGroup text_group(int g, int blocks, int groups) {
     if (groups <= 1) return TextGroup{0, blocks};
     // blocks / groups for at most 32 blocks: (blocks + 1/2) / groups stays 1/16 away from the next whole number
@@ -592,21 +590,6 @@ __global__ __launch_bounds__(256) void prefill_qpack_kernel(
 // "piece" (fp32, key-major); prefill_colfix_kernel adds a key group's pieces in a fixed order and
 // reduces over the text rows (Eq. 8 / Eq. 10).  Which block holds which piece is a function of the
 // shapes alone, so the result does not depend on timing.
-struct ColPlan { int P; long U; int nkg; int Gmax; int kb; int nbw; };   // kb: vision keys per unit (a power of two); nbw: text blocks
-
-// n / d; the index arithmetic of the sweeps fits 32 bits at all but the largest sizes, and a 64-bit division is four
-// times the instructions
-__device__ __forceinline__ long index_div(long n, long d) {
-    return ((n | d) >> 32) == 0 ? (long)((uint32_t)n / (uint32_t)d) : n / d;
-}
-__device__ __forceinline__ int unit_block(long u, int P, long U) { return (int)index_div((u + 1) * P - 1, U); }
-
-// The same decomposition over what matters (SampleRows, one entry per sample; written by the kernel before this
-// sweep): a sample has key_groups(vision) x text_groups(text_blocks) tiles, the text groups of a key group next to
-// each other, so that the blocks that read the same K rows run side by side on one XCD.
-// Fewer units than the host planned for means fewer blocks at work only where a tile would
-// otherwise be cut into more pieces than the workspace holds (Gmax).
-__device__ __forceinline__ int key_groups(int rows, int kb) { return (rows + kb - 1) / kb; }
 struct SampleTiles { int b, tile0, nk, nbl, nt; };                // a sample: first tile, key groups, text blocks and groups
 // All samples at once, one per lane (64 at a time): the number of tiles, and in `s` the sample that holds tile `t`
 // (find_tile) or sample `t` itself.  One vector load and a lane scan; a loop over scalar loads is a dependent chain.
@@ -638,18 +621,6 @@ __device__ __forceinline__ int find_sample(const SampleRows* __restrict__ rows, 
     }
     return tiles;
 }
-struct ColRun { long U; int P; };
-__device__ __forceinline__ ColRun effective_run(int tiles, int H, ColPlan cp) {
-    ColRun r;
-    r.U = (long)tiles * H;
-    long P = (long)(cp.Gmax - 1) * tiles;             // pieces per tile <= ceil(H*P/U) + 1 <= Gmax
-    if (cp.Gmax >= H || P > cp.P) P = cp.P;
-    if (P >= 8) P &= ~7L;                             // whole rounds over the 8 XCDs
-    if (P < 1) P = 1;
-    r.P = (int)P;
-    return r;
-}
-
 // MULTI: samples may have several text groups.
 template <int NBW, int KT, int KS, bool MULTI>
 __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
@@ -1247,65 +1218,6 @@ struct PrefillWorkspace {
     SampleRows* rows;
     size_t bytes;
 };
-
-// Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream; ColPlan col; int occ; };
-constexpr int kNumCU = 256;                          // MI355X
-
-ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
-    ScorePlan s;
-    s.nbt = (N + 31) / 32;                            // 32-row text blocks
-    s.nbw = s.nbt == 1 ? 1 : (s.nbt == 2 ? 2 : 4);    // text blocks per block, one per wave column
-    s.ng = (s.nbt + s.nbw - 1) / s.nbw;               // text groups: each goes over K, side by side
-    // sweep 1: blocks of four waves (two per CU) or of eight (one per CU; the chunks two small blocks would take meet in
-    // LDS), and the number of key chunks per (sample, head, text group), at least four 128-key units each.  Whole rounds
-    // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start
-    // (5), the keys it takes (ns per key, from alone on the chip to every place taken), the merge kernel for several chunks.
-    // Measured to within 20 % at 17 shapes; before -> after e.g. 13 x 1039 keys, 32 heads, 10 text rows: 36.6 -> 23.1,
-    // 6 x 1152 keys, 384 text rows: 250 -> 69, 5 x 774 keys, 16 heads, 60 text rows: 14.5 -> 13.1.
-    const int units = (Mv + N + 127) / 128;
-    const long n = (long)B * H * s.ng;
-    double best = 0;
-    for (int waves = 4; waves <= 8; waves += 4)
-        for (int nch = 1; nch <= kMaxChunks && (nch == 1 || nch <= units / 4); ++nch) {
-            const long blocks = n * nch, places = waves == 4 ? 2 * kNumCU : kNumCU;
-            const double fill = blocks < places ? (double)blocks / places : 1.0;
-            const double alone = s.nbw == 1 ? 7.5 : (s.nbw == 2 ? (waves == 8 ? 8.0 : 9.0) : (waves == 8 ? 11.0 : 14.0));
-            const double full = waves == 8 ? (s.nbw < 4 ? 11.5 : (s.ng > 1 ? 15.0 : 16.0)) : (s.nbw < 4 ? 21.0 : (s.ng > 1 ? 26.0 : 34.0));
-            const double per_key = alone + (full - alone) * fill;
-            const double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? 5.0 : 0.0);
-            if (best == 0 || t < 0.97 * best) { best = t; s.rs_waves = waves; s.nch = nch; }
-        }
-    // a vision K that outgrows the Infinity Cache before the second sweep comes to it is read with streaming loads: what
-    // the first sweep leaves in the cache then only has to be pushed out again (6 x 6009 keys, 32 heads: both sweeps 147 ->
-    // 136 us, 16 x 2880: 201 -> 188); where a good part of it survives, plain loads (8 x 2880 with 3/4 of the slots
-    // valid: 85 against 88).  Up to 64 text rows the line lies lower (3 x 5523, 40 heads, 170 MB: 81 -> 73; 13 x 1029, 110 MB: 49 -> 52)
-    const double k_mb = (double)B * Mv * H * d * 2 / 1e6;
-    s.rs_stream = k_mb > (s.nbw <= 2 ? 160.0 : 230.0);
-    // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
-    ColPlan& c = s.col;
-    c.kb = s.nbw == 1 ? 128 : 64;
-    c.nkg = (Mv + c.kb - 1) / c.kb;
-    c.nbw = s.nbw;
-    c.U = (long)B * c.nkg * H * s.ng;
-    // blocks per CU: two where a block holds four text blocks (the second block covers the first one's waits),
-    // and with two text blocks when the runs stay long enough (20 units per CU); otherwise one (fewer, longer
-    // runs: fewer pieces, fewer prologues; measured faster there)
-    s.occ = s.nbw == 4 || (s.nbw == 2 && c.U >= 20L * kNumCU) ? 2 : 1;
-    // (two of them where a single text block would leave three quarters of the CUs idle: 1 x 576 keys 9.2 us for the sweep
-    // + 5.9 for its pieces with four, 7.2 + 6.6 with two; 4 x 576 with 100 text rows 12.9 + 5.6 and 13.4 + 7.1; and 2 x 1121
-    // keys of 64, 32 heads, 28 text rows, with row normalisers: 28.7 and 29.1 for the call)
-    const long least = s.nbw == 1 && c.U < kNumCU ? 2 : 4;
-    long P = (c.U + least - 1) / least;
-    if (P > kNumCU * s.occ) P = kNumCU * s.occ;
-    if (P < 1) P = 1;
-    c.P = (int)P;
-    // pieces a key group can be cut into; sized for half the planned units (samples whose valid vision rows
-    // are a prefix of their slots bring fewer key groups), beyond that fewer blocks work
-    c.Gmax = (int)((2L * H * c.P + c.U - 1) / c.U) + 1;
-    if (c.Gmax > H) c.Gmax = H;
-    return s;
-}
 
 PrefillWorkspace carve_prefill(void* base, int B, int Mv, int N, int H, int Rcap) {
     Carver c(base);

@@ -1,0 +1,63 @@
+"""GPU parity of the column sweep where the mask or the prompts leave far fewer units than the launch was planned for: the
+workspace ends where the library says, what lies behind it stays as it was, and what the call did not write into it first
+(NaN patterns here) reaches no score."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from oracle import FILTER_BUDGET
+from parity import check_prefill
+
+pytestmark = pytest.mark.gpu
+
+
+def normalisers(t, Mv, vis, scale):
+    q, k = (wl.bf16_bits_to_f32(t[n]).astype(np.float64) for n in ("q_txt", "k"))
+    N = q.shape[1]
+    s = np.einsum("bihd,bjhd->bhij", q, k) * scale
+    text = np.broadcast_to(np.tril(np.ones((N, N), bool)), (len(q), N, N))
+    seen = np.concatenate([np.broadcast_to(vis[:, None] != 0, (len(q), N, Mv)), text], 2)
+    s = np.where(seen[:, None], s, -np.inf)
+    m = s.max(-1, keepdims=True)
+    return (m[..., 0] + np.log(np.exp(s - m).sum(-1))).astype(np.float32)
+
+
+def check(H, valid, N, txt, with_lse):
+    import torch
+    import paper_2411_10803_amd as md
+    from paper_2411_10803_amd import binding, harness
+    cfg = wl.tiny(wl.CONFIGS[2], B=len(valid), T=1, Hg=24, Wg=24, N=N, H=H, d=64, C=64)
+    t = wl.prefill_inputs(cfg)
+    Mv, R, scale = cfg.M, 96, 0.125
+    vis = np.zeros((cfg.B, Mv), np.uint8)
+    for b, n in enumerate(valid):
+        vis[b, :n] = 1
+    txt_len = None if txt is None else np.array(txt, np.int32)
+    lse = normalisers(t, Mv, vis, scale) if with_lse else None
+    gamma, alpha = 1.0 / Mv, 2.0 / (Mv + N)
+    dev = [harness.to_dev(t[n], True) for n in ("q_txt", "k", "v", "hidden")]
+    size = binding.prefill_workspace(cfg.B, Mv, N, H, R, "cuda").numel()
+    room = torch.full((size + (8 << 20),), 0xFF, dtype=torch.uint8, device="cuda")
+    out = md.mustdrop_prefill_filter(*dev, harness.to_dev(vis), harness.to_dev(txt_len), None, Mv, scale, FILTER_BUDGET, R,
+                                     gamma, alpha, R, row_lse=harness.to_dev(lse), workspace=room[:size])
+    torch.cuda.synchronize()
+    assert bool((room[size:] == 0xFF).all()), "written behind the workspace"
+    g = harness.outputs_to_host(out)
+    o = oracle.prefill_filter(t["q_txt"], t["k"], t["v"], t["hidden"], vis, txt_len, None, Mv, scale, FILTER_BUDGET, R, gamma,
+                              alpha, R)
+    check_prefill(g, o, t, Mv, vis, None, FILTER_BUDGET, R, gamma, alpha, R)
+
+
+@pytest.mark.parametrize("with_lse", [False, True])
+@pytest.mark.parametrize("valid", [1, 128, 144, 256])
+@pytest.mark.parametrize("H", [2, 12, 16, 32, 40])
+def test_few_valid_slots_of_one_image(H, valid, with_lse):
+    check(H, [valid], 20, None, with_lse)
+
+
+@pytest.mark.parametrize("N,valid,txt", [(32, [576, 130, 1], [0, 32, 5]), (9, [40, 576], [9, 0]), (60, [1, 64], [60, 0]),
+                                         (150, [70, 576, 3], [1, 0, 150])])
+@pytest.mark.parametrize("with_lse", [False, True])
+def test_prompts_without_rows(N, valid, txt, with_lse):
+    check(16, valid, N, txt, with_lse)

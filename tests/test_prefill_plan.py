@@ -1,0 +1,17 @@
+"""The cut of the column sweep into blocks and pieces, over shapes and over what a mask leaves of them (CPU, g++)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+def test_no_empty_run_and_no_piece_beyond_the_workspace(tmp_path):
+    exe = str(tmp_path / "prefill_plan")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-fsanitize=undefined", "-fno-sanitize-recover=all",
+                           os.path.join(HERE, "plan", "prefill_plan_main.cpp"), "-o", exe])
+    r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-3000:]
