@@ -137,6 +137,8 @@ constexpr int kClsRows = 8;
 __host__ __device__ __forceinline__ int cls_groups(int M) { return (M + 1 + kClsRows - 1) / kClsRows; }
 
 // it_first, it_end: the rows' 64-vector slices to work on (all of them, or with SLICED the one of this wave).
+// s_stat: the block's waves merge their groups' statistics (see ScoreBlocks); `part` then takes the maxima m alone, as
+// floats [b][h][group].
 template <bool BF, bool SLICED>
 __device__ __forceinline__ void cls_logits_rows(
     int b, int g, int it_first, int it_end, const void* __restrict__ q_cls, const void* __restrict__ k_cls, const uint8_t* __restrict__ valid,
@@ -169,6 +171,7 @@ __device__ __forceinline__ void cls_logits_rows(
     const float scale = 1.0f / sqrtf((float)p.dc);
     float* out = logits + ((size_t)b * (p.M + 1) + j0) * p.Hc;
     float2* pout = part + (size_t)b * p.Hc * gps + g;
+    float* pmax = reinterpret_cast<float*>(part) + (size_t)b * p.Hc * gps + g;
     // the R logits of one head -> numerators (in place) and their statistics (every lane that holds
     // them computes the same values)
     auto finish = [&](float (&lg)[R]) -> float2 {
@@ -216,8 +219,8 @@ __device__ __forceinline__ void cls_logits_rows(
                 if (idx < nvec && (lane & (vph - 1)) == 0) {
                     const int h = idx / vph;
                     const float2 st = finish(lg);
-                    pout[(size_t)h * gps] = st;
-                    if (s_stat) s_stat[h] = st;
+                    if (s_stat) { s_stat[h] = st; pmax[(size_t)h * gps] = st.x; }
+                    else pout[(size_t)h * gps] = st;
 #pragma unroll
                     for (int r = 0; r < R; ++r)
                         if (act[r]) out[(size_t)r * p.Hc + h] = lg[r];
@@ -233,8 +236,8 @@ __device__ __forceinline__ void cls_logits_rows(
                     if (lane == 0) {
                         const int h = it / per_head;
                         const float2 st = finish(lg);
-                        pout[(size_t)h * gps] = st;
-                        if (s_stat) s_stat[h] = st;
+                        if (s_stat) { s_stat[h] = st; pmax[(size_t)h * gps] = st.x; }
+                        else pout[(size_t)h * gps] = st;
 #pragma unroll
                         for (int r = 0; r < R; ++r)
                             if (act[r]) out[(size_t)r * p.Hc + h] = lg[r];
@@ -357,7 +360,7 @@ struct KeyScoreLds {
 };
 __device__ __forceinline__ void key_scores(
     int b, int chunk, const EncodeDims& p, const uint8_t* __restrict__ valid, const float* __restrict__ logits,
-    const float2* __restrict__ cls_part, const float2* __restrict__ block_stat, float* __restrict__ acls,
+    const float* __restrict__ group_max, const float2* __restrict__ block_stat, float* __restrict__ acls,
     float* __restrict__ a_cls_out, KeyScoreLds& s)
 {
     const int tid = threadIdx.x, M = p.M, Hc = p.Hc;
@@ -405,8 +408,8 @@ __device__ __forceinline__ void key_scores(
     }
     __syncthreads();
     for (int e = tid; e < ng * Hc; e += 256) {
-        const int hh = e / ng, g = e - hh * ng;      // groups contiguous in cls_part
-        s.f[g * Hc + hh] = fast_exp2(cls_part[((size_t)b * Hc + hh) * gps + g0 + g].x - s.m[hh]) * s.inv[hh];
+        const int hh = e / ng, g = e - hh * ng;      // groups contiguous in group_max
+        s.f[g * Hc + hh] = fast_exp2(group_max[((size_t)b * Hc + hh) * gps + g0 + g] - s.m[hh]) * s.inv[hh];
     }
     __syncthreads();
     if (j >= M) return;
@@ -431,7 +434,8 @@ __device__ __forceinline__ void key_scores(
 //   key rows alone,             then windows with the key-score blocks ahead of them: two launches for samples whose
 //                               decision wants the scores ready-made; the key scores hide behind the windows.
 //                               The key-row blocks (each within one sample) then also leave their groups' statistics
-//                               merged: block_stat[b][block of the sample][h].
+//                               merged: block_stat[b][block of the sample][h], in the half of cls_part that the
+//                               groups' sums do not need then (their maxima take the first half, as floats).
 struct ScoreBlocks { int keyscore, windows, rows, slices; };         // blocks of each kind, in grid order; waves per key-row group
 template <int WSM, bool XBF, bool QKBF>
 __global__ __launch_bounds__(256) void encode_scores_kernel(
@@ -444,7 +448,7 @@ __global__ __launch_bounds__(256) void encode_scores_kernel(
     int blk = blockIdx.x;
     if (blk < nb.keyscore) {
         const int chunks = (p.M + kKeyTokens - 1) / kKeyTokens;
-        key_scores(blk / chunks, blk % chunks, p, valid, logits, cls_part, block_stat, acls, a_cls_out, s.k);
+        key_scores(blk / chunks, blk % chunks, p, valid, logits, reinterpret_cast<const float*>(cls_part), block_stat, acls, a_cls_out, s.k);
         return;
     }
     blk -= nb.keyscore;
@@ -1223,7 +1227,7 @@ __global__ __launch_bounds__(256) void encode_emit_kernel(
 }
 
 struct EncodeWorkspace {
-    float* logits; float2* cls_part; float2* block_stat; float* acls; float* sim; uint8_t* iskey; uint8_t* wmerged;
+    float* logits; float2* cls_part; float* acls; float* sim; uint8_t* iskey; uint8_t* wmerged;
     int32_t* dstpos;
     size_t bytes;
 };
@@ -1233,7 +1237,6 @@ EncodeWorkspace carve_encode(void* base, int B, int M, int W, int Hc) {
     EncodeWorkspace ws;
     ws.logits = c.take<float>((size_t)B * (Hc > 0 ? Hc : 1) * (M + 1));
     ws.cls_part = c.take<float2>((size_t)B * (Hc > 0 ? Hc : 1) * cls_groups(M));
-    ws.block_stat = c.take<float2>((size_t)B * (Hc > 0 ? Hc : 1) * cls_blocks(M));
     ws.acls = c.take<float>((size_t)B * M);
     ws.sim = c.take<float>((size_t)B * W);
     ws.iskey = c.take<uint8_t>((size_t)B * M);
@@ -1365,9 +1368,11 @@ int encode_merge_impl(
     // 4 x 8064 66.8 / 56.5.  (The LDS of the former stays below 64 KiB.)
     const size_t dlds = decide_fast_lds_bytes(M), llds = 5 * (size_t)M;
     const bool fast_ok = M <= 5120 && (!with_keys || (Hc <= 16 && Hc % 4 == 0));
-    const bool large_ok = !fast_ok && M <= kLargeTokens && (!with_keys || (Hc <= kMaxMergedHeads && Hc % 4 == 0));
+    // (at least two groups of key rows: what their blocks leave then fits in half of cls_part)
+    const bool large_ok = !fast_ok && M <= kLargeTokens && (!with_keys || (Hc <= kMaxMergedHeads && Hc % 4 == 0 && cls_groups(M) >= 2));
     const bool xbf = x_dtype == MD_BF16, qkbf = qk_dtype == MD_BF16;
-    const ScoreArgs sa{x, q_cls, k_cls, valid, wsp.sim, wsp.logits, wsp.cls_part, large_ok ? wsp.block_stat : nullptr, wsp.acls, a_cls_out};
+    const ScoreArgs sa{x, q_cls, k_cls, valid, wsp.sim, wsp.logits, wsp.cls_part,
+                       large_ok && with_keys ? wsp.cls_part + (size_t)B * Hc * cls_groups(M) / 2 : nullptr, wsp.acls, a_cls_out};
     if (large_ok && with_keys) {
         launch_scores(ws, ScoreBlocks{0, 0, row_blocks, 1}, st, xbf, qkbf, p, sa);
         launch_scores(ws, ScoreBlocks{B * ((M + kKeyTokens - 1) / kKeyTokens), win_blocks, 0, 1}, st, xbf, qkbf, p, sa);

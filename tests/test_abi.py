@@ -123,6 +123,13 @@ def test_noalloc_rejects_shapes_beyond_the_static_buffer(lib):
     assert call(0, 1) == 1
 
 
+@pytest.mark.parametrize("B,T,side", [(160, 1, 24), (90, 1, 32), (32, 5, 24), (20, 8, 24), (16, 10, 24), (10, 1, 96)])
+def test_shapes_that_just_fit_the_static_buffer(lib, B, T, side):
+    # with 16 heads and 2x2 windows, on each side of the token counts at which the decision kernels change
+    assert lib.mustdrop_encode_merge_workspace_bytes(B, T, side, side, 16, 1, 2, 2) <= 8 << 20
+    assert lib.mustdrop_encode_merge_workspace_bytes(B + max(B // 16, 1), T, side, side, 16, 1, 2, 2) > 8 << 20
+
+
 def decode(lib, **kw):
     a = dict(q=P(0x1000), k=P(0x10000000), v=P(0x80000000), B=2, Lcap=4096, H=32, d=128, budget=1024,
              ws=P(0x100000000), wsb=1 << 30)
