@@ -137,9 +137,11 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
     }
     float* lb = logits + (long)b * p.Lcap * p.H;
     const float scale_l2 = scale * kLog2eD;
+    // The maxima start at the lowest finite number, not at -inf: the first entry of a wave may be one that the caller masks
+    // (logit -inf), and -inf - -inf would make the head's sum a NaN.
     float m[NIT], z[NIT];
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) { m[it] = -INFINITY; z[it] = 0.f; }
+    for (int it = 0; it < NIT; ++it) { m[it] = -3.402823466e38f; z[it] = 0.f; }
 
     const int n = min(max(len[b], 0), p.Lcap);
     // the state as it is before the selection changes it, for the other selection blocks of the sample
@@ -173,7 +175,7 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const float t2 = part[it] * scale_l2;
-            const float dlt = t2 - m[it];            // +inf on the first entry
+            const float dlt = t2 - m[it];            // huge on the first entry
             const float e = fast_exp2(-fabsf(dlt));
             z[it] = dlt > 0.f ? fmaf(z[it], e, 1.0f) : z[it] + e;
             m[it] = fmaxf(m[it], t2);

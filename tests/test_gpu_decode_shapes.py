@@ -25,7 +25,15 @@ def test_long_caches_with_few_entries(cut):
     check(32, 64, 1000, cut, False, 8000)
 
 
-def check(H, d, L0, cut, head_major, slots):
+# entries that a caller masks through their keys, on all heads or on some: their logits are -inf, their probabilities zero
+@pytest.mark.parametrize("H,d,L0,cut", [(40, 128, 1025, 1), (12, 64, 300, 100), (40, 64, 700, 1), (32, 128, 1025, 1),
+                                        (3, 128, 200, 50), (8, 32, 400, 1)])
+@pytest.mark.parametrize("head_major", [False, True])
+def test_masked_entries(H, d, L0, cut, head_major):
+    check(H, d, L0, cut, head_major, None, masked=True)
+
+
+def check(H, d, L0, cut, head_major, slots, masked=False):
     import torch
     import paper_2411_10803_amd as md
     from paper_2411_10803_amd import harness
@@ -37,6 +45,12 @@ def check(H, d, L0, cut, head_major, slots):
     s0 = {"k": t["k_cache"], "v": t["v_cache"], "acc": rng.random((B, Lcap)).astype(np.float32) * np.float32(1.0 / L0),
           "ids": np.stack([rng.permutation(2 * Lcap)[:Lcap] for _ in range(B)]).astype(np.int32),
           "protect": t["protect"].copy(), "len": t["len0"].copy()}
+    if masked:
+        minus_inf, plus_inf = 0xFF80, 0x7F80
+        sign = t["q_steps"][0][:, :, 0] >> 15                                    # [B, H]: an infinity of the other sign than q's
+        hide = rng.random((B, Lcap, H)) < 0.1
+        hide[:, ::7] = True
+        s0["k"][..., 0] = np.where(hide, np.where(sign[:, None] != 0, plus_inf, minus_inf), s0["k"][..., 0]).astype(np.uint16)
     scale, decay = 1.0 / np.sqrt(d), 0.75
     dv = harness.decode_state_to_dev(s0)
     q = harness.to_dev(t["q_steps"][0], True)
