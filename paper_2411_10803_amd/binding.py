@@ -96,6 +96,9 @@ def _call(name: str, *args):
     try:
         rc = fn(*args)
     except C.ArgumentError as e:
+        for t, value in zip(_SIGNATURES[name], args):
+            if t != "p":
+                _TYPES[t](value)                           # raises what the conversion itself raises, e.g. OverflowError
         raise TypeError(f"{name}: {e}") from None
     _check(rc)
 

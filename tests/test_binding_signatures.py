@@ -32,3 +32,12 @@ def test_wrong_argument_types_raise_type_error():
             binding._call("mustdrop_decode_append", *[None] * 8, bad, 1, 1, 8, 0, 1, None)
     with pytest.raises(md.MustDropError):                 # and right ones reach the library's own checks
         binding._call("mustdrop_decode_append", *[None] * 8, 1, 1, 1, 8, 0, 1, None)
+
+
+def test_errors_of_a_conversion_itself_come_through():
+    class Broken:
+        def __float__(self):
+            raise ValueError("no number")
+    for bad, error in ((10 ** 400, OverflowError), (Broken(), ValueError), ("1.0", TypeError)):
+        with pytest.raises(error):
+            binding._call("mustdrop_decode_evict", *[None] * 7, 1, 1, 1, 8, bad, 1.0, 1, *[None] * 3, 0, None)
