@@ -948,19 +948,25 @@ int decode_evict_impl(
     const size_t select_lds = sizeof(int) * ((size_t)Lcap + (lane_sums ? 0 : 16 * 32 * ((size_t)H / 4)));
     const bool select_fast = (d == 128 || d == 64) && pieces <= 16 && Lcap <= 8192 && H % 4 == 0 && H <= 128 && select_lds <= 64 * 1024;
     // Moves in the selection's launch: blocks per sample that together cover the CUs but do not share one (33 x 168
-    // entries: 264 blocks 16.7 us, 231 10.0, 132 9.4; as two launches 8.3 + 4.3), with no more teams than rows that can leave, and reading no more than 32 MB of logits between them.  Where that leaves neither half the chip nor all
-    // the teams, the caches are long or many, and a launch for the moves is the smaller price (us, one launch / two:
+    // entries: 264 blocks 16.7 us, 231 10.0, 132 9.4; as two launches 8.3 + 4.3), with no more teams than rows that can leave,
+    // and reading no more than 32 MB of logits between them, 64 MB where all logits fit half of an XCD's 4 MB L2.  Where that leaves
+    // neither half the chip nor all the teams nor 64 blocks for the one sample, the caches are long or many, and a launch
+    // for the moves is the smaller price (us, one launch / two:
     // 4 x 778 entries of 40 heads 13.1 / 15.7, 1 x 1724 of 16 heads 8.7 / 12.8, 60 x 748 of 40 heads 14.4 / 16.7;
-    // 64 x 1025 of 4352 slots 18.4 / 16.2, 18 x 4036 40.4 / 25.8, 64 x 4096 cut to 1024 407 / 387)
+    // 64 x 1025 of 4352 slots 18.4 / 16.2, 18 x 4036 40.4 / 25.8, 64 x 4096 cut to 1024 407 / 387).
+    // A few caches cut by much need the blocks for their rows, a steady loop does not mind them: 1 x 3500 entries of 32 heads
+    // cut to 1000, the call, 54.2 us with 32 blocks and 44.6 with 128 (two launches 50.6), one entry leaving 18.2 and 18.2;
+    // 2 x 2449 cut to 523 49.6 with 64 blocks, 46.4 with 212 (two launches 47.2), one leaving 19.2 and 19.3
     int select_x = B <= 256 ? 256 / B : 1;
-    const long leave_x = Lcap > budget ? (Lcap - budget + 3l) / 4 : 1, read_x = (32l << 20) / ((long)B * Lcap * H * 4);
+    const long logit_bytes = (long)B * Lcap * H * 4;
+    const long leave_x = Lcap > budget ? (Lcap - budget + 3l) / 4 : 1, read_x = (logit_bytes <= (2l << 20) ? 64l << 20 : 32l << 20) / logit_bytes;
     if (select_x > leave_x) select_x = (int)leave_x;
-    if (select_x > 32) select_x = 32;
+    if (select_x > 128) select_x = 128;
     if (select_x > read_x) select_x = (int)read_x;
     // (and where 64 MB or more could move, counted read and written: 138 blocks move the rows of 6 x 1838 entries cut to 345
     // more slowly than a launch over the whole chip, 30.3 against 15.1 + 13.1)
     const double move_bytes = (double)B * (Lcap > budget ? (Lcap - budget < budget ? Lcap - budget : budget) : 0) * H * d * 8;
-    const bool one_launch = select_fast && select_x >= 1 && move_bytes < 64e6 && (select_x * (long)B >= 128 || select_x == leave_x || select_x == 32);
+    const bool one_launch = select_fast && select_x >= 1 && move_bytes < 64e6 && (select_x * (long)B >= 128 || select_x == leave_x || select_x >= 64);
     if (!one_launch) select_x = 1;
     const StateArrays state{acc, ids, protect, len};
     const StateArrays copy = one_launch && select_x > 1 ? w.copy : StateArrays{nullptr, nullptr, nullptr, nullptr};

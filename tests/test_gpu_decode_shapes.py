@@ -25,6 +25,20 @@ def test_long_caches_with_few_entries(cut):
     check(32, 64, 1000, cut, False, 8000)
 
 
+# a cut of many rows by more than 64 blocks per sample, all teams busy and not
+@pytest.mark.parametrize("H,L0,cut,slots", [(32, 2400, 1900, None), (16, 700, 520, None), (4, 5000, 4100, 8192)])
+@pytest.mark.parametrize("head_major", [False, True])
+def test_many_blocks_per_sample(H, L0, cut, slots, head_major):
+    check(H, 64, L0, cut, head_major, slots)
+
+
+# the largest LDS a selection in registers asks for
+@pytest.mark.parametrize("H,slots", [(64, 8192), (96, 4096)])
+@pytest.mark.parametrize("cut", [1, 200])
+def test_most_lds(H, slots, cut):
+    check(H, 64, 1200, cut, False, slots)
+
+
 # entries that a caller masks through their keys, on all heads or on some: their logits are -inf, their probabilities zero
 @pytest.mark.parametrize("H,d,L0,cut", [(40, 128, 1025, 1), (12, 64, 300, 100), (40, 64, 700, 1), (32, 128, 1025, 1),
                                         (3, 128, 200, 50), (8, 32, 400, 1)])
