@@ -137,9 +137,9 @@ constexpr int kClsRows = 8;
 __host__ __device__ __forceinline__ int cls_groups(int M) { return (M + 1 + kClsRows - 1) / kClsRows; }
 
 // it_first, it_end: the rows' 64-vector slices to work on (all of them, or with SLICED the one of this wave).
-// s_stat: the block's waves merge their groups' statistics (see ScoreBlocks); `part` then takes the maxima m alone, as
-// floats [b][h][group].
-template <bool BF, bool SLICED>
+// MERGED: the block's waves merge their groups' statistics through s_stat (see ScoreBlocks); `part` then takes the
+// maxima m alone, as floats [b][h][group].
+template <bool BF, bool SLICED, bool MERGED>
 __device__ __forceinline__ void cls_logits_rows(
     int b, int g, int it_first, int it_end, const void* __restrict__ q_cls, const void* __restrict__ k_cls, const uint8_t* __restrict__ valid,
     const EncodeDims& p, float* __restrict__ logits, float2* __restrict__ part, float2* s_stat)
@@ -219,7 +219,7 @@ __device__ __forceinline__ void cls_logits_rows(
                 if (idx < nvec && (lane & (vph - 1)) == 0) {
                     const int h = idx / vph;
                     const float2 st = finish(lg);
-                    if (s_stat) { s_stat[h] = st; pmax[(size_t)h * gps] = st.x; }
+                    if (MERGED) { s_stat[h] = st; pmax[(size_t)h * gps] = st.x; }
                     else pout[(size_t)h * gps] = st;
 #pragma unroll
                     for (int r = 0; r < R; ++r)
@@ -236,7 +236,7 @@ __device__ __forceinline__ void cls_logits_rows(
                     if (lane == 0) {
                         const int h = it / per_head;
                         const float2 st = finish(lg);
-                        if (s_stat) { s_stat[h] = st; pmax[(size_t)h * gps] = st.x; }
+                        if (MERGED) { s_stat[h] = st; pmax[(size_t)h * gps] = st.x; }
                         else pout[(size_t)h * gps] = st;
 #pragma unroll
                         for (int r = 0; r < R; ++r)
@@ -460,14 +460,16 @@ __global__ __launch_bounds__(256) void encode_scores_kernel(
     const int gps = cls_groups(p.M);
     if (nb.slices > 1) {                             // a wave per (group of key rows, slice of the feature dimension)
         const int item = blk * kEncWaves + wave_id(), gs = item / nb.slices, sl = item - gs * nb.slices, b = gs / gps;
-        if (b < p.B) cls_logits_rows<QKBF, true>(b, gs - b * gps, sl, sl + 1, q_cls, k_cls, valid, p, logits, cls_part, nullptr);
+        if (b < p.B) cls_logits_rows<QKBF, true, false>(b, gs - b * gps, sl, sl + 1, q_cls, k_cls, valid, p, logits, cls_part, nullptr);
         return;
     }
     const int cb = cls_blocks(p.M), b = blk / cb, wb = blk % cb, g = wb * kEncWaves + wave_id();
     const int iters = (p.D / Vec<QKBF>::N + kWave - 1) / kWave;
-    if (g < gps)
-        cls_logits_rows<QKBF, false>(b, g, 0, iters, q_cls, k_cls, valid, p, logits, cls_part, block_stat ? s.stat[wave_id()] : nullptr);
-    if (!block_stat) return;
+    if (!block_stat) {
+        if (g < gps) cls_logits_rows<QKBF, false, false>(b, g, 0, iters, q_cls, k_cls, valid, p, logits, cls_part, nullptr);
+        return;
+    }
+    if (g < gps) cls_logits_rows<QKBF, false, true>(b, g, 0, iters, q_cls, k_cls, valid, p, logits, cls_part, s.stat[wave_id()]);
     __syncthreads();
     const int nw = min(kEncWaves, gps - wb * kEncWaves);
     for (int h = threadIdx.x; h < p.Hc; h += blockDim.x) {
