@@ -435,7 +435,8 @@ __device__ __forceinline__ void key_scores(
 //                               decision wants the scores ready-made; the key scores hide behind the windows.
 //                               The key-row blocks (each within one sample) then also leave their groups' statistics
 //                               merged: block_stat[b][block of the sample][h], in the half of cls_part that the
-//                               groups' sums do not need then (their maxima take the first half, as floats).
+//                               groups' sums do not need then (their maxima take the first half, as floats; it fits
+//                               from two groups on, and such calls have more).
 struct ScoreBlocks { int keyscore, windows, rows, slices; };         // blocks of each kind, in grid order; waves per key-row group
 template <int WSM, bool XBF, bool QKBF>
 __global__ __launch_bounds__(256) void encode_scores_kernel(
@@ -1367,12 +1368,16 @@ int encode_merge_impl(
     const int row_blocks = with_keys ? B * cls_blocks(M) : 0;
     // Up to 5120 tokens the decision kernel fetches the numerators itself; beyond that the scores are made beforehand
     // (two score launches, about 5 us more, against a decision 8 to 15 us shorter).  Measured, us per call, numerators /
-    // ready-made: 4 x 4608 tokens 41.1 / 41.7, 4 x 5760 48.5 / 49.6, 4 x 6144 51.3 / 47.9, 16 x 5760 135.5 / 131.5,
+    // ready-made: 4 x 4608 tokens 41.1 / 41.7, 4 x 5760 48.5 / 45.8, 4 x 6144 51.3 / 47.9, 16 x 5760 135.5 / 131.5,
     // 4 x 8064 66.8 / 56.5.  (The LDS of the former stays below 64 KiB.)
+    // With more heads than the former merges (16) the other choice is the general kernel behind the one score launch,
+    // sliced: its decision grows with tokens times heads, the two launches cost 10 to 20 us more in the scores.  General /
+    // ready-made: 1 x 351 tokens of 32 heads 22.4 / 32.0, 4 x 756 30.1 / 34.6, 16 x 756 53.3 / 53.9, 16 x 1024 66.8 / 65.1;
+    // 1 x 756 of 64 heads 34.6 / 41.4, 4 x 1024 51.7 / 48.3; 1 x 2048 of 20 heads 33.4 / 29.9.
     const size_t dlds = decide_fast_lds_bytes(M), llds = 5 * (size_t)M;
     const bool fast_ok = M <= 5120 && (!with_keys || (Hc <= 16 && Hc % 4 == 0));
-    // (at least two groups of key rows: what their blocks leave then fits in half of cls_part)
-    const bool large_ok = !fast_ok && M <= kLargeTokens && (!with_keys || (Hc <= kMaxMergedHeads && Hc % 4 == 0 && cls_groups(M) >= 2));
+    const bool few_ok = M <= 1024 && (long)M * Hc <= (B == 1 ? 49152 : 24576);
+    const bool large_ok = !fast_ok && M <= kLargeTokens && (!with_keys || (Hc <= kMaxMergedHeads && Hc % 4 == 0 && !few_ok));
     const bool xbf = x_dtype == MD_BF16, qkbf = qk_dtype == MD_BF16;
     const ScoreArgs sa{x, q_cls, k_cls, valid, wsp.sim, wsp.logits, wsp.cls_part,
                        large_ok && with_keys ? wsp.cls_part + (size_t)B * Hc * cls_groups(M) / 2 : nullptr, wsp.acls, a_cls_out};

@@ -43,17 +43,15 @@ def test_many_tokens_per_sample(M, win, Hc, extras):
     check_encode(g, o, x, wl.BF16, valid, *args[:7], 64, key_lambda=2.0)
 
 
-# more heads than the decision kernel merges itself: the scores come ready-made for few tokens too, from two groups of
-# key rows on (8 tokens), below that in the general kernel
-@pytest.mark.parametrize("M", [7, 8, 15, 16, 40])
-@pytest.mark.parametrize("Hc", [20, 64])
-def test_few_tokens_many_heads(M, Hc):
+# more heads than the decision kernel merges itself: the general kernel for few tokens, ready-made scores for more
+@pytest.mark.parametrize("B,M,Hc", [(3, 7, 20), (3, 384, 64), (3, 385, 64), (1, 768, 64), (1, 769, 64), (2, 1024, 24), (2, 1025, 24)])
+def test_more_than_sixteen_heads(B, M, Hc):
     from paper_2411_10803_amd import harness
     rng = np.random.default_rng(M)
-    x = wl.f32_to_bf16_bits(rng.standard_normal((3, M, Hc * 8), dtype=np.float32))
-    q = wl.f32_to_bf16_bits(rng.standard_normal((3, Hc, 8), dtype=np.float32))
-    k = wl.f32_to_bf16_bits(rng.standard_normal((3, 1 + M, Hc, 8), dtype=np.float32))
-    valid = (rng.random((3, M)) > 0.2).astype(np.uint8)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((B, M, Hc * 8), dtype=np.float32))
+    q = wl.f32_to_bf16_bits(rng.standard_normal((B, Hc, 8), dtype=np.float32))
+    k = wl.f32_to_bf16_bits(rng.standard_normal((B, 1 + M, Hc, 8), dtype=np.float32))
+    valid = (rng.random((B, M)) > 0.2).astype(np.uint8)
     args = (1, 1, M, 1, 1, 4, 0.0, 3)
     g = harness.encode_on_gpu(x, wl.BF16, q, k, wl.BF16, None, valid, *args)
     o = oracle.encode_merge(x, wl.BF16, q, k, wl.BF16, None, valid, *args)
