@@ -256,7 +256,7 @@ __device__ __forceinline__ void interleave_mfma_valu() {
     }
 }
 
-template <int NBW, int TW, int KS, bool STREAM>
+template <int NBW, int TW, int KS, bool STREAM, bool DEEP>
 __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     const uint16_t* __restrict__ q_txt, const uint16_t* __restrict__ k,
     const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ txt_len, PrefillDims p, float scale_log2e,
@@ -269,8 +269,9 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     constexpr int NW = NBW * TW;
     // LDS slots.  The eight-wave form runs with two (one step in flight while one is worked on): with more
     // requests outstanding per CU the sweep gets slower, not faster, when K comes from HBM (46.3 against 47.9 us);
-    // four tile lanes too: three slots of 128 rows would leave room for one block per CU instead of two
-    constexpr int S = TW == 1 ? 4 : (NBW == 1 || NBW == 4 ? 2 : 3);
+    // four tile lanes too: three slots of 128 rows would leave room for one block per CU instead of two, which is
+    // all that there is where the grid has no more (DEEP: 4 x 861 keys, 32 heads, 2 text rows 11.1 -> 10.1 us)
+    constexpr int S = TW == 1 ? 4 : (NBW == 4 || (NBW == 1 && !DEEP) ? 2 : 3);
     constexpr int SLOT_ROWS = 32 * TW, SLOT_BYTES = SLOT_ROWS * T::ROWB;
     constexpr int NLW = SLOT_ROWS / T::RPL / NW;      // load instructions per wave and step
     constexpr int QBYTES = NBW * 32 * T::ROWB;        // the block's query tiles during the prologue (one per wave column)
@@ -1222,9 +1223,10 @@ struct PrefillWorkspace {
 PrefillWorkspace carve_prefill(void* base, int B, int Mv, int N, int H, int Rcap) {
     Carver c(base);
     PrefillWorkspace w;
-    const ScorePlan s = plan_scores(B, Mv, N, H, 128);     // (the sizes do not depend on d)
+    const ScorePlan s = plan_scores(B, Mv, N, H, 128);     // (of the sizes only the number of chunks depends on d)
+    const int s64 = plan_scores(B, Mv, N, H, 64).nch, nch = s.nch > s64 ? s.nch : s64;
     const int Npad = s.nbt * 32;
-    w.partial = c.take<float2>((size_t)B * H * s.nch * Npad);
+    w.partial = c.take<float2>((size_t)B * H * nch * Npad);
     w.cstat = c.take<float>((size_t)B * H * Npad);
     w.qfrag = c.take<bf16x8>((size_t)B * H * Npad * 16);      // [B][H][NB][KS][64] fragments, d <= 128
     w.apart = c.take<float>((size_t)s.col.Gmax * B * Mv * Npad);
@@ -1244,20 +1246,21 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
     const uint16_t* kp = static_cast<const uint16_t*>(k);
     if (!row_lse) {
         const dim3 g1 = s.ng == 1 ? dim3(p.nch, p.H, p.B) : dim3((unsigned)(((long)p.nch * p.H * p.B + 7) / 8 * 8 * s.ng));
+#define MD_ROWSTATS2(NBW_, TW_, ST_, DEEP_)                                                                    \
+    MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_kernel<NBW_, TW_, KS, ST_, DEEP_>), g1, 64 * NBW_ * TW_, 0, \
+        qp, kp, vis_valid, txt_len, p, scale_log2e, w.partial, w.cstat, w.qfrag, w.rows)
 #define MD_ROWSTATS(NBW_, TW_)                                                                                 \
         do {                                                                                                   \
-            if (s.rs_stream)                                                                                   \
-                MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_kernel<NBW_, TW_, KS, true>), g1, 64 * NBW_ * TW_, 0, \
-                    qp, kp, vis_valid, txt_len, p, scale_log2e, w.partial, w.cstat, w.qfrag, w.rows);          \
-            else                                                                                               \
-                MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_kernel<NBW_, TW_, KS, false>), g1, 64 * NBW_ * TW_, 0, \
-                    qp, kp, vis_valid, txt_len, p, scale_log2e, w.partial, w.cstat, w.qfrag, w.rows);          \
+            if (s.rs_stream) MD_ROWSTATS2(NBW_, TW_, true, false);                                             \
+            else if (NBW_ == 1 && TW_ == 4 && s.rs_deep) MD_ROWSTATS2(NBW_, TW_, false, (NBW_ == 1 && TW_ == 4)); \
+            else MD_ROWSTATS2(NBW_, TW_, false, false);                                                        \
         } while (0)
         const bool big = s.rs_waves == 8;
         if (s.nbw == 1) { if (big) MD_ROWSTATS(1, 8); else MD_ROWSTATS(1, 4); }
         else if (s.nbw == 2) { if (big) MD_ROWSTATS(2, 4); else MD_ROWSTATS(2, 2); }
         else { if (big) MD_ROWSTATS(4, 2); else MD_ROWSTATS(4, 1); }
 #undef MD_ROWSTATS
+#undef MD_ROWSTATS2
         if (p.nch > 1) {
             const long n = (long)p.B * p.H * p.Npad;
             MD_LAUNCH("prefill_cstat", st, (prefill_cstat_kernel), (unsigned)((n + 255) / 256), 256, 0, w.partial, txt_len, p, w.cstat);

@@ -49,13 +49,19 @@ MD_PLAN_FN ColRun effective_run(int tiles, int H, ColPlan cp) {
 }
 
 // Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream; ColPlan col; int occ; };
+struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep; ColPlan col; int occ; };
 
 inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     ScorePlan s;
     s.nbt = (N + 31) / 32;                            // 32-row text blocks
     s.nbw = s.nbt == 1 ? 1 : (s.nbt == 2 ? 2 : 4);    // text blocks per block, one per wave column
     s.ng = (s.nbt + s.nbw - 1) / s.nbw;               // text groups: each goes over K, side by side
+    // a vision K that outgrows the Infinity Cache before the second sweep comes to it is read with streaming loads: what
+    // the first sweep leaves in the cache then only has to be pushed out again (6 x 6009 keys, 32 heads: both sweeps 147 ->
+    // 136 us, 16 x 2880: 201 -> 188); where a good part of it survives, plain loads (8 x 2880 with 3/4 of the slots
+    // valid: 85 against 88).  Up to 64 text rows the line lies lower (3 x 5523, 40 heads, 170 MB: 81 -> 73; 13 x 1029, 110 MB: 49 -> 52)
+    const double k_mb = (double)B * Mv * H * d * 2 / 1e6;
+    s.rs_stream = k_mb > (s.nbw <= 2 ? 160.0 : 230.0);
     // sweep 1: blocks of four waves (two per CU) or of eight (one per CU; the chunks two small blocks would take meet in
     // LDS), and the number of key chunks per (sample, head, text group), at least four 128-key units each.  Whole rounds
     // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start
@@ -67,20 +73,19 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     double best = 0;
     for (int waves = 4; waves <= 8; waves += 4)
         for (int nch = 1; nch <= kMaxChunks && (nch == 1 || nch <= units / 4); ++nch) {
-            const long blocks = n * nch, places = waves == 4 ? 2 * kNumCU : kNumCU;
+            const long blocks = n * nch, places = waves == 4 ? (s.nbw == 4 && d == 64 ? 3 : 2) * kNumCU : kNumCU;
             const double fill = blocks < places ? (double)blocks / places : 1.0;
-            const double alone = s.nbw == 1 ? 7.5 : (s.nbw == 2 ? (waves == 8 ? 8.0 : 9.0) : (waves == 8 ? 11.0 : 14.0));
-            const double full = waves == 8 ? (s.nbw < 4 ? 11.5 : (s.ng > 1 ? 15.0 : 16.0)) : (s.nbw < 4 ? 21.0 : (s.ng > 1 ? 26.0 : 34.0));
+            double alone = s.nbw == 1 ? 7.5 : (s.nbw == 2 ? (waves == 8 ? 8.0 : 9.0) : (waves == 8 ? 11.0 : 14.0));
+            double full = waves == 8 ? (s.nbw < 4 ? 11.5 : (s.ng > 1 ? 15.0 : 16.0)) : (s.nbw < 4 ? 21.0 : (s.ng > 1 ? 26.0 : 34.0));
+            // (heads of 64 with four text blocks: three blocks of four waves share a CU, one of eight waves no better than at
+            // d = 128; 2 x 8661 keys, 64 heads, 95 text rows 49.8 -> 38.6)
+            if (s.nbw == 4 && d == 64) { alone = waves == 8 ? 10.0 : 11.5; full = waves == 8 ? 10.5 : 21.0; }
+            if (s.nbw == 1 && waves == 4 && blocks <= kNumCU && !s.rs_stream) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
             const double per_key = alone + (full - alone) * fill;
             const double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? 5.0 : 0.0);
             if (best == 0 || t < 0.97 * best) { best = t; s.rs_waves = waves; s.nch = nch; }
         }
-    // a vision K that outgrows the Infinity Cache before the second sweep comes to it is read with streaming loads: what
-    // the first sweep leaves in the cache then only has to be pushed out again (6 x 6009 keys, 32 heads: both sweeps 147 ->
-    // 136 us, 16 x 2880: 201 -> 188); where a good part of it survives, plain loads (8 x 2880 with 3/4 of the slots
-    // valid: 85 against 88).  Up to 64 text rows the line lies lower (3 x 5523, 40 heads, 170 MB: 81 -> 73; 13 x 1029, 110 MB: 49 -> 52)
-    const double k_mb = (double)B * Mv * H * d * 2 / 1e6;
-    s.rs_stream = k_mb > (s.nbw <= 2 ? 160.0 : 230.0);
+    s.rs_deep = s.nbw == 1 && s.rs_waves == 4 && n * s.nch <= kNumCU && !s.rs_stream;
     // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
     ColPlan& c = s.col;
     c.kb = s.nbw == 1 ? 128 : 64;
