@@ -23,13 +23,13 @@ def normalisers(t, Mv, vis, scale):
     return (m[..., 0] + np.log(np.exp(s - m).sum(-1))).astype(np.float32)
 
 
-def check(H, valid, N, txt, with_lse):
+def check(H, valid, N, txt, with_lse, side=24):
     import torch
     import paper_2411_10803_amd as md
     from paper_2411_10803_amd import binding, harness
-    cfg = wl.tiny(wl.CONFIGS[2], B=len(valid), T=1, Hg=24, Wg=24, N=N, H=H, d=64, C=64)
+    cfg = wl.tiny(wl.CONFIGS[2], B=len(valid), T=1, Hg=side, Wg=side, N=N, H=H, d=64, C=64)
     t = wl.prefill_inputs(cfg)
-    Mv, R, scale = cfg.M, 96, 0.125
+    Mv, R, scale = cfg.M, min(96, cfg.M // 2), 0.125
     vis = np.zeros((cfg.B, Mv), np.uint8)
     for b, n in enumerate(valid):
         vis[b, :n] = 1
@@ -61,3 +61,13 @@ def test_few_valid_slots_of_one_image(H, valid, with_lse):
 @pytest.mark.parametrize("with_lse", [False, True])
 def test_prompts_without_rows(N, valid, txt, with_lse):
     check(16, valid, N, txt, with_lse)
+
+
+# more samples than a wave has lanes, some without valid slots' worth of a key group, some without text rows
+@pytest.mark.parametrize("N", [9, 150])
+@pytest.mark.parametrize("with_lse", [False, True])
+def test_more_than_64_samples(N, with_lse):
+    rng = np.random.default_rng(N)
+    valid = rng.integers(1, 145, 70).tolist()
+    txt = [0 if b % 9 == 4 else int(rng.integers(1, N + 1)) for b in range(70)]
+    check(3, valid, N, txt, with_lse, side=12)
