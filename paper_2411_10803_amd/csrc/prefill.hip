@@ -1208,6 +1208,7 @@ __global__ __launch_bounds__(256) void prefill_compact_kernel(
 
 // The same for K / V in other layouts: a row is gathered head slice by head slice (d contiguous
 // elements each) from the input layout and scattered to the output layout.
+template <bool STREAM>
 __global__ __launch_bounds__(256) void prefill_compact_strided_kernel(
     PrefillDims p, const int32_t* __restrict__ src_row,
     const u32x4* __restrict__ hidden, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -1221,18 +1222,19 @@ __global__ __launch_bounds__(256) void prefill_compact_strided_kernel(
     const int kvn = p.H * lph;
     const long sbase = (long)b * p.kv.batch + (long)src * p.kv.token;
     const long dbase = (long)b * out.batch + (long)o * out.token;
+    auto ld = [](const u32x4* q) { return STREAM ? __builtin_nontemporal_load(q) : *q; };
+    auto st = [](const u32x4& x, u32x4* q) { if (STREAM) __builtin_nontemporal_store(x, q); else *q = x; };
     for (int c = threadIdx.x; c < kvn; c += blockDim.x) {
         const int h = c / lph, w = c - h * lph;
         const long so = sbase + (long)h * p.kv.head + w * 8, d_o = dbase + (long)h * out.head + w * 8;
-        const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k + so));
-        const u32x4 c2 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(v + so));
+        const u32x4 a = ld(reinterpret_cast<const u32x4*>(k + so)), c2 = ld(reinterpret_cast<const u32x4*>(v + so));
         *reinterpret_cast<u32x4*>(k_out + d_o) = a;
-        __builtin_nontemporal_store(c2, reinterpret_cast<u32x4*>(v_out + d_o));
+        st(c2, reinterpret_cast<u32x4*>(v_out + d_o));
     }
     const int hv = p.C / 8;
     const u32x4* hs = hidden + ((long)b * p.L + src) * hv;
     u32x4* hd = hidden_out + ((long)b * rows_cap + o) * hv;
-    for (int c = threadIdx.x; c < hv; c += blockDim.x) __builtin_nontemporal_store(__builtin_nontemporal_load(hs + c), hd + c);
+    for (int c = threadIdx.x; c < hv; c += blockDim.x) st(ld(hs + c), hd + c);
 }
 
 struct PrefillWorkspace {
@@ -1421,10 +1423,17 @@ int prefill_filter_impl(
         MD_LAUNCH("prefill_compact", st, (prefill_compact_kernel), gc, 256, 0, p, src_row,
             static_cast<const u32x4*>(hidden), static_cast<const u32x4*>(k), static_cast<const u32x4*>(v),
             static_cast<u32x4*>(hidden_out), static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out), tr.enabled);
-    else
-        MD_LAUNCH("prefill_compact", st, (prefill_compact_strided_kernel), gc, 256, 0, p, src_row,
-            static_cast<const u32x4*>(hidden), static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),
-            static_cast<u32x4*>(hidden_out), static_cast<uint16_t*>(k_out), static_cast<uint16_t*>(v_out), lout);
+    else {
+        // Streaming where K, V and hidden together outgrow the Infinity Cache, so that the rows left in it are not written
+        // back under the next sweep (21 x 1163 keys, 40 heads of 64, 125 MB: compact + next row statistics 56.9 -> 53.8 us);
+        // smaller calls find their rows in L2, which streaming loads pass by (12 x 634, 32 heads of 64, 31 MB: 8.2 -> 6.0)
+#define MD_COMPACT_STRIDED(ST_)                                                                                \
+        MD_LAUNCH("prefill_compact", st, (prefill_compact_strided_kernel<ST_>), gc, 256, 0, p, src_row,            \
+            static_cast<const u32x4*>(hidden), static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),   \
+            static_cast<u32x4*>(hidden_out), static_cast<uint16_t*>(k_out), static_cast<uint16_t*>(v_out), lout)
+        if ((double)B * p.L * H * d * 2 > 100e6) MD_COMPACT_STRIDED(true); else MD_COMPACT_STRIDED(false);
+#undef MD_COMPACT_STRIDED
+    }
     return check_launch("prefill_filter");
 }
 
