@@ -104,6 +104,7 @@ __device__ __forceinline__ float dot8(const u32x4& a, const float (&qv)[8]) {
 // LAYOUT 0: dense rows of exactly NIT KiB (a load's offset is then a constant of the instruction: 0.6 us of 90 on 64
 // caches of 1025 entries).  1: dense rows that end inside a piece.  2: any other layout; a load instruction then
 // covers kWave/LPH head slices of d*2 contiguous bytes each instead of 1 KiB of one row.
+// Rows of more than NIT pieces are shared by gridDim.z blocks, each with heads of its own (layouts 1 and 2 only).
 // STREAM_ONCE: the cache is larger than what the L2 / Infinity Cache can hold until the row moves, so
 // the K rows are read with streaming loads (they would only evict each other and everything else).
 template <int LPH, int NIT, int LAYOUT, bool STREAM_ONCE>
@@ -119,6 +120,7 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
     const int wave_global = blockIdx.x * 4 + wv;
     const int nwaves = gridDim.x * 4;
     const int row = p.H * p.d, nvec = row / 8;
+    const int v0 = LAYOUT == 0 ? 0 : (int)blockIdx.z * (NIT * kWave), h0 = v0 / LPH;      // this block's first vector and head
     const u32x4* qb = reinterpret_cast<const u32x4*>(q + (long)b * row);
     const u32x4* kb = reinterpret_cast<const u32x4*>(k_cache + (long)b * p.Lcap * row);
     const uint16_t* ks = k_cache + (long)b * lay.batch;
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
     float qv[NIT][8];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int idx = it * kWave + lane;
+        const int idx = v0 + it * kWave + lane;
         vec[it] = LAYOUT == 0 ? idx : min(idx, nvec - 1);
         off[it] = (long)(vec[it] / LPH) * lay.head + (vec[it] % LPH) * 8;
         u32x4 w = qb[vec[it]];
@@ -145,7 +147,7 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
 
     const int n = min(max(len[b], 0), p.Lcap);
     // the state as it is before the selection changes it, for the other selection blocks of the sample
-    if (copy.acc) {
+    if (copy.acc && blockIdx.z == 0) {
         for (int j = blockIdx.x * 256 + threadIdx.x; j < n; j += gridDim.x * 256) {
             const long i = (long)b * p.Lcap + j;
             copy.acc[i] = state.acc[i]; copy.ids[i] = state.ids[i]; copy.protect[i] = state.protect[i];
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
         if ((lane & (LPH - 1)) == 0) {
 #pragma unroll
             for (int it = 0; it < NIT; ++it)
-                if (LAYOUT == 0 || it * HPI + lane / LPH < p.H) lb[(long)j * p.H + it * HPI + lane / LPH] = part[it] * scale;
+                if (LAYOUT == 0 || h0 + it * HPI + lane / LPH < p.H) lb[(long)j * p.H + h0 + it * HPI + lane / LPH] = part[it] * scale;
         }
     }
     if ((lane & (LPH - 1)) == 0) {
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
         for (int it = 0; it < NIT; ++it) { s_m[wv][it * HPI + lane / LPH] = m[it]; s_z[wv][it * HPI + lane / LPH] = z[it]; }
     }
     __syncthreads();
-    for (int h = threadIdx.x; h < p.H; h += blockDim.x) {
+    for (int h = threadIdx.x; h < min(NIT * HPI, p.H - h0); h += blockDim.x) {
         float mn = -INFINITY;
 #pragma unroll
         for (int w = 0; w < 4; ++w) mn = fmaxf(mn, s_m[w][h]);
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(256) void decode_logits_stream_kernel(
 #pragma unroll
             for (int w = 0; w < 4; ++w) zn += s_z[w][h] * fast_exp2(s_m[w][h] - mn);
         }
-        stat_partial[((long)b * gridDim.x + blockIdx.x) * p.H + h] = make_float2(mn, zn);
+        stat_partial[((long)b * gridDim.x + blockIdx.x) * p.H + h0 + h] = make_float2(mn, zn);
     }
 }
 
@@ -940,7 +942,11 @@ int decode_evict_impl(
     const int row_bytes = H * d * 2;
     // 1 KiB pieces of a row, rounded up to a form that is compiled (a piece behind the row's end costs a cached load)
     const int pieces = (row_bytes + 1023) / 1024;
-    const int nit = pieces <= 2 ? pieces : (pieces <= 4 ? 4 : (pieces <= 5 ? 5 : (pieces <= 8 ? 8 : (pieces <= 10 ? 10 : 16))));
+    // Sixteen pieces take all registers of a wave.  Only dense rows of exactly 16 KiB, whose offsets need none, are read so;
+    // other rows of more than ten pieces are shared by two blocks (32 x 1025 entries of 128 per head, 48 heads: 120 us in
+    // one, 74 in halves, the general kernel 102; 64 heads, head-major: 140, 96 and 127; 64 heads, dense, in one: 96)
+    const bool halves = pieces > 10 && !(dense && row_bytes == 16 * 1024);
+    const int nit = pieces <= 2 ? pieces : (pieces <= 4 ? 4 : (pieces <= 5 ? 5 : (pieces <= 8 || halves ? 8 : (pieces <= 10 ? 10 : 16))));
     int n_part = 0;                                   // > 0: the logits kernel left per-block softmax statistics
     // selection in registers: up to 8192 slots, and heads in fours (a power of two up to 32: sums over lanes; any other
     // number, where a wave's shares still fit the 64 KB a launch gets: sums through LDS)
@@ -975,12 +981,13 @@ int decode_evict_impl(
     const bool stream_once = cache_bytes > (size_t)128 << 20;
     if ((d == 128 || d == 64) && pieces <= 16) {
         // streaming shape: about 16 waves per CU in flight, each striding over its sample's entries
-        int blocks_x = (MD_DEC_BLOCKS + B - 1) / B;
+        const int parts = halves ? 2 : 1;
+        int blocks_x = (MD_DEC_BLOCKS / parts + B - 1) / B;
         const int max_x = (Lcap + 3) / 4;
         if (blocks_x > max_x) blocks_x = max_x;
         if (blocks_x > kMaxStatParts) blocks_x = kMaxStatParts;
         if (blocks_x < 1) blocks_x = 1;
-        dim3 g1(blocks_x, B);
+        dim3 g1(blocks_x, B, parts);
 #define MD_STREAM2(LPH_, NIT_, Y_, O_)                                                                             \
         MD_LAUNCH("decode_logits", st, (decode_logits_stream_kernel<LPH_, NIT_, Y_, O_>), g1, 256, 0,              \
             qp, kp, len, p, lay, softmax_scale, w.logits, w.stat_partial, state, copy)
@@ -998,7 +1005,10 @@ int decode_evict_impl(
             case 5: MD_STREAM(5); break;
             case 8: MD_STREAM(8); break;
             case 10: MD_STREAM(10); break;
-            default: MD_STREAM(16); break;
+            default:                                  // dense rows of exactly 16 KiB
+                if (d == 128) { if (stream_once) MD_STREAM2(16, 16, 0, true); else MD_STREAM2(16, 16, 0, false); }
+                else { if (stream_once) MD_STREAM2(8, 16, 0, true); else MD_STREAM2(8, 16, 0, false); }
+                break;
         }
 #undef MD_STREAM2
 #undef MD_STREAM1

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("H,d,L0,cut", [(12, 64, 130, 1), (20, 128, 1025, 1), (36, 64, 700, 300), (40, 64, 2100, 1),
                                         (40, 128, 1500, 900), (48, 128, 330, 1), (64, 128, 513, 100), (128, 64, 260, 3),
-                                        (3, 128, 200, 50), (40, 128, 4100, 3000)])
+                                        (3, 128, 200, 50), (40, 128, 4100, 3000), (44, 128, 300, 1), (124, 64, 260, 90)])
 @pytest.mark.parametrize("head_major", [False, True])
 def test_head_shapes(H, d, L0, cut, head_major):
     check(H, d, L0, cut, head_major, None)
