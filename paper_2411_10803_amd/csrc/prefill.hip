@@ -270,7 +270,8 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     // LDS slots.  The eight-wave form runs with two (one step in flight while one is worked on): with more
     // requests outstanding per CU the sweep gets slower, not faster, when K comes from HBM (46.3 against 47.9 us);
     // four tile lanes too: three slots of 128 rows would leave room for one block per CU instead of two, which is
-    // all that there is where the grid has no more (DEEP: 4 x 861 keys, 32 heads, 2 text rows 11.1 -> 10.1 us)
+    // all that there is where the grid has no more (DEEP: 4 x 861 keys, 32 heads, 2 text rows 11.1 -> 10.1 us; not for
+    // heads of 64, whose rows are half as long: 4 x 1510, 8 heads, 10 text rows 5.1 with two, 5.9 with three)
     constexpr int S = TW == 1 ? 4 : (NBW == 4 || (NBW == 1 && !DEEP) ? 2 : 3);
     constexpr int SLOT_ROWS = 32 * TW, SLOT_BYTES = SLOT_ROWS * T::ROWB;
     constexpr int NLW = SLOT_ROWS / T::RPL / NW;      // load instructions per wave and step
@@ -1275,7 +1276,7 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
 #define MD_ROWSTATS(NBW_, TW_)                                                                                 \
         do {                                                                                                   \
             if (s.rs_stream) MD_ROWSTATS2(NBW_, TW_, true, false);                                             \
-            else if (NBW_ == 1 && TW_ == 4 && s.rs_deep) MD_ROWSTATS2(NBW_, TW_, false, (NBW_ == 1 && TW_ == 4)); \
+            else if (KS == 8 && NBW_ == 1 && TW_ == 4 && s.rs_deep) MD_ROWSTATS2(NBW_, TW_, false, (KS == 8 && NBW_ == 1 && TW_ == 4)); \
             else MD_ROWSTATS2(NBW_, TW_, false, false);                                                        \
         } while (0)
         const bool big = s.rs_waves == 8;

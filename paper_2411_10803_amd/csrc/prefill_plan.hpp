@@ -80,12 +80,12 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
             // (heads of 64 with four text blocks: three blocks of four waves share a CU, one of eight waves no better than at
             // d = 128; 2 x 8661 keys, 64 heads, 95 text rows 49.8 -> 38.6)
             if (s.nbw == 4 && d == 64) { alone = waves == 8 ? 10.0 : 11.5; full = waves == 8 ? 10.5 : 21.0; }
-            if (s.nbw == 1 && waves == 4 && blocks <= kNumCU && !s.rs_stream) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
+            if (s.nbw == 1 && d == 128 && waves == 4 && blocks <= kNumCU && !s.rs_stream) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
             const double per_key = alone + (full - alone) * fill;
             const double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? 5.0 : 0.0);
             if (best == 0 || t < 0.97 * best) { best = t; s.rs_waves = waves; s.nch = nch; }
         }
-    s.rs_deep = s.nbw == 1 && s.rs_waves == 4 && n * s.nch <= kNumCU && !s.rs_stream;
+    s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && !s.rs_stream;
     // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
     ColPlan& c = s.col;
     c.kb = s.nbw == 1 ? 128 : 64;
