@@ -183,8 +183,8 @@ int mustdrop_encode_merge_adaptive(
  *   out_protect[B, Rcap+N] u8 or NULL: 1 for key tokens and text rows (the decode stage's protect flags)
  *   score_global, score_indiv [B, Mv] f32 or NULL: V_j and I_j (0 for invalid tokens)
  *
- * Limits: d in {64, 128}; N <= 1024 (tuned for N <= 128: a longer prompt re-reads K once per 64
- * text rows in the first sweep and once per 128 in the second); H <= 128; softmax_scale positive
+ * Limits: d in {64, 128}; N <= 1024 (tuned for N <= 128: a longer prompt is cut into groups of up to 128
+ * text rows, and every group goes over K in both sweeps); H <= 128; softmax_scale positive
  * and finite; C*2 and H*d*2 multiples of 16 bytes.
  */
 size_t mustdrop_prefill_filter_workspace_bytes(int B, int Mv, int N, int H, int Rcap);
@@ -219,8 +219,9 @@ int mustdrop_prefill_filter(
  *   evicted_ids [B, Lcap] or NULL: ids of the evicted entries in ascending (pre-compaction) slot order
  *   evicted_count [B] or NULL
  *
- * Limits: d a power of two in [8, 512]; H <= 1024 (rows of 1, 2, 4 or 8 KiB with d = 128 and
- * H in {4, 8, 16, 32, 64} take the streaming kernels, other shapes the general ones).
+ * Limits: d a power of two in [8, 512]; H <= 1024 (with d = 64 or 128 and rows of at most 16 KiB the scores
+ * come from the streaming kernel; the selection then runs in registers where Lcap <= 8192 and H is 4, 8, 16
+ * or 32, or another multiple of four with 4*Lcap + 512*H <= 65536; other shapes take the general kernels).
  * MD_EALIAS: q, the two caches, acc, ids, protect, len, the optional outputs and the workspace must be
  * pairwise disjoint.
  */

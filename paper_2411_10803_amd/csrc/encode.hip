@@ -4,9 +4,10 @@
 // Launch plan (all on the caller's stream, no host synchronisation):
 //   encode_scores_kernel one launch, two kinds of waves (two launches for many tokens, see ScoreBlocks):
 //       window waves     one wave per window: Gram matrix in registers -> S    (HBM: reads x once)
-//       key-row waves    one wave per eight key rows: q_cls . k_j per head     (HBM: reads k_cls once)
-//   encode_decide_kernel one block per sample: softmax + head mean, radix top-k -> O, merge
-//                        decisions, prefix sum of survivors, small outputs    (tiny)
+//       key-row waves    one wave per eight key rows, or per 64-vector slice of   (HBM: reads k_cls once)
+//                        them: q_cls . k_j per head
+//   encode_decide_*      one block per sample: softmax + head mean (or ready-made key scores), radix top-k -> O,
+//                        merge decisions, prefix sum of survivors, small outputs    (tiny)
 //   encode_emit_kernel  one wave per window: row copies / mass-weighted means (re-reads x, writes out_x)
 #include "md_device.hpp"
 #include "md_host.hpp"

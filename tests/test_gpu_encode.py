@@ -174,7 +174,7 @@ def test_adaptive_key_threshold(shape):
         cfg, samples = wl.CONFIGS[2], [0, 5, 11]
     elif shape == "ragged_small":
         cfg, samples = wl.tiny(wl.CONFIGS[2], B=3, T=2, Hg=6, Wg=10, D=200, Hc=25, dc=8, kt=2, kh=3, kw=2), None
-    else:                                            # more than 8192 tokens per sample: the general kernels
+    else:                                            # many tokens: ready-made scores (25 heads take the general kernel)
         cfg, samples = wl.tiny(wl.CONFIGS[2], B=1, T=1, Hg=96, Wg=96, D=64, Hc=4, dc=16), None
     e = wl.encode_inputs(cfg, samples)
     B = e["x"].shape[0]

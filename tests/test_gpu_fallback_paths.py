@@ -26,8 +26,8 @@ def test_encode_more_than_8192_tokens_per_sample(T, Hg, Wg):
 
 @pytest.mark.parametrize("T,Hg,Wg,Hc", [(2, 64, 64, 4), (1, 75, 80, 8), (1, 75, 80, 2)])
 def test_encode_between_4608_and_8192_tokens_per_sample(T, Hg, Wg, Hc):
-    # the register-resident decision kernel at eight tokens per thread, where its dynamic LDS exceeds 64 KiB
-    # (8192 and 6000 tokens); with a head count that is not a multiple of 4 the general kernel takes over
+    # the decision kernel that takes ready-made scores, at six and eight tokens per thread (6000 and 8192 tokens); with a
+    # head count that is not a multiple of 4 the general kernel takes over
     from paper_2411_10803_amd import harness
     cfg = wl.tiny(wl.CONFIGS[4], B=2, T=T, Hg=Hg, Wg=Wg, D=64, Hc=Hc, dc=64 // Hc, kt=1 if T == 1 else 2, kh=2, kw=2, key_budget=70)
     assert 4608 < cfg.M <= 8192

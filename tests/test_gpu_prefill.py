@@ -115,7 +115,7 @@ def test_padding_tails_of_different_lengths_are_skipped_not_scored():
 
 
 def test_long_prompts_more_than_128_text_rows():
-    # the column scores of a long prompt come from several launches (128 text rows each) that are merged
+    # the text rows of a long prompt are cut into groups of up to 128, whose column scores are merged
     cfg = wl.tiny(wl.CONFIGS[2], B=2, Hg=9, Wg=13, N=300, H=4, d=128, C=64)
     t = wl.prefill_inputs(cfg)
     txt_len = np.array([300, 131], dtype=np.int32)
