@@ -26,8 +26,9 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
 }
 
 // Division by a number that the host knows: n / d for 0 <= n < 2^31 as one wide multiplication and a shift, the
-// division by an invariant integer of Granlund and Montgomery (mul = ceil(2^(31+l) / d), l = ceil(log2 d), which is exact for 31-bit n).  A division by a run-time number is some
-// thirty dependent instructions, and an index takes several of them before a wave can ask for its first byte.
+// division by an invariant integer of Granlund and Montgomery (mul = ceil(2^(31+l) / d), l = ceil(log2 d), which is exact
+// for 31-bit n).  A division by a run-time number is some thirty dependent instructions, and an index takes several of
+// them before a wave can ask for its first byte.
 struct FastDiv {
     uint32_t mul, shift;
     int d;
