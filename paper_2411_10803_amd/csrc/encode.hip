@@ -432,13 +432,34 @@ __device__ __forceinline__ void key_scores(
 // (Eq. 6 logits; none when no key set is asked for).  A block does one of the three things below; the launch says
 // where in the grid each begins.
 //   windows, then key rows      one launch
-//   key rows alone,             then windows with the key-score blocks ahead of them: two launches for samples whose
-//                               decision wants the scores ready-made; the key scores hide behind the windows.
-//                               The key-row blocks (each within one sample) then also leave their groups' statistics
+//   key-score blocks, windows   the second of two launches for samples whose decision wants the scores ready-made;
+//                               the key scores hide behind the windows.  The first one takes the key rows alone: its
+//                               blocks (each within one sample) leave their groups' statistics
 //                               merged: block_stat[b][block of the sample][h], in the half of cls_part that the
 //                               groups' sums do not need then (their maxima take the first half, as floats; it fits
 //                               from two groups on, and such calls have more).
 struct ScoreBlocks { int keyscore, windows, rows, slices; };         // blocks of each kind, in grid order; waves per key-row group
+
+// The key rows of one block, with its groups' statistics merged.
+template <bool QKBF>
+__device__ __forceinline__ void merged_rows(
+    int blk, const void* __restrict__ q_cls, const void* __restrict__ k_cls, const uint8_t* __restrict__ valid, const EncodeDims& p,
+    float* __restrict__ logits, float2* __restrict__ cls_part, float2* __restrict__ block_stat, float2 (&s_stat)[kEncWaves][kMaxMergedHeads])
+{
+    const int gps = cls_groups(p.M), cb = cls_blocks(p.M), b = blk / cb, wb = blk % cb, g = wb * kEncWaves + wave_id();
+    const int iters = (p.D / Vec<QKBF>::N + kWave - 1) / kWave;
+    if (g < gps) cls_logits_rows<QKBF, false, true>(b, g, 0, iters, q_cls, k_cls, valid, p, logits, cls_part, s_stat[wave_id()]);
+    __syncthreads();
+    const int nw = min(kEncWaves, gps - wb * kEncWaves);
+    for (int h = threadIdx.x; h < p.Hc; h += blockDim.x) {
+        float mx = -INFINITY, z = 0.f;
+        for (int w = 0; w < nw; ++w) mx = fmaxf(mx, s_stat[w][h].x);
+        for (int w = 0; w < nw; ++w)
+            if (s_stat[w][h].x > -INFINITY) z = fmaf(s_stat[w][h].y, fast_exp2(s_stat[w][h].x - mx), z);
+        block_stat[((size_t)b * cb + wb) * p.Hc + h] = make_float2(mx, z);
+    }
+}
+
 template <int WSM, bool XBF, bool QKBF>
 __global__ __launch_bounds__(256) void encode_scores_kernel(
     const void* __restrict__ x, const void* __restrict__ q_cls, const void* __restrict__ k_cls,
@@ -466,22 +487,22 @@ __global__ __launch_bounds__(256) void encode_scores_kernel(
         if (b < p.B) cls_logits_rows<QKBF, true, false>(b, gs - b * gps, sl, sl + 1, q_cls, k_cls, valid, p, logits, cls_part, nullptr);
         return;
     }
-    const int cb = cls_blocks(p.M), b = blk / cb, wb = blk % cb, g = wb * kEncWaves + wave_id();
+    if constexpr (QKBF)
+        if (block_stat) { merged_rows<QKBF>(blk, q_cls, k_cls, valid, p, logits, cls_part, block_stat, s.stat); return; }
+    const int cb = cls_blocks(p.M), b = blk / cb, g = blk % cb * kEncWaves + wave_id();
     const int iters = (p.D / Vec<QKBF>::N + kWave - 1) / kWave;
-    if (!block_stat) {
-        if (g < gps) cls_logits_rows<QKBF, false, false>(b, g, 0, iters, q_cls, k_cls, valid, p, logits, cls_part, nullptr);
-        return;
-    }
-    if (g < gps) cls_logits_rows<QKBF, false, true>(b, g, 0, iters, q_cls, k_cls, valid, p, logits, cls_part, s.stat[wave_id()]);
-    __syncthreads();
-    const int nw = min(kEncWaves, gps - wb * kEncWaves);
-    for (int h = threadIdx.x; h < p.Hc; h += blockDim.x) {
-        float mx = -INFINITY, z = 0.f;
-        for (int w = 0; w < nw; ++w) mx = fmaxf(mx, s.stat[w][h].x);
-        for (int w = 0; w < nw; ++w)
-            if (s.stat[w][h].x > -INFINITY) z = fmaf(s.stat[w][h].y, fast_exp2(s.stat[w][h].x - mx), z);
-        block_stat[((size_t)b * cb + wb) * p.Hc + h] = make_float2(mx, z);
-    }
+    if (g < gps) cls_logits_rows<QKBF, false, false>(b, g, 0, iters, q_cls, k_cls, valid, p, logits, cls_part, nullptr);
+}
+
+// The first of the two launches for fp32 keys.  A kernel of its own: as one more path of encode_scores_kernel it made the calls
+// without it slower (88 x 416 tokens of 384 features 49.4 -> 51.8 us, 55 x 290 of 256 23.9 -> 25.0).  With bf16 keys it is
+// the other way round (16 x 576 tokens 22.2 with the path, 22.45 without; 8 x 2880 42.3 and 42.5), and it stays there.
+__global__ __launch_bounds__(256) void encode_rows_f32_kernel(
+    const void* __restrict__ q_cls, const void* __restrict__ k_cls, const uint8_t* __restrict__ valid, EncodeDims p,
+    float* __restrict__ logits, float2* __restrict__ cls_part, float2* __restrict__ block_stat)
+{
+    __shared__ float2 s_stat[kEncWaves][kMaxMergedHeads];
+    merged_rows<false>(blockIdx.x, q_cls, k_cls, valid, p, logits, cls_part, block_stat, s_stat);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1383,7 +1404,10 @@ int encode_merge_impl(
     const ScoreArgs sa{x, q_cls, k_cls, valid, wsp.sim, wsp.logits, wsp.cls_part,
                        large_ok && with_keys ? wsp.cls_part + (size_t)B * Hc * cls_groups(M) / 2 : nullptr, wsp.acls, a_cls_out};
     if (large_ok && with_keys) {
-        launch_scores(ws, ScoreBlocks{0, 0, row_blocks, 1}, st, xbf, qkbf, p, sa);
+        if (qkbf) launch_scores(ws, ScoreBlocks{0, 0, row_blocks, 1}, st, xbf, qkbf, p, sa);
+        else
+            MD_LAUNCH("encode_scores", st, (encode_rows_f32_kernel), (unsigned)row_blocks, 64 * kEncWaves, 0,
+                q_cls, k_cls, valid, p, wsp.logits, wsp.cls_part, sa.block_stat);
         // (a multiple of 8 of them: blocks go round the 8 XCDs in turn, and a window's rows are then still in the L2 of the
         // XCD whose block of the emit kernel reads them again: 2 x 756 tokens, 3072 fp32 features, emit 34.3 -> 18.6 us)
         const int score_blocks = (B * ((M + kKeyTokens - 1) / kKeyTokens) + 7) & ~7;
