@@ -11,7 +11,7 @@
 //                         softmax statistics per head, head mean, running score update, radix top-k among
 //                         unprotected entries, hole/mover lists, moves of the small per-entry arrays; for
 //                         short or few caches also the row moves (several blocks per sample, the same selection in each)
-//   decode_move_kernel    copies the K and V rows of the movers into the holes, where many may move
+//   decode_move_kernel    copies the K and V rows of the movers into the holes, where many may move, in every layer
 #include "md_device.hpp"
 #include "md_host.hpp"
 
@@ -21,6 +21,11 @@ namespace {
 constexpr float kLog2eD = 1.4426950408889634f;
 
 struct DecodeDims { int B, Lcap, H, d; };
+// Counters from which the blocks of decode_move_kernel claim their pieces, 128 bytes apart; cleared by the kernel before it.
+constexpr int kClaims = 16, kClaimStride = 32;
+__device__ __forceinline__ void clear_claims(int32_t* claims, int tid) {
+    if (tid < kClaims) claims[tid * kClaimStride] = 0;
+}
 constexpr int kMaxStatParts = 256;               // blocks per sample of the streaming logits kernel
 
 // The small per-entry state of a cache, [B, Lcap] each and len [B].
@@ -249,7 +254,7 @@ template <int IPT, int LPE>
 __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     DecodeDims p, const float* __restrict__ logits, const float2* __restrict__ stat_partial, int n_part,
     float decay, int budget, StateArrays in, StateArrays out, KvLayout lay, uint16_t* k_cache, uint16_t* v_cache, int stream_once,
-    int32_t* __restrict__ holes, int32_t* __restrict__ movers, int32_t* __restrict__ n_move,
+    int32_t* __restrict__ holes, int32_t* __restrict__ movers, int32_t* __restrict__ n_move, int32_t* __restrict__ claims,
     int32_t* __restrict__ evicted_ids, int32_t* __restrict__ evicted_count)
 {
     // [Lcap] a_t (and behind it, for LPE = 0, the waves' shares); once every thread has taken its a_t the same
@@ -264,6 +269,7 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     const int b = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wv = wave_id();
     const bool writer = blockIdx.x == 0;
     if (tid < 256) s_hist[tid] = 0;                  // for block_select_topk, after later barriers
+    if (n_move && b == 0) clear_claims(claims, tid);
     const int H = p.H;
     const float* lb = logits + (long)b * p.Lcap * H;
     const float* ai = in.acc + (long)b * p.Lcap;
@@ -559,7 +565,7 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
 __global__ __launch_bounds__(1024) void decode_select_kernel(
     DecodeDims p, const float* __restrict__ logits, float decay, int budget,
     float* __restrict__ acc, int32_t* __restrict__ ids, uint8_t* __restrict__ protect, int32_t* __restrict__ len,
-    uint8_t* __restrict__ keep, int32_t* __restrict__ holes, int32_t* __restrict__ movers, int32_t* __restrict__ n_move,
+    uint8_t* __restrict__ keep, int32_t* __restrict__ holes, int32_t* __restrict__ movers, int32_t* __restrict__ n_move, int32_t* __restrict__ claims,
     int32_t* __restrict__ evicted_ids, int32_t* __restrict__ evicted_count)
 {
     extern __shared__ float s_dyn[];                 // [2*H] max / inv, then [32][H] scratch
@@ -579,6 +585,7 @@ __global__ __launch_bounds__(1024) void decode_select_kernel(
     int32_t* hb = holes + (long)b * p.Lcap;
     int32_t* mvb = movers + (long)b * p.Lcap;
 
+    if (b == 0) clear_claims(claims, tid);
     if (n == 0) {
         if (tid == 0) { n_move[b] = 0; if (evicted_count) evicted_count[b] = 0; }
         return;
@@ -679,7 +686,7 @@ __global__ __launch_bounds__(1024) void decode_select_kernel(
 __global__ __launch_bounds__(1024) void decode_keep_plan_kernel(
     DecodeDims p, const uint8_t* __restrict__ keep, float* __restrict__ acc, int32_t* __restrict__ ids,
     uint8_t* __restrict__ protect, int32_t* __restrict__ len,
-    int32_t* __restrict__ holes, int32_t* __restrict__ movers, int32_t* __restrict__ n_move,
+    int32_t* __restrict__ holes, int32_t* __restrict__ movers, int32_t* __restrict__ n_move, int32_t* __restrict__ claims,
     int32_t* __restrict__ evicted_ids, int32_t* __restrict__ evicted_count)
 {
     __shared__ int s_red[16];
@@ -692,6 +699,7 @@ __global__ __launch_bounds__(1024) void decode_keep_plan_kernel(
     int32_t* hb = holes + (long)b * p.Lcap;
     int32_t* mvb = movers + (long)b * p.Lcap;
 
+    if (b == 0) clear_claims(claims, tid);
     int nk = 0;
     for (int j = tid; j < n; j += blockDim.x) nk += kf[j] != 0;
     const int new_len = block_sum_i(nk, s_red);
@@ -727,45 +735,98 @@ __global__ __launch_bounds__(1024) void decode_keep_plan_kernel(
     }
 }
 
-// Row moves: block (g, b, layer) copies movers[t] -> holes[t] for t = g, g + gridDim.x, ... in the
-// cache of its layer (layer_stride 16-byte vectors apart; one layer for the per-step policy).
-// STREAM_ONCE: caches too large to stay resident -- the source rows are dead after the move and the
-// destination rows will not be read from cache either, so both sides bypass it.
-template <bool STREAM_ONCE>
-__global__ __launch_bounds__(256) void decode_move_kernel(
-    DecodeDims p, const int32_t* __restrict__ holes, const int32_t* __restrict__ movers,
-    const int32_t* __restrict__ n_move, u32x4* __restrict__ k_cache, u32x4* __restrict__ v_cache, long layer_stride)
+// Row moves: movers[t] -> holes[t], t < n_move[b], of every sample in the caches of every layer (layer_stride elements
+// apart; one layer for the per-step policy).  Bound by the memory's rate at mixed reads and writes, and that depends on how
+// close together the rows lie that are under way at a time: blocks that take their rows in a fixed stride drift apart.
+// So the rows are cut into pieces of up to 1024 vectors (as a rule the K and the V row of one move, a vector a thread)
+// in the order of layers, samples and moves, and the blocks claim the next piece whenever they are done with one, as the
+// hardware would hand out blocks if the host knew the number of moves.  64 caches of 4096 entries, 896 rows of 8 KiB moved in
+// each: 357 us in strides, 320 so (5.9 TB/s); a block per move, their number known, takes 303.
+// A block's first piece is the one of its number; the claims for further ones go to kClaims counters, 128 bytes apart (one
+// counter for all takes 12 ns a claim: 683 us), counter c hands out every kClaims-th piece from gridDim.x + c on.  Fewer than
+// kClaims blocks are launched only where each has one piece at most.  The kernel before this one has cleared the counters.
+// K_ONCE: caches too large to stay resident -- the source rows are dead after the move and the destination rows will not be
+// read from cache either, so both sides bypass it.  V_ONCE: the V rows are not read on this path at all and are streamed
+// whatever their size, but where a head slice is shorter than a cache line.
+struct MovePieces {
+    int per_piece, per_move;                         // moves per piece, pieces per move: one of them is 1
+    int threads;                                     // of a block that have a vector
+    FastDiv by_pair;                                 // vectors of a K row and a V row together
+};
+inline MovePieces move_pieces(int H, int d) {
+    const int pair = 2 * H * (d / 8);
+    MovePieces mp;
+    mp.per_piece = pair < 1024 ? 1024 / pair : 1;
+    mp.per_move = (pair + 1023) / 1024;
+    mp.threads = mp.per_move == 1 ? mp.per_piece * pair : (pair + mp.per_move - 1) / mp.per_move;
+    mp.by_pair = FastDiv::make(pair);
+    return mp;
+}
+// ONE: a piece holds rows of one move only.
+template <bool K_ONCE, bool V_ONCE, bool ONE>
+__global__ __launch_bounds__(1024) void decode_move_kernel(
+    DecodeDims p, KvLayout lay, MovePieces mp, int n_layers, const int32_t* __restrict__ holes, const int32_t* __restrict__ movers,
+    const int32_t* __restrict__ n_move, int32_t* __restrict__ claims, uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache,
+    long layer_stride)
 {
-    const int b = blockIdx.y;
-    // the first pair of the lists is requested together with the count (the entry exists whatever the
-    // count is; it is used only if the count says so)
-    const int t0 = min((int)blockIdx.x, p.Lcap - 1);
-    int mv = movers[(long)b * p.Lcap + t0], hl = holes[(long)b * p.Lcap + t0];
-    const int nm = n_move[b];
-    const int rv = p.H * p.d / 8;
-    k_cache += blockIdx.z * layer_stride;
-    v_cache += blockIdx.z * layer_stride;
-    // source rows (beyond the new length) and destination rows (holes below it) never coincide, but
-    // the compiler cannot know: the vectors of a round are read into registers before any is written
-    for (int t = blockIdx.x; t < nm; t += gridDim.x) {
-        const long src = ((long)b * p.Lcap + mv) * rv;
-        const long dst = ((long)b * p.Lcap + hl) * rv;
-        const int tn = min(t + (int)gridDim.x, p.Lcap - 1);                  // next pair, in flight during the copy
-        mv = movers[(long)b * p.Lcap + tn];
-        hl = holes[(long)b * p.Lcap + tn];
-        for (int c = threadIdx.x; c < rv; c += 2 * blockDim.x) {
-            const int c2 = c + blockDim.x;
-            const bool two = c2 < rv;
-            auto ld = [](const u32x4* q) { return STREAM_ONCE ? __builtin_nontemporal_load(q) : *q; };
-            auto st = [](u32x4* q, const u32x4& v) { if (STREAM_ONCE) __builtin_nontemporal_store(v, q); else *q = v; };
-            // the V rows are not read on this path at all (only moved): always streamed
-            const u32x4 k0 = ld(k_cache + src + c), v0 = __builtin_nontemporal_load(v_cache + src + c);
-            u32x4 k1 = k0, v1 = v0;
-            if (two) { k1 = ld(k_cache + src + c2); v1 = __builtin_nontemporal_load(v_cache + src + c2); }
-            st(k_cache + dst + c, k0);
-            __builtin_nontemporal_store(v0, v_cache + dst + c);
-            if (two) { st(k_cache + dst + c2, k1); __builtin_nontemporal_store(v1, v_cache + dst + c2); }
+    __shared__ uint32_t s_next[2];
+    const int tid = threadIdx.x, lane = lane_id(), q = blockIdx.x % kClaims;
+    int32_t* my_claims = claims + q * kClaimStride;
+    // pieces of the 64 samples b0 .. b0 + 63, one per lane, and the sum of pieces up to and with each
+    int b0 = 0, mine = 0, incl = 0;
+    auto group = [&](int at, int before) {
+        b0 = at;
+        mine = b0 + lane < p.B ? (n_move[min(b0 + lane, p.B - 1)] + mp.per_piece - 1) / mp.per_piece * mp.per_move : 0;
+        incl = wave_incl_scan_i(mine) + before;
+    };
+    uint32_t total = 0;                              // of a layer (a piece is some 16 KiB: they fit the index)
+    for (int b = (p.B - 1) & ~63; b >= 0; b -= kWave) {              // the first 64 samples stay at hand
+        group(b, 0);
+        total += (uint32_t)__builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+    if (total == 0) return;
+    const uint32_t items = total * (uint32_t)n_layers;
+    int buf = 0;
+    for (uint32_t item = blockIdx.x; item < items;) {
+        uint32_t claimed = 0;                        // the claim of the next piece is under way with this one's rows
+        if (tid == 0) claimed = (uint32_t)atomicAdd(my_claims, 1);
+        const int layer = n_layers == 1 ? 0 : (int)(item / total), r = (int)(item - (uint32_t)layer * total);
+        if (r < __builtin_amdgcn_readlane(incl - mine, 0)) group(0, 0);
+        while (r >= __builtin_amdgcn_readlane(incl, kWave - 1)) group(b0 + kWave, __builtin_amdgcn_readlane(incl, kWave - 1));
+        const int l = __builtin_ctzll(__ballot(incl > r));
+        const int b = b0 + l, at = r - __builtin_amdgcn_readlane(incl - mine, l);        // the sample's piece
+        // this thread's row and vector of the pair; one move per piece: its rows come by scalar loads, which do not wait for the
+        // stores under way
+        int src, dst, x;
+        bool on;
+        if constexpr (ONE) {
+            const int t = mp.per_move == 1 ? at : at / mp.per_move;
+            const long li = (long)b * p.Lcap + t;
+            src = movers[li]; dst = holes[li];
+            x = (at - t * mp.per_move) * mp.threads + tid;
+            on = tid < mp.threads && x < mp.by_pair.d;
+        } else {
+            const int u = mp.by_pair.div(tid), t = at * mp.per_piece + u;
+            const long li = (long)b * p.Lcap + min(t, p.Lcap - 1);
+            src = movers[li]; dst = holes[li];
+            x = tid - u * mp.by_pair.d;
+            on = tid < mp.threads && t < n_move[b];
         }
+        if (on) {
+            const int rv = mp.by_pair.d >> 1, sh = __builtin_ctz(p.d) - 3;
+            const bool is_v = x >= rv;
+            const int c = is_v ? x - rv : x;         // head slices of 2^sh vectors
+            uint16_t* base = (is_v ? v_cache : k_cache) + layer * layer_stride + (long)b * lay.batch +
+                             (long)(c >> sh) * lay.head + (c & ((1 << sh) - 1)) * 8;
+            const u32x4* from = reinterpret_cast<const u32x4*>(base + (long)src * lay.token);
+            u32x4* to = reinterpret_cast<u32x4*>(base + (long)dst * lay.token);
+            if (is_v ? V_ONCE : K_ONCE) __builtin_nontemporal_store(__builtin_nontemporal_load(from), to);
+            else *to = *from;
+        }
+        buf ^= 1;
+        if (tid == 0) s_next[buf] = claimed;
+        block_sync_lds();                            // (the stores need not have arrived)
+        item = gridDim.x + (uint32_t)__builtin_amdgcn_readfirstlane((int)s_next[buf]) * kClaims + q;
     }
 }
 
@@ -793,30 +854,7 @@ __global__ __launch_bounds__(256) void decode_append_kernel(
     }
 }
 
-// The two kernels above for caches in other layouts: a row is walked head slice by head slice.
-__global__ __launch_bounds__(256) void decode_move_strided_kernel(
-    DecodeDims p, KvLayout lay, const int32_t* __restrict__ holes, const int32_t* __restrict__ movers,
-    const int32_t* __restrict__ n_move, uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache, long layer_stride)
-{
-    const int b = blockIdx.y;
-    const int nm = n_move[b];
-    const int lph = p.d / 8, rv = p.H * lph;
-    k_cache += blockIdx.z * layer_stride + (long)b * lay.batch;
-    v_cache += blockIdx.z * layer_stride + (long)b * lay.batch;
-    for (int t = blockIdx.x; t < nm; t += gridDim.x) {
-        const long src = (long)movers[(long)b * p.Lcap + t] * lay.token;
-        const long dst = (long)holes[(long)b * p.Lcap + t] * lay.token;
-        for (int c = threadIdx.x; c < rv; c += blockDim.x) {
-            const int h = c / lph, w = c - h * lph;
-            const long off = (long)h * lay.head + w * 8;
-            const u32x4 k0 = *reinterpret_cast<const u32x4*>(k_cache + src + off);
-            const u32x4 v0 = *reinterpret_cast<const u32x4*>(v_cache + src + off);
-            *reinterpret_cast<u32x4*>(k_cache + dst + off) = k0;
-            *reinterpret_cast<u32x4*>(v_cache + dst + off) = v0;
-        }
-    }
-}
-
+// The same for caches in other layouts: a row is walked head slice by head slice.
 __global__ __launch_bounds__(256) void decode_append_strided_kernel(
     DecodeDims p, KvLayout lay, const u32x4* __restrict__ k_new, const u32x4* __restrict__ v_new,
     uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache,
@@ -849,6 +887,7 @@ __global__ __launch_bounds__(256) void decode_append_strided_kernel(
 
 struct DecodeWorkspace {
     float* logits; float2* stat_partial; uint8_t* keep; int32_t* holes; int32_t* movers; int32_t* n_move;
+    int32_t* claims;
     StateArrays copy;
     size_t bytes;
 };
@@ -862,10 +901,32 @@ DecodeWorkspace carve_decode(void* base, int B, int Lcap, int H) {
     w.holes = c.take<int32_t>((size_t)B * Lcap);
     w.movers = c.take<int32_t>((size_t)B * Lcap);
     w.n_move = c.take<int32_t>((size_t)B);
+    w.claims = c.take<int32_t>((size_t)kClaims * kClaimStride);
     // (the general selection's keep flags and lists and the streaming one's copy of the state are never in use together)
     w.copy = StateArrays{reinterpret_cast<float*>(w.holes), w.movers, w.keep, w.n_move};
     w.bytes = c.off;
     return w;
+}
+
+// The row moves of every sample in the caches of n_layers layers; at most max_moves of them per sample.
+void launch_moves(const DecodeDims& p, const KvLayout& lay, const DecodeWorkspace& w, hipStream_t st, bool dense, size_t cache_bytes,
+                  int n_layers, long layer_stride, int max_moves, void* k_cache, void* v_cache) {
+    const MovePieces mp = move_pieces(p.H, p.d);
+    // Just under two blocks per CU, but no more than pieces there can be.  64 caches of 4096 entries cut to 1024, and 32 layers
+    // x 16 caches of 640 cut to 128: 348 and 342 us with 320 blocks, 320 and 337 with 448, 319 and 356 with 512, 319 and 356 with 768
+    const long most = (long)n_layers * p.B * ((max_moves + mp.per_piece - 1) / mp.per_piece) * mp.per_move;
+    const int blocks = (int)(most < 448 ? (most > 1 ? most : 1) : 448);
+    uint16_t* kc = static_cast<uint16_t*>(k_cache);
+    uint16_t* vc = static_cast<uint16_t*>(v_cache);
+#define MD_MOVE2(K_, V_, O_)                                                                                   \
+    MD_LAUNCH("decode_move", st, (decode_move_kernel<K_, V_, O_>), blocks, 1024, 0, p, lay, mp, n_layers, w.holes, w.movers, w.n_move,  \
+        w.claims, kc, vc, layer_stride)
+#define MD_MOVE(K_, V_) do { if (mp.per_piece == 1) MD_MOVE2(K_, V_, true); else MD_MOVE2(K_, V_, false); } while (0)
+    if (!dense && p.d < 64) MD_MOVE(false, false);
+    else if (cache_bytes > (size_t)128 << 20) MD_MOVE(true, true);
+    else MD_MOVE(false, true);
+#undef MD_MOVE2
+#undef MD_MOVE
 }
 
 int check_decode_dims(const char* who, int B, int Lcap, int H, int d) {
@@ -1034,7 +1095,7 @@ int decode_evict_impl(
     MD_LAUNCH("decode_select", st, (decode_select_fast_kernel<I, E>), dim3(select_x, B), 1024, select_lds,         \
         p, w.logits, w.stat_partial, n_part, decay, budget, copy.acc ? copy : state, state, lay,                   \
         static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache), stream_once ? 1 : 0,               \
-        w.holes, w.movers, one_launch ? nullptr : w.n_move, evicted_ids, evicted_count)
+        w.holes, w.movers, one_launch ? nullptr : w.n_move, w.claims, evicted_ids, evicted_count)
 #define MD_SELECT_FAST_H(I)                                                                                        \
     switch (H) {                                                                                                   \
         case 4: MD_SELECT_FAST(I, 1); break;                                                                       \
@@ -1056,20 +1117,9 @@ int decode_evict_impl(
     } else {
         const size_t lds = sizeof(float) * ((size_t)2 * H + 1024);
         MD_LAUNCH("decode_select", st, (decode_select_kernel), B, 1024, lds,
-            p, w.logits, decay, budget, acc, ids, protect, len, w.keep, w.holes, w.movers, w.n_move, evicted_ids, evicted_count);
+            p, w.logits, decay, budget, acc, ids, protect, len, w.keep, w.holes, w.movers, w.n_move, w.claims, evicted_ids, evicted_count);
     }
-    // blocks per sample: enough that a small batch still covers the chip and a block has one or two rows to move
-    const int move_x = B >= 32 ? 32 : (B >= 16 ? 64 : 128);
-    dim3 g3(move_x, B);
-    if (dense && cache_bytes > (size_t)128 << 20)
-        MD_LAUNCH("decode_move", st, (decode_move_kernel<true>), g3, 256, 0,
-            p, w.holes, w.movers, w.n_move, static_cast<u32x4*>(k_cache), static_cast<u32x4*>(v_cache), 0l);
-    else if (dense)
-        MD_LAUNCH("decode_move", st, (decode_move_kernel<false>), g3, 256, 0,
-            p, w.holes, w.movers, w.n_move, static_cast<u32x4*>(k_cache), static_cast<u32x4*>(v_cache), 0l);
-    else
-        MD_LAUNCH("decode_move", st, (decode_move_strided_kernel), g3, 256, 0,
-            p, lay, w.holes, w.movers, w.n_move, static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache), 0l);
+    launch_moves(p, lay, w, st, dense, cache_bytes, 1, 0l, Lcap > budget ? (Lcap - budget < budget ? Lcap - budget : budget) : 0, k_cache, v_cache);
     return check_launch("decode_evict");
 }
 
@@ -1109,20 +1159,8 @@ int decode_keep_impl(
     DecodeDims p{B, Lcap, H, d};
     hipStream_t st = static_cast<hipStream_t>(stream);
     MD_LAUNCH("decode_keep_plan", st, (decode_keep_plan_kernel), B, 1024, 0,
-        p, keep, acc, ids, protect, len, w.holes, w.movers, w.n_move, evicted_ids, evicted_count);
-    dim3 g3(32, B, n_layers);
-    if (dense && cache_bytes > (size_t)128 << 20)
-        MD_LAUNCH("decode_move", st, (decode_move_kernel<true>), g3, 256, 0,
-            p, w.holes, w.movers, w.n_move, static_cast<u32x4*>(k_cache), static_cast<u32x4*>(v_cache),
-            layer_stride / 8);
-    else if (dense)
-        MD_LAUNCH("decode_move", st, (decode_move_kernel<false>), g3, 256, 0,
-            p, w.holes, w.movers, w.n_move, static_cast<u32x4*>(k_cache), static_cast<u32x4*>(v_cache),
-            layer_stride / 8);
-    else
-        MD_LAUNCH("decode_move", st, (decode_move_strided_kernel), g3, 256, 0,
-            p, lay, w.holes, w.movers, w.n_move, static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache),
-            layer_stride);
+        p, keep, acc, ids, protect, len, w.holes, w.movers, w.n_move, w.claims, evicted_ids, evicted_count);
+    launch_moves(p, lay, w, st, dense, cache_bytes, n_layers, layer_stride, Lcap / 2, k_cache, v_cache);
     return check_launch("decode_keep");
 }
 

@@ -45,6 +45,14 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 // wave index within the block, as a scalar (the compiler cannot see that threadIdx.x / 64 is wave-uniform)
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 
+// Every LDS access of this wave has completed, then the block barrier.  (Global accesses
+// may still be under way; loads that write LDS directly are counted with those: the caller waits for them itself.)
+__device__ __forceinline__ void block_sync_lds() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // v_exp_f32 / v_log_f32: base-2, about 1 ulp, results below 2^-126 flush to zero.  Used where the
 // argument is a (score - max) difference, so neither overflow nor denormal results matter.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }

@@ -46,14 +46,6 @@ __device__ __forceinline__ int tile_row(int r, int lane) { return 8 * (r >> 2) +
 #define MD_VM_WAIT(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n) : "memory")
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-// Every LDS access of this wave has completed, then the block barrier.  (The loads that write LDS
-// directly are counted by vmcnt: the caller waits for those itself.)
-__device__ __forceinline__ void block_sync_lds() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 // Rows of an MFMA operand (one head slice of a key or a text query: 16*KS bf16 = CH chunks of 16
 // bytes) on their way from global memory to MFMA fragments, through LDS.
 //   global -> LDS  buffer loads that write LDS directly (no staging registers): a wave instruction
