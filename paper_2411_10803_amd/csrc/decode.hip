@@ -738,32 +738,35 @@ __global__ __launch_bounds__(1024) void decode_keep_plan_kernel(
 // Row moves: movers[t] -> holes[t], t < n_move[b], of every sample in the caches of every layer (layer_stride elements
 // apart; one layer for the per-step policy).  Bound by the memory's rate at mixed reads and writes, and that depends on how
 // close together the rows lie that are under way at a time: blocks that take their rows in a fixed stride drift apart.
-// So the rows are cut into pieces of up to 1024 vectors (as a rule the K and the V row of one move, a vector a thread)
+// So the rows are cut into pieces of up to 1024 threads (as a rule the K and the V row of one move, a vector a thread, or two)
 // in the order of layers, samples and moves, and the blocks claim the next piece whenever they are done with one, as the
 // hardware would hand out blocks if the host knew the number of moves.  64 caches of 4096 entries, 896 rows of 8 KiB moved in
 // each: 357 us in strides, 320 so (5.9 TB/s); a block per move, their number known, takes 303.
 // A block's first piece is the one of its number; the claims for further ones go to kClaims counters, 128 bytes apart (one
 // counter for all takes 12 ns a claim: 683 us), counter c hands out every kClaims-th piece from gridDim.x + c on.  Fewer than
 // kClaims blocks are launched only where each has one piece at most.  The kernel before this one has cleared the counters.
-// K_ONCE: caches too large to stay resident -- the source rows are dead after the move and the destination rows will not be
-// read from cache either, so both sides bypass it.  V_ONCE: the V rows are not read on this path at all and are streamed
-// whatever their size, but where a head slice is shorter than a cache line.
+// STREAM: both sides bypass the caches, also where K is small enough to stay there until the next step reads it: kept, the moved
+// rows push out as much (14 caches of 882 entries cut to 208, 40 heads: next scores and moves 24.2 + 22.5 us, 26.0 + 22.1 with
+// K kept).  Not where a head slice is shorter than a cache line.
 struct MovePieces {
     int per_piece, per_move;                         // moves per piece, pieces per move: one of them is 1
-    int threads;                                     // of a block that have a vector
+    int vectors, threads;                            // of a thread; of a block that have any
     FastDiv by_pair;                                 // vectors of a K row and a V row together
 };
+// Pairs of 1025 to 2048 vectors as one piece of two vectors per thread, not as two with a third of the threads idle: 14 caches of
+// 882 entries cut to 208, 40 heads of 128, 26.6 us in two, 22.5 in one.
 inline MovePieces move_pieces(int H, int d) {
     const int pair = 2 * H * (d / 8);
     MovePieces mp;
+    mp.vectors = pair <= 1024 ? 1 : 2;
     mp.per_piece = pair < 1024 ? 1024 / pair : 1;
-    mp.per_move = (pair + 1023) / 1024;
-    mp.threads = mp.per_move == 1 ? mp.per_piece * pair : (pair + mp.per_move - 1) / mp.per_move;
+    mp.per_move = (pair + 1024 * mp.vectors - 1) / (1024 * mp.vectors);
+    mp.threads = (mp.per_piece * pair + mp.per_move * mp.vectors - 1) / (mp.per_move * mp.vectors);
     mp.by_pair = FastDiv::make(pair);
     return mp;
 }
-// ONE: a piece holds rows of one move only.
-template <bool K_ONCE, bool V_ONCE, bool ONE>
+// NV: vectors per thread; 0: one, and a piece holds several moves.
+template <bool STREAM, int NV>
 __global__ __launch_bounds__(1024) void decode_move_kernel(
     DecodeDims p, KvLayout lay, MovePieces mp, int n_layers, const int32_t* __restrict__ holes, const int32_t* __restrict__ movers,
     const int32_t* __restrict__ n_move, int32_t* __restrict__ claims, uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache,
@@ -795,33 +798,43 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
         while (r >= __builtin_amdgcn_readlane(incl, kWave - 1)) group(b0 + kWave, __builtin_amdgcn_readlane(incl, kWave - 1));
         const int l = __builtin_ctzll(__ballot(incl > r));
         const int b = b0 + l, at = r - __builtin_amdgcn_readlane(incl - mine, l);        // the sample's piece
-        // this thread's row and vector of the pair; one move per piece: its rows come by scalar loads, which do not wait for the
-        // stores under way
-        int src, dst, x;
-        bool on;
-        if constexpr (ONE) {
+        // this thread's move and its vectors of the pair; one move per piece: its rows come by scalar loads, which do not wait
+        // for the stores under way
+        constexpr int N = NV ? NV : 1;
+        int src, dst, x[N];
+        bool on = tid < mp.threads;
+        if constexpr (NV > 0) {
             const int t = mp.per_move == 1 ? at : at / mp.per_move;
             const long li = (long)b * p.Lcap + t;
             src = movers[li]; dst = holes[li];
-            x = (at - t * mp.per_move) * mp.threads + tid;
-            on = tid < mp.threads && x < mp.by_pair.d;
+#pragma unroll
+            for (int i = 0; i < N; ++i) x[i] = ((at - t * mp.per_move) * N + i) * mp.threads + tid;
         } else {
             const int u = mp.by_pair.div(tid), t = at * mp.per_piece + u;
             const long li = (long)b * p.Lcap + min(t, p.Lcap - 1);
             src = movers[li]; dst = holes[li];
-            x = tid - u * mp.by_pair.d;
-            on = tid < mp.threads && t < n_move[b];
+            x[0] = tid - u * mp.by_pair.d;
+            on = on && t < n_move[b];
         }
         if (on) {
             const int rv = mp.by_pair.d >> 1, sh = __builtin_ctz(p.d) - 3;
-            const bool is_v = x >= rv;
-            const int c = is_v ? x - rv : x;         // head slices of 2^sh vectors
-            uint16_t* base = (is_v ? v_cache : k_cache) + layer * layer_stride + (long)b * lay.batch +
-                             (long)(c >> sh) * lay.head + (c & ((1 << sh) - 1)) * 8;
-            const u32x4* from = reinterpret_cast<const u32x4*>(base + (long)src * lay.token);
-            u32x4* to = reinterpret_cast<u32x4*>(base + (long)dst * lay.token);
-            if (is_v ? V_ONCE : K_ONCE) __builtin_nontemporal_store(__builtin_nontemporal_load(from), to);
-            else *to = *from;
+            u32x4 val[N], *to[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int xi = min(x[i], mp.by_pair.d - 1);          // (behind the pair: its last vector, dropped)
+                const bool is_v = xi >= rv;
+                const int c = is_v ? xi - rv : xi;   // head slices of 2^sh vectors
+                uint16_t* base = (is_v ? v_cache : k_cache) + layer * layer_stride + (long)b * lay.batch +
+                                 (long)(c >> sh) * lay.head + (c & ((1 << sh) - 1)) * 8;
+                const u32x4* from = reinterpret_cast<const u32x4*>(base + (long)src * lay.token);
+                to[i] = reinterpret_cast<u32x4*>(base + (long)dst * lay.token);
+                val[i] = STREAM ? __builtin_nontemporal_load(from) : *from;
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if (N > 1 && x[i] >= mp.by_pair.d) continue;
+                if (STREAM) __builtin_nontemporal_store(val[i], to[i]); else *to[i] = val[i];
+            }
         }
         buf ^= 1;
         if (tid == 0) s_next[buf] = claimed;
@@ -909,7 +922,7 @@ DecodeWorkspace carve_decode(void* base, int B, int Lcap, int H) {
 }
 
 // The row moves of every sample in the caches of n_layers layers; at most max_moves of them per sample.
-void launch_moves(const DecodeDims& p, const KvLayout& lay, const DecodeWorkspace& w, hipStream_t st, bool dense, size_t cache_bytes,
+void launch_moves(const DecodeDims& p, const KvLayout& lay, const DecodeWorkspace& w, hipStream_t st, bool dense,
                   int n_layers, long layer_stride, int max_moves, void* k_cache, void* v_cache) {
     const MovePieces mp = move_pieces(p.H, p.d);
     // Just under two blocks per CU, but no more than pieces there can be.  64 caches of 4096 entries cut to 1024, and 32 layers
@@ -918,13 +931,13 @@ void launch_moves(const DecodeDims& p, const KvLayout& lay, const DecodeWorkspac
     const int blocks = (int)(most < 448 ? (most > 1 ? most : 1) : 448);
     uint16_t* kc = static_cast<uint16_t*>(k_cache);
     uint16_t* vc = static_cast<uint16_t*>(v_cache);
-#define MD_MOVE2(K_, V_, O_)                                                                                   \
-    MD_LAUNCH("decode_move", st, (decode_move_kernel<K_, V_, O_>), blocks, 1024, 0, p, lay, mp, n_layers, w.holes, w.movers, w.n_move,  \
+#define MD_MOVE2(STREAM_, NV_)                                                                                 \
+    MD_LAUNCH("decode_move", st, (decode_move_kernel<STREAM_, NV_>), blocks, 1024, 0, p, lay, mp, n_layers, w.holes, w.movers, w.n_move,  \
         w.claims, kc, vc, layer_stride)
-#define MD_MOVE(K_, V_) do { if (mp.per_piece == 1) MD_MOVE2(K_, V_, true); else MD_MOVE2(K_, V_, false); } while (0)
-    if (!dense && p.d < 64) MD_MOVE(false, false);
-    else if (cache_bytes > (size_t)128 << 20) MD_MOVE(true, true);
-    else MD_MOVE(false, true);
+#define MD_MOVE(NV_) do { if (dense || p.d >= 64) MD_MOVE2(true, NV_); else MD_MOVE2(false, NV_); } while (0)
+    if (mp.per_piece > 1) MD_MOVE(0);
+    else if (mp.vectors == 1) MD_MOVE(1);
+    else MD_MOVE(2);
 #undef MD_MOVE2
 #undef MD_MOVE
 }
@@ -1119,7 +1132,7 @@ int decode_evict_impl(
         MD_LAUNCH("decode_select", st, (decode_select_kernel), B, 1024, lds,
             p, w.logits, decay, budget, acc, ids, protect, len, w.keep, w.holes, w.movers, w.n_move, w.claims, evicted_ids, evicted_count);
     }
-    launch_moves(p, lay, w, st, dense, cache_bytes, 1, 0l, Lcap > budget ? (Lcap - budget < budget ? Lcap - budget : budget) : 0, k_cache, v_cache);
+    launch_moves(p, lay, w, st, dense, 1, 0l, Lcap > budget ? (Lcap - budget < budget ? Lcap - budget : budget) : 0, k_cache, v_cache);
     return check_launch("decode_evict");
 }
 
@@ -1160,7 +1173,7 @@ int decode_keep_impl(
     hipStream_t st = static_cast<hipStream_t>(stream);
     MD_LAUNCH("decode_keep_plan", st, (decode_keep_plan_kernel), B, 1024, 0,
         p, keep, acc, ids, protect, len, w.holes, w.movers, w.n_move, w.claims, evicted_ids, evicted_count);
-    launch_moves(p, lay, w, st, dense, cache_bytes, n_layers, layer_stride, Lcap / 2, k_cache, v_cache);
+    launch_moves(p, lay, w, st, dense, n_layers, layer_stride, Lcap / 2, k_cache, v_cache);
     return check_launch("decode_keep");
 }
 
