@@ -7,7 +7,8 @@
 // that has them (row_lse) pays one sweep over K; otherwise a first sweep computes them:
 //   prefill_rowstats_kernel  per (sample, head, key chunk): S = K Q^T on the MFMA units, online
 //                            (max, sum-exp) per text row -> row statistics (prefill_cstat_kernel
-//                            merges the chunks); with row_lse only prefill_qpack_kernel runs
+//                            merges the chunks); prefill_rowstats_wide_kernel where there are several
+//                            text groups; with row_lse only prefill_qpack_kernel runs
 //   prefill_colscore_kernel  persistent blocks over units of (64 or 128 vision keys, one head): recompute
 //                            S, p = exp(s - m)/Z, accumulate the head mean a[i][j] of such a key tile
 //                            in registers; a block's share of a tile is written as one piece
@@ -69,7 +70,7 @@ struct LdsRows {
     template <bool STREAM = false>
     __device__ static __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, uint32_t row_bytes, int grow0, int slot_row,
                                                  char* lds_base, int lane, bool live) {
-        const int row = slot_row + lane / CH, pos = lane % CH;
+        const int row = slot_row + (int)((uint32_t)lane / CH), pos = (int)((uint32_t)lane % CH);
         const uint32_t off = live ? (uint32_t)(grow0 + row) * row_bytes + (uint32_t)((pos ^ swz(row)) << 4) : 0xFFFFFF00u;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(lds_base + slot_row * ROWB), 16, off, 0, 0, STREAM ? 2 : 0);
     }
@@ -79,6 +80,23 @@ struct LdsRows {
         const int r = lane & 31, g = lane >> 5;
         const uint32_t a = (uint32_t)(uintptr_t)(lds_ptr_t)const_cast<char*>(tile);
         return (a + r * ROWB) ^ (uint32_t)((g << 4) ^ (swz(r) << 4));
+    }
+    // the KS fragments of a tile, requested and waited for in one statement
+    __device__ static __forceinline__ void frags_wait(uint32_t fb, bf16x8 (&f)[KS]) {
+        uint32_t a;
+        if constexpr (KS == 8)
+            asm volatile("ds_read_b128 %0, %9\n\t"
+                         "v_xor_b32 %8, 32, %9\n\tds_read_b128 %1, %8\n\tv_xor_b32 %8, 64, %9\n\tds_read_b128 %2, %8\n\t"
+                         "v_xor_b32 %8, 0x60, %9\n\tds_read_b128 %3, %8\n\tv_xor_b32 %8, 0x80, %9\n\tds_read_b128 %4, %8\n\t"
+                         "v_xor_b32 %8, 0xa0, %9\n\tds_read_b128 %5, %8\n\tv_xor_b32 %8, 0xc0, %9\n\tds_read_b128 %6, %8\n\t"
+                         "v_xor_b32 %8, 0xe0, %9\n\tds_read_b128 %7, %8\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7]),
+                           "=&v"(a) : "v"(fb) : "memory");
+        else
+            asm volatile("ds_read_b128 %0, %5\n\t"
+                         "v_xor_b32 %4, 32, %5\n\tds_read_b128 %1, %4\n\tv_xor_b32 %4, 64, %5\n\tds_read_b128 %2, %4\n\t"
+                         "v_xor_b32 %4, 0x60, %5\n\tds_read_b128 %3, %4\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(a) : "v"(fb) : "memory");
     }
     // the KS fragments of a tile; returns once they are in registers
     __device__ static __forceinline__ void frags(uint32_t fb, bf16x8 (&f)[KS]) {
@@ -131,6 +149,80 @@ __device__ __forceinline__ int wave_max_int(int v) {
 }
 __device__ __forceinline__ int effective_rows(int last, int Mv) { return last < 0 ? 0 : min(Mv, (last + 32) & ~31); }
 
+// Validity of the 32 keys e0 .. e0+31 of the mask row `vb` of Mv bytes (bit r = key e0 + r is a valid vision token; bytes
+// beyond the row count as invalid); e0 is a multiple of 32.
+__device__ __forceinline__ uint32_t key_valid_mask(const uint8_t* __restrict__ vb, long e0, int Mv) {
+    uint32_t mask = 0;
+    if ((reinterpret_cast<uintptr_t>(vb) & 3) == 0) {             // block-uniform: the mask row is word-aligned
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(vb), 0, (Mv + 3) & ~3, 0x00020000);
+        uint32_t w[8];
+        const int off = (int)min(e0, (long)((Mv + 3) & ~3));    // beyond the row: out of the buffer's range, reads 0
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w[q] = __builtin_amdgcn_raw_buffer_load_b32(rv, off + 4 * q, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            mask |= (((w[q] & 0xFFu) ? 1u : 0u) | ((w[q] & 0xFF00u) ? 2u : 0u) | ((w[q] & 0xFF0000u) ? 4u : 0u) |
+                     ((w[q] & 0xFF000000u) ? 8u : 0u)) << (4 * q);
+    } else {
+        for (int r = 0; r < 32; ++r) mask |= (vb[min(e0 + r, (long)Mv - 1)] != 0 ? 1u : 0u) << r;
+    }
+    const long left = (long)Mv - e0;                            // slots of the row from this tile on
+    if (left < 32) mask &= left <= 0 ? 0u : (1u << left) - 1u;
+    return mask;
+}
+
+// The mask row of a sample for one wave, requested in one go: word w of a lane covers the 32 keys of tile 64 * w + lane, so
+// that the last valid key and the tiles' masks come out of the same loads (one round trip; a loop over the row and a
+// second look at the wave's own tiles were four to five: 8 x 2880 keys, 128 text rows, 3/4 of the slots valid 50.4 -> 49.4 us).
+struct MaskRow {
+    static constexpr int W = 5;                       // rows of up to 64 * 32 * W slots
+    u32x4 raw[W][2];
+    __device__ static __forceinline__ bool fits(const uint8_t* vb, int Mv) {
+        return vb && (reinterpret_cast<uintptr_t>(vb) & 3) == 0 && Mv <= W * kWave * 32;
+    }
+    __device__ __forceinline__ void request(const uint8_t* vb, int Mv, int lane) {
+        // (slots beyond the row read as invalid; the up to three bytes that fill its last word are cut off in `word`)
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(vb), 0, (Mv + 3) & ~3, 0x00020000);
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            if (w * kWave * 32 < Mv) {
+                raw[w][0] = __builtin_amdgcn_raw_buffer_load_b128(rv, (w * kWave + lane) * 32, 0, 0);
+                raw[w][1] = __builtin_amdgcn_raw_buffer_load_b128(rv, (w * kWave + lane) * 32 + 16, 0, 0);
+            } else {
+                raw[w][0] = raw[w][1] = u32x4{0, 0, 0, 0};
+            }
+    }
+    __device__ __forceinline__ uint32_t word(int w, int Mv, int lane) const {
+        uint32_t mask = 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            // byte != 0 -> its top bit (no carry leaves a byte), then the four top bits gathered
+            const uint32_t x = raw[w][q >> 2][q & 3], t = ((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x;
+            mask |= ((((t >> 7) & 0x01010101u) * 0x01020408u) >> 24 & 15u) << (4 * q);
+        }
+        const int left = Mv - (w * kWave + lane) * 32;
+        return left >= 32 ? mask : left <= 0 ? 0u : mask & ((1u << left) - 1u);
+    }
+    // the last valid key of the row (-1: none), and this lane's choice of a tile's mask (`tile`: any per lane)
+    __device__ __forceinline__ uint32_t digest(int Mv, int lane, int tile, int& last) const {
+        uint32_t mine = 0;
+        last = -1;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            if (w * kWave * 32 >= Mv) break;
+            const uint32_t v = word(w, Mv, lane);
+            const unsigned long long any = __ballot(v != 0);
+            if (any) {
+                const int l = 63 - __builtin_clzll(any);
+                last = (w * kWave + l) * 32 + 31 - __builtin_clz((uint32_t)__builtin_amdgcn_readlane((int)v, l));
+            }
+            const uint32_t got = (uint32_t)__builtin_amdgcn_ds_bpermute((tile & 63) * 4, (int)v);
+            if (tile >> 6 == w) mine = got;
+        }
+        return mine;
+    }
+};
+
 // What the kernels that follow need to know of a sample, written by the first one of a call.
 struct SampleRows { int vision; int text_blocks; };   // effective vision rows; 32-row blocks with text rows below txt_len
 // A block of a sweep holds up to `nbw` 32-row text blocks, one per wave column.  More of them (longer prompts) are
@@ -177,7 +269,7 @@ __device__ __forceinline__ void load_query_frags(const uint16_t* qb, long tok_st
 }
 
 // ---------------------------------------------------------------------------------------------
-// Sweep 1: row statistics.  Block = (key chunk, text group, head, sample), 4 or 8 waves.  The waves of a
+// Sweep 1: row statistics.  Block = (key chunk, head, sample), 4 or 8 waves, one text group (see the wide form below).  The waves of a
 // block share every K tile through LDS: wave w works on text block w % NBW of the group and on key
 // tile w / NBW of the TW tiles in flight per step, so a wave keeps the fragments of ONE
 // 32-row text block in registers and K is read once per block.  K tiles stream through S LDS slots
@@ -235,6 +327,26 @@ __device__ __forceinline__ void online_update_masked(f32x16 acc, uint32_t vis, f
     }
 }
 
+// The same where keys may be invisible (their scores -inf), up to all that were seen so far.
+__device__ __forceinline__ void online_update_any(const f32x16& acc, float scale_log2e, float& m, float& z) {
+    const float b0 = fmaxf(fmaxf(acc[0], acc[1]), acc[2]), b1 = fmaxf(fmaxf(acc[3], acc[4]), acc[5]);
+    const float b2 = fmaxf(fmaxf(acc[6], acc[7]), acc[8]), b3 = fmaxf(fmaxf(acc[9], acc[10]), acc[11]);
+    const float b4 = fmaxf(fmaxf(acc[12], acc[13]), acc[14]);
+    const float bm = fmaxf(fmaxf(fmaxf(b0, b1), b2), fmaxf(fmaxf(b3, b4), acc[15]));
+    const float mn = fmaxf(m, bm * scale_log2e);
+    const float nmn = mn > -INFINITY ? -mn : 0.f;
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; r += 4) {
+        s0 += fast_exp2(fmaf(acc[r], scale_log2e, nmn));
+        s1 += fast_exp2(fmaf(acc[r + 1], scale_log2e, nmn));
+        s2 += fast_exp2(fmaf(acc[r + 2], scale_log2e, nmn));
+        s3 += fast_exp2(fmaf(acc[r + 3], scale_log2e, nmn));
+    }
+    z = fmaf(z, fast_exp2(m + nmn), (s0 + s1) + (s2 + s3));
+    m = mn;
+}
+
 // The compiler's scheduler is asked to issue one MFMA, then a few vector and transcendental
 // instructions, and so on: a wave issues in order, and a chain of dependent MFMAs issued back to back
 // would hold up the independent vector work behind it.
@@ -274,23 +386,11 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     __shared__ int s_last[NW];
     const int lane = lane_id(), wv = wave_id();
     const int nbw = wv % NBW, tw = wv / NBW;
-    // one text group: grid (chunk, head, sample).  Several: the blocks of one (chunk, head, sample) read the same K at the
-    // same time, so they follow each other on one XCD (blocks go round-robin over the 8 XCDs, each with its own L2)
-    int ch = blockIdx.x, tg = 0, h = blockIdx.y, b = blockIdx.z;
-    if (p.ng > 1) {
-        const int q = (int)blockIdx.x >> 3;
-        tg = q % p.ng;
-        int item = (q / p.ng) * 8 + ((int)blockIdx.x & 7);
-        if (item >= p.B * p.H * p.nch) return;
-        ch = item % p.nch; item /= p.nch;
-        h = item % p.H; b = item / p.H;
-    }
+    const int ch = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int tl = txt_len ? min(max(txt_len[b], 0), p.N) : p.N;
-    const int nbl = text_blocks_of(tl), ngl = text_groups_of(nbl, NBW);
-    if (tg > 0 && tg >= ngl) return;                  // (group 0 stays: it says how many rows matter)
-    const TextGroup grp = ngl > 0 ? text_group(tg, nbl, ngl) : TextGroup{0, 0};
-    const int nbg = grp.first + nbw;                  // 32-row text block of this wave
-    const bool live = nbw < grp.count;
+    const int nbl = text_blocks_of(tl);               // (at most NBW)
+    const int nbg = nbw;                              // 32-row text block of this wave
+    const bool live = nbg < nbl;
     const int i0 = 32 * nbg;
     const uint16_t* kb = k + (long)b * p.kv.batch + (long)h * p.kv.head;
     const uint16_t* qb = q_txt + (long)b * p.q.batch + (long)h * p.q.head;
@@ -328,24 +428,7 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     // flight, the K tiles included, once per step.)
     auto key_valid_masks = [&](int g0) -> uint32_t {
         if (!vb) return 0xFFFFFFFFu;
-        const long e0 = (long)step_row0(g0 + lane) + tw * 32;         // first key of the tile; a multiple of 32
-        uint32_t mask = 0;
-        if ((reinterpret_cast<uintptr_t>(vb) & 3) == 0) {             // block-uniform: the mask row is word-aligned
-            const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(vb), 0, (p.Mv + 3) & ~3, 0x00020000);
-            uint32_t w[8];
-            const int off = (int)min(e0, (long)((p.Mv + 3) & ~3));    // beyond the row: out of the buffer's range, reads 0
-#pragma unroll
-            for (int q = 0; q < 8; ++q) w[q] = __builtin_amdgcn_raw_buffer_load_b32(rv, off + 4 * q, 0, 0);
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                mask |= (((w[q] & 0xFFu) ? 1u : 0u) | ((w[q] & 0xFF00u) ? 2u : 0u) | ((w[q] & 0xFF0000u) ? 4u : 0u) |
-                         ((w[q] & 0xFF000000u) ? 8u : 0u)) << (4 * q);
-        } else {
-            for (int r = 0; r < 32; ++r) mask |= (vb[min(e0 + r, (long)p.Mv - 1)] != 0 ? 1u : 0u) << r;
-        }
-        const long left = (long)p.Mv - e0;                            // slots of the row from this tile on
-        if (left < 32) mask &= left <= 0 ? 0u : (1u << left) - 1u;
-        return mask;
+        return key_valid_mask(vb, (long)step_row0(g0 + lane) + tw * 32, p.Mv);      // first key of the tile
     };
 
     // Prologue, one round trip: the query tiles (each wave column's tile, its rows split among the column's
@@ -378,14 +461,14 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
         for (int w2 = 1; w2 < NW; ++w2) last = max(last, s_last[w2]);
         Me = effective_rows(last, p.Mv);
         plan();
-        if (ch == 0 && tg == 0 && h == 0 && threadIdx.x == 0) rows[b] = SampleRows{Me, nbl};   // for the second sweep
+        if (ch == 0 && h == 0 && threadIdx.x == 0) rows[b] = SampleRows{Me, nbl};   // for the second sweep
         const int ahead = min(S - 1, max(nit, nit_guess));
         if (ahead > 0 && step_row0(ahead - 1) + SLOT_ROWS > Me) {            // a requested step reaches beyond Me: again, with the jump
 #pragma unroll
             for (int g = 0; g < S - 1; ++g)
                 if (g < nit) issue_step(g);
         }
-    } else if (ch == 0 && tg == 0 && h == 0 && threadIdx.x == 0) {
+    } else if (ch == 0 && h == 0 && threadIdx.x == 0) {
         rows[b] = SampleRows{p.Mv, nbl};
     }
 
@@ -487,13 +570,258 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
 #pragma unroll
             for (int t = 0; t < TW; ++t) zn += s_z[t * NBW + nb][r] * fast_exp2(s_m[t * NBW + nb][r] - mn);
         }
-        const int ii = 32 * (grp.first + nb) + r;
-        if (nb < grp.count) {
+        const int ii = 32 * nb + r;
+        if (nb < nbl) {
             if (p.nch == 1)     // the only chunk: fold the statistics right away (see fold_stats)
                 cstat[((long)b * p.H + h) * p.Npad + ii] = fold_stats(mn, zn, ii < tl, p.H);
             else
                 partial[(((long)b * p.H + h) * p.nch + ch) * p.Npad + ii] = make_float2(mn, zn);
         }
+    }
+}
+
+// The same for one (tile, text block) of the wide form, whose arithmetic starts with a tree of maxima.
+template <int KS>
+__device__ __forceinline__ void interleave_chain() {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, 14, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
+#pragma unroll
+    for (int q = 2; q < KS; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x400, KS == 8 ? 1 : 4, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, KS == 8 ? 2 : 7, 0);
+        __builtin_amdgcn_sched_group_barrier(0x400, KS == 8 ? 2 : 5, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, KS == 8 ? 3 : 7, 0);
+    }
+}
+
+// The same sweep with all text blocks of a group in every wave: block = (key chunk, text group, head, sample), four
+// waves, and a wave holds the fragments of up to four text blocks in registers and has key tiles, LDS slots and a place
+// in the sum of its own.  A key fragment is read from LDS once for all of the text blocks, not once per text block, and
+// the steady loop has no barrier: a wave waits for its own loads only.  Two such blocks fit a CU, so that one's prologue
+// runs beside the other's arithmetic (one block of eight waves per CU: 5 to 33 % slower at the sizes below).
+// Bound by the exponentials and the matrix product of a wave, which the steady loop interleaves, wherever K comes from L2,
+// as it does for all text groups of a sample but one: 6 x 1152 keys, 32 heads, 384 text rows 70 -> 53 us, 20 x 576 with 200
+// rows 79 -> 59, 3 x 9000 with 200 rows 86 -> 71; 4 x 4000 keys of 64, 32 heads, 300 rows 57 -> 50.
+template <int KS, bool STREAM>
+__global__ __launch_bounds__(256, 2) void prefill_rowstats_wide_kernel(
+    const uint16_t* __restrict__ q_txt, const uint16_t* __restrict__ k,
+    const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ txt_len, PrefillDims p, float scale_log2e,
+    float2* __restrict__ partial, float* __restrict__ cstat, bf16x8* __restrict__ qfrag, SampleRows* __restrict__ rows)
+{
+    using T = LdsRows<KS>;
+    constexpr int NW = 4, NBMAX = 4;
+    constexpr int S = KS == 8 ? 2 : 4;                // tiles under way per wave: 64 KB per block, two blocks per CU
+    constexpr int TILE_BYTES = 32 * T::ROWB;
+    constexpr int NLT = 32 / T::RPL;                  // load instructions per tile
+    // slot s of wave w at (s * NW + w) * TILE_BYTES; the query tiles lie in the last slots until they are in registers,
+    // a wave's statistics in its first one once the sweep is done
+    __shared__ __attribute__((aligned(1024))) char s_k[S * NW * TILE_BYTES];
+    static_assert(NBMAX <= NW && NBMAX * 32 * (int)sizeof(float2) <= TILE_BYTES, "query tiles and statistics fit the slots");
+    char* const s_q = s_k + (S - 1) * NW * TILE_BYTES;
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    // one text group: grid (chunk, head, sample).  Several: the blocks of one (chunk, head, sample) read the same K at the
+    // same time, so they follow each other on one XCD (blocks go round-robin over the 8 XCDs, each with its own L2)
+    int ch = blockIdx.x, tg = 0, h = blockIdx.y, b = blockIdx.z;
+    if (p.ng > 1) {
+        const int q = (int)blockIdx.x >> 3;
+        tg = q % p.ng;
+        int item = (q / p.ng) * 8 + ((int)blockIdx.x & 7);
+        if (item >= p.B * p.H * p.nch) return;
+        ch = item % p.nch; item /= p.nch;
+        h = item % p.H; b = item / p.H;
+    }
+    const int tl = txt_len ? min(max(txt_len[b], 0), p.N) : p.N;
+    const int nbl = text_blocks_of(tl), ngl = text_groups_of(nbl, NBMAX);
+    if (tg > 0 && tg >= ngl) return;                  // (group 0 stays: it says how many rows matter)
+    const TextGroup grp = ngl > 0 ? text_group(tg, nbl, ngl) : TextGroup{0, 0};
+    const uint16_t* kb = k + (long)b * p.kv.batch + (long)h * p.kv.head;
+    const uint16_t* qb = q_txt + (long)b * p.q.batch + (long)h * p.q.head;
+    const uint8_t* vb = vis_valid ? vis_valid + (long)b * p.Mv : nullptr;
+    const __amdgpu_buffer_rsrc_t rk = row_buffer(kb, p.L, p.kv.token, p.d);
+    const uint32_t krow = (uint32_t)(p.kv.token * 2);
+
+    // effective key positions as in prefill_rowstats_kernel; tile g of this wave is tile (g * nch + ch) * NW + wv
+    int Me = p.Mv, jump = 0, c1 = 0, nit = 0;
+    auto tile_row0 = [&](int g) { return ((g * p.nch + ch) * NW + wv) * 32; };
+    auto plan = [&]() {
+        jump = p.Mv - Me;
+        c1 = Me + p.N;
+        const int tiles = (c1 + 31) / 32, first = ch * NW + wv, every = p.nch * NW;
+        nit = tiles > first ? (tiles - first + every - 1) / every : 0;
+    };
+    auto slot_of = [&](int g) { return s_k + ((g % S) * NW + wv) * TILE_BYTES; };
+    auto issue_tile = [&](int g, bool live = true) {
+        const int row0 = tile_row0(g), src0 = row0 + (row0 >= Me ? jump : 0);
+        char* slot = slot_of(g);
+        int l = lane;
+        asm volatile("" : "+v"(l));                   // the lane's offsets are made anew: registers are what this kernel lacks
+#pragma unroll
+        for (int t = 0; t < NLT; ++t) T::template issue<STREAM>(rk, krow, src0, t * T::RPL, slot, l, live);
+    };
+    // validity of the 32 keys of the tiles g0 .. g0+63, one per lane (see prefill_rowstats_kernel)
+    auto key_valid_masks = [&](int g0) -> uint32_t {
+        if (!vb) return 0xFFFFFFFFu;
+        return key_valid_mask(vb, (long)tile_row0(g0 + lane), p.Mv);
+    };
+
+    // prologue, one round trip: the query tiles, the first S-1 tiles of K as if they lay below Me, the scan of the mask
+    // (every wave for itself)
+    plan();
+    {
+        const __amdgpu_buffer_rsrc_t rq = row_buffer(qb, tl, p.q.token, p.d);
+        for (int e = wv; e < grp.count * NLT; e += NW)
+            T::issue(rq, (uint32_t)(p.q.token * 2), 32 * (grp.first + e / NLT), (e % NLT) * T::RPL, s_q + (e / NLT) * TILE_BYTES, lane, true);
+    }
+    const bool one_go = MaskRow::fits(vb, p.Mv);      // block-uniform
+    MaskRow mrow;
+    if (one_go) mrow.request(vb, p.Mv, lane);
+#pragma unroll
+    for (int g = 0; g < S - 1; ++g) issue_tile(g, g < nit);
+    int last = p.Mv - 1;
+    uint32_t vismasks = 0xFFFFFFFFu;
+    if (one_go) {
+        vismasks = mrow.digest(p.Mv, lane, tile_row0(lane) / 32, last);
+    } else if (vb) {
+        last = __builtin_amdgcn_readfirstlane(wave_max_int(last_set_partial(vb, p.Mv, lane, kWave)));
+        vismasks = key_valid_masks(0);
+    }
+    MD_VM_WAIT((S - 1) * NLT);
+    block_sync_lds();                                 // query tiles complete
+    const int guess = nit;
+    Me = effective_rows(last, p.Mv);
+    plan();
+
+    auto sweep = [&](auto nbc) {
+        constexpr int NB = decltype(nbc)::value;
+        bf16x8 qf[NB][KS];
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            T::frags_wait(T::frag_base(s_q + t * TILE_BYTES, lane), qf[t]);
+            const int rows_here = tl - 32 * (grp.first + t);
+            if (rows_here < 32) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    if ((lane & 31) >= rows_here) qf[t][ks] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+            }
+        }
+        block_sync_lds();                             // the query tiles' place is free
+        {
+            const int ahead = min(S - 1, max(nit, guess));
+            const bool again = Me < p.Mv && ahead > 0 && tile_row0(ahead - 1) + 32 > Me;   // a requested tile reaches beyond Me
+#pragma unroll 1
+            for (int g = again ? 0 : S - 1; g < S; ++g)
+                if (g < nit) issue_tile(g);
+        }
+
+        float m[NB], z[NB];
+#pragma unroll
+        for (int t = 0; t < NB; ++t) { m[t] = -INFINITY; z[t] = 0.f; }
+        struct TileVis { bool all; int j0; uint32_t vmask; };         // first key; its valid vision keys
+        auto visibility = [&](int g) -> TileVis {
+            TileVis v;
+            v.j0 = tile_row0(g);
+            v.vmask = (uint32_t)__builtin_amdgcn_readlane((int)vismasks, g & 63);
+            if (v.j0 + 32 > Me) v.vmask &= v.j0 >= Me ? 0u : (1u << (Me - v.j0)) - 1u;
+            v.all = v.j0 + 32 <= Me && v.vmask == 0xFFFFFFFFu;
+            return v;
+        };
+        // scores of invisible keys to -inf: text row i of block t sees the valid vision keys and text keys 0 .. i
+        auto hide = [&](f32x16& acc, const TileVis& v, int t) {
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            auto below = [](int n) { return n >= 32 ? 0xFFFFFFFFu : n <= 0 ? 0u : (1u << n) - 1u; };
+            const int i = 32 * (grp.first + t) + (l & 31);
+            const uint32_t text = below(min(c1, Me + i + 1) - v.j0) & ~below(Me - v.j0);
+            const uint32_t vis = (v.vmask | text) >> (4 * (l >> 5));          // bit 8 * (r / 4) + r % 4: key of register r
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = (vis >> tile_row(r, 0)) & 1u ? acc[r] : -INFINITY;
+        };
+        // The MFMA chain of a (tile, text block) is issued together with the arithmetic on the one before it.
+        TileVis prev{false, c1, 0u};                  // before the first tile: nothing visible
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        for (int g = 0; g < nit; ++g) {
+            if (g + S - 1 < nit) { MD_VM_WAIT((S - 1) * NLT); } else { MD_VM_WAIT(0); }
+            bf16x8 kf[KS];
+            T::frags_wait(T::frag_base(slot_of(g), lane), kf);
+            if (g + S < nit) issue_tile(g + S);
+            const TileVis cur = visibility(g);
+            auto chain = [&](int t, int tu) {
+                const f32x16 nw = score_tile<KS>(kf, qf[t]);
+                online_update_any(acc, scale_log2e, m[tu], z[tu]);
+                acc = nw;
+            };
+            // (the two forms apart, so that the common one is straight-line code)
+            if (prev.all) {
+                chain(0, NB - 1);
+                interleave_chain<KS>();
+            } else {
+                hide(acc, prev, NB - 1);
+                chain(0, NB - 1);
+            }
+            if (cur.all) {
+#pragma unroll
+                for (int t = 1; t < NB; ++t) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    chain(t, t - 1);
+                    interleave_chain<KS>();
+                }
+            } else {
+#pragma unroll
+                for (int t = 1; t < NB; ++t) {
+                    hide(acc, cur, t - 1);
+                    chain(t, t - 1);
+                }
+            }
+            prev = cur;
+            if ((g & 63) == 63 && g + 1 < nit) vismasks = key_valid_masks(g + 1);
+        }
+        if (!prev.all) hide(acc, prev, NB - 1);
+        online_update_any(acc, scale_log2e, m[NB - 1], z[NB - 1]);
+        // the fragment-major copy of the text queries for the second sweep, shared out over the waves
+        if (ch == 0) {
+#pragma unroll
+            for (int t = 0; t < NB; ++t)
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    if (wv == ks % NW) qfrag[((((long)b * p.H + h) * (p.Npad / 32) + grp.first + t) * KS + ks) * kWave + lane] = qf[t][ks];
+        }
+        // merge the two lane halves (same text row, the other 16 keys); the wave's statistics go to its own first slot
+        float2* const sv = reinterpret_cast<float2*>(s_k + wv * TILE_BYTES);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            const float mo = __shfl_xor(m[t], 32, kWave), zo = __shfl_xor(z[t], 32, kWave);
+            const float mn = fmaxf(m[t], mo);
+            float zn = 0.f;
+            if (mn > -INFINITY) zn = z[t] * fast_exp2(m[t] - mn) + zo * fast_exp2(mo - mn);
+            if (lane < 32) sv[t * 32 + lane] = make_float2(mn, zn);
+        }
+    };
+    if (ch == 0 && tg == 0 && h == 0 && threadIdx.x == 0) rows[b] = SampleRows{effective_rows(last, p.Mv), nbl};   // for the second sweep
+    if (grp.count == 0) return;                       // no text rows in this sample
+    if (grp.count == 4) sweep(std::integral_constant<int, 4>());
+    else if (grp.count == 3) sweep(std::integral_constant<int, 3>());
+    else if (grp.count == 2) sweep(std::integral_constant<int, 2>());
+    else sweep(std::integral_constant<int, 1>());
+    __syncthreads();
+    if ((int)threadIdx.x < 32 * grp.count) {
+        const int r = threadIdx.x;
+        auto stat = [&](int w) { return reinterpret_cast<const float2*>(s_k + w * TILE_BYTES)[r]; };
+        float mn = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mn = fmaxf(mn, stat(w).x);
+        float zn = 0.f;
+        if (mn > -INFINITY) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) zn += stat(w).y * fast_exp2(stat(w).x - mn);
+        }
+        const int ii = 32 * grp.first + r;
+        if (p.nch == 1) cstat[((long)b * p.H + h) * p.Npad + ii] = fold_stats(mn, zn, ii < tl, p.H);
+        else partial[(((long)b * p.H + h) * p.nch + ch) * p.Npad + ii] = make_float2(mn, zn);
     }
 }
 
@@ -1271,10 +1599,16 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
             else if (KS == 8 && NBW_ == 1 && TW_ == 4 && s.rs_deep) MD_ROWSTATS2(NBW_, TW_, false, (KS == 8 && NBW_ == 1 && TW_ == 4)); \
             else MD_ROWSTATS2(NBW_, TW_, false, false);                                                        \
         } while (0)
+#define MD_ROWSTATS_WIDE(ST_)                                                                                  \
+    MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_wide_kernel<KS, ST_>), g1, 256, 0,                     \
+        qp, kp, vis_valid, txt_len, p, scale_log2e, w.partial, w.cstat, w.qfrag, w.rows)
         const bool big = s.rs_waves == 8;
-        if (s.nbw == 1) { if (big) MD_ROWSTATS(1, 8); else MD_ROWSTATS(1, 4); }
+        if (s.rs_wide) { if (s.rs_stream) MD_ROWSTATS_WIDE(true); else MD_ROWSTATS_WIDE(false); }
+        else if (s.nbw == 1) { if (big) MD_ROWSTATS(1, 8); else MD_ROWSTATS(1, 4); }
         else if (s.nbw == 2) { if (big) MD_ROWSTATS(2, 4); else MD_ROWSTATS(2, 2); }
-        else { if (big) MD_ROWSTATS(4, 2); else MD_ROWSTATS(4, 1); }
+        else if (big) MD_ROWSTATS(4, 2);
+        else if constexpr (KS == 4) MD_ROWSTATS(4, 1);    // (d = 128: the wide form)
+#undef MD_ROWSTATS_WIDE
 #undef MD_ROWSTATS
 #undef MD_ROWSTATS2
         if (p.nch > 1) {

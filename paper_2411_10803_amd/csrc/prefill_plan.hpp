@@ -49,7 +49,7 @@ MD_PLAN_FN ColRun effective_run(int tiles, int H, ColPlan cp) {
 }
 
 // Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep; ColPlan col; int occ; };
+struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide; ColPlan col; int occ; };
 
 inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     ScorePlan s;
@@ -67,24 +67,31 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start
     // (5), the keys it takes (ns per key, from alone on the chip to every place taken), the merge kernel for several chunks.
     // Measured to within 20 % at 17 shapes; before -> after e.g. 13 x 1039 keys, 32 heads, 10 text rows: 36.6 -> 23.1,
-    // 6 x 1152 keys, 384 text rows: 250 -> 69, 5 x 774 keys, 16 heads, 60 text rows: 14.5 -> 13.1.
+    // 6 x 1152 keys, 384 text rows: 250 -> 53 (in the wide form), 5 x 774 keys, 16 heads, 60 text rows: 14.5 -> 13.1.
     const int units = (Mv + N + 127) / 128;
     const long n = (long)B * H * s.ng;
     double best = 0;
-    for (int waves = 4; waves <= 8; waves += 4)
+    // The wide form takes all calls with several text groups.  With one, K comes from HBM and bounds the sweep: there it only
+    // takes the place of the blocks of four waves at d = 128 (13 x 1039 keys, 32 heads, 128 text rows 43 -> 40, 20 x 576, 40
+    // heads, 70 rows 53 -> 49); against one block of eight waves per head it pays for the merge of two chunks (8 x 2880,
+    // 128 rows 46.6 and 47.5 + 4), and heads of 64 have three smaller blocks per CU (8 x 2000, 128 rows 25 and 28).
+    for (int waves = 4; waves <= (s.ng > 1 ? 4 : 8); waves += 4)
         for (int nch = 1; nch <= kMaxChunks && (nch == 1 || nch <= units / 4); ++nch) {
-            const long blocks = n * nch, places = waves == 4 ? (s.nbw == 4 && d == 64 ? 3 : 2) * kNumCU : kNumCU;
+            const long blocks = n * nch, places = waves == 4 ? (s.nbw == 4 && s.ng == 1 && d == 64 ? 3 : 2) * kNumCU : kNumCU;
             const double fill = blocks < places ? (double)blocks / places : 1.0;
             double alone = s.nbw == 1 ? 7.5 : (s.nbw == 2 ? (waves == 8 ? 8.0 : 9.0) : (waves == 8 ? 11.0 : 14.0));
-            double full = waves == 8 ? (s.nbw < 4 ? 11.5 : (s.ng > 1 ? 15.0 : 16.0)) : (s.nbw < 4 ? 21.0 : (s.ng > 1 ? 26.0 : 34.0));
+            double full = waves == 8 ? (s.nbw < 4 ? 11.5 : 16.0) : 21.0;
             // (heads of 64 with four text blocks: three blocks of four waves share a CU, one of eight waves no better than at
             // d = 128; 2 x 8661 keys, 64 heads, 95 text rows 49.8 -> 38.6)
             if (s.nbw == 4 && d == 64) { alone = waves == 8 ? 10.0 : 11.5; full = waves == 8 ? 10.5 : 21.0; }
             if (s.nbw == 1 && d == 128 && waves == 4 && blocks <= kNumCU && !s.rs_stream) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
+            if (s.ng > 1) { alone = d == 64 ? 9.0 : 11.0; full = d == 64 ? 13.0 : 18.0; }
+            else if (s.nbw == 4 && d == 128 && waves == 4) full = 30.0;
             const double per_key = alone + (full - alone) * fill;
             const double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? 5.0 : 0.0);
             if (best == 0 || t < 0.97 * best) { best = t; s.rs_waves = waves; s.nch = nch; }
         }
+    s.rs_wide = s.ng > 1 || (s.nbw == 4 && d == 128 && s.rs_waves == 4);
     s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && !s.rs_stream;
     // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
     ColPlan& c = s.col;
