@@ -14,6 +14,7 @@
 //   decode_move_kernel    copies the K and V rows of the movers into the holes, where many may move, in every layer
 #include "md_device.hpp"
 #include "md_host.hpp"
+#include "decode_plan.hpp"
 
 namespace md {
 namespace {
@@ -21,8 +22,7 @@ namespace {
 constexpr float kLog2eD = 1.4426950408889634f;
 
 struct DecodeDims { int B, Lcap, H, d; };
-// Counters from which the blocks of decode_move_kernel claim their pieces, 128 bytes apart; cleared by the kernel before it.
-constexpr int kClaims = 16, kClaimStride = 32;
+// The counters from which the blocks of decode_move_kernel claim their pieces, cleared by the kernel before it.
 __device__ __forceinline__ void clear_claims(int32_t* claims, int tid) {
     if (tid < kClaims) claims[tid * kClaimStride] = 0;
 }
@@ -742,44 +742,25 @@ __global__ __launch_bounds__(1024) void decode_keep_plan_kernel(
 // in the order of layers, samples and moves, and the blocks claim the next piece whenever they are done with one, as the
 // hardware would hand out blocks if the host knew the number of moves.  64 caches of 4096 entries, 896 rows of 8 KiB moved in
 // each: 357 us in strides, 320 so (5.9 TB/s); a block per move, their number known, takes 303.
-// A block's first piece is the one of its number; the claims for further ones go to kClaims counters, 128 bytes apart (one
-// counter for all takes 12 ns a claim: 683 us), counter c hands out every kClaims-th piece from gridDim.x + c on.  Fewer than
-// kClaims blocks are launched only where each has one piece at most.  The kernel before this one has cleared the counters.
+// The kernel before this one has cleared the counters (decode_plan.hpp: which block claims which pieces).
 // STREAM: both sides bypass the caches, also where K is small enough to stay there until the next step reads it: kept, the moved
 // rows push out as much (14 caches of 882 entries cut to 208, 40 heads: next scores and moves 24.2 + 22.5 us, 26.0 + 22.1 with
 // K kept).  Not where a head slice is shorter than a cache line.
-struct MovePieces {
-    int per_piece, per_move;                         // moves per piece, pieces per move: one of them is 1
-    int vectors, threads;                            // of a thread; of a block that have any
-    FastDiv by_pair;                                 // vectors of a K row and a V row together
-};
-// Pairs of 1025 to 2048 vectors as one piece of two vectors per thread, not as two with a third of the threads idle: 14 caches of
-// 882 entries cut to 208, 40 heads of 128, 26.6 us in two, 22.5 in one.
-inline MovePieces move_pieces(int H, int d) {
-    const int pair = 2 * H * (d / 8);
-    MovePieces mp;
-    mp.vectors = pair <= 1024 ? 1 : 2;
-    mp.per_piece = pair < 1024 ? 1024 / pair : 1;
-    mp.per_move = (pair + 1024 * mp.vectors - 1) / (1024 * mp.vectors);
-    mp.threads = (mp.per_piece * pair + mp.per_move * mp.vectors - 1) / (mp.per_move * mp.vectors);
-    mp.by_pair = FastDiv::make(pair);
-    return mp;
-}
 // NV: vectors per thread; 0: one, and a piece holds several moves.
 template <bool STREAM, int NV>
 __global__ __launch_bounds__(1024) void decode_move_kernel(
-    DecodeDims p, KvLayout lay, MovePieces mp, int n_layers, const int32_t* __restrict__ holes, const int32_t* __restrict__ movers,
+    DecodeDims p, KvLayout lay, MovePieces mp, FastDiv by_pair, int n_layers, const int32_t* __restrict__ holes, const int32_t* __restrict__ movers,
     const int32_t* __restrict__ n_move, int32_t* __restrict__ claims, uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache,
     long layer_stride)
 {
     __shared__ uint32_t s_next[2];
-    const int tid = threadIdx.x, lane = lane_id(), q = blockIdx.x % kClaims;
+    const int tid = threadIdx.x, lane = lane_id(), q = blockIdx.x % claim_counters(gridDim.x);
     int32_t* my_claims = claims + q * kClaimStride;
     // pieces of the 64 samples b0 .. b0 + 63, one per lane, and the sum of pieces up to and with each
     int b0 = 0, mine = 0, incl = 0;
     auto group = [&](int at, int before) {
         b0 = at;
-        mine = b0 + lane < p.B ? (n_move[min(b0 + lane, p.B - 1)] + mp.per_piece - 1) / mp.per_piece * mp.per_move : 0;
+        mine = b0 + lane < p.B ? pieces_of(n_move[min(b0 + lane, p.B - 1)], mp) : 0;
         incl = wave_incl_scan_i(mine) + before;
     };
     uint32_t total = 0;                              // of a layer (a piece is some 16 KiB: they fit the index)
@@ -810,18 +791,18 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
 #pragma unroll
             for (int i = 0; i < N; ++i) x[i] = ((at - t * mp.per_move) * N + i) * mp.threads + tid;
         } else {
-            const int u = mp.by_pair.div(tid), t = at * mp.per_piece + u;
+            const int u = by_pair.div(tid), t = at * mp.per_piece + u;
             const long li = (long)b * p.Lcap + min(t, p.Lcap - 1);
             src = movers[li]; dst = holes[li];
-            x[0] = tid - u * mp.by_pair.d;
+            x[0] = tid - u * mp.pair;
             on = on && t < n_move[b];
         }
         if (on) {
-            const int rv = mp.by_pair.d >> 1, sh = __builtin_ctz(p.d) - 3;
+            const int rv = mp.pair >> 1, sh = __builtin_ctz(p.d) - 3;
             u32x4 val[N], *to[N];
 #pragma unroll
             for (int i = 0; i < N; ++i) {
-                const int xi = min(x[i], mp.by_pair.d - 1);          // (behind the pair: its last vector, dropped)
+                const int xi = min(x[i], mp.pair - 1);          // (behind the pair: its last vector, dropped)
                 const bool is_v = xi >= rv;
                 const int c = is_v ? xi - rv : xi;   // head slices of 2^sh vectors
                 uint16_t* base = (is_v ? v_cache : k_cache) + layer * layer_stride + (long)b * lay.batch +
@@ -832,14 +813,14 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
             }
 #pragma unroll
             for (int i = 0; i < N; ++i) {
-                if (N > 1 && x[i] >= mp.by_pair.d) continue;
+                if (N > 1 && x[i] >= mp.pair) continue;
                 if (STREAM) __builtin_nontemporal_store(val[i], to[i]); else *to[i] = val[i];
             }
         }
         buf ^= 1;
         if (tid == 0) s_next[buf] = claimed;
         block_sync_lds();                            // (the stores need not have arrived)
-        item = gridDim.x + (uint32_t)__builtin_amdgcn_readfirstlane((int)s_next[buf]) * kClaims + q;
+        item = claimed_piece(gridDim.x, q, (uint32_t)__builtin_amdgcn_readfirstlane((int)s_next[buf]));
     }
 }
 
@@ -921,19 +902,16 @@ DecodeWorkspace carve_decode(void* base, int B, int Lcap, int H) {
     return w;
 }
 
-// The row moves of every sample in the caches of n_layers layers; at most max_moves of them per sample.
+// The row moves of every sample in the caches of n_layers layers; at most `most` of them per sample.
 void launch_moves(const DecodeDims& p, const KvLayout& lay, const DecodeWorkspace& w, hipStream_t st, bool dense,
-                  int n_layers, long layer_stride, int max_moves, void* k_cache, void* v_cache) {
+                  int n_layers, long layer_stride, int most, void* k_cache, void* v_cache) {
     const MovePieces mp = move_pieces(p.H, p.d);
-    // Just under two blocks per CU, but no more than pieces there can be.  64 caches of 4096 entries cut to 1024, and 32 layers
-    // x 16 caches of 640 cut to 128: 348 and 342 us with 320 blocks, 320 and 337 with 448, 319 and 356 with 512, 319 and 356 with 768
-    const long most = (long)n_layers * p.B * ((max_moves + mp.per_piece - 1) / mp.per_piece) * mp.per_move;
-    const int blocks = (int)(most < 448 ? (most > 1 ? most : 1) : 448);
+    const int blocks = move_blocks(mp, n_layers, p.B, most);
     uint16_t* kc = static_cast<uint16_t*>(k_cache);
     uint16_t* vc = static_cast<uint16_t*>(v_cache);
 #define MD_MOVE2(STREAM_, NV_)                                                                                 \
-    MD_LAUNCH("decode_move", st, (decode_move_kernel<STREAM_, NV_>), blocks, 1024, 0, p, lay, mp, n_layers, w.holes, w.movers, w.n_move,  \
-        w.claims, kc, vc, layer_stride)
+    MD_LAUNCH("decode_move", st, (decode_move_kernel<STREAM_, NV_>), blocks, 1024, 0, p, lay, mp, FastDiv::make(mp.pair), n_layers, w.holes, \
+        w.movers, w.n_move, w.claims, kc, vc, layer_stride)
 #define MD_MOVE(NV_) do { if (dense || p.d >= 64) MD_MOVE2(true, NV_); else MD_MOVE2(false, NV_); } while (0)
     if (mp.per_piece > 1) MD_MOVE(0);
     else if (mp.vectors == 1) MD_MOVE(1);
@@ -1132,7 +1110,7 @@ int decode_evict_impl(
         MD_LAUNCH("decode_select", st, (decode_select_kernel), B, 1024, lds,
             p, w.logits, decay, budget, acc, ids, protect, len, w.keep, w.holes, w.movers, w.n_move, w.claims, evicted_ids, evicted_count);
     }
-    launch_moves(p, lay, w, st, dense, 1, 0l, Lcap > budget ? (Lcap - budget < budget ? Lcap - budget : budget) : 0, k_cache, v_cache);
+    launch_moves(p, lay, w, st, dense, 1, 0l, most_moves(Lcap, budget), k_cache, v_cache);
     return check_launch("decode_evict");
 }
 
@@ -1173,7 +1151,7 @@ int decode_keep_impl(
     hipStream_t st = static_cast<hipStream_t>(stream);
     MD_LAUNCH("decode_keep_plan", st, (decode_keep_plan_kernel), B, 1024, 0,
         p, keep, acc, ids, protect, len, w.holes, w.movers, w.n_move, w.claims, evicted_ids, evicted_count);
-    launch_moves(p, lay, w, st, dense, n_layers, layer_stride, Lcap / 2, k_cache, v_cache);
+    launch_moves(p, lay, w, st, dense, n_layers, layer_stride, most_moves(Lcap, 0), k_cache, v_cache);
     return check_launch("decode_keep");
 }
 

@@ -1,0 +1,59 @@
+// How the row moves of a cache cut are shaped into pieces and how the blocks of the move launch come by them: the
+// arithmetic of the host and of the kernel.  Without any HIP header, so that a CPU test can compile it and claim its way through.
+#pragma once
+#include <stdint.h>
+
+#ifndef MD_PLAN_FN
+#ifdef __HIPCC__
+#define MD_PLAN_FN __host__ __device__ __forceinline__
+#else
+#define MD_PLAN_FN inline
+#endif
+#endif
+
+namespace md {
+namespace {
+
+// Counters from which blocks claim their pieces, 128 bytes apart (one counter for all takes 12 ns a claim: 683 us instead of 320
+// for the moves of 64 caches of 4096 entries cut to 1024).
+constexpr int kClaims = 16, kClaimStride = 32;
+// Just under two blocks per CU.  64 caches of 4096 entries cut to 1024, and 32 layers x 16 caches of 640 cut to 128: 348 and
+// 342 us with 320 blocks, 320 and 337 with 448, 319 and 356 with 512, 319 and 356 with 768
+constexpr int kMoveBlocks = 448;
+
+struct MovePieces {
+    int per_piece, per_move;                         // moves per piece, pieces per move: one of them is 1
+    int vectors, threads;                            // of a thread; of a block that have any
+    int pair;                                        // vectors of a K row and a V row together
+};
+// Pairs of 1025 to 2048 vectors as one piece of two vectors per thread, not as two with a third of the threads idle: 14 caches of
+// 882 entries cut to 208, 40 heads of 128, 26.6 us in two, 22.5 in one.
+inline MovePieces move_pieces(int H, int d) {
+    MovePieces mp;
+    mp.pair = 2 * H * (d / 8);
+    mp.vectors = mp.pair <= 1024 ? 1 : 2;
+    mp.per_piece = mp.pair < 1024 ? 1024 / mp.pair : 1;
+    mp.per_move = (mp.pair + 1024 * mp.vectors - 1) / (1024 * mp.vectors);
+    mp.threads = (mp.per_piece * mp.pair + mp.per_move * mp.vectors - 1) / (mp.per_move * mp.vectors);
+    return mp;
+}
+MD_PLAN_FN int pieces_of(int moves, const MovePieces& mp) { return (moves + mp.per_piece - 1) / mp.per_piece * mp.per_move; }
+
+// Rows of one sample that can move when a cache of Lcap slots is cut to `budget` entries or more (protected entries stay beyond
+// the budget): a hole below the new length for each of them, and the new length is at least the budget.
+inline int most_moves(int Lcap, int budget) {
+    return Lcap <= budget ? 0 : (Lcap - budget < Lcap / 2 ? Lcap - budget : Lcap / 2);
+}
+// Blocks of the move launch: no more than pieces there can be.
+inline int move_blocks(const MovePieces& mp, int n_layers, int B, int moves) {
+    const long most = (long)n_layers * B * pieces_of(moves, mp);
+    return (int)(most < kMoveBlocks ? (most > 1 ? most : 1) : kMoveBlocks);
+}
+
+// A block's first piece is the one of its number.  Block i draws from counter i % claim_counters(blocks) -- a counter without
+// blocks would hand out its share to nobody -- and the n-th claim from counter c is piece claimed_piece(blocks, c, n).
+MD_PLAN_FN int claim_counters(int blocks) { return blocks < kClaims ? blocks : kClaims; }
+MD_PLAN_FN uint32_t claimed_piece(int blocks, int c, uint32_t n) { return (uint32_t)blocks + n * (uint32_t)claim_counters(blocks) + (uint32_t)c; }
+
+}  // namespace
+}  // namespace md

@@ -1,0 +1,59 @@
+// CPU check of the move launch's claims (csrc/decode_plan.hpp): whatever entries a cache cut keeps, no more rows move than the
+// host reckons with, and blocks that claim in any order take every piece exactly once, also where they are few.
+#include <stdio.h>
+#include <initializer_list>
+#include <random>
+#include <vector>
+
+#include "../../paper_2411_10803_amd/csrc/decode_plan.hpp"
+
+using namespace md;
+
+// Lets `blocks` blocks take `items` pieces in a random order; false: a piece was left out or taken twice.
+static bool drains(int blocks, long items, std::mt19937& rng) {
+    std::vector<uint32_t> claims(kClaims, 0u);
+    std::vector<char> taken(items, 0);
+    std::vector<long> at(blocks);
+    std::vector<int> active;
+    for (int i = 0; i < blocks; ++i)
+        if ((at[i] = i) < items) active.push_back(i);
+    long done = 0;
+    while (!active.empty()) {
+        const size_t a = rng() % active.size();
+        const int i = active[a], c = i % claim_counters(blocks);
+        if (taken[at[i]]++) return false;
+        ++done;
+        at[i] = (long)claimed_piece(blocks, c, claims[c]++);
+        if (at[i] >= items) { active[a] = active.back(); active.pop_back(); }
+    }
+    return done == items;
+}
+
+int main() {
+    std::mt19937 rng(1);
+    long cuts = 0, bad = 0;
+    for (int H : {1, 3, 4, 8, 32, 40, 65, 128, 1024})
+        for (int d : {8, 32, 64, 128, 256, 512})
+            for (int B : {1, 2, 15, 64})
+                for (int Lcap : {1, 2, 9, 200, 1000, 4352, 9000})
+                    for (int budget : {0, 1, 5, 16, 499, 1024, 4351, 20000})
+                        for (int share = 0; share <= 4; ++share) {
+                            const int n = Lcap - (share == 4), np = n * share / 4;       // entries, protected ones
+                            const MovePieces mp = move_pieces(H, d);
+                            const int extra = budget > np ? budget - np : 0, new_len = np + extra < n ? np + extra : n;
+                            const int moves = n <= budget ? 0 : (new_len < n - new_len ? new_len : n - new_len);
+                            const long items = (long)B * pieces_of(moves, mp);
+                            ++cuts;
+                            const char* why = nullptr;
+                            if (mp.per_piece != 1 && mp.per_move != 1) why = "piece";
+                            else if (mp.per_piece * mp.pair > mp.per_move * mp.vectors * mp.threads || mp.threads > 1024) why = "threads";
+                            else if (moves > most_moves(Lcap, budget)) why = "more moves than reckoned with";
+                            else if (items < 200000 && !drains(move_blocks(mp, 1, B, most_moves(Lcap, budget)), items, rng)) why = "pieces";
+                            if (why && ++bad <= 10) printf("H=%d d=%d B=%d Lcap=%d budget=%d protected=%d: %s\n", H, d, B, Lcap, budget, np, why);
+                        }
+    for (int blocks = 1; blocks <= 40; ++blocks)
+        for (long items : {0l, 1l, 15l, 16l, 17l, 333l, 1000l})
+            if (!drains(blocks, items, rng) && ++bad <= 10) printf("%ld pieces, %d blocks\n", items, blocks);
+    printf("%ld cuts, %ld wrong\n", cuts, bad);
+    return bad != 0;
+}
