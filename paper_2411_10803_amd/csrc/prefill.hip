@@ -950,18 +950,6 @@ __device__ __forceinline__ int find_sample(const SampleRows* __restrict__ rows, 
     return tiles;
 }
 
-// Between two MFMAs of a key tile's chain: the multiply-adds, exponentials and sums of 16 / KS probabilities.
-template <int KS>
-__device__ __forceinline__ void interleave_probs() {
-#pragma unroll
-    for (int q = 0; q < KS; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 16 / KS, 0);
-        __builtin_amdgcn_sched_group_barrier(0x400, 16 / KS, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 16 / KS, 0);
-    }
-}
-
 // MULTI: samples may have several text groups.
 template <int NBW, int KT, int KS, bool MULTI>
 __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
@@ -1132,9 +1120,7 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
         f32x16 accA, accB;
         frags(slot, 0, kfA);
         if constexpr (KT > 1) frags(slot, 1, kfB);
-        __builtin_amdgcn_sched_barrier(0);            // all fragments requested before the first chain waits for one
         accA = score_tile<KS>(kfA, qf);
-        if constexpr (KT > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int kt = 1; kt < KT; ++kt) {
             // the MFMA chain of tile kt together with the exp2 work of tile kt-1
@@ -1142,8 +1128,6 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
                 accB = score_tile<KS>(kfB, qf);
                 if (kt + 1 < KT) frags(slot, kt + 1, kfA);
                 add_probs(a_acc[kt - 1], accA, c_cur);
-                interleave_probs<KS>();
-                __builtin_amdgcn_sched_barrier(0);
             } else {
                 accA = score_tile<KS>(kfA, qf);
                 if (kt + 1 < KT) frags(slot, kt + 1, kfB);
