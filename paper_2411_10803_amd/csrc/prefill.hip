@@ -782,6 +782,8 @@ __global__ __launch_bounds__(256, 2) void prefill_rowstats_wide_kernel(
         }
         if (!prev.all) hide(acc, prev, NB - 1);
         online_update_any(acc, scale_log2e, m[NB - 1], z[NB - 1]);
+        // a wave that the mask left without tiles has waited for none of those it requested ahead, and its statistics go to one's place
+        MD_VM_WAIT(0);
         // the fragment-major copy of the text queries for the second sweep, shared out over the waves
         if (ch == 0) {
 #pragma unroll

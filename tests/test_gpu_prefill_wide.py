@@ -18,6 +18,22 @@ def normalisers(torch, q, k, Mv, valid, txt_len, scale):
     return lse
 
 
+def compare(torch, q, k, v, hidden, Mv, valid, txt, scale):
+    import paper_2411_10803_amd as md
+    N = q.shape[1]
+    txt_len = torch.tensor(txt, dtype=torch.int32, device="cuda") if txt else None
+    lse = normalisers(torch, q, k, Mv, valid, txt_len, scale)
+    got = []
+    for given in (None, lse):
+        out = md.mustdrop_prefill_filter(q, k, v, hidden, valid, txt_len, None, Mv, scale, md.FILTER_BUDGET, 1, 1.0 / Mv,
+                                         2.0 / (Mv + N), 1, row_lse=given)
+        got.append((out["score_global"].double(), out["score_indiv"].double()))
+    # a normaliser is a sum of at most 270 tiles per lane and a few merges of fp32 terms: 300 * 2^-24
+    for own, handed in zip(*got):
+        assert bool(torch.isfinite(own).all())
+        assert bool(((own - handed).abs() <= 2e-5 * handed.abs()).all()), float((own - handed).abs().max())
+
+
 @pytest.mark.parametrize("B,Mv,N,H,d,mask,txt", [
     (1, 1, 129, 1, 128, None, None),                     # text keys only, but for one
     (2, 31, 160, 2, 128, "holes", [160, 129]),           # groups of three and two; mask rows off a word
@@ -32,7 +48,6 @@ def normalisers(torch, q, k, Mv, valid, txt_len, scale):
 ])
 def test_row_statistics(B, Mv, N, H, d, mask, txt):
     import torch
-    import paper_2411_10803_amd as md
     g = torch.Generator(device="cuda").manual_seed(B * Mv + N)
     normal = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)  # noqa: E731
     q, k = normal(B, N, H, d), normal(B, Mv + N, H, d)
@@ -43,14 +58,16 @@ def test_row_statistics(B, Mv, N, H, d, mask, txt):
         slot = torch.arange(Mv, device="cuda")[None] / Mv
         valid = {"prefix": slot <= share, "none": slot < -share,
                  "holes": (torch.rand((B, Mv), generator=g, device="cuda") < 0.9) & (slot <= 0.5 + 0.5 * share)}[mask].to(torch.uint8).contiguous()
-    txt_len = torch.tensor(txt, dtype=torch.int32, device="cuda") if txt else None
-    lse = normalisers(torch, q, k, Mv, valid, txt_len, scale)
-    got = []
-    for given in (None, lse):
-        out = md.mustdrop_prefill_filter(q, k, v, hidden, valid, txt_len, None, Mv, scale, md.FILTER_BUDGET, 1, 1.0 / Mv,
-                                         2.0 / (Mv + N), 1, row_lse=given)
-        got.append((out["score_global"].double(), out["score_indiv"].double()))
-    # a normaliser is a sum of at most 270 tiles per lane and a few merges of fp32 terms: 300 * 2^-24
-    for own, handed in zip(*got):
-        assert bool(torch.isfinite(own).all())
-        assert bool(((own - handed).abs() <= 2e-5 * handed.abs()).all()), float((own - handed).abs().max())
+    compare(torch, q, k, v, hidden, Mv, valid, txt, scale)
+
+
+@pytest.mark.parametrize("N,d,counts", [(160, 128, [0, 1, 40]), (160, 64, [0, 1, 40]), (300, 128, [33, 0, 300])])
+def test_waves_without_tiles(N, d, counts):
+    """Seven or eight key chunks, of which the valid slots leave one to three: waves and whole blocks go without a tile."""
+    import torch
+    B, Mv, H = len(counts), 4096, 8
+    g = torch.Generator(device="cuda").manual_seed(N + d)
+    normal = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)  # noqa: E731
+    q, k, hidden = normal(B, N, H, d), normal(B, Mv + N, H, d), normal(B, Mv + N, 8)
+    valid = (torch.arange(Mv, device="cuda")[None] < torch.tensor(counts, device="cuda")[:, None]).to(torch.uint8).contiguous()
+    compare(torch, q, k, k, hidden, Mv, valid, None, d ** -0.5)
