@@ -763,18 +763,18 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
         mine = b0 + lane < p.B ? pieces_of(n_move[min(b0 + lane, p.B - 1)], mp) : 0;
         incl = wave_incl_scan_i(mine) + before;
     };
-    uint32_t total = 0;                              // of a layer (a piece is some 16 KiB: they fit the index)
+    uint32_t total = 0;                              // of a layer
     for (int b = (p.B - 1) & ~63; b >= 0; b -= kWave) {              // the first 64 samples stay at hand
         group(b, 0);
         total += (uint32_t)__builtin_amdgcn_readlane(incl, kWave - 1);
     }
     if (total == 0) return;
-    const uint32_t items = total * (uint32_t)n_layers;
+    const uint64_t items = piece_count(total, n_layers);
     int buf = 0;
-    for (uint32_t item = blockIdx.x; item < items;) {
+    for (uint64_t item = blockIdx.x; item < items;) {
         uint32_t claimed = 0;                        // the claim of the next piece is under way with this one's rows
         if (tid == 0) claimed = (uint32_t)atomicAdd(my_claims, 1);
-        const int layer = n_layers == 1 ? 0 : (int)(item / total), r = (int)(item - (uint32_t)layer * total);
+        const auto [layer, r] = piece_at(item, total, n_layers);
         if (r < __builtin_amdgcn_readlane(incl - mine, 0)) group(0, 0);
         while (r >= __builtin_amdgcn_readlane(incl, kWave - 1)) group(b0 + kWave, __builtin_amdgcn_readlane(incl, kWave - 1));
         const int l = __builtin_ctzll(__ballot(incl > r));

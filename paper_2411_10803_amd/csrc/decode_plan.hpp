@@ -50,10 +50,26 @@ inline int move_blocks(const MovePieces& mp, int n_layers, int B, int moves) {
     return (int)(most < kMoveBlocks ? (most > 1 ? most : 1) : kMoveBlocks);
 }
 
+// The pieces of a call go layer by layer, `total` in each.  A layer's fit 31 bits (a call has at most 2^28 slots, and a piece that is
+// but part of a move stands for 16 KiB and more of each tensor); those of all layers need not: 65536 rows moved in each of
+// 65535 layers come close to 2^32, and a sum that wrapped would leave rows behind.
+MD_PLAN_FN uint64_t piece_count(uint32_t total, int n_layers) { return (uint64_t)total * (uint32_t)n_layers; }
+struct PieceAt { int layer, r; };                    // r: piece of the layer
+MD_PLAN_FN PieceAt piece_at(uint64_t piece, uint32_t total, int n_layers) {
+    PieceAt at;
+    if (n_layers == 1) at.layer = 0;
+    else if ((piece >> 32) == 0) at.layer = (int)((uint32_t)piece / total);       // (a quarter of the instructions)
+    else at.layer = (int)(piece / total);
+    at.r = (int)(piece - (uint64_t)total * (uint32_t)at.layer);
+    return at;
+}
+
 // A block's first piece is the one of its number.  Block i draws from counter i % claim_counters(blocks) -- a counter without
 // blocks would hand out its share to nobody -- and the n-th claim from counter c is piece claimed_piece(blocks, c, n).
 MD_PLAN_FN int claim_counters(int blocks) { return blocks < kClaims ? blocks : kClaims; }
-MD_PLAN_FN uint32_t claimed_piece(int blocks, int c, uint32_t n) { return (uint32_t)blocks + n * (uint32_t)claim_counters(blocks) + (uint32_t)c; }
+MD_PLAN_FN uint64_t claimed_piece(int blocks, int c, uint32_t n) {
+    return (uint64_t)n * (uint32_t)claim_counters(blocks) + (uint32_t)(blocks + c);
+}
 
 }  // namespace
 }  // namespace md

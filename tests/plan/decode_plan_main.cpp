@@ -1,5 +1,5 @@
 // CPU check of the move launch's claims (csrc/decode_plan.hpp): whatever entries a cache cut keeps, no more rows move than the
-// host reckons with, and blocks that claim in any order take every piece exactly once, also where they are few.
+// host reckons with, and blocks that claim in any order take every piece exactly once, also where blocks are few or layers many.
 #include <stdio.h>
 #include <initializer_list>
 #include <random>
@@ -54,6 +54,25 @@ int main() {
     for (int blocks = 1; blocks <= 40; ++blocks)
         for (long items : {0l, 1l, 15l, 16l, 17l, 333l, 1000l})
             if (!drains(blocks, items, rng) && ++bad <= 10) printf("%ld pieces, %d blocks\n", items, blocks);
+    // as many layers and samples as a call takes: pieces beyond 2^32 keep their layer, and a claim stays behind the last one
+    for (uint32_t total : {1u, 3u, 65535u, 65537u, 98765u, 1u << 27})
+        for (int layers : {1, 2, 32, 65535}) {
+            const uint64_t all = (uint64_t)total * (uint64_t)layers;
+            bool ok = piece_count(total, layers) == all;
+            for (int i = 0; i < 2000; ++i) {
+                const uint64_t item = i == 0 ? all - 1 : (((uint64_t)rng() << 32) | rng()) % all;
+                const PieceAt at = piece_at(item, total, layers);
+                ok &= at.layer >= 0 && at.layer < layers && at.r >= 0 && (uint32_t)at.r < total && (uint64_t)at.layer * total + (uint64_t)at.r == item;
+                // the claim that hands out this piece, and the last ones from its counter
+                if (item < kMoveBlocks || all > (1ull << 36)) continue;
+                const uint64_t n = (item - kMoveBlocks) / kClaims;
+                const int c = (int)((item - kMoveBlocks) % kClaims);
+                ok &= claimed_piece(kMoveBlocks, c, (uint32_t)n) == item;
+                const uint64_t behind = (all - kMoveBlocks) / kClaims + kMoveBlocks;
+                ok &= behind >> 32 != 0 || claimed_piece(kMoveBlocks, c, (uint32_t)behind) >= all;
+            }
+            if (!ok && ++bad <= 10) printf("%u pieces in each of %d layers\n", total, layers);
+        }
     printf("%ld cuts, %ld wrong\n", cuts, bad);
     return bad != 0;
 }
