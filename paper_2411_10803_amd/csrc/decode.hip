@@ -746,28 +746,55 @@ __global__ __launch_bounds__(1024) void decode_keep_plan_kernel(
 // STREAM: both sides bypass the caches, also where K is small enough to stay there until the next step reads it: kept, the moved
 // rows push out as much (14 caches of 882 entries cut to 208, 40 heads: next scores and moves 24.2 + 22.5 us, 26.0 + 22.1 with
 // K kept).  Not where a head slice is shorter than a cache line.
-// NV: vectors per thread; 0: one, and a piece holds several moves.
-template <bool STREAM, int NV>
+// NV: vectors per thread; 0: one, and a piece holds several moves.  MANY: more samples than lanes.
+template <bool STREAM, int NV, bool MANY>
 __global__ __launch_bounds__(1024) void decode_move_kernel(
     DecodeDims p, KvLayout lay, MovePieces mp, FastDiv by_pair, int n_layers, const int32_t* __restrict__ holes, const int32_t* __restrict__ movers,
     const int32_t* __restrict__ n_move, int32_t* __restrict__ claims, uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache,
     long layer_stride)
 {
     __shared__ uint32_t s_next[2];
+    __shared__ int s_span[MANY ? kWave : 1], s_pieces[MANY ? kWave * kWave : 1];
     const int tid = threadIdx.x, lane = lane_id(), q = blockIdx.x % claim_counters(gridDim.x);
     int32_t* my_claims = claims + q * kClaimStride;
     // pieces of the 64 samples b0 .. b0 + 63, one per lane, and the sum of pieces up to and with each
     int b0 = 0, mine = 0, incl = 0;
-    auto group = [&](int at, int before) {
+    auto pieces_at = [&](int b) { return b < p.B ? pieces_of(n_move[min(b, p.B - 1)], mp) : 0; };
+    auto group = [&](int at, int pieces, int before) {
         b0 = at;
-        mine = b0 + lane < p.B ? pieces_of(n_move[min(b0 + lane, p.B - 1)], mp) : 0;
-        incl = wave_incl_scan_i(mine) + before;
+        mine = pieces;
+        incl = wave_incl_scan_i(pieces) + before;
     };
-    uint32_t total = 0;                              // of a layer
-    for (int b = (p.B - 1) & ~63; b >= 0; b -= kWave) {              // the first 64 samples stay at hand
-        group(b, 0);
-        total += (uint32_t)__builtin_amdgcn_readlane(incl, kWave - 1);
+    // MANY: 64 spans of samples, one per lane, with the sum of pieces up to and with each.  The waves share the spans, so that
+    // all counts are requested at once; a piece is found by its span and a look at 64 samples of it, in LDS up to 4096 samples.
+    // In rounds over the samples by every wave the kernel took, for 4096 samples of 64 entries, one of 50 with a row to move,
+    // 41 us (a block that looks at one sample only 29), in spans 5; half of the entries cut 86 (75) and 34.
+    const int span = (p.B + kWave * kWave - 1) / (kWave * kWave) * kWave;
+    int in_span = 0, upto_span = 0;
+    if constexpr (MANY) {
+        constexpr int SP = kWave / 16;               // spans of a wave
+        const int first = wave_id() * SP;
+        int sum[SP];
+#pragma unroll
+        for (int i = 0; i < SP; ++i) sum[i] = 0;
+        for (int o = lane; o < span; o += kWave)
+#pragma unroll
+            for (int i = 0; i < SP; ++i) sum[i] += pieces_at((first + i) * span + o);
+#pragma unroll
+        for (int i = 0; i < SP; ++i) {
+            if (span == kWave) s_pieces[(first + i) * kWave + lane] = sum[i];
+            const int all = wave_sum_i(sum[i]);
+            if (lane == 0) s_span[first + i] = all;
+        }
+        block_sync_lds();
+        in_span = s_span[lane];
+        upto_span = wave_incl_scan_i(in_span);
+        b0 = -1;                                     // no samples at hand yet
+    } else {
+        group(0, pieces_at(lane), 0);
+        upto_span = incl;
     }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane(upto_span, kWave - 1);      // of a layer
     if (total == 0) return;
     const uint64_t items = piece_count(total, n_layers);
     int buf = 0;
@@ -775,8 +802,12 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
         uint32_t claimed = 0;                        // the claim of the next piece is under way with this one's rows
         if (tid == 0) claimed = (uint32_t)atomicAdd(my_claims, 1);
         const auto [layer, r] = piece_at(item, total, n_layers);
-        if (r < __builtin_amdgcn_readlane(incl - mine, 0)) group(0, 0);
-        while (r >= __builtin_amdgcn_readlane(incl, kWave - 1)) group(b0 + kWave, __builtin_amdgcn_readlane(incl, kWave - 1));
+        if (MANY && (r < __builtin_amdgcn_readlane(incl - mine, 0) || r >= __builtin_amdgcn_readlane(incl, kWave - 1))) {
+            const int s = __builtin_ctzll(__ballot(upto_span > r));
+            auto look = [&](int at, int before) { group(at, span == kWave ? s_pieces[at + lane] : pieces_at(at + lane), before); };
+            if (b0 < s * span || r < __builtin_amdgcn_readlane(incl - mine, 0)) look(s * span, __builtin_amdgcn_readlane(upto_span - in_span, s));
+            while (r >= __builtin_amdgcn_readlane(incl, kWave - 1)) look(b0 + kWave, __builtin_amdgcn_readlane(incl, kWave - 1));
+        }
         const int l = __builtin_ctzll(__ballot(incl > r));
         const int b = b0 + l, at = r - __builtin_amdgcn_readlane(incl - mine, l);        // the sample's piece
         // this thread's move and its vectors of the pair; one move per piece: its rows come by scalar loads, which do not wait
@@ -909,13 +940,15 @@ void launch_moves(const DecodeDims& p, const KvLayout& lay, const DecodeWorkspac
     const int blocks = move_blocks(mp, n_layers, p.B, most);
     uint16_t* kc = static_cast<uint16_t*>(k_cache);
     uint16_t* vc = static_cast<uint16_t*>(v_cache);
-#define MD_MOVE2(STREAM_, NV_)                                                                                 \
-    MD_LAUNCH("decode_move", st, (decode_move_kernel<STREAM_, NV_>), blocks, 1024, 0, p, lay, mp, FastDiv::make(mp.pair), n_layers, w.holes, \
+#define MD_MOVE3(STREAM_, NV_, MANY_)                                                                          \
+    MD_LAUNCH("decode_move", st, (decode_move_kernel<STREAM_, NV_, MANY_>), blocks, 1024, 0, p, lay, mp, FastDiv::make(mp.pair), n_layers, w.holes, \
         w.movers, w.n_move, w.claims, kc, vc, layer_stride)
+#define MD_MOVE2(STREAM_, NV_) do { if (p.B > kWave) MD_MOVE3(STREAM_, NV_, true); else MD_MOVE3(STREAM_, NV_, false); } while (0)
 #define MD_MOVE(NV_) do { if (dense || p.d >= 64) MD_MOVE2(true, NV_); else MD_MOVE2(false, NV_); } while (0)
     if (mp.per_piece > 1) MD_MOVE(0);
     else if (mp.vectors == 1) MD_MOVE(1);
     else MD_MOVE(2);
+#undef MD_MOVE3
 #undef MD_MOVE2
 #undef MD_MOVE
 }

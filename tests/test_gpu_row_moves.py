@@ -1,5 +1,5 @@
 """Row moves of the cache cut, bit for bit against hole filling written out: pieces that hold many moves, one, or a part of
-one, more pieces than blocks, more than 64 samples, several layers, samples that move nothing, both cache layouts; and of the
+one, more pieces than blocks, more than 64 and more than 4096 samples, several layers, samples that move nothing, both cache layouts; and of the
 selection where more entries are protected than the budget has room for."""
 import numpy as np
 import pytest
@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("layers,B,Lcap,H,d", [(1, 70, 40, 4, 64), (3, 2, 300, 40, 128), (2, 1, 64, 8, 512), (2, 2, 50, 128, 128),
                                                (1, 1, 33, 3, 8), (2, 130, 24, 1, 16), (1, 3, 2000, 32, 128), (3, 66, 90, 4, 128),
-                                               (2, 2, 700, 65, 64)])
+                                               (2, 2, 700, 65, 64), (2, 1000, 24, 2, 8), (1, 4097, 12, 24, 64), (3, 8300, 10, 1, 8)])
 @pytest.mark.parametrize("head_major", [False, True])
 def test_hole_filling(layers, B, Lcap, H, d, head_major):
     import torch
