@@ -85,10 +85,20 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
             // d = 128; 2 x 8661 keys, 64 heads, 95 text rows 49.8 -> 38.6)
             if (s.nbw == 4 && d == 64) { alone = waves == 8 ? 10.0 : 11.5; full = waves == 8 ? 10.5 : 21.0; }
             if (s.nbw == 1 && d == 128 && waves == 4 && blocks <= kNumCU && !s.rs_stream) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
-            if (s.ng > 1) { alone = d == 64 ? 9.0 : 11.0; full = d == 64 ? 13.0 : 18.0; }
-            else if (s.nbw == 4 && d == 128 && waves == 4) full = 30.0;
+            if (s.nbw == 4 && d == 128 && waves == 4) full = 30.0;
             const double per_key = alone + (full - alone) * fill;
-            const double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? 5.0 : 0.0);
+            double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? 5.0 : 0.0);
+            if (s.ng > 1) {
+                // Several text groups: the last round by itself, at the full rate once a CU has two blocks of it.  Priced by its
+                // share of the places, it looked cheaper than it is: 4 x 5284 keys of 64, 32 heads, 374 text rows in 384 blocks
+                // 80 us, in 768 with the merge 71; 6 x 6000, 256 rows 97 and 86; 3 x 1592 keys of 128, 40 heads, 171 rows 27.6
+                // and 22.8.  At 84 random shapes the sweep and its merge take 2 % less, none more than 3 % more.
+                alone = d == 64 ? 8.0 : 11.0;
+                full = d == 64 ? 13.0 : 18.0;
+                const double keys = 1e-3 * (Mv + N) / nch;
+                const long last = blocks % places;
+                t = (double)(blocks / places) * (4.0 + full * keys) + (last > 0 ? 4.0 + (last > kNumCU ? full : alone) * keys : 0.0) + (nch > 1 ? 4.0 : 0.0);
+            }
             if (best == 0 || t < 0.97 * best) { best = t; s.rs_waves = waves; s.nch = nch; }
         }
     s.rs_wide = s.ng > 1 || (s.nbw == 4 && d == 128 && s.rs_waves == 4);
