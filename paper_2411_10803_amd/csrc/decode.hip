@@ -800,7 +800,11 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
     int buf = 0;
     for (uint64_t item = blockIdx.x; item < items;) {
         uint32_t claimed = 0;                        // the claim of the next piece is under way with this one's rows
-        if (tid == 0) claimed = (uint32_t)atomicAdd(my_claims, 1);
+        if (tid == 0) {
+            int at = 0;
+            asm volatile("" : "+v"(at));             // an address per lane: for a uniform one the compiler waits for the result on the spot
+            claimed = (uint32_t)atomicAdd(my_claims + at, 1);
+        }
         const auto [layer, r] = piece_at(item, total, n_layers);
         if (MANY && (r < __builtin_amdgcn_readlane(incl - mine, 0) || r >= __builtin_amdgcn_readlane(incl, kWave - 1))) {
             const int s = __builtin_ctzll(__ballot(upto_span > r));
@@ -819,6 +823,7 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
             const int t = mp.per_move == 1 ? at : at / mp.per_move;
             const long li = (long)b * p.Lcap + t;
             src = movers[li]; dst = holes[li];
+            asm volatile("" : "+s"(src), "+s"(dst));  // both requested before either is waited for
 #pragma unroll
             for (int i = 0; i < N; ++i) x[i] = ((at - t * mp.per_move) * N + i) * mp.threads + tid;
         } else {
@@ -828,9 +833,9 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
             x[0] = tid - u * mp.pair;
             on = on && t < n_move[b];
         }
+        u32x4 val[N], *to[N];
         if (on) {
             const int rv = mp.pair >> 1, sh = __builtin_ctz(p.d) - 3;
-            u32x4 val[N], *to[N];
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 const int xi = min(x[i], mp.pair - 1);          // (behind the pair: its last vector, dropped)
@@ -842,14 +847,16 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
                 to[i] = reinterpret_cast<u32x4*>(base + (long)dst * lay.token);
                 val[i] = STREAM ? __builtin_nontemporal_load(from) : *from;
             }
+        }
+        buf ^= 1;
+        if (tid == 0) s_next[buf] = claimed;         // (requested before the rows; before the stores, which nothing here waits for)
+        if (on) {
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 if (N > 1 && x[i] >= mp.pair) continue;
                 if (STREAM) __builtin_nontemporal_store(val[i], to[i]); else *to[i] = val[i];
             }
         }
-        buf ^= 1;
-        if (tid == 0) s_next[buf] = claimed;
         block_sync_lds();                            // (the stores need not have arrived)
         item = claimed_piece(gridDim.x, q, (uint32_t)__builtin_amdgcn_readfirstlane((int)s_next[buf]));
     }
