@@ -8,7 +8,8 @@
 //   prefill_rowstats_kernel  per (sample, head, key chunk): S = K Q^T on the MFMA units, online
 //                            (max, sum-exp) per text row -> row statistics (prefill_cstat_kernel
 //                            merges the chunks); prefill_rowstats_wide_kernel where there are several
-//                            text groups; with row_lse only prefill_qpack_kernel runs
+//                            text groups, and for one of three or four text blocks at d = 128 where
+//                            blocks of four waves are planned; with row_lse only prefill_qpack_kernel runs
 //   prefill_colscore_kernel  persistent blocks over units of (64 or 128 vision keys, one head): recompute
 //                            S, p = exp(s - m)/Z, accumulate the head mean a[i][j] of such a key tile
 //                            in registers; a block's share of a tile is written as one piece
@@ -173,7 +174,8 @@ __device__ __forceinline__ uint32_t key_valid_mask(const uint8_t* __restrict__ v
 
 // The mask row of a sample for one wave, requested in one go: word w of a lane covers the 32 keys of tile 64 * w + lane, so
 // that the last valid key and the tiles' masks come out of the same loads (one round trip; a loop over the row and a
-// second look at the wave's own tiles were four to five: 8 x 2880 keys, 128 text rows, 3/4 of the slots valid 50.4 -> 49.4 us).
+// second look at the wave's own tiles were four to five: 3 x 4608 keys, 100 to 300 text rows, 3/4 of the slots valid 40.2 -> 38.0
+// us, 3 x 9000 keys, 200 text rows, 9/10 valid 69.4 -> 64.1).
 struct MaskRow {
     static constexpr int W = 5;                       // rows of up to 64 * 32 * W slots
     u32x4 raw[W][2];
@@ -601,10 +603,11 @@ __device__ __forceinline__ void interleave_chain() {
 // waves, and a wave holds the fragments of up to four text blocks in registers and has key tiles, LDS slots and a place
 // in the sum of its own.  A key fragment is read from LDS once for all of the text blocks, not once per text block, and
 // the steady loop has no barrier: a wave waits for its own loads only.  Two such blocks fit a CU, so that one's prologue
-// runs beside the other's arithmetic (one block of eight waves per CU: 5 to 33 % slower at the sizes below).
+// runs beside the other's arithmetic (one block of eight waves per CU: 5 to 35 % slower at the sizes below).
 // Bound by the exponentials and the matrix product of a wave, which the steady loop interleaves, wherever K comes from L2,
-// as it does for all text groups of a sample but one: 6 x 1152 keys, 32 heads, 384 text rows 70 -> 53 us, 20 x 576 with 200
-// rows 79 -> 59, 3 x 9000 with 200 rows 86 -> 71; 4 x 4000 keys of 64, 32 heads, 300 rows 57 -> 50.
+// as it does for all text groups of a sample but one: 6 x 1152 keys, 32 heads, 384 text rows 69 -> 49 us, 20 x 576 with 200
+// rows 77 -> 59, 3 x 9000 with 200 rows 88 -> 77; heads of 64 with the merge, 4 x 4000 keys, 300 rows 63 -> 55, 8 x 2000, 160
+// rows 45 -> 31.
 template <int KS, bool STREAM>
 __global__ __launch_bounds__(256, 2) void prefill_rowstats_wide_kernel(
     const uint16_t* __restrict__ q_txt, const uint16_t* __restrict__ k,

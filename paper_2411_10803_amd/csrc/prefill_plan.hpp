@@ -67,7 +67,7 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start
     // (5), the keys it takes (ns per key, from alone on the chip to every place taken), the merge kernel for several chunks.
     // Measured to within 20 % at 17 shapes; before -> after e.g. 13 x 1039 keys, 32 heads, 10 text rows: 36.6 -> 23.1,
-    // 6 x 1152 keys, 384 text rows: 250 -> 53 (in the wide form), 5 x 774 keys, 16 heads, 60 text rows: 14.5 -> 13.1.
+    // 6 x 1152 keys, 384 text rows: 250 -> 49 (in the wide form), 5 x 774 keys, 16 heads, 60 text rows: 14.5 -> 13.1.
     const int units = (Mv + N + 127) / 128;
     const long n = (long)B * H * s.ng;
     double best = 0;
