@@ -228,9 +228,9 @@ def batches_in_flight(torch, pipe, steps, n):
 # 256 MiB device copy (FETCH_SIZE reads half the bytes moved: factor 2.0; WRITE_SIZE: factor 1.0).
 # The runs and the raw figures are in profiles/hbm_traffic_cfg3_llavanext_b8.txt.
 MEASURED_HBM_TRAFFIC_BYTES = {
-    "prefill_colscore": 190513343, "prefill_rowstats": 173952353, "prefill_compact": 126029922,
-    "encode_scores": 97188303, "encode_emit": 84400745, "prefill_select": 51049781, "decode_logits": 30719164,
-    "decode_select": 34016573, "prefill_colfix": 26081320, "encode_decide": 2366560,
+    "prefill_colscore": 190519522, "prefill_rowstats": 173952287, "prefill_compact": 126020673,
+    "encode_scores": 97230420, "encode_emit": 84396954, "prefill_select": 51041536, "decode_logits": 30719092,
+    "decode_select": 34023244, "prefill_colfix": 26081280, "encode_decide": 2381920,
 }
 
 

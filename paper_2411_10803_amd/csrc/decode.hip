@@ -768,7 +768,7 @@ __global__ __launch_bounds__(1024) void decode_move_kernel(
     // MANY: 64 spans of samples, one per lane, with the sum of pieces up to and with each.  The waves share the spans, so that
     // all counts are requested at once; a piece is found by its span and a look at 64 samples of it, in LDS up to 4096 samples.
     // In rounds over the samples by every wave the kernel took, for 4096 samples of 64 entries, one of 50 with a row to move,
-    // 41 us (a block that looks at one sample only 29), in spans 5; half of the entries cut 86 (75) and 34.
+    // 41 us (a block that looks at one sample only 29), in spans 5; half of the entries cut 86 (75) and 31.
     const int span = (p.B + kWave * kWave - 1) / (kWave * kWave) * kWave;
     int in_span = 0, upto_span = 0;
     if constexpr (MANY) {

@@ -17,9 +17,9 @@ namespace {
 // Counters from which blocks claim their pieces, 128 bytes apart (one counter for all takes 12 ns a claim: 683 us instead of 320
 // for the moves of 64 caches of 4096 entries cut to 1024).
 constexpr int kClaims = 16, kClaimStride = 32;
-// Just under two blocks per CU.  us with 320 / 448 / 512 / 640 blocks, heads of 128: 64 caches of 4096 entries cut to 1024 291 /
-// 271 / 284 / 285, 32 layers x 16 x 640 to 128 303 / 297 / 308 / 310, 64 x 1000 to a half 94 / 92 / 96 / 97, 14 x 882 of 40 heads to
-// a quarter 19.6 / 18.9 / 18.9 / 19.1, 4 x 2000 to a half 15.0 / 14.5 / 14.2 / 15.1; 300 x 500 of 8 heads to 2/5 68 / 58 / 55 / 57
+// Just under two blocks per CU.  us with 320 / 448 / 512 / 640 blocks, heads of 128: 64 caches of 4096 entries cut to 1024 284 /
+// 273 / 281 / 282, 32 layers x 16 x 640 to 128 296 / 296 / 309 / 309, 64 x 1000 to a half 91.5 / 90.5 / 92.7 / 94.3, 14 x 882 of 40
+// heads to a quarter 19.1 / 19.3 / 19.4 / 19.2, 4 x 2000 to a half 14.8 / 14.3 / 14.5 / 15.2; 300 x 500 of 8 heads to 2/5 61 / 54 / 52 / 54
 constexpr int kMoveBlocks = 448;
 
 struct MovePieces {
