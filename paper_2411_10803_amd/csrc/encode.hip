@@ -8,7 +8,8 @@
 //                        them: q_cls . k_j per head
 //   encode_decide_*      one block per sample: softmax + head mean (or ready-made key scores), radix top-k -> O,
 //                        merge decisions, prefix sum of survivors, small outputs    (tiny)
-//   encode_emit_kernel  one wave per window: row copies / mass-weighted means (re-reads x, writes out_x)
+//   encode_emit_kernel  one wave per window: row copies / mass-weighted means (re-reads x, writes out_x); not launched
+//                        where several blocks per sample make the decisions and write the rows behind them
 #include "md_device.hpp"
 #include "md_host.hpp"
 
@@ -24,6 +25,7 @@ constexpr int kMaxWindow = 16;                   // = the length of EncodeDims::
 #endif
 constexpr int kEncWaves = MD_ENC_WAVES;          // waves (= work items) per block of the wave-per-item kernels
 constexpr int kMaxClsHeads = 256;
+constexpr int kNumCU = 256;                      // MI355X
 
 struct EncodeDims {
     int B, T, Hg, Wg, D, Hc, dc;
@@ -663,6 +665,115 @@ __global__ __launch_bounds__(1024) void encode_decide_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
+// The rows of the survivors, written by the blocks that decide (EmitArgs::blocks of them per sample, each of which has worked
+// out the whole sample's decisions in its LDS; a launch of its own is 4 us and finds nothing of x requested).  An item is a
+// window and a slice of 64 16-byte vectors of its rows.  x does not wait for the decisions: a wave asks for its first item
+// before they are made, so that a third of x on 8 x 2880 tokens, and all of it on a few images, comes in behind their chain
+// of steps, which is what bounds the launch (17 of its 40 thousand cycles on 8 x 2880 tokens are the rows, the decision with its
+// fetch of the numerators the rest).  us per call, a launch for the rows / the deciding blocks: 1 x 576 tokens fp32 15.8 /
+// 13.6, 16 x 576 22.2 / 21.0, 8 x 2880 42.3 / 39.6, 16 x 2880 71.7 / 66.3; 2 x 4608 in 2x2x2 windows 35.1 / 33.0, 8 x 4608 64.3 /
+// 62.2.  Not for windows of more than eight members, whose rows do not fit the registers (3 x 1152 tokens in 3x3 windows
+// 22.4 / 23.8), nor beyond 5120 tokens, where the LDS of the decisions leaves sixteen waves per CU to copy (2 x 9216 46.5 / 47.1).
+struct EmitArgs {
+    const void* x; void* out_x;
+    int blocks, slices, bf16;                        // blocks per sample, slices per row, element type
+    FastDiv by_B, by_slices;
+};
+// a token's fate as the emitting waves read it: its output row (with kRowMerged for the mean of a window), or
+enum : int { kRowMerged = 1 << 30, kRowInvalid = -1, kRowGone = -2 };
+struct EmitItem { int w, c, tok; };                  // window, this lane's vector of the rows, lane m < ws: member m's token
+__device__ __forceinline__ EmitItem emit_item(const EncodeDims& p, const EmitArgs& e, int it, int lane) {
+    EmitItem i;
+    i.w = e.by_slices.div(it);
+    i.c = (it - i.w * e.slices) * kWave + lane;
+    i.tok = lane_member_token(p, i.w, lane);
+    return i;
+}
+template <int WS>
+__device__ __forceinline__ void emit_load(const EncodeDims& p, const EmitItem& i, const char* xb, int rowb, u32x4 (&v)[WS]) {
+    const int off = min(i.c * 16, rowb - 16);        // lanes beyond the row repeat its last vector and drop it
+#pragma unroll
+    for (int m = 0; m < WS; ++m)
+        if (m < p.ws)
+            v[m] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xb + (size_t)max(wave_member(i.tok, m), 0) * rowb + off));
+}
+// What an item's rows become: row_l: lane m's row (s_row), merged: the window is merged, with okmask its valid members.
+struct EmitFate { int row_l; uint64_t merged, okmask; float mass_l; };
+__device__ __forceinline__ EmitFate emit_fate(const EncodeDims& p, const EmitItem& i, const int* s_row, const float* mb) {
+    EmitFate f;
+    f.row_l = lane_id() < p.ws && i.tok >= 0 ? s_row[i.tok] : (int)kRowInvalid;
+    f.merged = __ballot(f.row_l >= 0 && (f.row_l & kRowMerged));
+    f.okmask = __ballot(f.row_l != kRowInvalid);
+    f.mass_l = f.merged != 0 && mb && f.row_l != kRowInvalid ? mb[i.tok] : 1.0f;
+    return f;
+}
+template <int WS>
+__device__ __forceinline__ void emit_copy(const EmitItem& i, const EmitFate& f, char* ob, int rowb, const u32x4 (&v)[WS]) {
+    if (i.c * 16 >= rowb) return;
+    char* o = ob + (size_t)i.c * 16;
+#pragma unroll
+    for (int m = 0; m < WS; ++m) {
+        const int row = wave_member(f.row_l, m);     // (lanes beyond the window: kRowInvalid)
+        if (row >= 0) __builtin_nontemporal_store(v[m], reinterpret_cast<u32x4*>(o + (size_t)row * rowb));
+    }
+}
+// The mass-weighted mean of the valid members, in ascending order, written at the first one.
+template <bool BF, int WS>
+__device__ __forceinline__ void emit_mean(const EmitItem& i, const EmitFate& f, char* ob, int rowb, const u32x4 (&v)[WS]) {
+    constexpr int VEC = Vec<BF>::N;
+    float acc[VEC], msum = 0.f;
+#pragma unroll
+    for (int q = 0; q < VEC; ++q) acc[q] = 0.f;
+#pragma unroll
+    for (int m = 0; m < WS; ++m) {
+        if (!((f.okmask >> m) & 1ull)) continue;
+        const float mm = lane_bcast_f(f.mass_l, m);
+        msum += mm;
+        float xv[VEC];
+        if constexpr (BF) Vec<true>::widen(v[m], xv);
+        else { const f32x4 x = __builtin_bit_cast(f32x4, v[m]); xv[0] = x.x; xv[1] = x.y; xv[2] = x.z; xv[3] = x.w; }
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) acc[q] = fmaf(mm, xv[q], acc[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < VEC; ++q) acc[q] = acc[q] / msum;
+    if (i.c * 16 < rowb)
+        Vec<BF>::store(ob + (size_t)(wave_member(f.row_l, __builtin_ctzll(f.merged)) & ~kRowMerged) * rowb + (size_t)i.c * 16, 0, acc);
+}
+// The block's share of the sample's items; the rows of the next one are on their way while one is written.  AHEAD: `cur` and
+// `v` are the wave's first item, already asked for.
+template <int WS, bool AHEAD>
+__device__ __forceinline__ void emit_rows(const EncodeDims& p, const EmitArgs& e, int b, int g, const int* s_row, const float* mb,
+                                          EmitItem cur, u32x4 (&v)[WS]) {
+    const int lane = lane_id(), rowb = p.D * (e.bf16 ? 2 : 4), items = p.W * e.slices, every = e.blocks * 16;
+    const char* xb = static_cast<const char*>(e.x) + (size_t)b * p.M * rowb;
+    char* ob = static_cast<char*>(e.out_x) + (size_t)b * p.M * rowb;
+    int it = wave_id() * e.blocks + g;
+    if (!AHEAD && it < items) {
+        cur = emit_item(p, e, it, lane);
+        emit_load<WS>(p, cur, xb, rowb, v);
+    }
+    for (; it < items; it += every) {
+        EmitItem nxt = cur;
+        u32x4 nv[WS];
+        const bool more = it + every < items;
+        if (more) {
+            nxt = emit_item(p, e, it + every, lane);
+            emit_load<WS>(p, nxt, xb, rowb, nv);
+        }
+        const EmitFate f = emit_fate(p, cur, s_row, mb);
+        if (f.merged == 0ull) emit_copy<WS>(cur, f, ob, rowb, v);
+        else if (e.bf16) emit_mean<true, WS>(cur, f, ob, rowb, v);
+        else emit_mean<false, WS>(cur, f, ob, rowb, v);
+        cur = nxt;
+        if (more) {
+#pragma unroll
+            for (int m = 0; m < WS; ++m) v[m] = nv[m];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // The same decisions for M <= 1024*IPT <= 5120 with a sample's tokens in registers (thread t owns the IPT
 // consecutive tokens t*IPT ..): the kernel is a chain of dependent steps on one CU per sample, so it
 // is built to be short rather than wide.
@@ -675,7 +786,9 @@ __global__ __launch_bounds__(1024) void encode_decide_kernel(
 #else
 #define MD_DTICK(k) do { } while (0)
 #endif
-template <int IPT, int WS>
+// EMIT: em.blocks blocks per sample (blocks of a sample em.by_B.d apart: with eight samples and more on one XCD, whose L2 they
+// share), each of which makes all of the decisions and then writes its share of the rows and of the small outputs.
+template <int IPT, int WS, bool EMIT>
 __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
     EncodeDims p, const uint8_t* __restrict__ valid, const float* __restrict__ mass_in,
     const float* __restrict__ logits, const float2* __restrict__ cls_part, const float* __restrict__ sim,
@@ -683,7 +796,7 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
     uint8_t* __restrict__ wmerged, int32_t* __restrict__ dstpos,
     int32_t* __restrict__ out_index, float* __restrict__ out_mass, uint8_t* __restrict__ out_is_key,
     uint8_t* __restrict__ out_valid, int32_t* __restrict__ out_count, int32_t* __restrict__ key_index,
-    float* __restrict__ a_cls_out, float* __restrict__ window_sim_out)
+    float* __restrict__ a_cls_out, float* __restrict__ window_sim_out, EmitArgs em)
 {
     // [M] merged-window mass / scores (float), then [M] key flags and [M] token states, which take the place of
     // the [groups][16] factors of Eq. 6 (see decide_fast_lds_bytes)
@@ -695,8 +808,9 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
     __shared__ long long ticks[12];
 #endif
     MD_DTICK(0);
-    const int b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+    const int g = EMIT ? em.by_B.div(blockIdx.x) : 0, b = blockIdx.x - g * p.B, tid = threadIdx.x, lane = lane_id(), wv = wave_id();
     const int M = p.M, W = p.W;
+    const bool writes = !EMIT || (em.blocks < 16 ? wv % em.blocks : wv) == g;     // the small outputs go by waves
     if (tid < 256) s_hist[tid] = 0;                         // for block_select_topk, after later barriers
     float* s_tmass = reinterpret_cast<float*>(s_dyn);
     uint8_t* s_key = s_dyn + 4 * (size_t)M;
@@ -758,41 +872,42 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
     bool sel[IPT];
 #pragma unroll
     for (int t = 0; t < IPT; ++t) sel[t] = false;
-    // What a window's decision needs besides the key flags, worked out while the loads above are on
-    // their way: its first token, which members are valid, their count, first one and total mass.
-    struct WinInfo { int base, first, n; uint32_t vmask; float total; };
+    // What a window's decision needs besides the key flags, on its way with the loads above: its first token, which members
+    // are valid, and the masses of the first four.  (Nothing here uses what a load of a mass returns: the wave would wait
+    // for everything requested so far.)
+    struct WinInfo { int base; uint32_t vmask; float mm[4]; };
     auto analyse = [&](int w) -> WinInfo {
         WinInfo wi;
         const WindowAt at = window_at(p, w);
-        wi.base = at.base; wi.first = -1; wi.n = 0; wi.vmask = 0u; wi.total = 0.f;
+        wi.base = at.base;
+        wi.vmask = 0u;
 #pragma unroll
-        for (int m0 = 0; m0 < WS; m0 += 4) {         // four members' flags and masses in flight (WS >= ws)
-            if (m0 >= p.ws) break;
-            uint32_t vv[4];
-            float mm[4];
-            int tk[4];
-            bool inb[4];
+        for (int m = 0; m < WS; ++m) wi.vmask |= (m < p.ws && member_exists(p, at, m) ? 1u : 0u) << m;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                inb[u] = m0 + u < p.ws && member_exists(p, at, m0 + u);
-                tk[u] = inb[u] ? wi.base + p.moff[m0 + u] : wi.base;     // the window's first token is always there
-            }
+        for (int u = 0; u < 4; ++u) wi.mm[u] = 1.0f;
+        if (mb) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) vv[u] = vb ? vb[tk[u]] : 1u;
+            for (int u = 0; u < 4; ++u) wi.mm[u] = mb[(wi.vmask >> u) & 1u ? wi.base + p.moff[u] : wi.base];   // the window's first token is always there
+        }
+        if (vb) {
+            uint32_t vv[WS];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) mm[u] = mb ? mb[tk[u]] : 1.0f;
+            for (int m = 0; m < WS; ++m) vv[m] = vb[(wi.vmask >> m) & 1u ? wi.base + p.moff[m] : wi.base];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (!inb[u] || vv[u] == 0) continue;
-                wi.vmask |= 1u << (m0 + u);
-                ++wi.n;
-                if (wi.first < 0) wi.first = tk[u];
-                wi.total += mm[u];
-            }
+            for (int m = 0; m < WS; ++m)
+                if (vv[m] == 0) wi.vmask &= ~(1u << m);
         }
         return wi;
     };
     WinInfo win0 = analyse(min(tid, W - 1));         // nearly always the thread's only window (W <= 1024)
+    constexpr bool AHEAD = EMIT && (WS == 4 || IPT <= 2);      // registers allow the first rows to be requested up front
+    EmitItem item{};
+    u32x4 rowv[WS];
+    if (AHEAD && wv * em.blocks + g < W * em.slices) {
+        const int rowb = p.D * (em.bf16 ? 2 : 4);
+        item = emit_item(p, em, wv * em.blocks + g, lane);
+        emit_load<WS>(p, item, static_cast<const char*>(em.x) + (size_t)b * M * rowb, rowb, rowv);
+    }
     MD_DTICK(8);
 
     if (with_keys) {
@@ -852,7 +967,7 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
             const int j = j0 + t;
             av[t] = s_a[min(j, M - 1)];
             const float a = ok[t] ? av[t] : -INFINITY;
-            if (j < M && a_cls_out) a_cls_out[(size_t)b * M + j] = a;
+            if (j < M && a_cls_out && writes) a_cls_out[(size_t)b * M + j] = a;
             rk[t] = ok[t] ? rank_key(a, j) : 0ull;
         }
         if (!key_adaptive) {                         // Eq. 7, budget form: the key_budget largest scores
@@ -880,7 +995,7 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
     } else if (a_cls_out) {
 #pragma unroll
         for (int t = 0; t < IPT; ++t)
-            if (j0 + t < M) a_cls_out[(size_t)b * M + j0 + t] = 0.f;
+            if (j0 + t < M && writes) a_cls_out[(size_t)b * M + j0 + t] = 0.f;
     }
     MD_DTICK(3);
 #pragma unroll
@@ -900,19 +1015,29 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
         bool has_key = false;
 #pragma unroll
         for (int m = 0; m < WS; ++m)
-            if (m < p.ws && ((wi.vmask >> m) & 1u)) has_key |= s_key[wi.base + p.moff[m]] != 0;
-        const bool mg = wi.n >= 2 && !has_key && simv[t] > tau;
+            if ((wi.vmask >> m) & 1u) has_key |= s_key[wi.base + p.moff[m]] != 0;
+        const bool mg = __popc(wi.vmask) >= 2 && !has_key && simv[t] > tau;
         if (mg) {
+            int first = -1;
+            float total = 0.f, mm[WS];
+#pragma unroll
+            for (int m = 0; m < WS; ++m) mm[m] = m < 4 ? wi.mm[m & 3] : 1.0f;
+            if (WS > 4 && mb) {
+#pragma unroll
+                for (int m = 4; m < WS; ++m) mm[m] = mb[(wi.vmask >> m) & 1u ? wi.base + p.moff[m] : wi.base];
+            }
 #pragma unroll
             for (int m = 0; m < WS; ++m) {
-                if (m >= p.ws || !((wi.vmask >> m) & 1u)) continue;
+                if (!((wi.vmask >> m) & 1u)) continue;
                 const int tok = wi.base + p.moff[m];
-                s_state[tok] = tok == wi.first ? 1 : 2;
+                s_state[tok] = first < 0 ? 1 : 2;
+                if (first < 0) first = tok;
+                total += mm[m];
             }
-            s_tmass[wi.first] = wi.total;
+            s_tmass[first] = total;
         }
-        wmerged[(size_t)b * W + w] = mg;
-        if (window_sim_out) window_sim_out[(size_t)b * W + w] = simv[t];
+        if (!EMIT) wmerged[(size_t)b * W + w] = mg;
+        if (window_sim_out && writes) window_sim_out[(size_t)b * W + w] = simv[t];
     }
     __syncthreads();
     MD_DTICK(5);
@@ -939,6 +1064,20 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
     int excl = wave_prefix_of_totals(s_red, total) + incl - packed;
     int kpos = excl >> 16, spos = excl & 0xFFFF;
     const int nkeys = total >> 16, nsurv = total & 0xFFFF;
+    if constexpr (EMIT) {
+        int* s_row = reinterpret_cast<int*>(s_tmass);        // (every mass is in a register)
+        int pos = spos;
+#pragma unroll
+        for (int t = 0; t < IPT; ++t) {
+            if (j0 + t < M) s_row[j0 + t] = !ok[t] ? (int)kRowInvalid : !surv[t] ? (int)kRowGone : merged[t] ? pos | kRowMerged : pos;
+            pos += surv[t] ? 1 : 0;
+        }
+        __syncthreads();
+        MD_DTICK(7);
+        emit_rows<WS, AHEAD>(p, em, b, g, s_row, mb, item, rowv);
+        MD_DTICK(11);
+    }
+    if (!writes) return;
 #pragma unroll
     for (int t = 0; t < IPT; ++t) {
         const int j = j0 + t;
@@ -946,7 +1085,7 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
             if (kpos < key_budget) key_index[(size_t)b * key_budget + kpos] = j;
             ++kpos;
         }
-        if (j < M) dstpos[(size_t)b * M + j] = surv[t] ? spos : -1;
+        if (j < M && !EMIT) dstpos[(size_t)b * M + j] = surv[t] ? spos : -1;
         if (surv[t]) {
             const size_t o = (size_t)b * M + spos;
             out_index[o] = j;
@@ -963,12 +1102,11 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
     if (out_valid)
         for (int s2 = tid; s2 < M; s2 += blockDim.x) out_valid[(size_t)b * M + s2] = s2 < nsurv;
 #ifdef MD_DECIDE_TICKS
-    MD_DTICK(7);
     if (threadIdx.x == 0 && blockIdx.x == 0)
-        printf("issue %d gm %d f %d bar %d | acls %d select %d keyflags %d windows %d scan %d writes %d total %d\n",
+        printf("issue %d gm %d f %d bar %d | acls %d select %d keyflags %d windows %d scan %d rows %d emit %d total %d\n",
                (int)(ticks[8] - ticks[0]), (int)(ticks[9] - ticks[8]), (int)(ticks[10] - ticks[9]), (int)(ticks[1] - ticks[10]),
                (int)(ticks[2] - ticks[1]), (int)(ticks[3] - ticks[2]), (int)(ticks[4] - ticks[3]), (int)(ticks[5] - ticks[4]),
-               (int)(ticks[6] - ticks[5]), (int)(ticks[7] - ticks[6]), (int)(ticks[7] - ticks[0]));
+               (int)(ticks[6] - ticks[5]), (int)(ticks[7] - ticks[6]), (int)(ticks[11] - ticks[7]), (int)(__builtin_readcyclecounter() - ticks[0]));
 #endif
 }
 
@@ -1422,13 +1560,30 @@ int encode_merge_impl(
         launch_scores(ws, ScoreBlocks{0, win_blocks, rb, sliced ? iters : 1}, st, xbf, qkbf, p, sa);
     }
     dim3 wgrid((unsigned)win_blocks);
-#define MD_DECIDE_FAST(IPT_, WS_)                                                                             \
-    MD_LAUNCH("encode_decide", st, (encode_decide_fast_kernel<IPT_, WS_>), B, 1024, dlds,                  \
+    // Survivors' rows by the deciding blocks (see EmitArgs): as many blocks per sample as have the chip to themselves in one round
+    // (more are a second round behind the decisions: 16 x 576 tokens 21.0 us a call with 256 blocks, 26.8 with 384), no more
+    // than there are items for their waves.  Two per sample at least (128 x 576 tokens 101.5 us a call with a launch for
+    // the rows, 99.4 without; 200 x 576 159.4 and 166.8).
+    const int row_slices = (int)(((long)D * xe / 16 + kWave - 1) / kWave);
+    const EmitArgs em{x, out_x, (int)min(((long)W * row_slices + 15) / 16, (long)max(kNumCU / B, 1)), row_slices, xbf ? 1 : 0,
+                      FastDiv::make(B), FastDiv::make(row_slices)};
+    // (not where a small output lies over an input of theirs: a block may still read what another one writes)
+    const size_t tokens = (size_t)B * M;
+    auto over = [&](const void* out, size_t n) { return overlaps(out, n, mass_in, 4 * tokens) || overlaps(out, n, valid, tokens); };
+    const bool emits = fast_ok && ws <= 8 && 2 * B <= kNumCU && row_slices <= 4096 && !over(out_index, 4 * tokens) &&
+                       !over(out_mass, 4 * tokens) && !over(out_is_key, tokens) && !over(out_valid, tokens) &&
+                       !over(a_cls_out, 4 * tokens) && !over(key_index, 4 * (size_t)B * key_budget);
+#define MD_DECIDE_FAST(IPT_, WS_, E_)                                                                             \
+    MD_LAUNCH("encode_decide", st, (encode_decide_fast_kernel<IPT_, WS_, E_>), E_ ? B * em.blocks : B, 1024, dlds,                  \
         p, valid, mass_in, wsp.logits, wsp.cls_part, wsp.sim, tau, key_budget, key_adaptive, key_lambda, key_count,  \
         wsp.wmerged, wsp.dstpos,                                                                                   \
-        out_index, out_mass, out_is_key, out_valid, out_count, key_index, a_cls_out, window_sim_out)
+        out_index, out_mass, out_is_key, out_valid, out_count, key_index, a_cls_out, window_sim_out, em)
 #define MD_DECIDE_FAST_WS(IPT_)                                                                               \
-    do { if (ws <= 4) MD_DECIDE_FAST(IPT_, 4); else if (ws <= 8) MD_DECIDE_FAST(IPT_, 8); else MD_DECIDE_FAST(IPT_, 16); } while (0)
+    do {                                                                                                     \
+        if (ws <= 4) { if (emits) MD_DECIDE_FAST(IPT_, 4, true); else MD_DECIDE_FAST(IPT_, 4, false); }      \
+        else if (ws <= 8) { if (emits) MD_DECIDE_FAST(IPT_, 8, true); else MD_DECIDE_FAST(IPT_, 8, false); } \
+        else MD_DECIDE_FAST(IPT_, 16, false);                                                                \
+    } while (0)
     if (fast_ok && M <= 1024) MD_DECIDE_FAST_WS(1);
     else if (fast_ok && M <= 2048) MD_DECIDE_FAST_WS(2);
     else if (fast_ok && M <= 3072) MD_DECIDE_FAST_WS(3);     // e.g. five tiles of 24 x 24 tokens
@@ -1461,6 +1616,7 @@ int encode_merge_impl(
             out_index, out_mass, out_is_key, out_valid, out_count, key_index, a_cls_out, window_sim_out);
 #undef MD_DECIDE_FAST_WS
 #undef MD_DECIDE_FAST
+    if (emits) return check_launch("encode_merge");
     if (x_dtype == MD_BF16) MD_LAUNCH("encode_emit", st, (encode_emit_kernel<true>), wgrid, 64 * kEncWaves, 0, x, valid, mass_in, p, wsp.wmerged, wsp.dstpos, out_x);
     else MD_LAUNCH("encode_emit", st, (encode_emit_kernel<false>), wgrid, 64 * kEncWaves, 0, x, valid, mass_in, p, wsp.wmerged, wsp.dstpos, out_x);
     return check_launch("encode_merge");

@@ -1,0 +1,56 @@
+"""GPU parity of the survivors' rows where the deciding blocks write them and around the line where a launch of its own does:
+token counts at the edges of the decision kernel's forms, clipped windows, rows that are no whole number of 64-vector
+slices, samples with more and with fewer blocks than the small outputs have waves, masses and padding."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from parity import check_encode
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,M,win,D,bf16,extras", [
+    (1, 1, (1, 1, 2), 8, True, False), (1, 3, (1, 1, 4), 16, False, True), (2, 1023, (1, 1, 4), 72, True, True),
+    (3, 1025, (1, 1, 8), 520, True, True), (1, 2049, (1, 1, 5), 264, False, True), (2, 3072, (1, 1, 4), 48, True, False),
+    (1, 3073, (1, 1, 7), 40, True, True), (1, 5120, (1, 1, 4), 80, False, True), (1, 5120, (1, 1, 8), 64, True, False),
+    (17, 130, (1, 1, 4), 1032, True, True), (128, 37, (1, 1, 2), 32, True, True), (129, 37, (1, 1, 2), 32, True, True),
+    (2, 90, (1, 1, 9), 136, True, True)])
+def test_rows(B, M, win, D, bf16, extras):
+    from paper_2411_10803_amd import harness
+    kt, kh, kw = win
+    dt = wl.BF16 if bf16 else wl.F32
+    rng = np.random.default_rng(M * D)
+    x = np.repeat(rng.standard_normal((B, -(-M // kw), D), dtype=np.float32), kw, axis=1)[:, :M]
+    x = x + np.float32(rng.choice([0.05, 1.0], size=(B, -(-M // kw), 1)).repeat(kw, axis=1)[:, :M]) * rng.standard_normal((B, M, D), dtype=np.float32)
+    x = wl.f32_to_bf16_bits(x) if bf16 else x
+    valid = (rng.random((B, M)) > 0.1).astype(np.uint8) if extras else None
+    mass = rng.integers(1, 5, size=(B, M)).astype(np.float32) if extras else None
+    keys, dc = min(M, 5), 8                              # heads of eight features, as many as fit; fewer for wide rows
+    q = k = None
+    Hc = D // dc
+    if Hc <= 16:
+        q = rng.standard_normal((B, Hc, dc), dtype=np.float32)
+        k = rng.standard_normal((B, 1 + M, Hc, dc), dtype=np.float32)
+    else:
+        keys = 0
+    args = (1, 1, M, kt, kh, kw, 0.7, keys)
+    print(f"B={B} M={M} window={win} D={D} bf16={bf16} extras={extras} keys={keys}", flush=True)
+    g = harness.encode_on_gpu(x, dt, q, k, wl.F32, mass, valid, *args)
+    o = oracle.encode_merge(x, dt, q, k, wl.F32, mass, valid, *args)
+    check_encode(g, o, x, dt, valid, *args)
+
+
+def test_rows_with_outputs_over_inputs():
+    """Masses and flags that are written over the ones read (nothing merges, so that a launch of its own gives the rows)."""
+    import torch
+    import paper_2411_10803_amd as md
+    B, M, D = 2, 700, 64
+    rng = np.random.default_rng(5)
+    x = torch.from_numpy(rng.standard_normal((B, M, D), dtype=np.float32)).cuda()
+    mass = torch.from_numpy(rng.integers(1, 5, size=(B, M)).astype(np.float32)).cuda()
+    want = mass.clone()
+    out = md.mustdrop_encode_merge(x, None, None, mass, None, 1, 1, M, 1, 1, 2, 2.0, 0)
+    got = md.mustdrop_encode_merge(x, None, None, mass, None, 1, 1, M, 1, 1, 2, 2.0, 0, out=dict(out, out_mass=mass))
+    assert torch.equal(got["out_mass"], want) and torch.equal(got["out_x"], x) and torch.equal(out["out_x"], x)
