@@ -16,6 +16,8 @@
 #include "md_host.hpp"
 #include "decode_plan.hpp"
 
+#include <type_traits>
+
 namespace md {
 namespace {
 
@@ -249,6 +251,10 @@ __device__ __forceinline__ void move_rows(const DecodeDims& p, const KvLayout& l
 // t, t+1024, ... (coalesced loads; the first one does not depend on the live length, so it is
 // requested before the length arrives).  IPT >= ceil(Lcap / 1024).  One round of global loads for
 // the common case, then block-level phases only.
+// Bound by that chain and by the instructions of sixteen waves on one CU.  In a steady loop one entry leaves: the writer alone works
+// (62 blocks per sample that all read the same logits were in each other's way), the row that will move is under way from
+// the start and the statistics are read as they lie in memory.  us per launch, before / after: 4 x 778 entries of 40
+// heads, head-major 14.1 / 10.2, 64 x 1025 of 32 13.8 / 12.4; per step 16 x 1025 of 32 heads 42.9 / 39.5, 1 x 1025 20.1 / 16.4.
 // LPE = lanes per entry = H / 4 where that is a power of two up to 8; 0: any other H that is a multiple of four.
 template <int IPT, int LPE>
 __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
@@ -261,7 +267,8 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     // memory holds the list of evicted slots below the new length and, in its second half, that of the kept ones behind it
     extern __shared__ __attribute__((aligned(16))) int s_holes[];
     float* s_at = reinterpret_cast<float*>(s_holes);
-    __shared__ __attribute__((aligned(16))) float s_cm[1024], s_cz[1024];    // per head: max (log2 domain), 1 / (Z * H)
+    __shared__ __attribute__((aligned(16))) float s_cm[128], s_cz[128];      // per head: max (log2 domain), 1 / (Z * H)
+    __shared__ float2 s_st[1024];
     __shared__ int s_red[16];
     __shared__ int s_hist[kSelectHistInts];
     __shared__ uint64_t s_red64[16];
@@ -303,39 +310,73 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
     constexpr int PFR = IPT < 2 ? IPT : 2;           // rounds requested before the length is known
     constexpr int LPE1 = LPE ? LPE : 1;
     constexpr int EPI = kWave / LPE1;                // entries per load instruction
-    f32x4 lpf[PFR][LPE1];
+    f32x4 lpf[PFR][LPE1], hpf[2][5];
     // Logits are requested ahead only up to where a steady decode loop has entries: behind them a cache with room to
     // spare holds nothing but old logits, which come from far away (33 x 168 of 949 slots, 8 blocks each: 35.6 -> 32.7 us).
     // One block per sample takes all at once: a cut to a quarter would wait twice (6 x 1838 entries: 15 us, 18.6 so)
+    // (Buffer loads: what lies behind the last entry that is asked for reads as zero.  A predicate and an address for each of
+    // the loads is what four waves per SIMD spend their time on here.)
     const int ahead = gridDim.x > 1 && budget < p.Lcap - 64 ? budget + 64 : p.Lcap;
+    const int len_b = in.len[b];
+    // Up to budget + 1 entries one leaves at most, and the writer sees to that alone.  The other blocks wait for the length before
+    // they ask for anything: they would all go for the lines that the writer waits for.
+    if (!writer && len_b <= budget + 1) return;
+    uint32_t pbyte[PFR];
 #pragma unroll
     for (int t = 0; t < PFR; ++t) {
-        const int j = tid + t * 1024;
-        const bool there = j < p.Lcap;               // readable whatever the live length is
-        a_old[t] = there ? ai[j] : 0.f;
-        id[t] = there ? ii[j] : 0;
-        prot[t] = there ? pi[j] != 0 : false;
-        const int base = t * 1024 + wv * kWave;
+        const int j = min(tid + t * 1024, p.Lcap - 1);                   // readable whatever the live length is
+        a_old[t] = ai[j];
+        id[t] = ii[j];
+        pbyte[t] = pi[j];
+    }
+    const __amdgpu_buffer_rsrc_t rlog = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lb), 0, ahead * H * 4, 0x00020000);
+    const int wave_off = wv * kWave * H * 4, lane_off = lane * 16;       // bytes of the wave's 64 entries, of the lane within them
+    auto request = [&](int off, int imm) -> f32x4 {
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rlog, lane_off + imm, off, 0));
+    };
 #pragma unroll
-        for (int u = 0; u < LPE; ++u) {
-            const int e = base + u * EPI + lane / LPE1;
-            lpf[t][u] = e < ahead ? reinterpret_cast<const f32x4*>(lb + (long)base * H)[u * kWave + lane]
-                                  : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+    for (int t = 0; t < PFR; ++t)
+#pragma unroll
+        for (int u = 0; u < LPE; ++u) lpf[t][u] = request(t * 1024 * H * 4 + wave_off, u * 1024);
+    // LPE = 0: the wave's first 64 entries, 32 at a time, where they are no more than five vectors per lane
+    const int vpe = H >> 2;
+    if (LPE == 0 && vpe <= 10) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int u = 0; u < 5; ++u) hpf[r][u] = request(wave_off + r * 32 * H * 4, u * 1024);
     }
-    // the logits kernel's partial statistics: `parts` consecutive lanes (a power of two) share a head, each takes a slice
-    const int parts = min(1 << (31 - __clz(1024 / H)), kWave), sh = tid / parts, sq = tid % parts;
+    // the logits kernel's partial statistics, as they lie in memory: thread = (slice of its blocks, head), heads contiguous
+    const uint32_t hmul = (1u << 20) / (uint32_t)H + 1u;                 // x / H = x * hmul >> 20 for x <= 1024
+    const int nsl = (int)((1024u * hmul) >> 20), sl = (int)(((uint32_t)tid * hmul) >> 20), hh = tid - sl * H;
     float mn = -INFINITY, zn = 0.f;
-    if (sh < H) {
-        const float2* sp = stat_partial + (long)b * n_part * H + sh;
-        for (int c = sq; c < n_part; c += parts) {
-            const float2 v = sp[(long)c * H];
-            const float m2 = fmaxf(mn, v.x);
-            if (m2 > -INFINITY) zn = zn * fast_exp2(mn - m2) + v.y * fast_exp2(v.x - m2);
+    if (sl < nsl) {
+        const float2* sp = stat_partial + (long)b * n_part * H + hh;
+        auto merge = [&](int c0, auto count) {       // count partials, in flight together
+            constexpr int N = decltype(count)::value;
+            double v[N];                             // (pairs of floats; as such, the halves would be loaded one after the other)
+            float m2 = mn;
+#pragma unroll
+            for (int u = 0; u < N; ++u) v[u] = *reinterpret_cast<const double*>(sp + min(c0 + u * nsl, n_part - 1) * H);
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                if (c0 + u * nsl < n_part) m2 = fmaxf(m2, __builtin_bit_cast(float2, v[u]).x);
+            if (m2 > -INFINITY) {
+                zn *= fast_exp2(mn - m2);
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const float2 w = __builtin_bit_cast(float2, v[u]);
+                    if (c0 + u * nsl < n_part) zn = fmaf(w.y, fast_exp2(w.x - m2), zn);
+                }
+            }
             mn = m2;
-        }
+        };
+        if (n_part <= 2 * nsl) merge(sl, std::integral_constant<int, 2>());
+        else
+            for (int c0 = sl; c0 < n_part; c0 += 8 * nsl) merge(c0, std::integral_constant<int, 8>());
+        s_st[tid] = make_float2(mn, zn);
     }
-    const int n = min(max(in.len[b], 0), p.Lcap);
+    const int n = min(max(len_b, 0), p.Lcap);
     if (n == 0) {
         if (writer && tid == 0 && evicted_count) evicted_count[b] = 0;
         if (n_move && tid == 0) n_move[b] = 0;
@@ -344,11 +385,16 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
 #pragma unroll
     for (int t = 0; t < PFR; ++t) {
         live[t] = tid + t * 1024 < n;
-        if (!live[t]) { prot[t] = false; a_old[t] = 0.f; }
+        prot[t] = live[t] && pbyte[t] != 0;
+        if (!live[t]) a_old[t] = 0.f;
     }
 #pragma unroll
     for (int t = PFR; t < IPT; ++t) {                // further rounds only for long caches
         const int j = tid + t * 1024;
+        live[t] = prot[t] = false;
+        a_old[t] = 0.f;
+        id[t] = 0;
+        if (t * 1024 >= n) continue;                 // block-uniform
         live[t] = j < n;
         a_old[t] = live[t] ? ai[j] : 0.f;
         id[t] = live[t] ? ii[j] : 0;
@@ -363,16 +409,48 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
                 if (e >= ahead && e < n) lpf[t][u] = reinterpret_cast<const f32x4*>(lb + (long)base * H)[u * kWave + lane];
             }
     }
-    // the lanes of a head finish the merge: group maximum, then the group sum of the rescaled sums
+    // Where one entry leaves as a rule (a steady decode loop), the last one's rows will fill its place: on their way already
+    const int sh_v = __builtin_ctz(p.d / 8), rv = H << sh_v;             // 16-byte vectors of a head slice (log2), of a row
+    const bool row_ahead = writer && n == budget + 1 && rv <= 1024;
+    u32x4 mrow[2];
+    auto row_vector = [&](int i, int slot, bool& of_v) -> u32x4* {       // this thread's i-th vector of the K row and the V row behind it
+        const int x = min(tid + i * 1024, 2 * rv - 1);
+        of_v = x >= rv;
+        const int y = of_v ? x - rv : x;
+        return reinterpret_cast<u32x4*>((of_v ? v_cache : k_cache) + (long)slot * lay.token + (long)(y >> sh_v) * lay.head + (y & ((1 << sh_v) - 1)) * 8);
+    };
+    // (requested whatever the case: behind a branch, a wait for anything older would be one for these rows too)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        bool of_v;
+        mrow[i] = __builtin_nontemporal_load(row_vector(i, n - 1, of_v));
+    }
     {
-        float gm = mn;
+        int np = 0;                                  // the wave's protected entries
+#pragma unroll
+        for (int t = 0; t < IPT; ++t) np += __popcll(__ballot(prot[t]));
+        if (lane == 0) s_red[wv] = np;
+    }
+    __syncthreads();
+    // `parts` consecutive lanes (a power of two) finish a head: maximum, then the sum of the rescaled sums
+    {
+        const int lg = min(31 - __clz(nsl), 6), parts = 1 << lg, sh = tid >> lg, sq = tid & (parts - 1), ns = min(nsl, n_part);
+        float gm = -INFINITY, gz = 0.f;
+        if (sh < H)
+            for (int c = sq; c < ns; c += parts) {
+                const float2 v = s_st[c * H + sh];
+                const float m2 = fmaxf(gm, v.x);
+                if (m2 > -INFINITY) gz = gz * fast_exp2(gm - m2) + v.y * fast_exp2(v.x - m2);
+                gm = m2;
+            }
+        const float own = gm;
         if (parts >= 2) gm = fmaxf(gm, dpp_f<0xB1>(gm));
         if (parts >= 4) gm = fmaxf(gm, dpp_f<0x4E>(gm));
         if (parts >= 8) gm = fmaxf(gm, dpp_f<0x141>(gm));
         if (parts >= 16) gm = fmaxf(gm, dpp_f<0x140>(gm));
         if (parts >= 32) gm = fmaxf(gm, __shfl_xor(gm, 16, kWave));
         if (parts >= 64) gm = fmaxf(gm, __shfl_xor(gm, 32, kWave));
-        const float zs = group_sum_rt(gm > -INFINITY ? zn * fast_exp2(mn - gm) : 0.f, parts);
+        const float zs = group_sum_rt(gm > -INFINITY ? gz * fast_exp2(own - gm) : 0.f, parts);
         if (sh < H && sq == 0) { s_cm[sh] = gm; s_cz[sh] = __frcp_rn(zs * (float)H); }
     }
     __syncthreads();
@@ -384,30 +462,24 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
         // H / 4 = `vpe` vectors of 16 bytes per entry, not a power of two: a wave takes 32 entries at a time, 32 * vpe
         // consecutive vectors.  A lane's vectors belong to changing heads, so it takes their statistics from LDS, and
         // a vector's share goes through LDS to the lane that adds up the entry's shares, in head order.
-        const int vpe = H >> 2;
         const uint32_t vmul = 65536u / (uint32_t)vpe + 1u;               // x / vpe = x * vmul >> 16 for x < 32 * vpe <= 1024
         float* s_share = s_at + p.Lcap + wv * (32 * vpe);
-        for (int e0 = wv * kWave; e0 < n; e0 += (e0 & 32) ? 1024 - 32 : 32) {
-            const f32x4* lv = reinterpret_cast<const f32x4*>(lb + (long)e0 * H);
-            const int ne = min(n - e0, 32), nv = ne * vpe;               // live entries of this round, their vectors
-            for (int u0 = 0; u0 < nv; u0 += 5 * kWave) {
-                f32x4 v[5];
+        auto shares = [&](int u0, int nv, const f32x4 (&v)[5]) {
 #pragma unroll
-                for (int u = 0; u < 5; ++u) v[u] = lv[min(u0 + u * kWave + lane, nv - 1)];
-#pragma unroll
-                for (int u = 0; u < 5; ++u) {
-                    const int x = u0 + u * kWave + lane;
-                    if (x < nv) {
-                        const int g = x - (int)(((uint32_t)x * vmul) >> 16) * vpe;
-                        const f32x4 cm = reinterpret_cast<const f32x4*>(s_cm)[g], cz = reinterpret_cast<const f32x4*>(s_cz)[g];
-                        float part = fast_exp2(fmaf(v[u].x, kLog2eD, -cm.x)) * cz.x;
-                        part = fmaf(fast_exp2(fmaf(v[u].y, kLog2eD, -cm.y)), cz.y, part);
-                        part = fmaf(fast_exp2(fmaf(v[u].z, kLog2eD, -cm.z)), cz.z, part);
-                        part = fmaf(fast_exp2(fmaf(v[u].w, kLog2eD, -cm.w)), cz.w, part);
-                        s_share[x] = part;
-                    }
+            for (int u = 0; u < 5; ++u) {
+                const int x = u0 + u * kWave + lane;
+                if (x < nv) {
+                    const int g = x - (int)(((uint32_t)x * vmul) >> 16) * vpe;
+                    const f32x4 cm = reinterpret_cast<const f32x4*>(s_cm)[g], cz = reinterpret_cast<const f32x4*>(s_cz)[g];
+                    float part = fast_exp2(fmaf(v[u].x, kLog2eD, -cm.x)) * cz.x;
+                    part = fmaf(fast_exp2(fmaf(v[u].y, kLog2eD, -cm.y)), cz.y, part);
+                    part = fmaf(fast_exp2(fmaf(v[u].z, kLog2eD, -cm.z)), cz.z, part);
+                    part = fmaf(fast_exp2(fmaf(v[u].w, kLog2eD, -cm.w)), cz.w, part);
+                    s_share[x] = part;
                 }
             }
+        };
+        auto sums = [&](int e0, int ne) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -419,6 +491,28 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        int e_first = wv * kWave;
+        if (vpe <= 10 && n <= ahead) {               // block-uniform: the first 64 entries are here
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int e0 = wv * kWave + 32 * r, ne = min(n - e0, 32);
+                if (ne <= 0) break;
+                shares(0, ne * vpe, hpf[r]);
+                sums(e0, ne);
+            }
+            e_first += 1024;
+        }
+        for (int e0 = e_first; e0 < n; e0 += (e0 & 32) ? 1024 - 32 : 32) {
+            const f32x4* lv = reinterpret_cast<const f32x4*>(lb + (long)e0 * H);
+            const int ne = min(n - e0, 32), nv = ne * vpe;               // live entries of this round, their vectors
+            for (int u0 = 0; u0 < nv; u0 += 5 * kWave) {
+                f32x4 v[5];
+#pragma unroll
+                for (int u = 0; u < 5; ++u) v[u] = lv[min(u0 + u * kWave + lane, nv - 1)];
+                shares(u0, nv, v);
+            }
+            sums(e0, ne);
         }
 #pragma unroll
         for (int t = 0; t < IPT; ++t) a_new[t] = live[t] ? fmaf(decay, a_old[t], s_at[tid + t * 1024]) : 0.f;
@@ -433,6 +527,7 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
             const int base = t * 1024 + wv * kWave;
 #pragma unroll
             for (int u = 0; u < LPE; ++u) {
+                if (base + u * EPI >= n) break;
                 const int e = base + u * EPI + lane / LPE;
                 f32x4 v;
                 if (t < PFR) v = lpf[t < PFR ? t : 0][u];
@@ -451,10 +546,7 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
             a_new[t] = live[t] ? fmaf(decay, a_old[t], s_at[j]) : 0.f;
         }
     }
-    int np = 0;
-#pragma unroll
-    for (int t = 0; t < IPT; ++t) np += prot[t];
-    np = block_sum_i(np, s_red);
+    const int np = wave_sum_i(lane < 16 ? s_red[lane] : 0);
 
     if (n <= budget) {                               // nothing leaves: only the scores change
         if (!writer) return;
@@ -478,14 +570,33 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
         uint64_t mine = ~0ull;
         int mine_slot = 0;
 #pragma unroll
-        for (int t = 0; t < IPT; ++t) if (key[t] != 0 && key[t] < mine) { mine = key[t]; mine_slot = tid + t * 1024; }
-        const uint64_t victim = block_min_u64(mine, s_red64);
-        __shared__ int s_pair[2];
-        if (mine == victim) s_pair[0] = mine_slot;   // keys are unique: one writer
-        if (tid == 0) s_pair[1] = n - 1;
+        for (int t = 0; t < IPT; ++t)
+            if (t * 1024 < n && key[t] != 0 && key[t] < mine) { mine = key[t]; mine_slot = tid + t * 1024; }
+        const uint64_t least = wave_min_u64(mine);
+        const int least_slot = __builtin_amdgcn_readlane(mine_slot, __builtin_ctzll(__ballot(mine == least)));
+        __shared__ int s_slot[16], s_pair[2];
+        if (lane == 0) { s_red64[wv] = least; s_slot[wv] = least_slot; }
         __syncthreads();
-        const int vslot = s_pair[0], last = n - 1;
-        move(s_pair + 1, s_pair, vslot != last ? 1 : 0);
+        const uint64_t other = s_red64[lane & 15];
+        const uint64_t victim = wave_min_u64(other);                     // (keys are unique, and there is one)
+        const int vslot = s_slot[__builtin_ctzll(__ballot(other == victim))], last = n - 1;
+        if (row_ahead) {
+            if (n_move && tid == 0) n_move[b] = 0;
+            if (vslot != last) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (tid + i * 1024 < 2 * rv) {
+                        bool of_v;
+                        u32x4* dst = row_vector(i, vslot, of_v);
+                        if (stream_once || of_v) __builtin_nontemporal_store(mrow[i], dst);
+                        else *dst = mrow[i];
+                    }
+            }
+        } else {
+            if (tid == 0) { s_pair[0] = vslot; s_pair[1] = last; }
+            __syncthreads();
+            move(s_pair + 1, s_pair, vslot != last ? 1 : 0);
+        }
 #pragma unroll
         for (int t = 0; t < IPT; ++t) {
             const int j = tid + t * 1024;

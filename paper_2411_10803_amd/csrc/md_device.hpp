@@ -386,16 +386,6 @@ __device__ __forceinline__ SelectBound block_select_topk(const uint64_t (&key)[I
     }, k, hist);
 }
 
-// Block-wide minimum of 64-bit values (same result on every thread).  `red` holds >= blockDim.x/64 entries.
-__device__ __forceinline__ uint64_t block_min_u64(uint64_t v, uint64_t* red) {
-    v = wave_min_u64(v);
-    __syncthreads();
-    if (lane_id() == 0) red[wave_id()] = v;
-    __syncthreads();
-    const int nw = blockDim.x >> 6;
-    return wave_min_u64(lane_id() < nw ? red[lane_id()] : ~0ull);
-}
-
 // Exclusive prefix sum over the block, in thread order.  Returns this thread's prefix; `total` =
 // block sum.  `red` holds >= blockDim.x/64 ints.  Several small counters can share the word.
 __device__ __forceinline__ int block_exscan_i(int v, int* red, int& total) {
