@@ -14,6 +14,7 @@
 //                            S, p = exp(s - m)/Z, accumulate the head mean a[i][j] of such a key tile
 //                            in registers; a block's share of a tile is written as one piece
 //   prefill_colfix_kernel    sums a tile's pieces in a fixed order, column sum / max -> V_j, I_j
+//   prefill_colown_kernel    in place of both on small calls: a block takes a tile with all heads
 // The N x Mv probability matrix of a head is never written to memory.
 //   prefill_select_kernel    per sample: G, the filter rule (threshold) or radix top-k (budget),
 //                            prefix sum -> kept_index, row map for the copy
@@ -1160,6 +1161,127 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
     if (u < u1) unit_step(u, 0);
 }
 
+// The same where one block takes a tile of 32 keys and 32 text rows with all of its heads (ScorePlan::own): no piece is handed
+// over and no launch follows.  Block = (sample, 32 vision keys, text block), eight waves of every eighth head each.  A wave's K
+// rows lie in two LDS slots of its own, so that the loop over the heads has no barrier; the K rows of the head after next and the
+// fragments of the next one are under way while a head is worked on.  What the waves have summed up meets in LDS, where V and I
+// come out of it, of each text block by itself (the selection adds them up).  The row statistics of several key chunks are merged here.
+// Bound by latency up to a round of blocks (rows of a sample, K and query fragments, the meeting in LDS), then by the fragments,
+// which come from L2 once for every 32 keys.  1 x 576 keys, 32 text rows: 7.1 + 6.1 us in the persistent form and its sum of the
+// pieces, 9.5 here.
+template <int KS>
+__global__ __launch_bounds__(512) void prefill_colown_kernel(
+    const bf16x8* __restrict__ qfrag, const uint16_t* __restrict__ k, const float* __restrict__ cstat, const float2* __restrict__ partial,
+    const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ txt_len, const SampleRows* __restrict__ rows, PrefillDims p,
+    float scale_log2e, float* __restrict__ Vout, float* __restrict__ Iout)
+{
+    using T = LdsRows<KS>;
+    constexpr int W = 8, TILE_BYTES = 32 * T::ROWB, NLT = 32 / T::RPL;
+    constexpr int CH = kOwnChunks;
+    __shared__ __attribute__((aligned(1024))) char s_k[W * 2 * TILE_BYTES];
+    const int lane = lane_id(), wv = wave_id(), i = lane & 31;
+    // neighbouring tiles of a sample on one XCD (blocks go round the 8 of them), whose L2 then holds the sample's query fragments
+    const int nbt = p.Npad / 32, nkg = (p.Mv + 31) / 32, items = p.B * nkg * nbt, per_xcd = (items + 7) / 8;
+    const int item = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (item >= items) return;
+    const int tile = item / nbt, nb = item - tile * nbt, b = tile / nkg, j0 = (tile - b * nkg) * 32;
+    const uint16_t* kb = k + (long)b * p.kv.batch;
+    const uint32_t krow = (uint32_t)(p.kv.token * 2);
+    char* const slots = s_k + wv * 2 * TILE_BYTES;
+    // (behind the last head the last one is asked for again: the loads stay unconditional, so that those in flight can be counted)
+    auto issue_k = [&](int h, int slot) {
+        const __amdgpu_buffer_rsrc_t rk = row_buffer(kb + (long)min(h, p.H - 1) * p.kv.head, p.L, p.kv.token, p.d);
+#pragma unroll
+        for (int t = 0; t < NLT; ++t) T::issue(rk, krow, j0, t * T::RPL, slots + slot * TILE_BYTES, lane, true);
+    };
+    struct Query { bf16x8 f[KS]; float c; float2 st[CH]; };
+    auto load_q = [&](int h, Query& q) {
+        const long bh = (long)b * p.H + min(h, p.H - 1);
+        const bf16x8* qh = qfrag + (bh * nbt + nb) * KS * kWave + lane;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) q.f[ks] = qh[ks * kWave];
+        if (p.nch == 1) q.c = cstat[bh * p.Npad + 32 * nb + i];
+        else {
+#pragma unroll
+            for (int u = 0; u < CH; ++u) q.st[u] = partial[(bh * p.nch + min(u, p.nch - 1)) * p.Npad + 32 * nb + i];
+        }
+    };
+    const int tl = txt_len ? min(max(txt_len[b], 0), p.N) : p.N;
+    // the statistic of this lane's text row: see prefill_cstat_kernel
+    auto statistic = [&](const Query& q) -> float {
+        if (p.nch == 1) return q.c;
+        float mn = -INFINITY, zn = 0.f;
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+            if (u < p.nch) mn = fmaxf(mn, q.st[u].x);
+        if (mn > -INFINITY) {
+#pragma unroll
+            for (int u = 0; u < CH; ++u)
+                if (u < p.nch) zn = fmaf(q.st[u].y, fast_exp2(q.st[u].x - mn), zn);
+        }
+        return fold_stats(mn, zn, 32 * nb + i < tl, p.H);
+    };
+    f32x16 sum;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+    issue_k(wv, 0);
+    issue_k(wv + W, 1);
+    const bool work = j0 < rows[b].vision && 32 * nb < tl;                 // block-uniform
+    if (work && wv < p.H) {
+        Query qa, qb;
+        load_q(wv, qa);
+        // one head: its K rows are in `slot`, its fragments in q; the next head's go to qn
+        auto head = [&](int h, int slot, Query& q, Query& qn) {
+            MD_VM_WAIT(NLT);                          // all but the K rows of the next head
+            bf16x8 kf[KS];
+            T::frags(T::frag_base(slots + slot * TILE_BYTES, lane), kf);
+            load_q(h + W, qn);
+            issue_k(h + 2 * W, slot);
+            const f32x16 acc = score_tile<KS>(kf, q.f);
+            const float c = statistic(q);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[r] += fast_exp2(fmaf(acc[r], scale_log2e, c));
+        };
+        int h = wv;
+        for (; h + W < p.H; h += 2 * W) {
+            head(h, 0, qa, qb);
+            head(h + W, 1, qb, qa);
+        }
+        if (h < p.H) head(h, 0, qa, qb);
+    }
+    MD_VM_WAIT(0);                                    // (nothing writes LDS any more)
+    float v_sum = 0.f, i_max = 0.f;                   // of the key 4 * wv + lane / 16, whose text rows 16 lanes share
+    if (work) {
+        // sums of the waves, [wave][key][text row]
+        float* mine = reinterpret_cast<float*>(s_k) + wv * 1024;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mine[tile_row(r, lane) * 32 + i] = sum[r];
+        __syncthreads();
+        const float2* part = reinterpret_cast<const float2*>(s_k) + (4 * wv + (lane >> 4)) * 16 + (lane & 15);
+        float2 a = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const float2 x = part[w * 512];
+            a.x += x.x;
+            a.y += x.y;
+        }
+        v_sum = group_sum<16>(a.x + a.y);
+        i_max = fmaxf(a.x, a.y);
+        i_max = fmaxf(i_max, dpp_f<0xB1>(i_max));
+        i_max = fmaxf(i_max, dpp_f<0x4E>(i_max));
+        i_max = fmaxf(i_max, dpp_f<0x141>(i_max));
+        i_max = fmaxf(i_max, dpp_f<0x140>(i_max));
+    }
+    const int j = j0 + 4 * wv + (lane >> 4);
+    if ((lane & 15) == 0 && j < p.Mv) {
+        const bool ok = !vis_valid || vis_valid[(long)b * p.Mv + j];
+        const long o = ((long)nb * p.B + b) * p.Mv + j;
+        Vout[o] = ok ? v_sum : 0.f;
+        Iout[o] = ok ? i_max : 0.f;
+    }
+}
+
 // Column statistics (Eq. 8 / Eq. 10): a[i][j] = sum over the pieces of j's key group (fixed order);
 // V_j = sum_i a[i][j], I_j = max_i a[i][j].  A wave takes four neighbouring vision keys at a time (same
 // key group, same pieces), lanes over text rows; all loads of a piece are in flight together.
@@ -1376,9 +1498,10 @@ __device__ __forceinline__ void copy_text_rows(
         __builtin_nontemporal_store(__builtin_nontemporal_load(tr.hidden + src * hv + c), tr.hidden_out + dst * hv + c);
 }
 
-template <int IPT>
+// PARTS: V and I come as one array per text block.
+template <int IPT, bool PARTS>
 __global__ __launch_bounds__(1024) void prefill_select_fast_kernel(
-    PrefillDims p, const float* __restrict__ V, const float* __restrict__ I,
+    PrefillDims p, const float* __restrict__ V, const float* __restrict__ I, int parts,
     const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ txt_len, const uint8_t* __restrict__ is_key,
     int mode, int budget, float gamma, float alpha,
     int32_t* __restrict__ src_row,
@@ -1411,6 +1534,22 @@ __global__ __launch_bounds__(1024) void prefill_select_fast_kernel(
         for (int t = 0; t < IPT; ++t) vv[t] = vis_valid ? vis_valid[(long)b * Mv + min(tid + t * 1024, Mv - 1)] : 1u;
 #pragma unroll
         for (int t = 0; t < IPT; ++t) kk[t] = is_key ? is_key[(long)b * Mv + min(tid + t * 1024, Mv - 1)] : 0u;
+        if constexpr (PARTS) {
+            float vq[kOwnParts - 1][IPT], iq[kOwnParts - 1][IPT];
+#pragma unroll
+            for (int q = 1; q < kOwnParts; ++q)
+#pragma unroll
+                for (int t = 0; t < IPT; ++t) {
+                    const long o = ((long)min(q, parts - 1) * p.B + b) * Mv + min(tid + t * 1024, Mv - 1);
+                    vq[q - 1][t] = V[o];
+                    iq[q - 1][t] = I[o];
+                }
+#pragma unroll
+            for (int q = 1; q < kOwnParts; ++q)
+#pragma unroll
+                for (int t = 0; t < IPT; ++t)
+                    if (q < parts) { v[t] += vq[q - 1][t]; iv[t] = fmaxf(iv[t], iq[q - 1][t]); }
+        }
 #pragma unroll
         for (int t = 0; t < IPT; ++t) {
             const bool in = tid + t * 1024 < Mv;
@@ -1567,6 +1706,13 @@ struct PrefillWorkspace {
     float2* partial; float* cstat; bf16x8* qfrag; float* apart; float* V; float* I; float* score; int32_t* src_row;
     SampleRows* rows;
     size_t bytes;
+    // V and I as the column sweep leaves them: one array each, or one per text block (ScorePlan::own) in the memory of the pieces,
+    // which that form does not write (a piece is at least 32 floats per key and text block)
+    struct ScoreParts { float* V; float* I; int parts; };
+    ScoreParts score_parts(const PrefillDims& p, const ScorePlan& s) const {
+        if (!s.own || s.nbt == 1) return ScoreParts{V, I, 1};
+        return ScoreParts{apart, apart + (size_t)s.nbt * p.B * p.Mv, s.nbt};
+    }
 };
 
 PrefillWorkspace carve_prefill(void* base, int B, int Mv, int N, int H, int Rcap) {
@@ -1616,7 +1762,7 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
 #undef MD_ROWSTATS_WIDE
 #undef MD_ROWSTATS
 #undef MD_ROWSTATS2
-        if (p.nch > 1) {
+        if (p.nch > 1 && !s.own) {
             const long n = (long)p.B * p.H * p.Npad;
             MD_LAUNCH("prefill_cstat", st, (prefill_cstat_kernel), (unsigned)((n + 255) / 256), 256, 0, w.partial, txt_len, p, w.cstat);
         }
@@ -1624,6 +1770,11 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
         const long items = (long)p.B * p.H * s.nbt;
         MD_LAUNCH("prefill_qpack", st, (prefill_qpack_kernel<KS>), (unsigned)((items + 3) / 4 + p.B), 256, 0, qp, vis_valid, txt_len,
                   row_lse, p, w.qfrag, w.cstat, w.rows);
+    }
+    if (s.own) {
+        MD_LAUNCH("prefill_colscore", st, (prefill_colown_kernel<KS>), (unsigned)((s.own_blocks + 7) / 8 * 8), 512, 0, w.qfrag, kp, w.cstat, w.partial, vis_valid, txt_len, w.rows,
+                  p, scale_log2e, w.score_parts(p, s).V, w.score_parts(p, s).I);
+        return MD_OK;
     }
 #define MD_COLSCORE(NBW_, KT_, M_)                                                                             \
     MD_LAUNCH("prefill_colscore", st, (prefill_colscore_kernel<NBW_, KT_, KS, M_>), s.col.P, 256, 0,               \
@@ -1719,7 +1870,8 @@ int prefill_filter_impl(
     PrefillDims p;
     p.B = B; p.Mv = Mv; p.N = N; p.H = H; p.d = d; p.C = C; p.L = Mv + N; p.Rcap = Rcap;
     p.q = lq; p.kv = lkv;
-    const ScorePlan sp = plan_scores(B, Mv, N, H, d);
+    ScorePlan sp = plan_scores(B, Mv, N, H, d);
+    if (row_lse) { sp.nch = 1; sp.own = sp.own_lse; }         // (one statistic per row)
     p.Npad = sp.nbt * 32;
     p.nch = sp.nch; p.ng = sp.ng;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1734,10 +1886,12 @@ int prefill_filter_impl(
                 static_cast<u32x4*>(hidden_out), static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out), 0};
     tr.enabled = (mode == MD_FILTER_BUDGET && dense_io && Mv <= 8192) ? 1 : 0;
     const int sel_blocks = B + (tr.enabled ? B * ((N + kTextRowsPerBlock - 1) / kTextRowsPerBlock) : 0);
-#define MD_PSELECT_FAST(IPT_)                                                                               \
-    MD_LAUNCH("prefill_select", st, (prefill_select_fast_kernel<IPT_>), sel_blocks, 1024, 0,        \
-        p, w.V, w.I, vis_valid, txt_len, is_key, (int)mode, budget, gamma, alpha,                          \
+    const PrefillWorkspace::ScoreParts parts = w.score_parts(p, sp);
+#define MD_PSELECT_FAST2(IPT_, P_)                                                                               \
+    MD_LAUNCH("prefill_select", st, (prefill_select_fast_kernel<IPT_, P_>), sel_blocks, 1024, 0,        \
+        p, parts.V, parts.I, parts.parts, vis_valid, txt_len, is_key, (int)mode, budget, gamma, alpha,     \
         src_row, kept_index, kept_count, out_len, out_protect, score_global, score_indiv, tr)
+#define MD_PSELECT_FAST(IPT_) do { if (parts.parts > 1) MD_PSELECT_FAST2(IPT_, true); else MD_PSELECT_FAST2(IPT_, false); } while (0)
     if (Mv <= 1024) MD_PSELECT_FAST(1);
     else if (Mv <= 2048) MD_PSELECT_FAST(2);
     else if (Mv <= 3072) MD_PSELECT_FAST(3);
@@ -1750,6 +1904,7 @@ int prefill_filter_impl(
             p, w.V, w.I, vis_valid, txt_len, is_key, (int)mode, budget, gamma, alpha,
             w.score, src_row, kept_index, kept_count, out_len, out_protect, score_global, score_indiv);
 #undef MD_PSELECT_FAST
+#undef MD_PSELECT_FAST2
     dim3 gc(tr.enabled ? Rcap : Rcap + N, B);         // the text rows beyond the kept vision rows are already in place
     if (dense_io)
         MD_LAUNCH("prefill_compact", st, (prefill_compact_kernel), gc, 256, 0, p, src_row,
