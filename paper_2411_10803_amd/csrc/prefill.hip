@@ -1163,12 +1163,13 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
 
 // The same where one block takes a tile of 32 keys and 32 text rows with all of its heads (ScorePlan::own): no piece is handed
 // over and no launch follows.  Block = (sample, 32 vision keys, text block), eight waves of every eighth head each.  A wave's K
-// rows lie in two LDS slots of its own, so that the loop over the heads has no barrier; the K rows of the head after next and the
-// fragments of the next one are under way while a head is worked on.  What the waves have summed up meets in LDS, where V and I
+// rows lie in two LDS slots of its own, so that the loop over the heads has no barrier; the K rows of the next head and the fragments
+// of several are under way while a head is worked on.  What the waves have summed up meets in LDS, where V and I
 // come out of it, of each text block by itself (the selection adds them up).  The row statistics of several key chunks are merged here.
-// Bound by latency up to a round of blocks (rows of a sample, K and query fragments, the meeting in LDS), then by the fragments,
-// which come from L2 once for every 32 keys.  1 x 576 keys, 32 text rows: 7.1 + 6.1 us in the persistent form and its sum of the
-// pieces, 9.5 here.
+// Bound by what a CU can take in: half a megabyte of K and query fragments per block at 64 bytes per clock, 3.6 us, asked for as far
+// ahead as the registers hold (four heads' fragments; one head's: 1 x 3810 keys, 18 text rows, 16 heads 34.6 -> 33.2 us a call).
+// 1 x 576 keys, 32 text rows: 7.1 + 6.1 us in the persistent form and its sum of the pieces, 11.7 here, and 8.8 -> 6.7 for the
+// first sweep, whose chunks may be shorter.
 template <int KS>
 __global__ __launch_bounds__(512) void prefill_colown_kernel(
     const bf16x8* __restrict__ qfrag, const uint16_t* __restrict__ k, const float* __restrict__ cstat, const float2* __restrict__ partial,
@@ -1224,30 +1225,33 @@ __global__ __launch_bounds__(512) void prefill_colown_kernel(
     f32x16 sum;
 #pragma unroll
     for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+    // K rows of two heads and the fragments of QH are asked for before it is known whether the tile has a valid key
+    constexpr int QH = KS == 8 ? 4 : 2;               // (heads of 64: two blocks per CU keep their registers; 4 x 2122 keys, 50 rows 52 us, 57 with four)
+    Query q[QH];
     issue_k(wv, 0);
     issue_k(wv + W, 1);
-    const bool work = j0 < rows[b].vision && 32 * nb < tl;                 // block-uniform
-    if (work && wv < p.H) {
-        Query qa, qb;
-        load_q(wv, qa);
-        // one head: its K rows are in `slot`, its fragments in q; the next head's go to qn
-        auto head = [&](int h, int slot, Query& q, Query& qn) {
-            MD_VM_WAIT(NLT);                          // all but the K rows of the next head
-            bf16x8 kf[KS];
-            T::frags(T::frag_base(slots + slot * TILE_BYTES, lane), kf);
-            load_q(h + W, qn);
-            issue_k(h + 2 * W, slot);
-            const f32x16 acc = score_tile<KS>(kf, q.f);
-            const float c = statistic(q);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sum[r] += fast_exp2(fmaf(acc[r], scale_log2e, c));
-        };
-        int h = wv;
-        for (; h + W < p.H; h += 2 * W) {
-            head(h, 0, qa, qb);
-            head(h + W, 1, qb, qa);
+    for (int u = 0; u < QH; ++u)
+        if (wv + u * W < p.H) load_q(wv + u * W, q[u]);
+    const bool work = j0 < rows[b].vision && 32 * nb < tl;                 // block-uniform
+    if (work) {
+        for (int h0 = wv; h0 < p.H; h0 += QH * W) {
+#pragma unroll
+            for (int u = 0; u < QH; ++u) {
+                const int h = h0 + u * W;
+                if (h >= p.H) break;
+                const int slot = u & 1;
+                MD_VM_WAIT(NLT);                      // all but the K rows of the next head
+                bf16x8 kf[KS];
+                T::frags(T::frag_base(slots + slot * TILE_BYTES, lane), kf);
+                issue_k(h + 2 * W, slot);
+                const f32x16 acc = score_tile<KS>(kf, q[u].f);
+                const float c = statistic(q[u]);
+                if (h + QH * W < p.H) load_q(h + QH * W, q[u]);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[r] += fast_exp2(fmaf(acc[r], scale_log2e, c));
+            }
         }
-        if (h < p.H) head(h, 0, qa, qb);
     }
     MD_VM_WAIT(0);                                    // (nothing writes LDS any more)
     float v_sum = 0.f, i_max = 0.f;                   // of the key 4 * wv + lane / 16, whose text rows 16 lanes share
