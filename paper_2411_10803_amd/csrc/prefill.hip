@@ -1287,72 +1287,74 @@ __global__ __launch_bounds__(512) void prefill_colown_kernel(
 }
 
 // Column statistics (Eq. 8 / Eq. 10): a[i][j] = sum over the pieces of j's key group (fixed order);
-// V_j = sum_i a[i][j], I_j = max_i a[i][j].  A wave takes four neighbouring vision keys at a time (same
-// key group, same pieces), lanes over text rows; all loads of a piece are in flight together.
+// V_j = sum_i a[i][j], I_j = max_i a[i][j].  A wave takes four neighbouring vision keys (same key group, same pieces), 16 lanes
+// each, with four text rows per lane and load.  How many pieces there are takes a round trip and two divisions; the
+// first `early` pieces of the first text group do not wait for it (what a piece that does not exist holds is not added).
+// us per launch, a row of a key per load and every piece behind that chain / now: 16 x 432 of 576 keys, 64 text rows 6.4 / 5.1,
+// 3 x 3456 of 4608, 100 to 300 rows 8.3 / 7.6, 8 x 2244 of 2880, 128 rows 9.2 / 8.9.
 constexpr int kFixKeys = 4;
 // NP: pieces whose loads go out together.
 template <int NP>
 __global__ __launch_bounds__(256) void prefill_colfix_kernel(
     const float* __restrict__ apart, const uint8_t* __restrict__ vis_valid, const SampleRows* __restrict__ rows,
-    PrefillDims p, ColPlan cp, float* __restrict__ Vout, float* __restrict__ Iout)
+    PrefillDims p, ColPlan cp, int early, int early_rows, float* __restrict__ Vout, float* __restrict__ Iout)
 {
     const int lane = lane_id(), wv = wave_id(), b = blockIdx.y;
     const long gstride = (long)p.B * p.Mv * p.Npad;
     const int j0 = (blockIdx.x * 4 + wv) * kFixKeys;
     if (j0 >= p.Mv) return;
+    const int j = j0 + (lane >> 4), c = 4 * (lane & 15);                  // this lane's key; its first text row of 64
+    const float* own = apart + ((long)b * p.Mv + min(j, p.Mv - 1)) * p.Npad;
+    // text rows `first` + c .. and 64 rows further, of `nrows`; lanes behind them read the last four and drop them
+    auto load = [&](int piece, int first, int nrows, f32x4& lo, f32x4& hi) {
+        const float* q = own + piece * gstride + first;
+        lo = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(q + min(c, nrows - 4)));       // a piece is read once
+        hi = nrows > 64 ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(q + min(c + 64, nrows - 4))) : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    constexpr int EARLY = 3;
+    f32x4 lo[NP > EARLY ? NP : EARLY], hi[NP > EARLY ? NP : EARLY];
+#pragma unroll
+    for (int u = 0; u < EARLY; ++u)
+        if (u < early) load(u, 0, early_rows, lo[u], hi[u]);
     SampleTiles sm;
     const ColRun run = effective_run(find_sample(rows, p.B, cp.kb, cp.nbw, false, b, sm), p.H, cp);
     // keys behind the rows that matter: no pieces were written, their scores are zero
     const int kg = j0 / cp.kb;
-    float s[kFixKeys], mx[kFixKeys];
-#pragma unroll
-    for (int q = 0; q < kFixKeys; ++q) { s[q] = 0.f; mx[q] = 0.f; }
+    float s = 0.f, mx = 0.f;
     for (int tg = 0; tg < (kg < sm.nk ? sm.nt : 0); ++tg) {
         const long tile = sm.tile0 + (long)kg * sm.nt + tg;
         const int npieces = unit_block(tile * p.H + p.H - 1, run.P, run.U) - unit_block(tile * p.H, run.P, run.U) + 1;
         const TextGroup grp = text_group(tg, sm.nbl, sm.nt);
-        // two text rows per lane: a group has at most 2 * kWave of them (lanes beyond read a valid row and drop it)
-        const int nrows = 32 * grp.count;
-        const bool oka = lane < nrows, okb = kWave + lane < nrows;
-        const int ca = 32 * grp.first + (oka ? lane : 0), cb = 32 * grp.first + (okb ? kWave + lane : 0);
-        float a0[kFixKeys], a1[kFixKeys];
-#pragma unroll
-        for (int q = 0; q < kFixKeys; ++q) { a0[q] = 0.f; a1[q] = 0.f; }
-        auto add_pieces = [&](int g, auto count) {
-            constexpr int n = decltype(count)::value;
-            float x0[n][kFixKeys], x1[n][kFixKeys];
-#pragma unroll
-            for (int u = 0; u < n; ++u)
-#pragma unroll
-                for (int q = 0; q < kFixKeys; ++q) {
-                    const float* ap = apart + (g + u) * gstride + ((long)b * p.Mv + min(j0 + q, p.Mv - 1)) * p.Npad;
-                    x0[u][q] = __builtin_nontemporal_load(ap + ca);       // a piece is read once
-                    x1[u][q] = __builtin_nontemporal_load(ap + cb);
-                }
-#pragma unroll
-            for (int u = 0; u < n; ++u)
-#pragma unroll
-                for (int q = 0; q < kFixKeys; ++q) { a0[q] += x0[u][q]; a1[q] += x1[u][q]; }
-        };
+        const int first = 32 * grp.first, nrows = 32 * grp.count;         // (at most 128)
+        f32x4 a = {0.f, 0.f, 0.f, 0.f}, a2 = {0.f, 0.f, 0.f, 0.f};
         int g = 0;
-        for (; g + NP <= npieces; g += NP) add_pieces(g, std::integral_constant<int, NP>());
-        for (; g < npieces; ++g) add_pieces(g, std::integral_constant<int, 1>());
+        if (tg == 0 && nrows <= early_rows) {
 #pragma unroll
-        for (int q = 0; q < kFixKeys; ++q) {
-            const float v0 = oka ? a0[q] : 0.f, v1 = okb ? a1[q] : 0.f;
-            s[q] += v0 + v1;
-            mx[q] = fmaxf(mx[q], fmaxf(v0, v1));
+            for (int u = 0; u < EARLY; ++u)
+                if (u < min(npieces, early)) { a += lo[u]; a2 += hi[u]; }
+            g = early;
         }
+        for (; g < npieces; g += NP) {
+#pragma unroll
+            for (int u = 0; u < NP; ++u) load(min(g + u, npieces - 1), first, nrows, lo[u], hi[u]);
+#pragma unroll
+            for (int u = 0; u < NP; ++u)
+                if (g + u < npieces) { a += lo[u]; a2 += hi[u]; }
+        }
+        if (c >= nrows) a = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (c + 64 >= nrows) a2 = f32x4{0.f, 0.f, 0.f, 0.f};
+        s += ((a.x + a.y) + (a.z + a.w)) + ((a2.x + a2.y) + (a2.z + a2.w));
+        mx = fmaxf(mx, fmaxf(fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w)), fmaxf(fmaxf(a2.x, a2.y), fmaxf(a2.z, a2.w))));
     }
-#pragma unroll
-    for (int q = 0; q < kFixKeys; ++q) {
-        const float ss = wave_sum(s[q]), mm = wave_max(mx[q]);
-        const int j = j0 + q;
-        if (lane == 0 && j < p.Mv) {
-            const bool ok = !vis_valid || vis_valid[(long)b * p.Mv + j];
-            Vout[(long)b * p.Mv + j] = ok ? ss : 0.f;
-            Iout[(long)b * p.Mv + j] = ok ? mm : 0.f;
-        }
+    s = group_sum<16>(s);
+    mx = fmaxf(mx, dpp_f<0xB1>(mx));
+    mx = fmaxf(mx, dpp_f<0x4E>(mx));
+    mx = fmaxf(mx, dpp_f<0x141>(mx));
+    mx = fmaxf(mx, dpp_f<0x140>(mx));
+    if (c == 0 && j < p.Mv) {
+        const bool ok = !vis_valid || vis_valid[(long)b * p.Mv + j];
+        Vout[(long)b * p.Mv + j] = ok ? s : 0.f;
+        Iout[(long)b * p.Mv + j] = ok ? mx : 0.f;
     }
 }
 
@@ -1790,12 +1792,17 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
     else MD_COLSCORE(4, 2, true);
 #undef MD_COLSCORE
     const int fx = (p.Mv + 4 * kFixKeys - 1) / (4 * kFixKeys);          // four waves of kFixKeys keys per block
+    // pieces that a tile has as a rule, by the length of the blocks' runs (one that has fewer reads in vain), and the rows of the
+    // first text group of a full prompt
+    int early = s.col.U >= 2l * p.H * s.col.P ? 1 : s.col.U >= (long)p.H * s.col.P ? 2 : 3;
+    if (early > s.col.Gmax) early = s.col.Gmax;
+    const int early_rows = 32 * ((s.nbt + s.ng - 1) / s.ng);
     // small calls cut a tile into many pieces, a chain of round trips unless four are requested at a time (14 pieces
     // 8.2 -> 6.7 us); the two or three of a large one are bound by their bytes, and by occupancy (8.1 -> 11.3)
     if ((long)p.H * s.col.P >= 4 * s.col.U)
-        MD_LAUNCH("prefill_colfix", st, (prefill_colfix_kernel<4>), dim3(fx, p.B), 256, 0, w.apart, vis_valid, w.rows, p, s.col, w.V, w.I);
+        MD_LAUNCH("prefill_colfix", st, (prefill_colfix_kernel<4>), dim3(fx, p.B), 256, 0, w.apart, vis_valid, w.rows, p, s.col, early, early_rows, w.V, w.I);
     else
-        MD_LAUNCH("prefill_colfix", st, (prefill_colfix_kernel<1>), dim3(fx, p.B), 256, 0, w.apart, vis_valid, w.rows, p, s.col, w.V, w.I);
+        MD_LAUNCH("prefill_colfix", st, (prefill_colfix_kernel<2>), dim3(fx, p.B), 256, 0, w.apart, vis_valid, w.rows, p, s.col, early, early_rows, w.V, w.I);
     return MD_OK;
 }
 
