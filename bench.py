@@ -247,6 +247,7 @@ def stage_bytes(cfg, pipe, counts):
         "encode_scores": B * M * D * e + B * (M + 1) * D * e + B * (M + 1) * cfg.Hc * 4,
         "encode_decide": B * (M + 1) * cfg.Hc * 4 + B * M * 16,
         "encode_emit": B * M * D * e + surv * D * e,
+        "encode_decide_emit": B * (M + 1) * cfg.Hc * 4 + B * M * 16 + B * M * D * e + surv * D * e,      # both in one launch
         "prefill_rowstats": (vrows + 2 * B * N) * H * d * 2,
         "prefill_cstat": B * H * N * 12,
         "prefill_qpack": 2 * B * N * H * d * 2,

@@ -671,8 +671,8 @@ __global__ __launch_bounds__(1024) void encode_decide_kernel(
 // before they are made, so that a third of x on 8 x 2880 tokens, and all of it on a few images, comes in behind their chain
 // of steps, which is what bounds the launch (17 of its 40 thousand cycles on 8 x 2880 tokens are the rows, the decision with its
 // fetch of the numerators the rest).  us per call, a launch for the rows / the deciding blocks: 1 x 576 tokens fp32 15.8 /
-// 13.6, 16 x 576 22.2 / 21.0, 8 x 2880 42.3 / 39.6, 16 x 2880 71.7 / 66.3; 2 x 4608 in 2x2x2 windows 35.1 / 33.0, 8 x 4608 64.3 /
-// 62.2.  Not for windows of more than eight members, whose rows do not fit the registers (3 x 1152 tokens in 3x3 windows
+// 13.4, 16 x 576 22.3 / 20.5, 8 x 2880 42.3 / 39.7, 16 x 2880 71.7 / 65.4; 2 x 4608 in 2x2x2 windows 35.1 / 32.6, 8 x 4608 64.3 /
+// 62.0.  Not for windows of more than eight members, whose rows do not fit the registers (3 x 1152 tokens in 3x3 windows
 // 22.4 / 23.8), nor beyond 5120 tokens, where the LDS of the decisions leaves sixteen waves per CU to copy (2 x 9216 46.5 / 47.1).
 struct EmitArgs {
     const void* x; void* out_x;
@@ -693,9 +693,8 @@ template <int WS>
 __device__ __forceinline__ void emit_load(const EncodeDims& p, const EmitItem& i, const char* xb, int rowb, u32x4 (&v)[WS]) {
     const int off = min(i.c * 16, rowb - 16);        // lanes beyond the row repeat its last vector and drop it
 #pragma unroll
-    for (int m = 0; m < WS; ++m)
-        if (m < p.ws)
-            v[m] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xb + (size_t)max(wave_member(i.tok, m), 0) * rowb + off));
+    for (int m = 0; m < WS; ++m)                     // (members beyond the window repeat its last one)
+        v[m] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xb + (size_t)max(wave_member(i.tok, min(m, p.ws - 1)), 0) * rowb + off));
 }
 // What an item's rows become: row_l: lane m's row (s_row), merged: the window is merged, with okmask its valid members.
 struct EmitFate { int row_l; uint64_t merged, okmask; float mass_l; };
@@ -903,9 +902,9 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
     constexpr bool AHEAD = EMIT && (WS == 4 || IPT <= 2);      // registers allow the first rows to be requested up front
     EmitItem item{};
     u32x4 rowv[WS];
-    if (AHEAD && wv * em.blocks + g < W * em.slices) {
+    if constexpr (AHEAD) {                           // (whatever the case: a wait for anything older could not tell these loads apart)
         const int rowb = p.D * (em.bf16 ? 2 : 4);
-        item = emit_item(p, em, wv * em.blocks + g, lane);
+        item = emit_item(p, em, min(wv * em.blocks + g, W * em.slices - 1), lane);
         emit_load<WS>(p, item, static_cast<const char*>(em.x) + (size_t)b * M * rowb, rowb, rowv);
     }
     MD_DTICK(8);
@@ -1563,7 +1562,7 @@ int encode_merge_impl(
     // Survivors' rows by the deciding blocks (see EmitArgs): as many blocks per sample as have the chip to themselves in one round
     // (more are a second round behind the decisions: 16 x 576 tokens 21.0 us a call with 256 blocks, 26.8 with 384), no more
     // than there are items for their waves.  Two per sample at least (128 x 576 tokens 101.5 us a call with a launch for
-    // the rows, 99.4 without; 200 x 576 159.4 and 166.8).
+    // the rows, 98.3 without; 200 x 576 159.4 and 166.8).
     const int row_slices = (int)(((long)D * xe / 16 + kWave - 1) / kWave);
     const EmitArgs em{x, out_x, (int)min(((long)W * row_slices + 15) / 16, (long)max(kNumCU / B, 1)), row_slices, xbf ? 1 : 0,
                       FastDiv::make(B), FastDiv::make(row_slices)};
@@ -1574,7 +1573,7 @@ int encode_merge_impl(
                        !over(out_mass, 4 * tokens) && !over(out_is_key, tokens) && !over(out_valid, tokens) &&
                        !over(a_cls_out, 4 * tokens) && !over(key_index, 4 * (size_t)B * key_budget);
 #define MD_DECIDE_FAST(IPT_, WS_, E_)                                                                             \
-    MD_LAUNCH("encode_decide", st, (encode_decide_fast_kernel<IPT_, WS_, E_>), E_ ? B * em.blocks : B, 1024, dlds,                  \
+    MD_LAUNCH(E_ ? "encode_decide_emit" : "encode_decide", st, (encode_decide_fast_kernel<IPT_, WS_, E_>), E_ ? B * em.blocks : B, 1024, dlds,                  \
         p, valid, mass_in, wsp.logits, wsp.cls_part, wsp.sim, tau, key_budget, key_adaptive, key_lambda, key_count,  \
         wsp.wmerged, wsp.dstpos,                                                                                   \
         out_index, out_mass, out_is_key, out_valid, out_count, key_index, a_cls_out, window_sim_out, em)
