@@ -1719,13 +1719,16 @@ struct PrefillWorkspace {
         if (!s.own || s.nbt == 1) return ScoreParts{V, I, 1};
         return ScoreParts{apart, apart + (size_t)s.nbt * p.B * p.Mv, s.nbt};
     }
+    float2* chunk_stats(const PrefillDims& p, const ScorePlan& s) const {
+        return s.partial_in_pieces ? reinterpret_cast<float2*>(apart + 2 * (size_t)s.nbt * p.B * p.Mv) : partial;
+    }
 };
 
 PrefillWorkspace carve_prefill(void* base, int B, int Mv, int N, int H, int Rcap) {
     Carver c(base);
     PrefillWorkspace w;
     const ScorePlan s = plan_scores(B, Mv, N, H, 128);     // (of the sizes only the number of chunks depends on d)
-    const int s64 = plan_scores(B, Mv, N, H, 64).nch, nch = s.nch > s64 ? s.nch : s64;
+    const int s64 = plan_scores(B, Mv, N, H, 64).nch_ws, nch = s.nch_ws > s64 ? s.nch_ws : s64;
     const int Npad = s.nbt * 32;
     w.partial = c.take<float2>((size_t)B * H * nch * Npad);
     w.cstat = c.take<float>((size_t)B * H * Npad);
@@ -1745,11 +1748,12 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
                   const void* k, const uint8_t* vis_valid, const int32_t* txt_len, const float* row_lse, float scale_log2e) {
     const uint16_t* qp = static_cast<const uint16_t*>(q_txt);
     const uint16_t* kp = static_cast<const uint16_t*>(k);
+    float2* const partial = w.chunk_stats(p, s);
     if (!row_lse) {
         const dim3 g1 = s.ng == 1 ? dim3(p.nch, p.H, p.B) : dim3((unsigned)(((long)p.nch * p.H * p.B + 7) / 8 * 8 * s.ng));
 #define MD_ROWSTATS2(NBW_, TW_, ST_, DEEP_)                                                                    \
     MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_kernel<NBW_, TW_, KS, ST_, DEEP_>), g1, 64 * NBW_ * TW_, 0, \
-        qp, kp, vis_valid, txt_len, p, scale_log2e, w.partial, w.cstat, w.qfrag, w.rows)
+        qp, kp, vis_valid, txt_len, p, scale_log2e, partial, w.cstat, w.qfrag, w.rows)
 #define MD_ROWSTATS(NBW_, TW_)                                                                                 \
         do {                                                                                                   \
             if (s.rs_stream) MD_ROWSTATS2(NBW_, TW_, true, false);                                             \
@@ -1758,7 +1762,7 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
         } while (0)
 #define MD_ROWSTATS_WIDE(ST_)                                                                                  \
     MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_wide_kernel<KS, ST_>), g1, 256, 0,                     \
-        qp, kp, vis_valid, txt_len, p, scale_log2e, w.partial, w.cstat, w.qfrag, w.rows)
+        qp, kp, vis_valid, txt_len, p, scale_log2e, partial, w.cstat, w.qfrag, w.rows)
         const bool big = s.rs_waves == 8;
         if (s.rs_wide) { if (s.rs_stream) MD_ROWSTATS_WIDE(true); else MD_ROWSTATS_WIDE(false); }
         else if (s.nbw == 1) { if (big) MD_ROWSTATS(1, 8); else MD_ROWSTATS(1, 4); }
@@ -1770,7 +1774,7 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
 #undef MD_ROWSTATS2
         if (p.nch > 1 && !s.own) {
             const long n = (long)p.B * p.H * p.Npad;
-            MD_LAUNCH("prefill_cstat", st, (prefill_cstat_kernel), (unsigned)((n + 255) / 256), 256, 0, w.partial, txt_len, p, w.cstat);
+            MD_LAUNCH("prefill_cstat", st, (prefill_cstat_kernel), (unsigned)((n + 255) / 256), 256, 0, partial, txt_len, p, w.cstat);
         }
     } else {
         const long items = (long)p.B * p.H * s.nbt;
@@ -1778,7 +1782,7 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
                   row_lse, p, w.qfrag, w.cstat, w.rows);
     }
     if (s.own) {
-        MD_LAUNCH("prefill_colscore", st, (prefill_colown_kernel<KS>), (unsigned)((s.own_blocks + 7) / 8 * 8), 512, 0, w.qfrag, kp, w.cstat, w.partial, vis_valid, txt_len, w.rows,
+        MD_LAUNCH("prefill_colscore", st, (prefill_colown_kernel<KS>), (unsigned)((s.own_blocks + 7) / 8 * 8), 512, 0, w.qfrag, kp, w.cstat, partial, vis_valid, txt_len, w.rows,
                   p, scale_log2e, w.score_parts(p, s).V, w.score_parts(p, s).I);
         return MD_OK;
     }

@@ -50,7 +50,7 @@ MD_PLAN_FN ColRun effective_run(int tiles, int H, ColPlan cp) {
 }
 
 // Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide, own, own_lse; long own_blocks; ColPlan col; int occ; };
+struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; ColPlan col; int occ; };
 
 inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     ScorePlan s;
@@ -63,62 +63,6 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     // valid: 85 against 88).  Up to 64 text rows the line lies lower (3 x 5523, 40 heads, 170 MB: 81 -> 73; 13 x 1029, 110 MB: 49 -> 52)
     const double k_mb = (double)B * Mv * H * d * 2 / 1e6;
     s.rs_stream = k_mb > (s.nbw <= 2 ? 160.0 : 230.0);
-    // Sweep 2 by blocks of one tile (32 keys, 32 text rows, all heads) where they are no more than two rounds, of one block per CU or,
-    // with heads of 64, of two: the blocks of the persistent form hand over their sums through memory and another launch, and
-    // leave most of the chip idle on small calls.  us per call, persistent / single tiles: 1 x 576 keys, 32 text rows 33 / 28, 128 rows
-    // 39 / 28; 14 x 576, 32 rows 64 / 57 (252 blocks), 28 x 576 118 / 111 (504), 2 x 1246, 114 rows, 16 heads 41 / 35 (312); heads of 64, 12 x
-    // 300, 20 rows 28 / 20, 20 x 1000, 28 rows 84 / 72 (640).  Behind that the query fragments, read for every 32 keys, come to more:
-    // 4 x 4248, 25 rows 112 / 119 (532), 8 x 1955, 118 rows 144 / 183 (1984); heads of 64, 3 x 7055, 92 rows 125 / 134 (1989).  (Of
-    // 26 calls of 257 to 512 blocks 20 gain 2 to 15 %, none loses more than 1.5.)
-    const long own_round = d == 64 ? 2l * kNumCU : kNumCU;
-    s.own_blocks = (long)B * ((Mv + 31) / 32) * s.nbt;
-    s.own = s.nbt <= kOwnParts && Mv <= 8192 && s.own_blocks <= 2 * own_round;
-    // (with the caller's row normalisers, K has not been read before: one round, 23 x 181 keys, 45 text rows, 276 blocks 50 / 54)
-    s.own_lse = s.own && s.own_blocks <= own_round;
-    // sweep 1: blocks of four waves (two per CU) or of eight (one per CU; the chunks two small blocks would take meet in
-    // LDS), and the number of key chunks per (sample, head, text group), at least four 128-key units each.  Whole rounds
-    // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start
-    // (5), the keys it takes (ns per key, from alone on the chip to every place taken), the merge kernel for several chunks.
-    // Measured to within 20 % at 17 shapes; before -> after e.g. 13 x 1039 keys, 32 heads, 10 text rows: 36.6 -> 23.1,
-    // 6 x 1152 keys, 384 text rows: 250 -> 49 (in the wide form), 5 x 774 keys, 16 heads, 60 text rows: 14.5 -> 13.1.
-    // (single tiles: the merge of the chunks is part of sweep 2, and a chunk may be shorter; 2 x 576 keys, 128 text rows 36 -> 32)
-    const double merge_us = s.own ? 1.0 : 5.0;
-    const int most = s.own ? kOwnChunks : kMaxChunks, least_units = !s.own ? 4 : s.nbw < 4 ? 1 : 2;
-    const int units = (Mv + N + 127) / 128;
-    const long n = (long)B * H * s.ng;
-    double best = 0;
-    // The wide form takes all calls with several text groups.  With one, K comes from HBM and bounds the sweep: there it only
-    // takes the place of the blocks of four waves at d = 128 (13 x 1039 keys, 32 heads, 128 text rows 43 -> 40, 20 x 576, 40
-    // heads, 70 rows 53 -> 49); against one block of eight waves per head it pays for the merge of two chunks (8 x 2880,
-    // 128 rows 46.6 and 47.5 + 4), and heads of 64 have three smaller blocks per CU (8 x 2000, 128 rows 25 and 28).
-    for (int waves = 4; waves <= (s.ng > 1 ? 4 : 8); waves += 4)
-        for (int nch = 1; nch <= most && (nch == 1 || nch <= units / least_units); ++nch) {
-            const long blocks = n * nch, places = waves == 4 ? (s.nbw == 4 && s.ng == 1 && d == 64 ? 3 : 2) * kNumCU : kNumCU;
-            const double fill = blocks < places ? (double)blocks / places : 1.0;
-            double alone = s.nbw == 1 ? 7.5 : (s.nbw == 2 ? (waves == 8 ? 8.0 : 9.0) : (waves == 8 ? 11.0 : 14.0));
-            double full = waves == 8 ? (s.nbw < 4 ? 11.5 : 16.0) : 21.0;
-            // (heads of 64 with four text blocks: three blocks of four waves share a CU, one of eight waves no better than at
-            // d = 128; 2 x 8661 keys, 64 heads, 95 text rows 49.8 -> 38.6)
-            if (s.nbw == 4 && d == 64) { alone = waves == 8 ? 10.0 : 11.5; full = waves == 8 ? 10.5 : 21.0; }
-            if (s.nbw == 1 && d == 128 && waves == 4 && blocks <= kNumCU && !s.rs_stream) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
-            if (s.nbw == 4 && d == 128 && waves == 4) full = 30.0;
-            const double per_key = alone + (full - alone) * fill;
-            double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? merge_us : 0.0);
-            if (s.ng > 1) {
-                // Several text groups: the last round by itself, at the full rate once a CU has two blocks of it.  Priced by its
-                // share of the places, it looked cheaper than it is: 4 x 5284 keys of 64, 32 heads, 374 text rows in 384 blocks
-                // 80 us, in 768 with the merge 71; 6 x 6000, 256 rows 97 and 86; 3 x 1592 keys of 128, 40 heads, 171 rows 27.6
-                // and 22.8.  At 84 random shapes the sweep and its merge take 2 % less, none more than 3 % more.
-                alone = d == 64 ? 8.0 : 11.0;
-                full = d == 64 ? 13.0 : 18.0;
-                const double keys = 1e-3 * (Mv + N) / nch;
-                const long last = blocks % places;
-                t = (double)(blocks / places) * (4.0 + full * keys) + (last > 0 ? 4.0 + (last > kNumCU ? full : alone) * keys : 0.0) + (nch > 1 ? (s.own ? merge_us : 4.0) : 0.0);
-            }
-            if (best == 0 || t < 0.97 * best) { best = t; s.rs_waves = waves; s.nch = nch; }
-        }
-    s.rs_wide = s.ng > 1 || (s.nbw == 4 && d == 128 && s.rs_waves == 4);
-    s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && !s.rs_stream;
     // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
     ColPlan& c = s.col;
     c.kb = s.nbw == 1 ? 128 : 64;
@@ -141,6 +85,73 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     // are a prefix of their slots bring fewer key groups), beyond that fewer blocks work
     c.Gmax = (int)((2L * H * c.P + c.U - 1) / c.U) + 1;
     if (c.Gmax > H) c.Gmax = H;
+    // Sweep 2 by blocks of one tile (32 keys, 32 text rows, all heads) where they are no more than two rounds, of one block per CU or,
+    // with heads of 64, of two: the blocks of the persistent form hand over their sums through memory and another launch, and
+    // leave most of the chip idle on small calls.  us per call, persistent / single tiles: 1 x 576 keys, 32 text rows 33 / 28, 128 rows
+    // 39 / 28; 14 x 576, 32 rows 64 / 57 (252 blocks), 28 x 576 118 / 111 (504), 2 x 1246, 114 rows, 16 heads 41 / 35 (312); heads of 64, 12 x
+    // 300, 20 rows 28 / 20, 20 x 1000, 28 rows 84 / 72 (640).  Behind that the query fragments, read for every 32 keys, come to more:
+    // 4 x 4248, 25 rows 112 / 119 (532), 8 x 1955, 118 rows 144 / 183 (1984); heads of 64, 3 x 7055, 92 rows 125 / 134 (1989).  (Of
+    // 26 calls of 257 to 512 blocks 20 gain 2 to 15 %, none loses more than 1.5.)
+    const long own_round = d == 64 ? 2l * kNumCU : kNumCU;
+    s.own_blocks = (long)B * ((Mv + 31) / 32) * s.nbt;
+    s.own = s.nbt <= kOwnParts && Mv <= 8192 && s.own_blocks <= 2 * own_round;
+    // (with the caller's row normalisers, K has not been read before: one round, 23 x 181 keys, 45 text rows, 276 blocks 50 / 54)
+    s.own_lse = s.own && s.own_blocks <= own_round;
+    // sweep 1: blocks of four waves (two per CU) or of eight (one per CU; the chunks two small blocks would take meet in
+    // LDS), and the number of key chunks per (sample, head, text group), at least four 128-key units each.  Whole rounds
+    // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start
+    // (5), the keys it takes (ns per key, from alone on the chip to every place taken), the merge kernel for several chunks.
+    // Measured to within 20 % at 17 shapes; before -> after e.g. 13 x 1039 keys, 32 heads, 10 text rows: 36.6 -> 23.1,
+    // 6 x 1152 keys, 384 text rows: 250 -> 49 (in the wide form), 5 x 774 keys, 16 heads, 60 text rows: 14.5 -> 13.1.
+    const int units = (Mv + N + 127) / 128;
+    const long n = (long)B * H * s.ng;
+    // The wide form takes all calls with several text groups.  With one, K comes from HBM and bounds the sweep: there it only
+    // takes the place of the blocks of four waves at d = 128 (13 x 1039 keys, 32 heads, 128 text rows 43 -> 40, 20 x 576, 40
+    // heads, 70 rows 53 -> 49); against one block of eight waves per head it pays for the merge of two chunks (8 x 2880,
+    // 128 rows 46.6 and 47.5 + 4), and heads of 64 have three smaller blocks per CU (8 x 2000, 128 rows 25 and 28).
+    auto pick = [&](double merge_us, int most, int least_units) {
+        double best = 0;
+        for (int waves = 4; waves <= (s.ng > 1 ? 4 : 8); waves += 4)
+            for (int nch = 1; nch <= most && (nch == 1 || nch <= units / least_units); ++nch) {
+                const long blocks = n * nch, places = waves == 4 ? (s.nbw == 4 && s.ng == 1 && d == 64 ? 3 : 2) * kNumCU : kNumCU;
+                const double fill = blocks < places ? (double)blocks / places : 1.0;
+                double alone = s.nbw == 1 ? 7.5 : (s.nbw == 2 ? (waves == 8 ? 8.0 : 9.0) : (waves == 8 ? 11.0 : 14.0));
+                double full = waves == 8 ? (s.nbw < 4 ? 11.5 : 16.0) : 21.0;
+                // (heads of 64 with four text blocks: three blocks of four waves share a CU, one of eight waves no better than at
+                // d = 128; 2 x 8661 keys, 64 heads, 95 text rows 49.8 -> 38.6)
+                if (s.nbw == 4 && d == 64) { alone = waves == 8 ? 10.0 : 11.5; full = waves == 8 ? 10.5 : 21.0; }
+                if (s.nbw == 1 && d == 128 && waves == 4 && blocks <= kNumCU && !s.rs_stream) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
+                if (s.nbw == 4 && d == 128 && waves == 4) full = 30.0;
+                const double per_key = alone + (full - alone) * fill;
+                double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? merge_us : 0.0);
+                if (s.ng > 1) {
+                    // Several text groups: the last round by itself, at the full rate once a CU has two blocks of it.  Priced by its
+                    // share of the places, it looked cheaper than it is: 4 x 5284 keys of 64, 32 heads, 374 text rows in 384 blocks
+                    // 80 us, in 768 with the merge 71; 6 x 6000, 256 rows 97 and 86; 3 x 1592 keys of 128, 40 heads, 171 rows 27.6
+                    // and 22.8.  At 84 random shapes the sweep and its merge take 2 % less, none more than 3 % more.
+                    alone = d == 64 ? 8.0 : 11.0;
+                    full = d == 64 ? 13.0 : 18.0;
+                    const double keys = 1e-3 * (Mv + N) / nch;
+                    const long last = blocks % places;
+                    t = (double)(blocks / places) * (4.0 + full * keys) + (last > 0 ? 4.0 + (last > kNumCU ? full : alone) * keys : 0.0) + (nch > 1 ? 4.0 : 0.0);
+                }
+                if (best == 0 || t < 0.97 * best) { best = t; s.rs_waves = waves; s.nch = nch; }
+            }
+    };
+    pick(5.0, kMaxChunks, 4);
+    s.nch_ws = s.nch;
+    s.partial_in_pieces = false;
+    if (s.own) {
+        // single tiles: the merge of the chunks is part of sweep 2, and a chunk may be shorter (2 x 576 keys, 128 text rows 36 -> 32 us).  The
+        // workspace stays as it is: more chunks than the persistent form would take have their statistics in the memory of the
+        // pieces, behind V and I, as many as fit there.
+        const long Npad = 32l * s.nbt, fit = ((long)s.col.Gmax * Mv * Npad - 2l * s.nbt * Mv) / (2l * H * Npad);
+        const long most = fit > s.nch_ws ? fit : s.nch_ws;
+        pick(1.0, most < kOwnChunks ? (int)most : kOwnChunks, s.nbw < 4 ? 1 : 2);
+        s.partial_in_pieces = s.nch > s.nch_ws;
+    }
+    s.rs_wide = s.ng > 1 || (s.nbw == 4 && d == 128 && s.rs_waves == 4);
+    s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && !s.rs_stream;
     return s;
 }
 
