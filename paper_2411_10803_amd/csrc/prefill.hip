@@ -1168,7 +1168,7 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
 // come out of it, of each text block by itself (the selection adds them up).  The row statistics of several key chunks are merged here.
 // Bound by what a CU can take in: half a megabyte of K and query fragments per block at 64 bytes per clock, 3.6 us, asked for as far
 // ahead as the registers hold (four heads' fragments; one head's: 1 x 3810 keys, 18 text rows, 16 heads 34.6 -> 33.2 us a call).
-// 1 x 576 keys, 32 text rows: 7.1 + 6.1 us in the persistent form and its sum of the pieces, 11.7 here, and 8.8 -> 6.7 for the
+// 1 x 576 keys, 32 text rows: 7.1 + 6.1 us in the persistent form and its sum of the pieces, 10.6 here, and 8.8 -> 7 for the
 // first sweep, whose chunks may be shorter.
 template <int KS>
 __global__ __launch_bounds__(512) void prefill_colown_kernel(
