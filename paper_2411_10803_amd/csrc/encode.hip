@@ -671,9 +671,11 @@ __global__ __launch_bounds__(1024) void encode_decide_kernel(
 // before they are made, so that a third of x on 8 x 2880 tokens, and all of it on a few images, comes in behind their chain
 // of steps, which is what bounds the launch (17 of its 40 thousand cycles on 8 x 2880 tokens are the rows, the decision with its
 // fetch of the numerators the rest).  us per call, a launch for the rows / the deciding blocks: 1 x 576 tokens fp32 15.8 /
-// 13.4, 16 x 576 22.3 / 20.5, 8 x 2880 42.3 / 39.7, 16 x 2880 71.7 / 65.4; 2 x 4608 in 2x2x2 windows 35.1 / 32.6, 8 x 4608 64.3 /
-// 62.0.  Not for windows of more than eight members, whose rows do not fit the registers (3 x 1152 tokens in 3x3 windows
-// 22.4 / 23.8), nor beyond 5120 tokens, where the LDS of the decisions leaves sixteen waves per CU to copy (2 x 9216 46.5 / 47.1).
+// 13.4, 16 x 576 22.3 / 20.5, 8 x 2880 42.3 / 39.7, 16 x 2880 71.7 / 65.4.  Not for windows of more than eight members, whose rows
+// do not fit the registers (3 x 1152 tokens in 3x3 windows 22.4 / 23.8), nor beyond 3072 tokens: a call by itself still gains
+// up to 5120 (4 x 4608 in 2x2x2 windows 42.8 / 42.0), but the longer decisions on all CUs are in the way of other streams' kernels
+// (that workload's whole step, two batches in flight 128 / 135, four 112 / 117; 8 x 2880 165 / 163 and 169 / 169); and with
+// ready-made scores it loses by itself too (2 x 9216 46.5 / 47.1).
 struct EmitArgs {
     const void* x; void* out_x;
     int blocks, slices, bf16;                        // blocks per sample, slices per row, element type
@@ -1569,7 +1571,7 @@ int encode_merge_impl(
     // (not where a small output lies over an input of theirs: a block may still read what another one writes)
     const size_t tokens = (size_t)B * M;
     auto over = [&](const void* out, size_t n) { return overlaps(out, n, mass_in, 4 * tokens) || overlaps(out, n, valid, tokens); };
-    const bool emits = fast_ok && ws <= 8 && 2 * B <= kNumCU && row_slices <= 4096 && !over(out_index, 4 * tokens) &&
+    const bool emits = fast_ok && M <= 3072 && ws <= 8 && 2 * B <= kNumCU && row_slices <= 4096 && !over(out_index, 4 * tokens) &&
                        !over(out_mass, 4 * tokens) && !over(out_is_key, tokens) && !over(out_valid, tokens) &&
                        !over(a_cls_out, 4 * tokens) && !over(key_index, 4 * (size_t)B * key_budget);
 #define MD_DECIDE_FAST(IPT_, WS_, E_)                                                                             \
@@ -1578,14 +1580,18 @@ int encode_merge_impl(
         wsp.wmerged, wsp.dstpos,                                                                                   \
         out_index, out_mass, out_is_key, out_valid, out_count, key_index, a_cls_out, window_sim_out, em)
 #define MD_DECIDE_FAST_WS(IPT_)                                                                               \
-    do {                                                                                                     \
-        if (ws <= 4) { if (emits) MD_DECIDE_FAST(IPT_, 4, true); else MD_DECIDE_FAST(IPT_, 4, false); }      \
-        else if (ws <= 8) { if (emits) MD_DECIDE_FAST(IPT_, 8, true); else MD_DECIDE_FAST(IPT_, 8, false); } \
-        else MD_DECIDE_FAST(IPT_, 16, false);                                                                \
-    } while (0)
+    do { if (ws <= 4) MD_DECIDE_FAST(IPT_, 4, false); else if (ws <= 8) MD_DECIDE_FAST(IPT_, 8, false); else MD_DECIDE_FAST(IPT_, 16, false); } while (0)
+#define MD_DECIDE_EMIT_WS(IPT_)                                                                               \
+    do { if (ws <= 4) MD_DECIDE_FAST(IPT_, 4, true); else MD_DECIDE_FAST(IPT_, 8, true); } while (0)
+    if (emits) {
+        if (M <= 1024) MD_DECIDE_EMIT_WS(1);
+        else if (M <= 2048) MD_DECIDE_EMIT_WS(2);
+        else MD_DECIDE_EMIT_WS(3);                           // e.g. five tiles of 24 x 24 tokens
+        return check_launch("encode_merge");
+    }
     if (fast_ok && M <= 1024) MD_DECIDE_FAST_WS(1);
     else if (fast_ok && M <= 2048) MD_DECIDE_FAST_WS(2);
-    else if (fast_ok && M <= 3072) MD_DECIDE_FAST_WS(3);     // e.g. five tiles of 24 x 24 tokens
+    else if (fast_ok && M <= 3072) MD_DECIDE_FAST_WS(3);
     else if (fast_ok && M <= 4096) MD_DECIDE_FAST_WS(4);
     else if (fast_ok) MD_DECIDE_FAST_WS(5);                  // e.g. eight frames of 24 x 24 tokens
     else if (large_ok) {
@@ -1613,9 +1619,9 @@ int encode_merge_impl(
             p, valid, mass_in, wsp.logits, wsp.cls_part, wsp.sim, tau, key_budget, key_adaptive, key_lambda, key_count,
             wsp.acls, wsp.iskey, wsp.wmerged, wsp.dstpos,
             out_index, out_mass, out_is_key, out_valid, out_count, key_index, a_cls_out, window_sim_out);
+#undef MD_DECIDE_EMIT_WS
 #undef MD_DECIDE_FAST_WS
 #undef MD_DECIDE_FAST
-    if (emits) return check_launch("encode_merge");
     if (x_dtype == MD_BF16) MD_LAUNCH("encode_emit", st, (encode_emit_kernel<true>), wgrid, 64 * kEncWaves, 0, x, valid, mass_in, p, wsp.wmerged, wsp.dstpos, out_x);
     else MD_LAUNCH("encode_emit", st, (encode_emit_kernel<false>), wgrid, 64 * kEncWaves, 0, x, valid, mass_in, p, wsp.wmerged, wsp.dstpos, out_x);
     return check_launch("encode_merge");
