@@ -329,22 +329,27 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
         id[t] = ii[j];
         pbyte[t] = pi[j];
     }
-    const __amdgpu_buffer_rsrc_t rlog = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lb), 0, ahead * H * 4, 0x00020000);
-    const int wave_off = wv * kWave * H * 4, lane_off = lane * 16;       // bytes of the wave's 64 entries, of the lane within them
-    auto request = [&](int off, int imm) -> f32x4 {
-        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rlog, lane_off + imm, off, 0));
+    auto range_from = [&](int entry) -> __amdgpu_buffer_rsrc_t {         // (uniform over the wave)
+        const LogitRange r = logit_range(entry, ahead, H);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lb + r.first), 0, r.bytes, 0x00020000);
+    };
+    auto request = [&](__amdgpu_buffer_rsrc_t from, int byte) -> f32x4 {
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(from, byte, 0, 0));
     };
 #pragma unroll
-    for (int t = 0; t < PFR; ++t)
+    for (int t = 0; t < PFR; ++t) {
+        const __amdgpu_buffer_rsrc_t from = range_from(t * 1024 + wv * kWave);
 #pragma unroll
-        for (int u = 0; u < LPE; ++u) lpf[t][u] = request(t * 1024 * H * 4 + wave_off, u * 1024);
+        for (int u = 0; u < LPE; ++u) lpf[t][u] = request(from, logit_vector(lane, u, 0, H));
+    }
     // LPE = 0: the wave's first 64 entries, 32 at a time, where they are no more than five vectors per lane
     const int vpe = H >> 2;
     if (LPE == 0 && vpe <= 10) {
+        const __amdgpu_buffer_rsrc_t from = range_from(wv * kWave);
 #pragma unroll
         for (int r = 0; r < 2; ++r)
 #pragma unroll
-            for (int u = 0; u < 5; ++u) hpf[r][u] = request(wave_off + r * 32 * H * 4, u * 1024);
+            for (int u = 0; u < 5; ++u) hpf[r][u] = request(from, logit_vector(lane, u, 32 * r, H));
     }
     // the logits kernel's partial statistics, as they lie in memory: thread = (slice of its blocks, head), heads contiguous
     const uint32_t hmul = (1u << 20) / (uint32_t)H + 1u;                 // x / H = x * hmul >> 20 for x <= 1024

@@ -1,5 +1,6 @@
-// How the row moves of a cache cut are shaped into pieces and how the blocks of the move launch come by them: the
-// arithmetic of the host and of the kernel.  Without any HIP header, so that a CPU test can compile it and claim its way through.
+// How the row moves of a cache cut are shaped into pieces and how the blocks of the move launch come by them, and which logits
+// the selection asks for ahead: the arithmetic of the host and of the kernels.  Without any HIP header, so that a CPU test can
+// compile it, claim its way through and follow every request.
 #pragma once
 #include <stdint.h>
 
@@ -71,6 +72,17 @@ MD_PLAN_FN int claim_counters(int blocks) { return blocks < kClaims ? blocks : k
 MD_PLAN_FN uint64_t claimed_piece(int blocks, int c, uint32_t n) {
     return (uint64_t)n * (uint32_t)claim_counters(blocks) + (uint32_t)(blocks + c);
 }
+
+// What a wave of the selection asks for of a sample's logits [.., H] in one go: the vectors of the entries from `entry` on, up to
+// entry `ahead`, as the base and the range of a buffer of its own.  The wave's place is in the base and not in the scalar offset of
+// the loads: that one is not part of what is compared with the range, or wraps round where it is larger.
+struct LogitRange { long first; int bytes; };        // first float; bytes that may be read from it on
+MD_PLAN_FN LogitRange logit_range(int entry, int ahead, int H) {
+    const int e = entry < ahead ? entry : ahead;
+    return LogitRange{(long)e * H, (ahead - e) * H * 4};
+}
+// byte of a lane's u-th vector, `entry` entries further on
+MD_PLAN_FN int logit_vector(int lane, int u, int entry, int H) { return lane * 16 + u * 1024 + entry * H * 4; }
 
 }  // namespace
 }  // namespace md

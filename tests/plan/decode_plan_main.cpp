@@ -1,5 +1,7 @@
 // CPU check of the move launch's claims (csrc/decode_plan.hpp): whatever entries a cache cut keeps, no more rows move than the
 // host reckons with, and blocks that claim in any order take every piece exactly once, also where blocks are few or layers many.
+// And of the selection's requests: a wave's range ends with the last entry that may be asked for, wherever it begins, and what lies
+// before that is all there.
 #include <stdio.h>
 #include <initializer_list>
 #include <random>
@@ -72,6 +74,32 @@ int main() {
                 ok &= behind >> 32 != 0 || claimed_piece(kMoveBlocks, c, (uint32_t)behind) >= all;
             }
             if (!ok && ++bad <= 10) printf("%u pieces in each of %d layers\n", total, layers);
+        }
+    for (int H = 4; H <= 128; H += 4)
+        for (int ahead : {1, 2, 31, 32, 63, 64, 65, 66, 130, 1000, 1023, 1024, 1025, 1088, 2047, 2048, 3000, 8192}) {
+            const int vpe = H / 4;
+            const long end = (long)ahead * H;                                  // floats that may be read
+            const bool by_lanes = vpe == 1 || vpe == 2 || vpe == 4 || vpe == 8;
+            bool ok = true;
+            for (int round = 0; round < (by_lanes ? 2 : 1); ++round)
+                for (int wave = 0; wave < 16; ++wave) {
+                    const int e0 = round * 1024 + wave * 64;
+                    const LogitRange r = logit_range(e0, ahead, H);
+                    ok &= r.first >= 0 && r.bytes >= 0 && r.first + r.bytes / 4 <= end && r.bytes % 16 == 0;
+                    std::vector<char> got(64 * vpe, 0);
+                    for (int step = 0; step < (by_lanes ? 1 : 2); ++step)
+                        for (int u = 0; u < (by_lanes ? vpe : 5); ++u)
+                            for (int lane = 0; lane < 64; ++lane) {
+                                const int byte = logit_vector(lane, u, 32 * step, H);
+                                ok &= byte >= 0;
+                                if (byte + 16 > r.bytes) continue;             // reads as zero
+                                if (byte / 16 < 64 * vpe) got[byte / 16] = 1;
+                            }
+                    if (!by_lanes && vpe > 10) continue;                       // asked for later
+                    for (int x = 0; x < 64 * vpe; ++x)
+                        if (e0 + x / vpe < ahead) ok &= got[x] == 1;
+                }
+            if (!ok && ++bad <= 10) printf("requests of %d heads up to entry %d\n", H, ahead);
         }
     printf("%ld cuts, %ld wrong\n", cuts, bad);
     return bad != 0;
