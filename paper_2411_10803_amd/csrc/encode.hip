@@ -12,6 +12,7 @@
 //                        where several blocks per sample make the decisions and write the rows behind them
 #include "md_device.hpp"
 #include "md_host.hpp"
+#include "encode_plan.hpp"
 
 #include <mutex>
 
@@ -836,21 +837,20 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
 #pragma unroll
         for (int u = 0; u < NPB; ++u) pv[u] = pp[min(lane + u * kWave, gps - 1)];
     }
-    // Numerators of the tokens tid + 1024*t: the 16 heads of a token are 64 consecutive bytes, four
-    // 16-byte buffer loads (the token's offset in a vector register, the quarter's and the batch's in the
-    // instruction and a scalar; tokens beyond M and heads beyond Hc fall outside the buffer's range and
-    // read as zero).  The scores change hands through LDS afterwards.
+    // Numerators of the tokens tid + 1024*t: the 16 heads of a token are 64 consecutive bytes, four 16-byte buffer loads (tokens
+    // beyond M and heads beyond Hc fall outside the buffer's range and read as zero: see numerator_vector).  The scores change
+    // hands through LDS afterwards.
     constexpr int PT = IPT < 4 ? IPT : 4;            // tokens per batch
-    const int nrec = M * p.Hc * 4;
-    const __amdgpu_buffer_rsrc_t rnum = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lg + p.Hc), 0, nrec, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rnum = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lg + p.Hc), 0, numerator_bytes(M, p.Hc), 0x00020000);
     f32x4 xl[PT][4];
     auto request_numerators = [&](int t0) {
 #pragma unroll
         for (int t = 0; t < PT; ++t)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                xl[t][q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                    rnum, 4 * q < p.Hc ? tid * p.Hc * 4 + 16 * q : nrec, (t0 + t) * 1024 * p.Hc * 4, 0));
+                if (t0 + t < IPT)
+                    xl[t][q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                        rnum, numerator_vector(tid, t0 + t, q, M, p.Hc), 0, 0));
     };
     bool ok[IPT];
     float mass[IPT], simv[IPT];
@@ -945,6 +945,7 @@ __global__ __launch_bounds__(1024) void encode_decide_fast_kernel(
             if (t0 > 0) request_numerators(t0);
 #pragma unroll
             for (int t = 0; t < PT; ++t) {
+                if (t0 + t >= IPT) continue;
                 const int j = tid + 1024 * (t0 + t);
                 const f32x4* fr = reinterpret_cast<const f32x4*>(s_f + (size_t)(min(j, M - 1) + 1) / kClsRows * PRE);
                 float a = 0.f;
