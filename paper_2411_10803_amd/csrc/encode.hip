@@ -1569,12 +1569,10 @@ int encode_merge_impl(
     const int row_slices = (int)(((long)D * xe / 16 + kWave - 1) / kWave);
     const EmitArgs em{x, out_x, (int)min(((long)W * row_slices + 15) / 16, (long)max(kNumCU / B, 1)), row_slices, xbf ? 1 : 0,
                       FastDiv::make(B), FastDiv::make(row_slices)};
-    // (not where a small output lies over an input of theirs: a block may still read what another one writes)
-    const size_t tokens = (size_t)B * M;
-    auto over = [&](const void* out, size_t n) { return overlaps(out, n, mass_in, 4 * tokens) || overlaps(out, n, valid, tokens); };
-    const bool emits = fast_ok && M <= 3072 && ws <= 8 && 2 * B <= kNumCU && row_slices <= 4096 && !over(out_index, 4 * tokens) &&
-                       !over(out_mass, 4 * tokens) && !over(out_is_key, tokens) && !over(out_valid, tokens) &&
-                       !over(a_cls_out, 4 * tokens) && !over(key_index, 4 * (size_t)B * key_budget);
+    // (not where an output lies over an input of theirs: a block may still read what another one writes)
+    const EncodeOutputs written{out_x, out_index, out_mass, out_is_key, out_valid, out_count, key_index, key_count, a_cls_out, window_sim_out};
+    const bool emits = fast_ok && M <= 3072 && ws <= 8 && 2 * B <= kNumCU && row_slices <= 4096 &&
+                       !outputs_over(written, B, M, W, D * xe, key_budget, mass_in, valid);
 #define MD_DECIDE_FAST(IPT_, WS_, E_)                                                                             \
     MD_LAUNCH(E_ ? "encode_decide_emit" : "encode_decide", st, (encode_decide_fast_kernel<IPT_, WS_, E_>), E_ ? B * em.blocks : B, 1024, dlds,                  \
         p, valid, mass_in, wsp.logits, wsp.cls_part, wsp.sim, tau, key_budget, key_adaptive, key_lambda, key_count,  \

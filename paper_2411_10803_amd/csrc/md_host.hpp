@@ -7,6 +7,7 @@
 #include <stdio.h>
 
 #include "../../include/mustdrop.h"
+#include "md_overlap.hpp"
 
 namespace md {
 
@@ -15,12 +16,6 @@ int fail(int code, const char* fmt, ...);   // formats into the buffer, returns 
 void clear_error();
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
-inline bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
-    if (!a || !b || na == 0 || nb == 0) return false;
-    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
-    return pa < pb + nb && pb < pa + na;
-}
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 

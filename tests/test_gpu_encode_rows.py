@@ -43,7 +43,7 @@ def test_rows(B, M, win, D, bf16, extras):
 
 
 def test_rows_with_outputs_over_inputs():
-    """Masses and flags that are written over the ones read (nothing merges, so that a launch of its own gives the rows)."""
+    """Masses that are written over the ones read (nothing merges, so that a launch of its own gives the rows)."""
     import torch
     import paper_2411_10803_amd as md
     B, M, D = 2, 700, 64
@@ -54,3 +54,31 @@ def test_rows_with_outputs_over_inputs():
     out = md.mustdrop_encode_merge(x, None, None, mass, None, 1, 1, M, 1, 1, 2, 2.0, 0)
     got = md.mustdrop_encode_merge(x, None, None, mass, None, 1, 1, M, 1, 1, 2, 2.0, 0, out=dict(out, out_mass=mass))
     assert torch.equal(got["out_mass"], want) and torch.equal(got["out_x"], x) and torch.equal(out["out_x"], x)
+
+
+@pytest.mark.parametrize("name", ["out_mass", "out_index", "out_is_key", "out_valid", "out_count", "key_index", "key_count", "a_cls", "window_sim"])
+def test_every_output_over_the_masses(name):
+    """The same for each output, with tokens missing, so that what is written differs from what was there: the decisions are one
+    block's, and the rows have a launch of their own."""
+    import torch
+    import paper_2411_10803_amd as md
+    from paper_2411_10803_amd import binding
+    M, D, keys = 700, 64, 40
+    rng = np.random.default_rng(6)
+    dev = lambda a: torch.from_numpy(a).cuda()                                                       # noqa: E731
+    x, q, k = (dev(rng.standard_normal(s, dtype=np.float32)) for s in ((1, M, D), (1, 4, 16), (1, 1 + M, 4, 16)))
+    valid = dev((rng.random((1, M)) > 0.3).astype(np.uint8))
+    mass = dev(rng.integers(1, 5, size=(1, M)).astype(np.float32))
+    call = lambda m, out=None: md.mustdrop_encode_merge_adaptive(x, q, k, m, valid, 1, 1, M, 1, 1, 2, 2.0, 1.0, keys, out=out)  # noqa: E731
+    want = {n: t.clone() for n, t in call(mass.clone()).items() if n != "workspace"}
+    n = int(want["out_count"][0])
+    assert n < 600
+    fresh = {n_: torch.zeros_like(t) for n_, t in want.items()}
+    fresh[name] = mass.view(-1).view(want[name].dtype)[:want[name].numel()].view(want[name].shape)
+    binding.profile_start()
+    got = call(mass, fresh)
+    torch.cuda.synchronize()
+    assert "encode_emit" in binding.profile_stop()
+    for n_, t in want.items():
+        rows = n if n_ in ("out_x", "out_index", "out_mass", "out_is_key") else t.shape[1] if t.dim() > 1 else 1
+        assert torch.equal(got[n_][:, :rows] if t.dim() > 1 else got[n_], t[:, :rows] if t.dim() > 1 else t), n_
