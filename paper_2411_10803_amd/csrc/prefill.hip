@@ -1271,7 +1271,7 @@ __global__ __launch_bounds__(512) void prefill_colown_kernel(
             a.y += x.y;
         }
         v_sum = group_sum<16>(a.x + a.y);
-        i_max = fmaxf(a.x, a.y);
+        i_max = fmaxf(0.f, fmaxf(a.x, a.y));         // (of scores that are not numbers, 0: see prefill_colfix_kernel)
         i_max = fmaxf(i_max, dpp_f<0xB1>(i_max));
         i_max = fmaxf(i_max, dpp_f<0x4E>(i_max));
         i_max = fmaxf(i_max, dpp_f<0x141>(i_max));

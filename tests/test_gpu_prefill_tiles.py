@@ -53,3 +53,27 @@ def test_single_tiles(B, Mv, N, H, d, head_major, mask, with_lse):
     g = harness.outputs_to_host(out)
     o = oracle.prefill_filter(t["q_txt"], t["k"], t["v"], t["hidden"], vis, txt_len, None, Mv, scale, mode, budget, gamma, alpha, R)
     check_prefill(g, o, t, Mv, vis, None, mode, budget, gamma, alpha, R)
+
+
+# a key whose K row is no number in one head: its V is none either, and the maximum over scores that are none is 0, in both forms
+# of the sweep (30 images are 540 blocks of single tiles, beyond two rounds)
+@pytest.mark.parametrize("B", [1, 3, 30])
+@pytest.mark.parametrize("with_lse", [False, True])
+def test_key_row_that_is_no_number(B, with_lse):
+    from paper_2411_10803_amd import harness
+    cfg = wl.tiny(wl.CONFIGS[2], B=B, T=1, Hg=24, Wg=24, N=32, H=3, d=128, C=8)
+    t = wl.prefill_inputs(cfg)
+    Mv, scale = cfg.M, 1.0 / np.sqrt(128)
+    lse = normalisers(t, Mv, np.ones((B, Mv), np.uint8), scale) if with_lse else None
+    call = lambda: harness.prefill_on_gpu(t, Mv, None, None, None, scale, FILTER_BUDGET, 50, 1.0 / Mv, 0.1, 50, row_lse=lse)  # noqa: E731
+    usual = call()
+    t["k"][0, 70, 1, 5] = 0x7FC0
+    g = call()
+    for n, there in (("score_global", np.nan), ("score_indiv", 0.0)):
+        if with_lse:                                                             # the other keys' scores do not depend on this one
+            usual[n][0, 70] = there
+            np.testing.assert_array_equal(g[n], usual[n])
+        else:
+            np.testing.assert_array_equal(g[n][0, 70], there)
+            assert np.isfinite(np.delete(g[n][0], 70)).all()
+            np.testing.assert_array_equal(g[n][1:], usual[n][1:])
