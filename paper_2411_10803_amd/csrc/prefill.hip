@@ -1289,9 +1289,10 @@ __global__ __launch_bounds__(512) void prefill_colown_kernel(
 // Column statistics (Eq. 8 / Eq. 10): a[i][j] = sum over the pieces of j's key group (fixed order);
 // V_j = sum_i a[i][j], I_j = max_i a[i][j].  A wave takes four neighbouring vision keys (same key group, same pieces), 16 lanes
 // each, with four text rows per lane and load.  How many pieces there are takes a round trip and two divisions; the
-// first `early` pieces of the first text group do not wait for it (what a piece that does not exist holds is not added).
-// us per launch, a row of a key per load and every piece behind that chain / now: 16 x 432 of 576 keys, 64 text rows 6.4 / 5.1,
-// 3 x 3456 of 4608, 100 to 300 rows 8.3 / 7.6, 8 x 2244 of 2880, 128 rows 9.2 / 8.9.
+// first `early` pieces of the first text group wait only for the sample's rows to reach the keys at all (what a piece that does
+// not exist holds is not added; slots behind the last valid one have none, and reading there all the same took 8 x 950 of 2880
+// keys 8.8 us).  us per launch, a row of a key per load and every piece behind that chain / now: 16 x 432 of 576 keys, 64 text
+// rows 5.8 / 4.3, 3 x 3456 of 4608, 100 to 300 rows 8.8 / 8.0, 8 x 2160 of 2880, 128 rows 8.4 / 7.7, 8 x 950 6.9 / 5.8.
 constexpr int kFixKeys = 4;
 // NP: pieces whose loads go out together.
 template <int NP>
@@ -1315,7 +1316,7 @@ __global__ __launch_bounds__(256) void prefill_colfix_kernel(
     f32x4 lo[NP > EARLY ? NP : EARLY], hi[NP > EARLY ? NP : EARLY];
 #pragma unroll
     for (int u = 0; u < EARLY; ++u)
-        if (u < early) load(u, 0, early_rows, lo[u], hi[u]);
+        if (u < early && j0 < rows[b].vision) load(u, 0, early_rows, lo[u], hi[u]);
     SampleTiles sm;
     const ColRun run = effective_run(find_sample(rows, p.B, cp.kb, cp.nbw, false, b, sm), p.H, cp);
     // keys behind the rows that matter: no pieces were written, their scores are zero
