@@ -94,9 +94,16 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     // 26 calls of 257 to 512 blocks 20 gain 2 to 15 %, none loses more than 1.5.)
     const long own_round = d == 64 ? 2l * kNumCU : kNumCU;
     s.own_blocks = (long)B * ((Mv + 31) / 32) * s.nbt;
-    s.own = s.nbt <= kOwnParts && Mv <= 8192 && s.own_blocks <= 2 * own_round;
+    // A block takes in all heads one after the other on one CU, the persistent form spreads them: with many heads and few blocks that
+    // is the longer way, with heads of 64 from 1.4 times as many on.  us per call, persistent / single tiles, heads of 128: 1 x 576
+    // keys, 32 text rows (18 blocks), 56 heads 37.3 / 36.8, 64 37.2 / 38.0, 96 43.7 / 49.8, 128 49.3 / 58.9; 128 rows (72) 80 heads
+    // 50.6 / 47.8, 96 53.4 / 56.4; 6 x 576, 32 rows (108) 96 85.8 / 85.2, 128 105.8 / 108.4; with the caller's normalisers 1 x 576, 32
+    // rows 48 heads 31.1 / 31.0, 64 33.9 / 35.6; 4000 keys (125) 72 44.8 / 43.4, 80 47.9 / 49.1.  Heads of 64, 18 blocks: 80 34.7 / 33.7, 96
+    // 34.9 / 36.5; 72 blocks 112 44.3 / 43.0.
+    const double heads = d == 64 ? H / 1.4 : H;
+    s.own = s.nbt <= kOwnParts && Mv <= 8192 && s.own_blocks <= 2 * own_round && heads <= 54 + 0.4 * s.own_blocks;
     // (with the caller's row normalisers, K has not been read before: one round, 23 x 181 keys, 45 text rows, 276 blocks 50 / 54)
-    s.own_lse = s.own && s.own_blocks <= own_round;
+    s.own_lse = s.own && s.own_blocks <= own_round && heads <= 46 + 0.22 * s.own_blocks;
     // sweep 1: blocks of four waves (two per CU) or of eight (one per CU; the chunks two small blocks would take meet in
     // LDS), and the number of key chunks per (sample, head, text group), at least four 128-key units each.  Whole rounds
     // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start

@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
     (1, 1, 1, 1, 64, False, False), (2, 31, 33, 3, 128, False, True), (3, 32, 64, 8, 64, True, True), (2, 33, 65, 9, 128, True, False),
     (1, 575, 128, 20, 64, False, True), (4, 130, 97, 7, 128, False, True), (1, 2049, 32, 4, 128, False, True), (2, 700, 100, 2, 64, True, False),
     (16, 1024, 3, 2, 64, False, True), (16, 1025, 30, 2, 128, False, True), (128, 33, 127, 1, 64, False, True), (129, 33, 127, 1, 64, False, False),
-    (1, 8192, 33, 2, 128, False, True), (1, 8193, 5, 2, 128, False, True)])
+    (1, 8192, 33, 2, 128, False, True), (1, 8193, 5, 2, 128, False, True),
+    (1, 200, 40, 96, 64, False, True), (3, 150, 97, 96, 64, True, True), (1, 65, 7, 128, 128, False, False)])   # many heads
 @pytest.mark.parametrize("with_lse", [False, True])
 def test_single_tiles(B, Mv, N, H, d, head_major, mask, with_lse):
     import paper_2411_10803_amd as md
