@@ -1569,9 +1569,16 @@ int encode_merge_impl(
     const int row_slices = (int)(((long)D * xe / 16 + kWave - 1) / kWave);
     const EmitArgs em{x, out_x, (int)min(((long)W * row_slices + 15) / 16, (long)max(kNumCU / B, 1)), row_slices, xbf ? 1 : 0,
                       FastDiv::make(B), FastDiv::make(row_slices)};
+    // And only as long as x stays in the 256 MB Infinity Cache between the scores and the rows: few blocks that wait for their
+    // decisions fetch from HBM more slowly than a launch over the whole chip (64 x 2048 tokens, 268 MB, 181 us a call with a launch for the
+    // rows, 189 without; 112 x 576 fp32, 264 MB, 179 / 190; 42 x 2880, 247 MB, 171 / 177; 48 x 1152 fp32, 226 MB, 157 / 152; 24 x 576 of
+    // 4096 fp32 features, 226 MB, 168 / 160).
+    // Nor where two blocks per sample leave a fifth of the CUs idle and have neither little to write nor enough to make up for it
+    // (86 x 196 tokens 30.6 / 30.9, 86 x 256 36.4 / 37.2, 95 x 196 32.4 / 32.9; 86 x 120 24.2 / 23.1, 86 x 400 51.3 / 50.7, 110 x 256 44.2 / 43.9).
     // (not where an output lies over an input of theirs: a block may still read what another one writes)
     const EncodeOutputs written{out_x, out_index, out_mass, out_is_key, out_valid, out_count, key_index, key_count, a_cls_out, window_sim_out};
-    const bool emits = fast_ok && M <= 3072 && ws <= 8 && 2 * B <= kNumCU && row_slices <= 4096 &&
+    const bool idle = kNumCU / B == 2 && 5 * B < 2 * kNumCU && M > 128 && M <= 256;
+    const bool emits = fast_ok && !idle && M <= 3072 && ws <= 8 && 2 * B <= kNumCU && row_slices <= 4096 && xbytes <= 230000000 &&
                        !outputs_over(written, B, M, W, D * xe, key_budget, mass_in, valid);
 #define MD_DECIDE_FAST(IPT_, WS_, E_)                                                                             \
     MD_LAUNCH(E_ ? "encode_decide_emit" : "encode_decide", st, (encode_decide_fast_kernel<IPT_, WS_, E_>), E_ ? B * em.blocks : B, 1024, dlds,                  \

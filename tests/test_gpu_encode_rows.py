@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
     (3, 1025, (1, 1, 8), 520, True, True), (1, 2049, (1, 1, 5), 264, False, True), (2, 3072, (1, 1, 4), 48, True, False),
     (1, 3073, (1, 1, 7), 40, True, True), (1, 5120, (1, 1, 4), 80, False, True), (1, 5120, (1, 1, 8), 64, True, False),
     (17, 130, (1, 1, 4), 1032, True, True), (128, 37, (1, 1, 2), 32, True, True), (129, 37, (1, 1, 2), 32, True, True),
-    (2, 90, (1, 1, 9), 136, True, True)])
+    (2, 90, (1, 1, 9), 136, True, True), (86, 129, (1, 1, 4), 32, True, True), (102, 256, (1, 1, 2), 16, False, False), (103, 256, (1, 1, 4), 32, True, True)])
 def test_rows(B, M, win, D, bf16, extras):
     from paper_2411_10803_amd import harness
     kt, kh, kw = win
@@ -82,3 +82,28 @@ def test_every_output_over_the_masses(name):
     for n_, t in want.items():
         rows = n if n_ in ("out_x", "out_index", "out_mass", "out_is_key") else t.shape[1] if t.dim() > 1 else 1
         assert torch.equal(got[n_][:, :rows] if t.dim() > 1 else got[n_], t[:, :rows] if t.dim() > 1 else t), n_
+
+
+def test_rows_beyond_the_cache():
+    """240 MB of features in one call, whose rows have a launch of their own, and in two, whose deciding blocks write them."""
+    import torch
+    import paper_2411_10803_amd as md
+    from paper_2411_10803_amd import binding
+    B, M, D, Hc, keys = 102, 576, 1024, 16, 32
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.empty((B, M // 4, 1, D), device="cuda").normal_(generator=g).expand(B, M // 4, 4, D).reshape(B, M, D).clone()
+    x += torch.empty((B, M, D), device="cuda").normal_(generator=g) * (torch.rand((B, M // 4, 1, 1), generator=g, device="cuda") > 0.4).float().expand(
+        B, M // 4, 4, 1).reshape(B, M, 1)
+    q = torch.empty((B, Hc, D // Hc), device="cuda").normal_(generator=g)
+    k = torch.empty((B, 1 + M, Hc, D // Hc), device="cuda").normal_(generator=g)
+    call = lambda a, b: md.mustdrop_encode_merge(x[a:b], q[a:b], k[a:b], None, None, 1, 1, M, 1, 1, 4, 0.85, keys)  # noqa: E731
+    launched, outs = [], []
+    for a, b in ((0, B), (0, B // 2), (B // 2, B)):
+        binding.profile_start()
+        outs.append(call(a, b))
+        torch.cuda.synchronize()
+        launched.append(sorted(binding.profile_stop()))
+    assert "encode_emit" in launched[0] and "encode_decide_emit" in launched[1] and "encode_decide_emit" in launched[2]
+    assert int(outs[0]["out_count"].max()) < M
+    for n in ("out_x", "out_index", "out_mass", "out_is_key", "out_valid", "out_count", "key_index", "a_cls", "window_sim"):
+        assert torch.equal(outs[0][n], torch.cat([outs[1][n], outs[2][n]])), n
