@@ -73,9 +73,10 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     // and with two text blocks when the runs stay long enough (20 units per CU); otherwise one (fewer, longer
     // runs: fewer pieces, fewer prologues; measured faster there)
     s.occ = s.nbw == 4 || (s.nbw == 2 && c.U >= 20L * kNumCU) ? 2 : 1;
-    // (two of them where a single text block would leave three quarters of the CUs idle: 1 x 576 keys 9.2 us for the sweep
-    // + 5.9 for its pieces with four, 7.2 + 6.6 with two; 4 x 576 with 100 text rows 12.9 + 5.6 and 13.4 + 7.1; and 2 x 1121
-    // keys of 64, 32 heads, 28 text rows, with row normalisers: 28.7 and 29.1 for the call)
+    // (two of them where a single text block would leave three quarters of the CUs idle.  Nearly all such calls take single tiles now
+    // and this only sizes their workspace; those of many heads still run so.  Measured on calls that have left: 1 x 576 keys 9.2 us for
+    // the sweep + 5.9 for its pieces with four, 7.2 + 6.6 with two; 4 x 576 with 100 text rows 12.9 + 5.6 and 13.4 + 7.1; and 2 x
+    // 1121 keys of 64, 32 heads, 28 text rows, with row normalisers: 28.7 and 29.1 for the call)
     const long least = s.nbw == 1 && c.U < kNumCU ? 2 : 4;
     long P = (c.U + least - 1) / least;
     if (P > kNumCU * s.occ) P = kNumCU * s.occ;

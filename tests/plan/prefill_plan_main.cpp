@@ -1,8 +1,11 @@
 // CPU check of the column sweep's decomposition (csrc/prefill_plan.hpp): for every number of tiles that the valid vision
 // rows and the text lengths can leave of a plan, no block of the run is empty, every unit lies in the block that
-// unit_block names, and no tile is cut into more pieces than the workspace holds.
+// unit_block names, and no tile is cut into more pieces than the workspace holds.  And of the sweep by single tiles: what it keeps
+// in the memory of the pieces (V and I per text block, the statistics of more chunks than the workspace has room for)
+// fits there, whichever head size the workspace was measured with, and it is taken where its kernels can.
 #include <stdio.h>
 #include <initializer_list>
+#include <random>
 
 #include "../../paper_2411_10803_amd/csrc/prefill_plan.hpp"
 
@@ -36,6 +39,37 @@ int main() {
                             printf("B=%d Mv=%d N=%d H=%d: %ld of %ld tiles, P=%d of %d, Gmax=%d: %s\n", B, Mv, N, H, tiles, all, r.P, c.P, c.Gmax, why);
                     }
                 }
+    std::mt19937 rng(1);
+    long own = 0, behind = 0;
+    auto log_uniform = [&](int lo, int hi) {
+        const double r = (double)rng() / 4294967296.0, lg = r * __builtin_log((double)(hi + 1) / lo);
+        const int v = (int)(lo * __builtin_exp(lg));
+        return v < lo ? lo : (v > hi ? hi : v);
+    };
+    for (int i = 0; i < 300000; ++i) {
+        const int B = log_uniform(1, 200), Mv = log_uniform(1, 10000), N = log_uniform(1, 300), H = log_uniform(1, 128);
+        const ScorePlan both[2] = {plan_scores(B, Mv, N, H, 64), plan_scores(B, Mv, N, H, 128)};
+        const long room = both[0].nch_ws > both[1].nch_ws ? both[0].nch_ws : both[1].nch_ws;          // as the workspace has it
+        const char* why = nullptr;
+        if (both[0].col.Gmax != both[1].col.Gmax || both[0].col.P != both[1].col.P || both[0].nbt != both[1].nbt) why = "sizes by head size";
+        for (const ScorePlan& s : both) {
+            if (s.own_lse && !s.own) why = "with normalisers only";
+            if (!s.own) {
+                if (s.partial_in_pieces || s.nch != s.nch_ws) why = "chunks of the persistent form";
+                continue;
+            }
+            ++own;
+            const long Npad = 32l * s.nbt, pieces = (long)s.col.Gmax * B * Mv * Npad;                // floats
+            const long scores = s.nbt > 1 || s.partial_in_pieces ? 2l * s.nbt * B * Mv : 0, stats = 2l * B * H * s.nch * Npad;
+            if (s.ng != 1 || s.nbt > kOwnParts || Mv > 8192 || s.nch < 1 || s.nch > kOwnChunks || s.own_blocks != (long)B * ((Mv + 31) / 32) * s.nbt) why = "form";
+            else if (scores > pieces) why = "scores";
+            else if (s.partial_in_pieces ? scores + stats > pieces : s.nch > room) why = "chunk statistics";
+            behind += s.partial_in_pieces;
+        }
+        if (why && ++bad <= 10) printf("B=%d Mv=%d N=%d H=%d: %s\n", B, Mv, N, H, why);
+    }
+    if (own < 10000 || behind < 1000) { ++bad; printf("too few single tiles looked at\n"); }
+    printf("%ld plans of single tiles, %ld with statistics behind the scores\n", own, behind);
     printf("%ld plans, %ld runs, %ld wrong\n", plans, runs, bad);
     return bad != 0;
 }

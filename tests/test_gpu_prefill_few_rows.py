@@ -23,7 +23,7 @@ def normalisers(t, Mv, vis, scale):
     return (m[..., 0] + np.log(np.exp(s - m).sum(-1))).astype(np.float32)
 
 
-def check(H, valid, N, txt, with_lse, side=24):
+def check(H, valid, N, txt, with_lse, side=24, pieces=False):
     import torch
     import paper_2411_10803_amd as md
     from paper_2411_10803_amd import binding, harness
@@ -39,9 +39,12 @@ def check(H, valid, N, txt, with_lse, side=24):
     dev = [harness.to_dev(t[n], True) for n in ("q_txt", "k", "v", "hidden")]
     size = binding.prefill_workspace(cfg.B, Mv, N, H, R, "cuda").numel()
     room = torch.full((size + (8 << 20),), 0xFF, dtype=torch.uint8, device="cuda")
+    binding.profile_start()
     out = md.mustdrop_prefill_filter(*dev, harness.to_dev(vis), harness.to_dev(txt_len), None, Mv, scale, FILTER_BUDGET, R,
                                      gamma, alpha, R, row_lse=harness.to_dev(lse), workspace=room[:size])
     torch.cuda.synchronize()
+    launches = binding.profile_stop()
+    assert not pieces or "prefill_colfix" in launches, "meant for the persistent sweep"
     assert bool((room[size:] == 0xFF).all()), "written behind the workspace"
     g = harness.outputs_to_host(out)
     o = oracle.prefill_filter(t["q_txt"], t["k"], t["v"], t["hidden"], vis, txt_len, None, Mv, scale, FILTER_BUDGET, R, gamma,
@@ -71,3 +74,22 @@ def test_more_than_64_samples(N, with_lse):
     valid = rng.integers(1, 145, 70).tolist()
     txt = [0 if b % 9 == 4 else int(rng.integers(1, N + 1)) for b in range(70)]
     check(3, valid, N, txt, with_lse, side=12)
+
+
+# Most of the calls above are small enough for single tiles.  Those below take the persistent form with its pieces: one image
+# with many heads, and batches beyond two rounds of tiles, with one text block per group and with two.
+@pytest.mark.parametrize("with_lse", [False, True])
+@pytest.mark.parametrize("valid", [1, 128, 144, 256])
+@pytest.mark.parametrize("H", [96, 128])
+def test_few_valid_slots_of_one_image_in_pieces(H, valid, with_lse):
+    check(H, [valid], 20, None, with_lse, pieces=True)
+
+
+@pytest.mark.parametrize("B,N,H", [(60, 20, 3), (60, 32, 12), (32, 60, 2), (32, 64, 9)])
+@pytest.mark.parametrize("with_lse", [False, True])
+def test_few_units_of_many_planned(B, N, H, with_lse):
+    rng = np.random.default_rng(B * N)
+    valid = [int(v) for v in rng.choice([1, 2, 31, 64, 128, 130], size=B)]
+    valid[B // 2] = 576
+    txt = [0 if b % 9 == 4 else int(rng.integers(1, N + 1)) for b in range(B)]
+    check(H, valid, N, txt, with_lse, pieces=True)
