@@ -1243,7 +1243,7 @@ __global__ __launch_bounds__(512) void prefill_colown_kernel(
                 const int slot = u & 1;
                 MD_VM_WAIT(NLT);                      // all but the K rows of the next head
                 bf16x8 kf[KS];
-                T::frags(T::frag_base(slots + slot * TILE_BYTES, lane), kf);
+                T::frags_wait(T::frag_base(slots + slot * TILE_BYTES, lane), kf);
                 issue_k(h + 2 * W, slot);
                 const f32x16 acc = score_tile<KS>(kf, q[u].f);
                 const float c = statistic(q[u]);
