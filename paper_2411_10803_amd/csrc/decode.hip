@@ -254,7 +254,8 @@ __device__ __forceinline__ void move_rows(const DecodeDims& p, const KvLayout& l
 // Bound by that chain and by the instructions of sixteen waves on one CU.  In a steady loop one entry leaves: the writer alone works
 // (62 blocks per sample that all read the same logits were in each other's way), the row that will move is under way from
 // the start and the statistics are read as they lie in memory.  us per launch, before / after: 4 x 778 entries of 40
-// heads, head-major 14.1 / 10.2, 64 x 1025 of 32 13.8 / 12.4; per step 16 x 1025 of 32 heads 42.9 / 39.5, 1 x 1025 20.1 / 16.4.
+// heads, head-major 13.2 / 9.4, 64 x 1025 of 32 12.2 / 11.0, 16 x 8001 of 32, whose form spills four registers, 38.2 / 36.5; none
+// leaves: 16 x 1000 of 32 heads 9.0 / 8.2, 64 x 1000 6.9 / 7.6; per step 16 x 1025 of 32 heads 42.9 / 39.5, 1 x 1025 20.1 / 16.4.
 // LPE = lanes per entry = H / 4 where that is a power of two up to 8; 0: any other H that is a multiple of four.
 template <int IPT, int LPE>
 __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
@@ -342,7 +343,8 @@ __global__ __launch_bounds__(1024) void decode_select_fast_kernel(
 #pragma unroll
         for (int u = 0; u < LPE; ++u) lpf[t][u] = request(from, logit_vector(lane, u, 0, H));
     }
-    // LPE = 0: the wave's first 64 entries, 32 at a time, where they are no more than five vectors per lane
+    // LPE = 0: the wave's first 64 entries, 32 at a time, where they are no more than five vectors per lane (with six, eight registers
+    // more: 4 x 778 entries of 44 heads 10.5 -> 10.0 us a launch, but of 36 and 40 heads 9.4 -> 9.7 and 9.8)
     const int vpe = H >> 2;
     if (LPE == 0 && vpe <= 10) {
         const __amdgpu_buffer_rsrc_t from = range_from(wv * kWave);
