@@ -228,9 +228,9 @@ def batches_in_flight(torch, pipe, steps, n):
 # 256 MiB device copy (FETCH_SIZE reads half the bytes moved: factor 2.0; WRITE_SIZE: factor 1.0).
 # The runs and the raw figures are in profiles/hbm_traffic_cfg3_llavanext_b8.txt.
 MEASURED_HBM_TRAFFIC_BYTES = {
-    "prefill_colscore": 190481295, "prefill_rowstats": 173936947, "prefill_compact": 126029899,
-    "encode_scores": 97210268, "encode_decide_emit": 86391389, "prefill_select": 51037432,
-    "prefill_colfix": 35853312, "decode_select": 34964317, "decode_logits": 30719116,
+    "prefill_colscore": 190492564, "prefill_rowstats": 173936945, "prefill_compact": 126029897,
+    "encode_scores": 97180133, "encode_decide_emit": 86400352, "prefill_select": 51049728,
+    "decode_select": 34046309, "decode_logits": 30719242, "prefill_colfix": 28230656,
 }
 
 
