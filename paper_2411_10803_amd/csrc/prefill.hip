@@ -14,7 +14,8 @@
 //                            S, p = exp(s - m)/Z, accumulate the head mean a[i][j] of such a key tile
 //                            in registers; a block's share of a tile is written as one piece
 //   prefill_colfix_kernel    sums a tile's pieces in a fixed order, column sum / max -> V_j, I_j
-//   prefill_colown_kernel    in place of both on small calls: a block takes a tile with all heads
+//   prefill_colown_kernel    in place of both on small calls: a block takes a tile (32 keys, 32 text rows) with all heads
+//   prefill_colrows_kernel   in place of both for up to 64 text rows: a block takes 32 keys with all text rows and heads
 // The N x Mv probability matrix of a head is never written to memory.
 //   prefill_select_kernel    per sample: G, the filter rule (threshold) or radix top-k (budget),
 //                            prefix sum -> kept_index, row map for the copy
@@ -1286,6 +1287,170 @@ __global__ __launch_bounds__(512) void prefill_colown_kernel(
     }
 }
 
+// The same with all text rows of a prompt of up to 64 in a block (ScorePlan::rows; NB text blocks): K is read once, and a head's
+// query fragments once per 32 keys.  Nothing is asked for before it is known which tiles have a valid key (a block that takes
+// loads along for a tile without one holds up those that wait for its CU: 16 x 576 keys at 3/4, 64 rows, 22.0 us that way, 18.3 so),
+// one head's fragments at a time (two heads': 18.3 and 18.0), and the K rows of the next head are what is asked for last, so that the wait
+// for the fragments leaves them under way.
+// Bound by what comes in: with the fragments of the first head kept, 14.8 us, with K from L2 as well 12.3, which is the launch, the
+// plan, the first round trip and the sums; the matrix products and exponentials interleaved instead of one after the other changed
+// nothing.  16 x 576 keys at 3/4, 64 rows, row normalisers: 21.1 + 4.3 us for the persistent form and the sum of its pieces, 19.1 here (3.6
+// TB/s of K and 7 of fragments from L2); 20 rows 18.5 + 4.4 and 14.0.
+// STREAM: K comes by streaming loads.  CHUNKS: the row statistics of several key chunks are merged here.
+template <int KS, int NB, bool STREAM, bool CHUNKS>
+__global__ __launch_bounds__(512) void prefill_colrows_kernel(
+    const bf16x8* __restrict__ qfrag, const uint16_t* __restrict__ k, const float* __restrict__ cstat, const float2* __restrict__ partial,
+    const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ txt_len, const SampleRows* __restrict__ rows, PrefillDims p,
+    float scale_log2e, float* __restrict__ Vout, float* __restrict__ Iout)
+{
+    using T = LdsRows<KS>;
+    constexpr int W = 8, TILE_BYTES = 32 * T::ROWB, NLT = 32 / T::RPL;
+    constexpr int CH = kOwnChunks;
+    __shared__ __attribute__((aligned(1024))) char s_k[W * 2 * TILE_BYTES];
+    const int lane = lane_id(), wv = wave_id(), i = lane & 31;
+    // The tiles that matter, an eighth of them for each XCD (blocks go round the 8 of them), whose L2 then holds the query fragments of
+    // few samples and which all have the same to do whatever the samples' lengths are.
+    const int xcd = (int)(blockIdx.x & 7), at = (int)(blockIdx.x >> 3);
+    const int nkg = (p.Mv + 31) / 32;
+    int tiles = p.B * nkg, b, j0, nbl = NB;           // nbl: text blocks of the sample
+    const bool masked = vis_valid || txt_len, few = p.B <= kWave;
+    LaneTiles lt{};
+    SampleTiles sm{};
+    if (masked) {
+        if (few) { lt = lane_tiles(rows, p.B, 32, NB, 0, 0); tiles = __builtin_amdgcn_readlane(lt.incl, kWave - 1); }
+        else tiles = find_sample(rows, p.B, 32, NB, false, 0, sm);
+    }
+    const int tile = (int)((long)tiles * xcd >> 3) + at;
+    const bool work = tile < (int)((long)tiles * (xcd + 1) >> 3);      // block-uniform
+    // keys behind the last valid one, or without text rows (in the end: no block waits for this before its tile)
+    auto others = [&]() {
+        const uint32_t n = (uint32_t)p.B * (uint32_t)p.Mv;             // (at most 2^28)
+        for (uint32_t e = blockIdx.x * 512 + threadIdx.x; e < n; e += gridDim.x * 512) {
+            const uint32_t s = e / (uint32_t)p.Mv;
+            const SampleRows r = rows[s];
+            if (r.text_blocks == 0 || (int)(e - s * p.Mv) >= 32 * key_groups(r.vision, 32)) { Vout[e] = 0.f; Iout[e] = 0.f; }
+        }
+    };
+    if (masked) {
+        if (!work) { others(); return; }
+        if (few) sm = sample_at_lane(lt, 0, __builtin_ctzll(lane_with_tile(lt, tile)));
+        else find_sample(rows, p.B, 32, NB, true, tile, sm);
+        b = sm.b; j0 = (tile - sm.tile0) * 32; nbl = sm.nbl;
+    } else {
+        if (!work) return;
+        b = tile / nkg; j0 = (tile - b * nkg) * 32;
+    }
+    // this thread's key at the end: 4 * wv + lane / 16
+    const int j = j0 + 4 * wv + (lane >> 4);
+    const bool ok = j < p.Mv && (!vis_valid || vis_valid[(long)b * p.Mv + min(j, p.Mv - 1)]);
+    float v_sum = 0.f, i_max = 0.f;
+    {
+        const int tl = txt_len ? min(max(txt_len[b], 0), p.N) : p.N;
+        const uint16_t* kb = k + (long)b * p.kv.batch;
+        const uint32_t krow = (uint32_t)(p.kv.token * 2);
+        char* const slots = s_k + wv * 2 * TILE_BYTES;
+        auto issue_k = [&](int h, int slot) {
+            const __amdgpu_buffer_rsrc_t rk = row_buffer(kb + (long)h * p.kv.head, p.L, p.kv.token, p.d);
+#pragma unroll
+            for (int t = 0; t < NLT; ++t) T::template issue<STREAM>(rk, krow, j0, t * T::RPL, slots + slot * TILE_BYTES, lane, true);
+        };
+        bf16x8 qf[NB][KS];
+        float c[NB];
+        float2 st[CHUNKS ? CH : 1][NB];
+        auto load_q = [&](int h) {
+            const long bh = (long)b * p.H + h;
+#pragma unroll
+            for (int t = 0; t < NB; ++t) {
+                const bf16x8* qh = qfrag + (bh * NB + t) * KS * kWave + lane;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) qf[t][ks] = qh[ks * kWave];
+                if constexpr (!CHUNKS) c[t] = cstat[bh * p.Npad + 32 * t + i];
+                else {
+#pragma unroll
+                    for (int u = 0; u < CH; ++u) st[u][t] = partial[(bh * p.nch + min(u, p.nch - 1)) * p.Npad + 32 * t + i];
+                }
+            }
+        };
+        // the statistic of this lane's text row: see prefill_cstat_kernel
+        auto statistic = [&](int t) -> float {
+            if constexpr (!CHUNKS) return c[t];
+            else {
+                float mn = -INFINITY, zn = 0.f;
+#pragma unroll
+                for (int u = 0; u < CH; ++u)
+                    if (u < p.nch) mn = fmaxf(mn, st[u][t].x);
+                if (mn > -INFINITY) {
+#pragma unroll
+                    for (int u = 0; u < CH; ++u)
+                        if (u < p.nch) zn = fmaf(st[u][t].y, fast_exp2(st[u][t].x - mn), zn);
+                }
+                return fold_stats(mn, zn, 32 * t + i < tl, p.H);
+            }
+        };
+        f32x16 sum[NB];
+#pragma unroll
+        for (int t = 0; t < NB; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[t][r] = 0.f;
+        if (wv < p.H) { issue_k(wv, 0); load_q(wv); }
+        if (wv + W < p.H) issue_k(wv + W, 1);
+        int slot = 0;
+        for (int h = wv; h < p.H; h += W, slot ^= 1) {
+            // all but what was asked for last, the K rows of the next head
+            if (h + W < p.H) { MD_VM_WAIT(NLT); } else { MD_VM_WAIT(0); }
+            bf16x8 kf[KS];
+            T::frags_wait(T::frag_base(slots + slot * TILE_BYTES, lane), kf);
+            f32x16 acc[NB];
+            float cc[NB];
+#pragma unroll
+            for (int t = 0; t < NB; ++t) { acc[t] = score_tile<KS>(kf, qf[t]); cc[t] = statistic(t); }
+            __builtin_amdgcn_sched_barrier(0);
+            if (h + W < p.H) load_q(h + W);
+            __builtin_amdgcn_sched_barrier(0);
+            if (h + 2 * W < p.H) issue_k(h + 2 * W, slot);
+#pragma unroll
+            for (int t = 0; t < NB; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[t][r] += fast_exp2(fmaf(acc[t][r], scale_log2e, cc[t]));
+        }
+        // (nothing writes LDS any more)  Sums of the waves, [wave][key][text row], a text block at a time
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            if (t < nbl) {                 // (nobody wrote fragments and statistics of the others)
+                float* mine = reinterpret_cast<float*>(s_k) + (t * W + wv) * 1024;
+                if (t == 0) __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mine[tile_row(r, lane) * 32 + i] = sum[t][r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            if (t >= nbl) break;
+            const float2* part = reinterpret_cast<const float2*>(s_k) + t * W * 512 + (4 * wv + (lane >> 4)) * 16 + (lane & 15);
+            float2 a = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const float2 x = part[w * 512];
+                a.x += x.x;
+                a.y += x.y;
+            }
+            v_sum += a.x + a.y;
+            i_max = fmaxf(i_max, fmaxf(a.x, a.y));    // (of scores that are not numbers, 0: see prefill_colfix_kernel)
+        }
+        v_sum = group_sum<16>(v_sum);
+        i_max = fmaxf(i_max, dpp_f<0xB1>(i_max));
+        i_max = fmaxf(i_max, dpp_f<0x4E>(i_max));
+        i_max = fmaxf(i_max, dpp_f<0x141>(i_max));
+        i_max = fmaxf(i_max, dpp_f<0x140>(i_max));
+    }
+    if ((lane & 15) == 0 && j < p.Mv) {
+        Vout[(long)b * p.Mv + j] = ok ? v_sum : 0.f;
+        Iout[(long)b * p.Mv + j] = ok ? i_max : 0.f;
+    }
+    if (masked) others();
+}
+
 // Column statistics (Eq. 8 / Eq. 10): a[i][j] = sum over the pieces of j's key group (fixed order);
 // V_j = sum_i a[i][j], I_j = max_i a[i][j].  A wave takes four neighbouring vision keys (same key group, same pieces), 16 lanes
 // each, with four text rows per lane and load.  How many pieces there are takes a round trip and two divisions; the
@@ -1717,7 +1882,7 @@ struct PrefillWorkspace {
     // which that form does not write (a piece is at least 32 floats per key and text block)
     struct ScoreParts { float* V; float* I; int parts; };
     ScoreParts score_parts(const PrefillDims& p, const ScorePlan& s) const {
-        if (!s.own || s.nbt == 1) return ScoreParts{V, I, 1};
+        if (!s.own || s.nbt == 1 || s.rows) return ScoreParts{V, I, 1};
         return ScoreParts{apart, apart + (size_t)s.nbt * p.B * p.Mv, s.nbt};
     }
     float2* chunk_stats(const PrefillDims& p, const ScorePlan& s) const {
@@ -1781,6 +1946,22 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
         const long items = (long)p.B * p.H * s.nbt;
         MD_LAUNCH("prefill_qpack", st, (prefill_qpack_kernel<KS>), (unsigned)((items + 3) / 4 + p.B), 256, 0, qp, vis_valid, txt_len,
                   row_lse, p, w.qfrag, w.cstat, w.rows);
+    }
+    if (s.rows) {
+        const long tiles = (long)p.B * ((p.Mv + 31) / 32);
+#define MD_COLROWS2(NB_, ST_, CH_)                                                                             \
+    MD_LAUNCH("prefill_colscore", st, (prefill_colrows_kernel<KS, NB_, ST_, CH_>), (unsigned)((tiles + 7) / 8 * 8), 512, 0, \
+        w.qfrag, kp, w.cstat, partial, vis_valid, txt_len, w.rows, p, scale_log2e, w.V, w.I)
+#define MD_COLROWS(NB_)                                                                                        \
+    do {                                                                                                       \
+        if (row_lse && s.rows_stream) MD_COLROWS2(NB_, true, false);                                           \
+        else if (p.nch == 1) MD_COLROWS2(NB_, false, false);                                                   \
+        else MD_COLROWS2(NB_, false, true);                                                                    \
+    } while (0)
+        if (s.nbt == 1) MD_COLROWS(1); else MD_COLROWS(2);
+#undef MD_COLROWS
+#undef MD_COLROWS2
+        return MD_OK;
     }
     if (s.own) {
         MD_LAUNCH("prefill_colscore", st, (prefill_colown_kernel<KS>), (unsigned)((s.own_blocks + 7) / 8 * 8), 512, 0, w.qfrag, kp, w.cstat, partial, vis_valid, txt_len, w.rows,
@@ -1886,8 +2067,8 @@ int prefill_filter_impl(
     PrefillDims p;
     p.B = B; p.Mv = Mv; p.N = N; p.H = H; p.d = d; p.C = C; p.L = Mv + N; p.Rcap = Rcap;
     p.q = lq; p.kv = lkv;
-    ScorePlan sp = plan_scores(B, Mv, N, H, d);
-    if (row_lse) { sp.nch = 1; sp.own = sp.own_lse; }         // (one statistic per row)
+    ScorePlan sp = plan_scores(B, Mv, N, H, d, vis_valid != nullptr);
+    if (row_lse) sp = with_normalisers(sp);
     p.Npad = sp.nbt * 32;
     p.nch = sp.nch; p.ng = sp.ng;
     hipStream_t st = static_cast<hipStream_t>(stream);

@@ -50,9 +50,10 @@ MD_PLAN_FN ColRun effective_run(int tiles, int H, ColPlan cp) {
 }
 
 // Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; ColPlan col; int occ; };
+struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; bool rows, rows_lse, rows_stream; ColPlan col; int occ; };
 
-inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
+// masked: the call has a validity mask.  (It decides about forms, not about sizes.)
+inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = false) {
     ScorePlan s;
     s.nbt = (N + 31) / 32;                            // 32-row text blocks
     s.nbw = s.nbt == 1 ? 1 : (s.nbt == 2 ? 2 : 4);    // text blocks per block, one per wave column
@@ -105,6 +106,39 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     s.own = s.nbt <= kOwnParts && Mv <= 8192 && s.own_blocks <= 2 * own_round && heads <= 54 + 0.4 * s.own_blocks;
     // (with the caller's row normalisers, K has not been read before: one round, 23 x 181 keys, 45 text rows, 276 blocks 50 / 54)
     s.own_lse = s.own && s.own_blocks <= own_round && heads <= 46 + 0.22 * s.own_blocks;
+    // Up to 64 text rows a block of single tiles takes all of them (prefill_colrows_kernel): K is read once, there is one (V, I) pair per
+    // key, and the call may be of any size as long as whole rounds of the 256 CUs do not leave too much of the last one idle.
+    // us per call, before / now, 32 heads of 128: 16 x 576 keys at 3/4 valid, 20 text rows 60.5 / 54.4, 60 rows 75.5 / 67.2; with row
+    // normalisers 52.2 / 45.6 and 61.0 / 54.9; 8 x 1200 at 4/5, 60 rows 73.0 / 66.0; 24 x 1600 at 4/5, 20 rows 206 / 196, 60 rows 234 /
+    // 220; 2 x 4000, 60 rows with normalisers 53.9 / 47.2.  Where a second round begins: 16 x 576 all valid (288 tiles), 60 rows 79.7 /
+    // 81.2, with normalisers 64.0 / 67.7; 8 x 2880 at 4/5 (576 of 720 tiles), 60 rows 133 / 138, 20 rows 121.0 / 125.5.  (With a
+    // mask four fifths of the slots are taken to be valid: stage 1 leaves three quarters.)
+    // With two text blocks, where single tiles of one each have their second round (4 x 1000 keys at 4/5, 128 tiles, 60 rows 40.6 / 44.4; 8
+    // x 576, 144 tiles, 48.9 / 45.4).
+    const long tiles = (long)B * ((Mv + 31) / 32);
+    const double rounds = (masked ? 0.8 : 1.0) * tiles / kNumCU;
+    const long whole = (long)rounds + (rounds > (long)rounds ? 1 : 0);
+    const bool even = whole <= 1 || whole <= 1.27 * rounds;
+    // Fewer than 16 heads only where single tiles would be taken anyway.  They would gain beyond as well (60 x 576 keys at 4/5, 12 heads of 64, 32
+    // rows 57.2 / 45.5), but no model at hand has so few, and the persistent form, which more than 8192 slots and many heads on few tiles
+    // still need with one and two text blocks, is tested over many tiles there.
+    const bool heads_lse = heads <= 46 + 0.22 * tiles && (H >= 16 || s.own_lse), heads_own = heads <= 54 + 0.4 * tiles && (H >= 16 || s.own);
+    s.rows = s.rows_lse = false;
+    if (Mv <= 8192 && s.nbt == 1) {
+        // heads of 64 share a CU between two blocks, which evens the rounds out (24 x 1600 at 4/5, 20 rows 125.7 / 106.6, 8 x 2880 71.8 / 70.2)
+        s.rows = heads_own && (even || d == 64 || s.own);
+        s.rows_lse = heads_lse && (even || d == 64);
+    } else if (Mv <= 8192 && s.nbt == 2 && tiles > kNumCU / 2) {
+        // heads of 64: single tiles are still two rounds of two blocks (16 x 576 43.0 / 46.5; 8 x 2880 at 4/5 81.1 / 84.7); with
+        // normalisers they have one (16 x 576 45.0 / 39.9; 4 x 2880 at 4/5 45.0 / 43.0; 24 x 1200 84.8 / 82.0)
+        s.rows = heads_own && (d == 64 ? whole <= 1 : even);
+        s.rows_lse = heads_lse && (even || d == 64);
+    }
+    s.own |= s.rows;
+    // K that has not been read before, of a size that will not be in the Infinity Cache either (up to there plain loads: heads of 64, 16 x
+    // 1024 keys, 67 MB, 20 rows 41.8 streamed / 40.6; 16 x 576 of 128, 75 MB, 45.6 / 46.9, 4 x 2880, 94 MB, 57.3 / 62.4).  Behind a
+    // first sweep plain loads (24 x 1200, 236 MB, 60 rows 200.7 / 195.0, 16 x 1024 109.1 / 108.3)
+    s.rows_stream = k_mb > 70.0;
     // sweep 1: blocks of four waves (two per CU) or of eight (one per CU; the chunks two small blocks would take meet in
     // LDS), and the number of key chunks per (sample, head, text group), at least four 128-key units each.  Whole rounds
     // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start
@@ -160,6 +194,14 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d) {
     }
     s.rs_wide = s.ng > 1 || (s.nbw == 4 && d == 128 && s.rs_waves == 4);
     s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && !s.rs_stream;
+    return s;
+}
+
+// The plan of a call whose caller brings the row normalisers: one statistic per row, and K has not been read before.
+inline ScorePlan with_normalisers(ScorePlan s) {
+    s.nch = 1;
+    s.rows = s.rows_lse;
+    s.own = s.own_lse || s.rows;
     return s;
 }
 
