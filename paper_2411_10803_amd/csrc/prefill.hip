@@ -1630,6 +1630,7 @@ struct TextRows {
     const u32x4* hidden; const u32x4* k; const u32x4* v;
     u32x4* hidden_out; u32x4* k_out; u32x4* v_out;
     int enabled;
+    int stream_k;                                    // see prefill_compact_kernel
 };
 constexpr int kTextRowsPerBlock = 4;                 // 1024 threads = four rows of 256 threads
 
@@ -1661,11 +1662,16 @@ __device__ __forceinline__ void copy_text_rows(
     const int rows_cap = p.Rcap + p.N;
     const int hv = p.C / 8, kv = p.H * p.d / 8, c0 = tid % 256;
     const long src = (long)b * p.L + Mv + i, dst = (long)b * rows_cap + nkept + i;
-    for (int c = c0; c < kv; c += 256) {
-        const u32x4 a = __builtin_nontemporal_load(tr.k + src * kv + c), a2 = __builtin_nontemporal_load(tr.v + src * kv + c);
-        tr.k_out[dst * kv + c] = a;
-        __builtin_nontemporal_store(a2, tr.v_out + dst * kv + c);          // streaming stores: see prefill_compact_kernel
-    }
+    // (a loop each: a branch around the one store would be folded into a plain one)
+    auto kv_rows = [&](auto stream_k) {
+        for (int c = c0; c < kv; c += 256) {
+            const u32x4 a = __builtin_nontemporal_load(tr.k + src * kv + c), a2 = __builtin_nontemporal_load(tr.v + src * kv + c);
+            if constexpr (decltype(stream_k)::value) __builtin_nontemporal_store(a, tr.k_out + dst * kv + c);
+            else tr.k_out[dst * kv + c] = a;
+            __builtin_nontemporal_store(a2, tr.v_out + dst * kv + c);      // streaming stores: see prefill_compact_kernel
+        }
+    };
+    if (tr.stream_k) kv_rows(std::true_type()); else kv_rows(std::false_type());
     for (int c = c0; c < hv; c += 256)
         __builtin_nontemporal_store(__builtin_nontemporal_load(tr.hidden + src * hv + c), tr.hidden_out + dst * hv + c);
 }
@@ -1797,6 +1803,8 @@ __global__ __launch_bounds__(1024) void prefill_select_fast_kernel(
 }
 
 // One block per output row: copies the hidden, K and V rows named by the row map.
+// STREAM_K: the K rows too are written with streaming stores.
+template <bool STREAM_K>
 __global__ __launch_bounds__(256) void prefill_compact_kernel(
     PrefillDims p, const int32_t* __restrict__ src_row,
     const u32x4* __restrict__ hidden, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
@@ -1818,7 +1826,7 @@ __global__ __launch_bounds__(256) void prefill_compact_kernel(
     // hidden and V rows are written with streaming stores: nothing on this path reads them again, and left as
     // dirty lines in the Infinity Cache they would be written back in the middle of whatever kernel streams
     // through it next (measured: the sweep that follows 150 MB of plain stores takes 10 us longer); the K
-    // rows, which a scoring pass reads next, keep plain stores
+    // rows, which a scoring pass reads next, keep plain stores where they are few (see the launch)
     auto put = [](u32x4* q, const u32x4& v, bool nt) { if (nt) __builtin_nontemporal_store(v, q); else *q = v; };
     auto copy2 = [&](const u32x4* __restrict__ s0, u32x4* __restrict__ d0, const u32x4* __restrict__ s1,
                      u32x4* __restrict__ d1, int n, bool nt0, bool nt1) {
@@ -1834,7 +1842,7 @@ __global__ __launch_bounds__(256) void prefill_compact_kernel(
             if (two) { put(d0 + c2, b0, nt0); put(d1 + c2, b1, nt1); }
         }
     };
-    copy2(ks, kd, vs, vd, kv, false, true);
+    copy2(ks, kd, vs, vd, kv, STREAM_K, true);
     const int half = (hv + 1) / 2;                   // the hidden row as two halves
     copy2(hs, hd, hs + half, hd + half, hv - half, true, true);
     if (hv & 1) {                                    // odd vector count: the first half has one more
@@ -1845,7 +1853,7 @@ __global__ __launch_bounds__(256) void prefill_compact_kernel(
 
 // The same for K / V in other layouts: a row is gathered head slice by head slice (d contiguous
 // elements each) from the input layout and scattered to the output layout.
-template <bool STREAM>
+template <bool STREAM, bool STREAM_K>
 __global__ __launch_bounds__(256) void prefill_compact_strided_kernel(
     PrefillDims p, const int32_t* __restrict__ src_row,
     const u32x4* __restrict__ hidden, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -1865,7 +1873,8 @@ __global__ __launch_bounds__(256) void prefill_compact_strided_kernel(
         const int h = c / lph, w = c - h * lph;
         const long so = sbase + (long)h * p.kv.head + w * 8, d_o = dbase + (long)h * out.head + w * 8;
         const u32x4 a = ld(reinterpret_cast<const u32x4*>(k + so)), c2 = ld(reinterpret_cast<const u32x4*>(v + so));
-        *reinterpret_cast<u32x4*>(k_out + d_o) = a;
+        if (STREAM_K) __builtin_nontemporal_store(a, reinterpret_cast<u32x4*>(k_out + d_o));
+        else *reinterpret_cast<u32x4*>(k_out + d_o) = a;
         st(c2, reinterpret_cast<u32x4*>(v_out + d_o));
     }
     const int hv = p.C / 8;
@@ -2080,7 +2089,16 @@ int prefill_filter_impl(
     int32_t* src_row = out_ids ? out_ids : w.src_row;     // the row map doubles as the optional out_ids
     const bool dense_io = is_dense(lkv, (long)L, H, d) && is_dense(lout, (long)Rcap + N, H, d);
     TextRows tr{static_cast<const u32x4*>(hidden), static_cast<const u32x4*>(k), static_cast<const u32x4*>(v),
-                static_cast<u32x4*>(hidden_out), static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out), 0};
+                static_cast<u32x4*>(hidden_out), static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out), 0, 0};
+    // K rows of many MB stay in the cache as dirty lines, and writing them back under the sweep that comes next takes longer than the
+    // decode stage gains by finding them there: they are streamed from 16 MB on, from 28 MB where no first sweep follows.  us per call,
+    // repeated on other inputs, plain / streamed: 16 x 576 keys, 128 rows (42 MB) 116.8 / 109.1, 60 rows at 4/5 (25 MB) 71.5 / 65.7; 24 x
+    // 1600, 30 rows (84 MB) 216 / 194; 8 x 2880, 128 rows at 3/4 (29 MB) 126.2 / 123.8; 4 x 2880, 120 rows (14 MB) 83.8 / 85.0; with row
+    // normalisers 24 x 1600 164 / 152, 12 x 1000, 100 rows (29 MB) 82.6 / 81.8, 16 x 576 at 3/4, 64 rows (25 MB) 56.8 / 57.1, 8 x 576, 128
+    // rows (20 MB) 55.1 / 56.5.  A whole step of encode, prefill and decode: 16 x 576 131 / 123, 4 x 4608 168 / 165, 8 x 2880 204 / 203.
+    const double kout_mb = (double)B * (Rcap + N) * H * d * 2 / 1e6;
+    const bool stream_k = kout_mb > (row_lse ? 28.0 : 16.0);
+    tr.stream_k = stream_k ? 1 : 0;
     tr.enabled = (mode == MD_FILTER_BUDGET && dense_io && Mv <= 8192) ? 1 : 0;
     const int sel_blocks = B + (tr.enabled ? B * ((N + kTextRowsPerBlock - 1) / kTextRowsPerBlock) : 0);
     const PrefillWorkspace::ScoreParts parts = w.score_parts(p, sp);
@@ -2103,19 +2121,25 @@ int prefill_filter_impl(
 #undef MD_PSELECT_FAST
 #undef MD_PSELECT_FAST2
     dim3 gc(tr.enabled ? Rcap : Rcap + N, B);         // the text rows beyond the kept vision rows are already in place
-    if (dense_io)
-        MD_LAUNCH("prefill_compact", st, (prefill_compact_kernel), gc, 256, 0, p, src_row,
-            static_cast<const u32x4*>(hidden), static_cast<const u32x4*>(k), static_cast<const u32x4*>(v),
-            static_cast<u32x4*>(hidden_out), static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out), tr.enabled);
-    else {
+    if (dense_io) {
+#define MD_COMPACT(SK_)                                                                                        \
+        MD_LAUNCH("prefill_compact", st, (prefill_compact_kernel<SK_>), gc, 256, 0, p, src_row,                    \
+            static_cast<const u32x4*>(hidden), static_cast<const u32x4*>(k), static_cast<const u32x4*>(v),         \
+            static_cast<u32x4*>(hidden_out), static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out), tr.enabled)
+        if (stream_k) MD_COMPACT(true); else MD_COMPACT(false);
+#undef MD_COMPACT
+    } else {
         // Streaming where K, V and hidden together outgrow the Infinity Cache, so that the rows left in it are not written
         // back under the next sweep (21 x 1163 keys, 40 heads of 64, 125 MB: compact + next row statistics 56.9 -> 53.8 us);
-        // smaller calls find their rows in L2, which streaming loads pass by (12 x 634, 32 heads of 64, 31 MB: 8.2 -> 6.0)
-#define MD_COMPACT_STRIDED(ST_)                                                                                \
-        MD_LAUNCH("prefill_compact", st, (prefill_compact_strided_kernel<ST_>), gc, 256, 0, p, src_row,            \
+        // smaller calls find their rows in L2, which streaming loads pass by (12 x 634, 32 heads of 64, 31 MB: 8.2 -> 6.0).  K out with
+        // them as above, but not with row normalisers (head-major, 24 x 1200, 60 rows 184 -> 181, with them 140 -> 143)
+#define MD_COMPACT_STRIDED(ST_, SK_)                                                                           \
+        MD_LAUNCH("prefill_compact", st, (prefill_compact_strided_kernel<ST_, SK_>), gc, 256, 0, p, src_row,       \
             static_cast<const u32x4*>(hidden), static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),   \
             static_cast<u32x4*>(hidden_out), static_cast<uint16_t*>(k_out), static_cast<uint16_t*>(v_out), lout)
-        if ((double)B * p.L * H * d * 2 > 100e6) MD_COMPACT_STRIDED(true); else MD_COMPACT_STRIDED(false);
+        if ((double)B * p.L * H * d * 2 <= 100e6) MD_COMPACT_STRIDED(false, false);
+        else if (stream_k && !row_lse) MD_COMPACT_STRIDED(true, true);
+        else MD_COMPACT_STRIDED(true, false);
 #undef MD_COMPACT_STRIDED
     }
     return check_launch("prefill_filter");
