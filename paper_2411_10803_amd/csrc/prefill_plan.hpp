@@ -50,7 +50,7 @@ MD_PLAN_FN ColRun effective_run(int tiles, int H, ColPlan cp) {
 }
 
 // Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; bool rows, rows_lse, rows_stream; ColPlan col; int occ; };
+struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; bool rows, rows_lse, rows_stream; ColPlan col; int occ; };
 
 // masked: the call has a validity mask.  (It decides about forms, not about sizes.)
 inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = false) {
@@ -58,12 +58,10 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     s.nbt = (N + 31) / 32;                            // 32-row text blocks
     s.nbw = s.nbt == 1 ? 1 : (s.nbt == 2 ? 2 : 4);    // text blocks per block, one per wave column
     s.ng = (s.nbt + s.nbw - 1) / s.nbw;               // text groups: each goes over K, side by side
-    // a vision K that outgrows the Infinity Cache before the second sweep comes to it is read with streaming loads: what
-    // the first sweep leaves in the cache then only has to be pushed out again (6 x 6009 keys, 32 heads: both sweeps 147 ->
-    // 136 us, 16 x 2880: 201 -> 188); where a good part of it survives, plain loads (8 x 2880 with 3/4 of the slots
-    // valid: 85 against 88).  Up to 64 text rows the line lies lower (3 x 5523, 40 heads, 170 MB: 81 -> 73; 13 x 1029, 110 MB: 49 -> 52)
+    // Sweep 1 reads K with plain loads whatever its size: the second sweep finds part of it in the Infinity Cache, also of one that is larger
+    // (us per call, streamed / plain: 24 x 1600 keys, 315 MB, 30 text rows 195 / 188, 10 x 3000, 246 MB, 100 rows 165 / 156, 16 x 2880, 377 MB,
+    // 120 rows 233 / 224, 20 x 2800, 459 MB, 40 rows 241 / 240).
     const double k_mb = (double)B * Mv * H * d * 2 / 1e6;
-    s.rs_stream = k_mb > (s.nbw <= 2 ? 160.0 : 230.0);
     // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
     ColPlan& c = s.col;
     c.kb = s.nbw == 1 ? 128 : 64;
@@ -162,7 +160,7 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
                 // (heads of 64 with four text blocks: three blocks of four waves share a CU, one of eight waves no better than at
                 // d = 128; 2 x 8661 keys, 64 heads, 95 text rows 49.8 -> 38.6)
                 if (s.nbw == 4 && d == 64) { alone = waves == 8 ? 10.0 : 11.5; full = waves == 8 ? 10.5 : 21.0; }
-                if (s.nbw == 1 && d == 128 && waves == 4 && blocks <= kNumCU && !s.rs_stream) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
+                if (s.nbw == 1 && d == 128 && waves == 4 && blocks <= kNumCU && k_mb <= 160.0) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
                 if (s.nbw == 4 && d == 128 && waves == 4) full = 30.0;
                 const double per_key = alone + (full - alone) * fill;
                 double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? merge_us : 0.0);
@@ -193,7 +191,7 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
         s.partial_in_pieces = s.nch > s.nch_ws;
     }
     s.rs_wide = s.ng > 1 || (s.nbw == 4 && d == 128 && s.rs_waves == 4);
-    s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && !s.rs_stream;
+    s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && k_mb <= 160.0;
     return s;
 }
 
