@@ -147,8 +147,8 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     const long n = (long)B * H * s.ng;
     // The wide form takes all calls with several text groups.  With one, K comes from HBM and bounds the sweep: there it only
     // takes the place of the blocks of four waves at d = 128 (13 x 1039 keys, 32 heads, 128 text rows 43 -> 40, 20 x 576, 40
-    // heads, 70 rows 53 -> 49); against one block of eight waves per head it pays for the merge of two chunks (8 x 2880,
-    // 128 rows 46.6 and 47.5 + 4), and heads of 64 have three smaller blocks per CU (8 x 2000, 128 rows 25 and 28).
+    // heads, 70 rows 53 -> 49), where it is one chunk as well of those of eight; heads of 64 have three smaller blocks per CU (8 x 2000,
+    // 128 rows 25 and 28).
     auto pick = [&](double merge_us, int most, int least_units) {
         double best = 0;
         for (int waves = 4; waves <= (s.ng > 1 ? 4 : 8); waves += 4)
@@ -179,6 +179,12 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
             }
     };
     pick(5.0, kMaxChunks, 4);
+    // Where the estimate is off: one wide block of four waves per (sample, head), one or two on a CU, is at least as fast as what it picks
+    // for 65 to 128 text rows when the heads of all samples nearly fill the CUs and the keys are many, and when they are more than two rounds
+    // of it.  us per call, picked / wide: 6 x 2600 keys, 100 rows (192 heads in all) 107.2 / 103.5, 8 x 2600 (256) 126.4 / 122.1, 8 x
+    // 2880 at 3/4, 128 rows 124.2 / 122.6, 17 x 500, 128 rows (544) 111.4 / 101.7, 24 x 1700 (768) 255 / 247; not 5 x 2600 (160) 93.8 / 95.2,
+    // 8 x 576, 128 rows 62.0 / 63.1, 9 x 1700 (288) 119.7 / 122.1.
+    if (s.nbw == 4 && s.ng == 1 && d == 128 && !s.own && (n > 2 * kNumCU || (n > 176 && n <= kNumCU && Mv + N >= 1000))) { s.rs_waves = 4; s.nch = 1; }
     s.nch_ws = s.nch;
     s.partial_in_pieces = false;
     if (s.own) {
