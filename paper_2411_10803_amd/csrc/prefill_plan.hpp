@@ -180,11 +180,13 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     };
     pick(5.0, kMaxChunks, 4);
     // Where the estimate is off: one wide block of four waves per (sample, head), one or two on a CU, is at least as fast as what it picks
-    // for 65 to 128 text rows when the heads of all samples nearly fill the CUs and the keys are many, and when they are more than two rounds
-    // of it.  us per call, picked / wide: 6 x 2600 keys, 100 rows (192 heads in all) 107.2 / 103.5, 8 x 2600 (256) 126.4 / 122.1, 8 x
-    // 2880 at 3/4, 128 rows 124.2 / 122.6, 17 x 500, 128 rows (544) 111.4 / 101.7, 24 x 1700 (768) 255 / 247; not 5 x 2600 (160) 93.8 / 95.2,
-    // 8 x 576, 128 rows 62.0 / 63.1, 9 x 1700 (288) 119.7 / 122.1.
-    if (s.nbw == 4 && s.ng == 1 && d == 128 && !s.own && (n > 2 * kNumCU || (n > 176 && n <= kNumCU && Mv + N >= 1000))) { s.rs_waves = 4; s.nch = 1; }
+    // for 65 to 128 text rows when the heads of all samples nearly fill the CUs, the keys are many and K is small or it picks several
+    // chunks, which cost the merge too, and when the heads are more than two rounds of the CUs.  us per call, picked / wide: 6 x 2600 keys, 100 rows (192 heads
+    // in all) 107.2 / 103.5, 6 x 4000, 128 rows 147.3 / 139.3, 7 x 2880 (224) 132.5 / 126.9, 6 x 2880, 40 heads (240) 131.3 / 126.3, 17 x 500,
+    // 128 rows (544) 111.4 / 101.7, 24 x 1700 (768) 255 / 247; not 5 x 2600 (160) 93.8 / 95.2, 8 x 576, 128 rows 62.0 / 63.1, 9 x 1700 (288)
+    // 119.7 / 122.1.  Eight waves in one chunk (256 heads) stay where K is large: 8 x 2880, 128 rows 124.6 / 123.3 with K half in the
+    // Infinity Cache, and the sweep alone on new inputs, all of K from HBM, 57.2 / 63.7 (1800: 46.0 / 47.5, 1152: 25.6 / 23.7).
+    if (s.nbw == 4 && s.ng == 1 && d == 128 && !s.own && (n > 2 * kNumCU || (n > 176 && n <= kNumCU && (s.nch > 1 || k_mb <= 105.0) && Mv + N >= 1000))) { s.rs_waves = 4; s.nch = 1; }
     s.nch_ws = s.nch;
     s.partial_in_pieces = false;
     if (s.own) {
