@@ -14,7 +14,8 @@
 //                            S, p = exp(s - m)/Z, accumulate the head mean a[i][j] of such a key tile
 //                            in registers; a block's share of a tile is written as one piece
 //   prefill_colfix_kernel    sums a tile's pieces in a fixed order, column sum / max -> V_j, I_j
-//   prefill_colown_kernel    in place of both on small calls: a block takes a tile (32 keys, 32 text rows) with all heads
+//   prefill_colown_kernel    in place of both on small calls with two to four text blocks: a block takes a tile (32 keys, 32
+//                            text rows) with all heads
 //   prefill_colrows_kernel   in place of both for up to 64 text rows: a block takes 32 keys with all text rows and heads
 // The N x Mv probability matrix of a head is never written to memory.
 //   prefill_select_kernel    per sample: G, the filter rule (threshold) or radix top-k (budget),
@@ -1168,9 +1169,10 @@ __global__ __launch_bounds__(256, 2) void prefill_colscore_kernel(
 // of several are under way while a head is worked on.  What the waves have summed up meets in LDS, where V and I
 // come out of it, of each text block by itself (the selection adds them up).  The row statistics of several key chunks are merged here.
 // Bound by what a CU can take in: half a megabyte of K and query fragments per block at 64 bytes per clock, 3.6 us, asked for as far
-// ahead as the registers hold (four heads' fragments; one head's: 1 x 3810 keys, 18 text rows, 16 heads 34.6 -> 33.2 us a call).
-// 1 x 576 keys, 32 text rows: 7.1 + 6.1 us in the persistent form and its sum of the pieces, 10.6 here, and 8.8 -> 7 for the
-// first sweep, whose chunks may be shorter.
+// ahead as the registers hold (four heads' fragments; one head's, measured with one text block: 1 x 3810 keys, 18 text rows, 16 heads
+// 34.6 -> 33.2 us a call).  For two to four text blocks (one, and two on more than half of the CUs: prefill_colrows_kernel).
+// 1 x 576 keys, 128 text rows: 39 us a call in the persistent form with its sum of the pieces, 28 so; the first sweep gains too, as its
+// chunks may be shorter.
 template <int KS>
 __global__ __launch_bounds__(512) void prefill_colown_kernel(
     const bf16x8* __restrict__ qfrag, const uint16_t* __restrict__ k, const float* __restrict__ cstat, const float2* __restrict__ partial,

@@ -87,7 +87,8 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     if (c.Gmax > H) c.Gmax = H;
     // Sweep 2 by blocks of one tile (32 keys, 32 text rows, all heads) where they are no more than two rounds, of one block per CU or,
     // with heads of 64, of two: the blocks of the persistent form hand over their sums through memory and another launch, and
-    // leave most of the chip idle on small calls.  us per call, persistent / single tiles: 1 x 576 keys, 32 text rows 33 / 28, 128 rows
+    // leave most of the chip idle on small calls.  us per call, persistent / single tiles (up to 32 text rows before the form further
+    // down, which takes those now, was there): 1 x 576 keys, 32 text rows 33 / 28, 128 rows
     // 39 / 28; 14 x 576, 32 rows 64 / 57 (252 blocks), 28 x 576 118 / 111 (504), 2 x 1246, 114 rows, 16 heads 41 / 35 (312); heads of 64, 12 x
     // 300, 20 rows 28 / 20, 20 x 1000, 28 rows 84 / 72 (640).  Behind that the query fragments, read for every 32 keys, come to more:
     // 4 x 4248, 25 rows 112 / 119 (532), 8 x 1955, 118 rows 144 / 183 (1984); heads of 64, 3 x 7055, 92 rows 125 / 134 (1989).  (Of
