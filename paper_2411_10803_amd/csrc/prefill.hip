@@ -2102,6 +2102,7 @@ int prefill_filter_impl(
     // 1600, 30 rows (84 MB) 216 / 194; 8 x 2880, 128 rows at 3/4 (29 MB) 126.2 / 123.8; 4 x 2880, 120 rows (14 MB) 83.8 / 85.0; with row
     // normalisers 24 x 1600 164 / 152, 12 x 1000, 100 rows (29 MB) 82.6 / 81.8, 16 x 576 at 3/4, 64 rows (25 MB) 56.8 / 57.1, 8 x 576, 128
     // rows (20 MB) 55.1 / 56.5.  A whole step of encode, prefill and decode: 16 x 576 131 / 123, 4 x 4608 168 / 165, 8 x 2880 204 / 203.
+    // A single call on buffers that nothing has touched before has only the cost: 8 x 2880, 128 rows 165 / 169 (the copies 20 / 24).
     const double kout_mb = (double)B * (Rcap + N) * H * d * 2 / 1e6;
     const bool stream_k = kout_mb > (row_lse ? 28.0 : 16.0);
     tr.stream_k = stream_k ? 1 : 0;
