@@ -1828,7 +1828,7 @@ __global__ __launch_bounds__(256) void prefill_compact_kernel(
     // hidden and V rows are written with streaming stores: nothing on this path reads them again, and left as
     // dirty lines in the Infinity Cache they would be written back in the middle of whatever kernel streams
     // through it next (measured: the sweep that follows 150 MB of plain stores takes 10 us longer); the K
-    // rows, which a scoring pass reads next, keep plain stores where they are few (see the launch)
+    // rows, which a scoring pass reads next, keep plain stores where streams_k_out says so
     auto put = [](u32x4* q, const u32x4& v, bool nt) { if (nt) __builtin_nontemporal_store(v, q); else *q = v; };
     auto copy2 = [&](const u32x4* __restrict__ s0, u32x4* __restrict__ d0, const u32x4* __restrict__ s1,
                      u32x4* __restrict__ d1, int n, bool nt0, bool nt1) {
@@ -2096,15 +2096,7 @@ int prefill_filter_impl(
     const bool dense_io = is_dense(lkv, (long)L, H, d) && is_dense(lout, (long)Rcap + N, H, d);
     TextRows tr{static_cast<const u32x4*>(hidden), static_cast<const u32x4*>(k), static_cast<const u32x4*>(v),
                 static_cast<u32x4*>(hidden_out), static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out), 0, 0};
-    // K rows of many MB stay in the cache as dirty lines, and writing them back under the sweep that comes next takes longer than the
-    // decode stage gains by finding them there: they are streamed from 16 MB on, from 28 MB where no first sweep follows.  us per call,
-    // repeated on other inputs, plain / streamed: 16 x 576 keys, 128 rows (42 MB) 116.8 / 109.1, 60 rows at 4/5 (25 MB) 71.5 / 65.7; 24 x
-    // 1600, 30 rows (84 MB) 216 / 194; 8 x 2880, 128 rows at 3/4 (29 MB) 126.2 / 123.8; 4 x 2880, 120 rows (14 MB) 83.8 / 85.0; with row
-    // normalisers 24 x 1600 164 / 152, 12 x 1000, 100 rows (29 MB) 82.6 / 81.8, 16 x 576 at 3/4, 64 rows (25 MB) 56.8 / 57.1, 8 x 576, 128
-    // rows (20 MB) 55.1 / 56.5.  A whole step of encode, prefill and decode: 16 x 576 131 / 123, 4 x 4608 168 / 165, 8 x 2880 204 / 203.
-    // A single call on buffers that nothing has touched before has only the cost: 8 x 2880, 128 rows 165 / 169 (the copies 20 / 24).
-    const double kout_mb = (double)B * (Rcap + N) * H * d * 2 / 1e6;
-    const bool stream_k = kout_mb > (row_lse ? 28.0 : 16.0);
+    const bool stream_k = streams_k_out(B, Mv, N, H, d, C, Rcap, mode == MD_FILTER_THRESHOLD, row_lse != nullptr);
     tr.stream_k = stream_k ? 1 : 0;
     tr.enabled = (mode == MD_FILTER_BUDGET && dense_io && Mv <= 8192) ? 1 : 0;
     const int sel_blocks = B + (tr.enabled ? B * ((N + kTextRowsPerBlock - 1) / kTextRowsPerBlock) : 0);

@@ -212,5 +212,31 @@ inline ScorePlan with_normalisers(ScorePlan s) {
     return s;
 }
 
+// Whether the kept K rows leave by streaming stores, as the kept rows of V and hidden always do.
+//
+// Rule: where there are more than 16 MB of them and the call's K, V and hidden, in and out, come to more than 200 MB,
+// so that the Infinity Cache (256 MB) would have to write them back before anything that is sure to come reads them;
+// with the caller's row normalisers only from 36 MB on, as one sweep of K less runs into the lines to be written back.
+// In threshold mode Rcap is no more than room: an eighth of the slots is taken to be kept (of 576 tokens the printed
+// rule keeps 64 on average).
+//
+// us per call on three states in turn, plain / streaming stores: 16 x 576 keys, 64 text rows, 192 kept (34 MB) 95.7 /
+// 88.8; 12 x 576 (25 MB, 264 MB in all) 66.4 / 61.5; 8 x 576 (17 MB, 176 MB) 49.7 / 49.4; 8 x 2880 at 3/4, 128 rows
+// (29 MB) 127.8 / 124.2; 4 x 2880, 120 rows (14 MB) 88.9 / 89.7; by threshold, kept of 576 about 64: 16 samples 73.6 /
+// 70.8, 12 51.9 / 50.9, 4 29.6 / 30.1.  With normalisers 16 x 576, 128 kept (25 MB) 56.3 / 56.7, 192 kept (34 MB) 77.3 /
+// 77.1, 16 x 1152, 100 rows (38 MB) 108.4 / 103.5, 24 x 576 (50 MB) 104.9 / 98.8.
+// With 600 MB of other data read before each call, that time included, 16 x 576 255.0 / 252.8 and 8 x 2880 287.0 / 281.7.
+// Call after call on the same buffers the rows never leave the cache, and streaming them costs: 16 x 576 above 86.6 /
+// 88.8, with normalisers 8 x 2880, 128 rows (29 MB) 103.1 / 106.3 and 24 x 576 95.2 / 102.3.  So it does where the next
+// layer's filter reads them at once: 16 x 576 -> 192 -> 128 -> 64 takes 183.5 us all plain, 188.5 with the first call's
+// streamed (as here), 190.2 with all calls' streamed (24 x 576 -> 192 -> 64: 177.9, 176, 175.4).  Nothing in a call tells the
+// one use from the other.
+inline bool streams_k_out(int B, int Mv, int N, int H, int d, int C, int Rcap, bool threshold, bool row_lse) {
+    const int kept = threshold && Rcap > Mv / 8 ? Mv / 8 : Rcap;
+    const double out_mb = (double)B * (kept + N) * H * d * 2e-6;
+    const double all_mb = (double)B * (Mv + kept + 2.0 * N) * (2.0 * H * d + C) * 2e-6;
+    return out_mb > (row_lse ? 36.0 : 16.0) && all_mb > 200.0;
+}
+
 }  // namespace
 }  // namespace md

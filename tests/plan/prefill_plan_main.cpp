@@ -2,7 +2,8 @@
 // rows and the text lengths can leave of a plan, no block of the run is empty, every unit lies in the block that
 // unit_block names, and no tile is cut into more pieces than the workspace holds.  And of the sweep by single tiles: what it keeps
 // in the memory of the pieces (V and I per text block, the statistics of more chunks than the workspace has room for)
-// fits there, whichever head size the workspace was measured with, and it is taken where its kernels can.
+// fits there, whichever head size the workspace was measured with, and it is taken where its kernels can.  And of the rule for the
+// stores of the kept K rows.
 #include <stdio.h>
 #include <initializer_list>
 #include <random>
@@ -68,6 +69,18 @@ int main() {
         }
         if (why && ++bad <= 10) printf("B=%d Mv=%d N=%d H=%d: %s\n", B, Mv, N, H, why);
     }
+    // which calls write the kept K rows past the Infinity Cache: not those whose next reader finds them there
+    struct { int B, Mv, N, H, d, Rcap; bool threshold, lse, want; } const moves[] = {
+        {16, 576, 64, 32, 128, 192, false, false, true}, {16, 192, 64, 32, 128, 128, false, false, false},       // successive layers
+        {16, 128, 64, 32, 128, 64, false, false, false}, {4, 4608, 64, 32, 128, 512, false, false, true},
+        {8, 2880, 128, 32, 128, 320, false, false, true}, {8, 2880, 128, 32, 128, 320, false, true, false},      // 29 MB
+        {24, 1600, 30, 32, 128, 400, false, true, true}, {8, 576, 64, 32, 128, 192, false, false, false},
+        {4, 576, 64, 32, 128, 576, true, false, false}, {12, 576, 64, 32, 128, 576, true, false, false},         // room for all, few kept
+        {16, 576, 64, 32, 128, 576, true, false, true}, {8, 2880, 64, 32, 128, 2880, true, false, true},
+        {1, 1, 1, 1, 64, 1, true, true, false}, {1, 64, 1, 1, 64, 0, false, false, false}};
+    for (const auto& m : moves)
+        if (streams_k_out(m.B, m.Mv, m.N, m.H, m.d, m.H * m.d, m.Rcap, m.threshold, m.lse) != m.want && ++bad)
+            printf("B=%d Mv=%d N=%d Rcap=%d threshold=%d lse=%d: K rows out\n", m.B, m.Mv, m.N, m.Rcap, m.threshold, m.lse);
     if (own < 10000 || behind < 1000) { ++bad; printf("too few single tiles looked at\n"); }
     printf("%ld plans of single tiles, %ld with statistics behind the scores\n", own, behind);
     printf("%ld plans, %ld runs, %ld wrong\n", plans, runs, bad);
