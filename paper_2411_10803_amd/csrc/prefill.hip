@@ -365,7 +365,7 @@ __device__ __forceinline__ void interleave_mfma_valu() {
     }
 }
 
-template <int NBW, int TW, int KS, bool DEEP>
+template <int NBW, int TW, int KS, bool STREAM, bool DEEP>
 __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
     const uint16_t* __restrict__ q_txt, const uint16_t* __restrict__ k,
     const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ txt_len, PrefillDims p, float scale_log2e,
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(64 * NBW * TW) void prefill_rowstats_kernel(
 #pragma unroll
         for (int t = 0; t < NLW; ++t) {
             const int sr = (t * NW + wv) * T::RPL;
-            T::issue(rk, krow, row0 + (row0 + sr >= Me ? jump : 0), sr, slot, lane, true);
+            T::template issue<STREAM>(rk, krow, row0 + (row0 + sr >= Me ? jump : 0), sr, slot, lane, true);
         }
     };
     // Validity of the 32 keys of this wave's tile in the steps g0 .. g0+63: lane l fetches the 32 mask bytes of
@@ -612,7 +612,7 @@ __device__ __forceinline__ void interleave_chain() {
 // as it does for all text groups of a sample but one: 6 x 1152 keys, 32 heads, 384 text rows 69 -> 49 us, 20 x 576 with 200
 // rows 77 -> 59, 3 x 9000 with 200 rows 88 -> 77; heads of 64 with the merge, 4 x 4000 keys, 300 rows 63 -> 55, 8 x 2000, 160
 // rows 45 -> 31.
-template <int KS>
+template <int KS, bool STREAM>
 __global__ __launch_bounds__(256, 2) void prefill_rowstats_wide_kernel(
     const uint16_t* __restrict__ q_txt, const uint16_t* __restrict__ k,
     const uint8_t* __restrict__ vis_valid, const int32_t* __restrict__ txt_len, PrefillDims p, float scale_log2e,
@@ -666,7 +666,7 @@ __global__ __launch_bounds__(256, 2) void prefill_rowstats_wide_kernel(
         int l = lane;
         asm volatile("" : "+v"(l));                   // the lane's offsets are made anew: registers are what this kernel lacks
 #pragma unroll
-        for (int t = 0; t < NLT; ++t) T::issue(rk, krow, src0, t * T::RPL, slot, l, live);
+        for (int t = 0; t < NLT; ++t) T::template issue<STREAM>(rk, krow, src0, t * T::RPL, slot, l, live);
     };
     // validity of the 32 keys of the tiles g0 .. g0+63, one per lane (see prefill_rowstats_kernel)
     auto key_valid_masks = [&](int g0) -> uint32_t {
@@ -1928,22 +1928,25 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
     float2* const partial = w.chunk_stats(p, s);
     if (!row_lse) {
         const dim3 g1 = s.ng == 1 ? dim3(p.nch, p.H, p.B) : dim3((unsigned)(((long)p.nch * p.H * p.B + 7) / 8 * 8 * s.ng));
-#define MD_ROWSTATS2(NBW_, TW_, DEEP_)                                                                         \
-    MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_kernel<NBW_, TW_, KS, DEEP_>), g1, 64 * NBW_ * TW_, 0,     \
+#define MD_ROWSTATS2(NBW_, TW_, ST_, DEEP_)                                                                    \
+    MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_kernel<NBW_, TW_, KS, ST_, DEEP_>), g1, 64 * NBW_ * TW_, 0, \
         qp, kp, vis_valid, txt_len, p, scale_log2e, partial, w.cstat, w.qfrag, w.rows)
 #define MD_ROWSTATS(NBW_, TW_)                                                                                 \
         do {                                                                                                   \
-            if (KS == 8 && NBW_ == 1 && TW_ == 4 && s.rs_deep) MD_ROWSTATS2(NBW_, TW_, (KS == 8 && NBW_ == 1 && TW_ == 4)); \
-            else MD_ROWSTATS2(NBW_, TW_, false);                                                               \
+            if (NBW_ * TW_ == 4 && s.rs_stream) MD_ROWSTATS2(NBW_, TW_, (NBW_ * TW_ == 4), false);             \
+            else if (KS == 8 && NBW_ == 1 && TW_ == 4 && s.rs_deep) MD_ROWSTATS2(NBW_, TW_, false, (KS == 8 && NBW_ == 1 && TW_ == 4)); \
+            else MD_ROWSTATS2(NBW_, TW_, false, false);                                                        \
         } while (0)
+#define MD_ROWSTATS_WIDE(ST_)                                                                                  \
+    MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_wide_kernel<KS, ST_>), g1, 256, 0,                     \
+        qp, kp, vis_valid, txt_len, p, scale_log2e, partial, w.cstat, w.qfrag, w.rows)
         const bool big = s.rs_waves == 8;
-        if (s.rs_wide)
-            MD_LAUNCH("prefill_rowstats", st, (prefill_rowstats_wide_kernel<KS>), g1, 256, 0,
-                qp, kp, vis_valid, txt_len, p, scale_log2e, partial, w.cstat, w.qfrag, w.rows);
+        if (s.rs_wide) { if (KS == 8 && s.rs_stream) MD_ROWSTATS_WIDE((KS == 8)); else MD_ROWSTATS_WIDE(false); }
         else if (s.nbw == 1) { if (big) MD_ROWSTATS(1, 8); else MD_ROWSTATS(1, 4); }
         else if (s.nbw == 2) { if (big) MD_ROWSTATS(2, 4); else MD_ROWSTATS(2, 2); }
         else if (big) MD_ROWSTATS(4, 2);
         else if constexpr (KS == 4) MD_ROWSTATS(4, 1);    // (d = 128: the wide form)
+#undef MD_ROWSTATS_WIDE
 #undef MD_ROWSTATS
 #undef MD_ROWSTATS2
         if (p.nch > 1 && !s.own) {

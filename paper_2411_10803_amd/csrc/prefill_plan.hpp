@@ -50,7 +50,7 @@ MD_PLAN_FN ColRun effective_run(int tiles, int H, ColPlan cp) {
 }
 
 // Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; bool rows, rows_lse, rows_stream; ColPlan col; int occ; };
+struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; bool rows, rows_lse, rows_stream; ColPlan col; int occ; };
 
 // masked: the call has a validity mask.  (It decides about forms, not about sizes.)
 inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = false) {
@@ -58,10 +58,17 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     s.nbt = (N + 31) / 32;                            // 32-row text blocks
     s.nbw = s.nbt == 1 ? 1 : (s.nbt == 2 ? 2 : 4);    // text blocks per block, one per wave column
     s.ng = (s.nbt + s.nbw - 1) / s.nbw;               // text groups: each goes over K, side by side
-    // Sweep 1 reads K with plain loads whatever its size: the second sweep finds part of it in the Infinity Cache, also of one that is larger
-    // (us per call, streamed / plain: 24 x 1600 keys, 315 MB, 30 text rows 195 / 188, 10 x 3000, 246 MB, 100 rows 165 / 156, 16 x 2880, 377 MB,
-    // 120 rows 233 / 224, 20 x 2800, 459 MB, 40 rows 241 / 240).
     const double k_mb = (double)B * Mv * H * d * 2 / 1e6;
+    // Sweep 1 reads K with streaming loads where K outgrows the Infinity Cache and there is one text group, up to 64
+    // text rows from 300 MB on, else from 230.  Plain loads leave part of K to the second sweep, but on inputs that
+    // were just written they push the others' dirty lines out under the sweep.
+    // us per call, plain / streaming, on three states in turn and on inputs just made: 100 to 128 rows 8 x 2880 keys of 40 heads
+    // (236 MB) 176 / 187 and 218 / 192, 10 x 3000 (246) 178 / 185 and 220 / 193, 16 x 2880 (377) 253 / 263 and 313 /
+    // 291, 24 x 2880 (566) 360 / 368 and 426 / 391; 20 to 60 rows 8 x 2880 (189) 120 / 125 and 143 / 139, 16 x 2000 (262) 155 /
+    // 168 and 203 / 206, 12 x 2880 (283) 172 / 179 and 225 / 210, 14 x 2880 (330) 191 / 194 and 246 / 228, 16 x 2880 (377) 195 /
+    // 193 and 250 / 237, 20 x 2800 (459) 270 / 269 and 327 / 307.  Several text groups go over K one after the other and
+    // find it in the cache: 6 x 6000 (295), 384 rows 477 / 480 and 483 / 514, 10 x 3600 (295), 200 rows 325 / 345 and 357 / 382.
+    const bool big_k = s.ng == 1 && k_mb > (s.nbw <= 2 ? 300.0 : 230.0);
     // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
     ColPlan& c = s.col;
     c.kb = s.nbw == 1 ? 128 : 64;
@@ -150,6 +157,9 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     // takes the place of the blocks of four waves at d = 128 (13 x 1039 keys, 32 heads, 128 text rows 43 -> 40, 20 x 576, 40
     // heads, 70 rows 53 -> 49), where it is one chunk as well of those of eight; heads of 64 have three smaller blocks per CU (8 x 2000,
     // 128 rows 25 and 28).
+    // (three slots, rs_deep: with K of 160 MB at most; beyond it is alike, us per call with two / three: 8 x 2880 keys, 20 text rows, 189
+    // MB 102.1 / 102.3, 4 x 8000, 30 rows, 262 MB 134.6 / 134.9, and the workspace hangs on the estimate)
+    const bool deep_k = k_mb <= 160.0;
     auto pick = [&](double merge_us, int most, int least_units) {
         double best = 0;
         for (int waves = 4; waves <= (s.ng > 1 ? 4 : 8); waves += 4)
@@ -161,7 +171,7 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
                 // (heads of 64 with four text blocks: three blocks of four waves share a CU, one of eight waves no better than at
                 // d = 128; 2 x 8661 keys, 64 heads, 95 text rows 49.8 -> 38.6)
                 if (s.nbw == 4 && d == 64) { alone = waves == 8 ? 10.0 : 11.5; full = waves == 8 ? 10.5 : 21.0; }
-                if (s.nbw == 1 && d == 128 && waves == 4 && blocks <= kNumCU && k_mb <= 160.0) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
+                if (s.nbw == 1 && d == 128 && waves == 4 && blocks <= kNumCU && deep_k) { alone = 6.0; full = 16.0; }   // (three slots: rs_deep)
                 if (s.nbw == 4 && d == 128 && waves == 4) full = 30.0;
                 const double per_key = alone + (full - alone) * fill;
                 double t = (double)((blocks + places - 1) / places) * (5.0 + 1e-3 * per_key * (Mv + N) / nch) + (nch > 1 ? merge_us : 0.0);
@@ -199,8 +209,9 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
         pick(1.0, most < kOwnChunks ? (int)most : kOwnChunks, s.nbw < 4 ? 1 : 2);
         s.partial_in_pieces = s.nch > s.nch_ws;
     }
+    s.rs_stream = big_k && s.rs_waves == 4;           // (what the estimate picks for K of that size)
     s.rs_wide = s.ng > 1 || (s.nbw == 4 && d == 128 && s.rs_waves == 4);
-    s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && k_mb <= 160.0;
+    s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && deep_k;
     return s;
 }
 

@@ -2,8 +2,8 @@
 // rows and the text lengths can leave of a plan, no block of the run is empty, every unit lies in the block that
 // unit_block names, and no tile is cut into more pieces than the workspace holds.  And of the sweep by single tiles: what it keeps
 // in the memory of the pieces (V and I per text block, the statistics of more chunks than the workspace has room for)
-// fits there, whichever head size the workspace was measured with, and it is taken where its kernels can.  And of the rule for the
-// stores of the kept K rows.
+// fits there, whichever head size the workspace was measured with, and it is taken where its kernels can.  And of the rules for
+// the loads of K in the first sweep and for the stores of the kept K rows.
 #include <stdio.h>
 #include <initializer_list>
 #include <random>
@@ -54,6 +54,7 @@ int main() {
         const char* why = nullptr;
         if (both[0].col.Gmax != both[1].col.Gmax || both[0].col.P != both[1].col.P || both[0].nbt != both[1].nbt) why = "sizes by head size";
         for (const ScorePlan& s : both) {
+            if (s.rs_stream && (s.ng != 1 || s.rs_waves != 4 || s.rs_deep)) why = "streamed row statistics";
             if (s.own_lse && !s.own) why = "with normalisers only";
             if (!s.own) {
                 if (s.partial_in_pieces || s.nch != s.nch_ws) why = "chunks of the persistent form";
@@ -69,6 +70,14 @@ int main() {
         }
         if (why && ++bad <= 10) printf("B=%d Mv=%d N=%d H=%d: %s\n", B, Mv, N, H, why);
     }
+    // which calls read K for the row statistics past the Infinity Cache: one text group and K well beyond the cache
+    struct { int B, Mv, N, H, d; bool want; } const reads[] = {
+        {24, 2880, 100, 32, 128, true}, {10, 3000, 100, 32, 128, true}, {8, 2880, 128, 32, 128, false}, {7, 9172, 113, 28, 64, true},
+        {20, 2800, 40, 32, 128, true}, {12, 2880, 60, 32, 128, false}, {2, 18500, 32, 32, 128, true}, {2, 18700, 64, 32, 128, true},
+        {8, 9161, 30, 33, 64, true}, {8, 9200, 48, 32, 64, true}, {6, 6000, 384, 32, 128, false}, {1, 1, 1, 1, 64, false}};
+    for (const auto& r : reads)
+        if (plan_scores(r.B, r.Mv, r.N, r.H, r.d).rs_stream != r.want && ++bad)
+            printf("B=%d Mv=%d N=%d H=%d d=%d: K of the row statistics\n", r.B, r.Mv, r.N, r.H, r.d);
     // which calls write the kept K rows past the Infinity Cache: not those whose next reader finds them there
     struct { int B, Mv, N, H, d, Rcap; bool threshold, lse, want; } const moves[] = {
         {16, 576, 64, 32, 128, 192, false, false, true}, {16, 192, 64, 32, 128, 128, false, false, false},       // successive layers
