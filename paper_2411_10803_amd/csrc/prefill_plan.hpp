@@ -112,33 +112,34 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     s.own = s.nbt <= kOwnParts && Mv <= 8192 && s.own_blocks <= 2 * own_round && heads <= 54 + 0.4 * s.own_blocks;
     // (with the caller's row normalisers, K has not been read before: one round, 23 x 181 keys, 45 text rows, 276 blocks 50 / 54)
     s.own_lse = s.own && s.own_blocks <= own_round && heads <= 46 + 0.22 * s.own_blocks;
-    // Up to 64 text rows a block of single tiles takes all of them (prefill_colrows_kernel): K is read once, there is one (V, I) pair per
-    // key, and the call may be of any size as long as whole rounds of the 256 CUs do not leave too much of the last one idle.
-    // us per call, before / now, 32 heads of 128: 16 x 576 keys at 3/4 valid, 20 text rows 60.5 / 54.4, 60 rows 75.5 / 67.2; with row
-    // normalisers 52.2 / 45.6 and 61.0 / 54.9; 8 x 1200 at 4/5, 60 rows 73.0 / 66.0; 24 x 1600 at 4/5, 20 rows 206 / 196, 60 rows 234 /
-    // 220; 2 x 4000, 60 rows with normalisers 53.9 / 47.2.  Where a second round begins: 16 x 576 all valid (288 tiles), 60 rows 79.7 /
-    // 81.2, with normalisers 64.0 / 67.7; 8 x 2880 at 4/5 (576 of 720 tiles), 60 rows 133 / 138, 20 rows 121.0 / 125.5.  (With a
-    // mask four fifths of the slots are taken to be valid: stage 1 leaves three quarters.)
-    // With two text blocks, where single tiles of one each have their second round (4 x 1000 keys at 4/5, 128 tiles, 60 rows 40.6 / 44.4; 8
-    // x 576, 144 tiles, 48.9 / 45.4).
+    // Up to 64 text rows: blocks of 32 keys that take all text rows and heads (prefill_colrows_kernel).  K is read once and
+    // there is one (V, I) pair per key, but a block is long, and the CUs that the last round of blocks leaves idle
+    // are what the form can lose by.  (With a mask four fifths of the slots are taken to be valid: stage 1 leaves three quarters.)
+    // idle: that part of a round, times its length in heads.
+    //
+    // One text block: always; with the caller's normalisers, when K has not been read before and the persistent form is
+    // no longer bound by it alone, where idle is at most 20.  Two: where single tiles of one text block would have a second
+    // round, and idle is at most 20 with normalisers, else 16 in two rounds, 12 in three, 10 in four (the persistent
+    // form's part that does not shrink with K, its pieces, counts for less in more rounds).  Heads of 64 share a CU between two
+    // blocks, which evens the rounds out: they need only be beyond the two rounds of single tiles.
+    //
+    // us per call, persistent or single tiles / this form, 32 heads of 128 unless said otherwise:
+    // one text block, 8 x 1085 keys (1.06 rounds) 60.1 / 60.4, 8 x 2918 (2.85) 126.7 / 120.8, 24 x 1600 at 4/5 192.6 / 181.3; with
+    // normalisers 1.06 rounds 51.7 / 53.2, 1.4 61.4 / 58.9, 2.06 78.4 / 80.5, 2.85 99.5 / 94.2;
+    // two, 16 x 576 at 4/5 75.6 / 66.0; 1.2 rounds 75.1 / 75.8, 1.6 88.7 / 86.3, 2.3 112.1 / 119.2, 2.85 133.4 / 134.8, 3.16 147.3 / 154.4,
+    // 3.75 (24 x 1600 at 4/5) 228.0 / 211.4; 16 heads, 1.2 rounds 52.5 / 49.3, 2.6 79.8 / 75.2, 3.06 88.6 / 90.2, 4.1 at 4/5 115.1 /
+    // 122.9; 8 heads, 3.4 rounds 76.4 / 70.6; with normalisers 1.2 rounds 61.7 / 64.7, 1.6 73.1 / 70.9, 2.06 86.1 / 90.8, 3.4 127.7 /
+    // 124.5, 16 heads 2.06 57.9 / 58.1, 3.4 76.9 / 74.5; 4 x 1000 at 4/5 (128 tiles) 40.6 / 44.4;
+    // heads of 64, two text blocks, 16 x 576 44.3 / 45.6, 24 x 900 89.9 / 84.4, 4 x 7000 at 4/5 97.0 / 88.8, 12 heads 60 x 576 66.1 / 60.9; with
+    // normalisers 16 x 576 45.8 / 39.8, 24 x 1600 105.6 / 101.7.
     const long tiles = (long)B * ((Mv + 31) / 32);
     const double rounds = (masked ? 0.8 : 1.0) * tiles / kNumCU;
     const long whole = (long)rounds + (rounds > (long)rounds ? 1 : 0);
-    const bool even = whole <= 1 || whole <= 1.27 * rounds;
-    // Fewer than 16 heads only where single tiles would be taken anyway.  They would gain beyond as well (60 x 576 keys at 4/5, 12 heads of 64, 32
-    // rows 57.2 / 45.5), but no model at hand has so few, and the persistent form, which more than 8192 slots and many heads on few tiles
-    // still need with one and two text blocks, is tested over many tiles there.
-    const bool heads_lse = heads <= 46 + 0.22 * tiles && (H >= 16 || s.own_lse), heads_own = heads <= 54 + 0.4 * tiles && (H >= 16 || s.own);
+    const double idle = (whole - rounds) * H;
     s.rows = s.rows_lse = false;
-    if (Mv <= 8192 && s.nbt == 1) {
-        // heads of 64 share a CU between two blocks, which evens the rounds out (24 x 1600 at 4/5, 20 rows 125.7 / 106.6, 8 x 2880 71.8 / 70.2)
-        s.rows = heads_own && (even || d == 64 || s.own);
-        s.rows_lse = heads_lse && (even || d == 64);
-    } else if (Mv <= 8192 && s.nbt == 2 && tiles > kNumCU / 2) {
-        // heads of 64: single tiles are still two rounds of two blocks (16 x 576 43.0 / 46.5; 8 x 2880 at 4/5 81.1 / 84.7); with
-        // normalisers they have one (16 x 576 45.0 / 39.9; 4 x 2880 at 4/5 45.0 / 43.0; 24 x 1200 84.8 / 82.0)
-        s.rows = heads_own && (d == 64 ? whole <= 1 : even);
-        s.rows_lse = heads_lse && (even || d == 64);
+    if (Mv <= 8192 && (s.nbt == 1 || (s.nbt == 2 && tiles > kNumCU / 2))) {
+        s.rows = heads <= 54 + 0.4 * tiles && (s.nbt == 1 || whole <= 1 || (d == 64 ? !s.own : idle <= 4.0 + 24.0 / whole));
+        s.rows_lse = heads <= 46 + 0.22 * tiles && (whole <= 1 || d == 64 || idle <= 20.0);
     }
     s.own |= s.rows;
     // K that has not been read before, of a size that will not be in the Infinity Cache either (up to there plain loads: heads of 64, 16 x

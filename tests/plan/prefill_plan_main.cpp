@@ -2,7 +2,8 @@
 // rows and the text lengths can leave of a plan, no block of the run is empty, every unit lies in the block that
 // unit_block names, and no tile is cut into more pieces than the workspace holds.  And of the sweep by single tiles: what it keeps
 // in the memory of the pieces (V and I per text block, the statistics of more chunks than the workspace has room for)
-// fits there, whichever head size the workspace was measured with, and it is taken where its kernels can.  And of the rules for
+// fits there, whichever head size the workspace was measured with and whatever a mask or the caller's normalisers change of the
+// form, and it is taken where its kernels can.  And of the rules for the form that takes all text rows of a tile, for
 // the loads of K in the first sweep and for the stores of the kept K rows.
 #include <stdio.h>
 #include <initializer_list>
@@ -41,7 +42,7 @@ int main() {
                     }
                 }
     std::mt19937 rng(1);
-    long own = 0, behind = 0;
+    long own = 0, behind = 0, rows = 0, by_mask = 0;
     auto log_uniform = [&](int lo, int hi) {
         const double r = (double)rng() / 4294967296.0, lg = r * __builtin_log((double)(hi + 1) / lo);
         const int v = (int)(lo * __builtin_exp(lg));
@@ -50,25 +51,49 @@ int main() {
     for (int i = 0; i < 300000; ++i) {
         const int B = log_uniform(1, 200), Mv = log_uniform(1, 10000), N = log_uniform(1, 300), H = log_uniform(1, 128);
         const ScorePlan both[2] = {plan_scores(B, Mv, N, H, 64), plan_scores(B, Mv, N, H, 128)};
+        const ScorePlan with_mask[2] = {plan_scores(B, Mv, N, H, 64, true), plan_scores(B, Mv, N, H, 128, true)};
         const long room = both[0].nch_ws > both[1].nch_ws ? both[0].nch_ws : both[1].nch_ws;          // as the workspace has it
         const char* why = nullptr;
         if (both[0].col.Gmax != both[1].col.Gmax || both[0].col.P != both[1].col.P || both[0].nbt != both[1].nbt) why = "sizes by head size";
-        for (const ScorePlan& s : both) {
+        for (int m = 0; m < 8 && !why; ++m) {         // head size x mask x normalisers
+            const ScorePlan& plain = both[m & 1];
+            const ScorePlan s = m & 4 ? with_normalisers(m & 2 ? with_mask[m & 1] : plain) : m & 2 ? with_mask[m & 1] : plain;
+            if (s.col.Gmax != plain.col.Gmax || s.col.P != plain.col.P || s.col.U != plain.col.U || s.col.kb != plain.col.kb || s.nbt != plain.nbt ||
+                s.nch_ws != plain.nch_ws) why = "sizes by mask";
             if (s.rs_stream && (s.ng != 1 || s.rs_waves != 4 || s.rs_deep)) why = "streamed row statistics";
-            if (s.own_lse && !s.own) why = "with normalisers only";
+            if (m & 4 && s.nch != 1) why = "chunks with normalisers";
+            if (s.rows && (!s.own || s.nbt > 2)) why = "all text rows of a tile";
+            by_mask += m < 4 && (m & 2) && s.rows != plain.rows;
+            rows += s.rows;
             if (!s.own) {
-                if (s.partial_in_pieces || s.nch != s.nch_ws) why = "chunks of the persistent form";
+                if (!(m & 4) && (s.partial_in_pieces || s.nch != s.nch_ws)) why = "chunks of the persistent form";
                 continue;
             }
             ++own;
             const long Npad = 32l * s.nbt, pieces = (long)s.col.Gmax * B * Mv * Npad;                // floats
-            const long scores = s.nbt > 1 || s.partial_in_pieces ? 2l * s.nbt * B * Mv : 0, stats = 2l * B * H * s.nch * Npad;
+            const long scores = (s.nbt > 1 && !s.rows) || s.partial_in_pieces ? 2l * s.nbt * B * Mv : 0, stats = 2l * B * H * s.nch * Npad;
             if (s.ng != 1 || s.nbt > kOwnParts || Mv > 8192 || s.nch < 1 || s.nch > kOwnChunks || s.own_blocks != (long)B * ((Mv + 31) / 32) * s.nbt) why = "form";
             else if (scores > pieces) why = "scores";
+            else if (m & 4) continue;                 // (one statistic per row, in memory of its own)
             else if (s.partial_in_pieces ? scores + stats > pieces : s.nch > room) why = "chunk statistics";
             behind += s.partial_in_pieces;
         }
         if (why && ++bad <= 10) printf("B=%d Mv=%d N=%d H=%d: %s\n", B, Mv, N, H, why);
+    }
+    // Blocks that take all text rows of a key tile: few heads as well as many, whole rounds of blocks and those that leave
+    // little of the last one idle.  plan: without and with the caller's normalisers.
+    struct { int B, Mv, N, H, d; bool masked, rows, rows_lse; } const forms[] = {
+        {60, 576, 32, 12, 64, true, true, true}, {60, 576, 32, 8, 128, true, true, true}, {24, 1600, 60, 4, 128, true, true, true},
+        {32, 576, 60, 12, 128, false, true, true}, {24, 576, 20, 4, 128, false, true, true},
+        {16, 576, 60, 32, 128, true, true, true}, {8, 1085, 20, 32, 128, false, true, false}, {8, 2109, 20, 32, 128, false, true, false},
+        {8, 2662, 20, 32, 128, false, true, true}, {8, 1843, 60, 32, 128, false, true, true}, {8, 2355, 60, 32, 128, false, false, false},
+        {8, 3235, 60, 32, 128, false, false, false}, {24, 1600, 60, 32, 128, true, true, true}, {16, 2600, 60, 16, 128, true, false, true},
+        {8, 2355, 60, 16, 128, false, true, true}, {16, 576, 60, 32, 64, false, false, true}, {4, 7000, 60, 32, 64, true, true, true},
+        {4, 1000, 60, 32, 128, true, false, false}, {5, 8193, 20, 12, 64, true, false, false}, {1, 576, 20, 96, 64, false, false, false}};
+    for (const auto& f : forms) {
+        const ScorePlan s = plan_scores(f.B, f.Mv, f.N, f.H, f.d, f.masked);
+        if ((s.rows != f.rows || with_normalisers(s).rows != f.rows_lse) && ++bad)
+            printf("B=%d Mv=%d N=%d H=%d d=%d masked=%d: all text rows of a tile %d %d\n", f.B, f.Mv, f.N, f.H, f.d, f.masked, s.rows, with_normalisers(s).rows);
     }
     // which calls read K for the row statistics past the Infinity Cache: one text group and K well beyond the cache
     struct { int B, Mv, N, H, d; bool want; } const reads[] = {
@@ -90,8 +115,8 @@ int main() {
     for (const auto& m : moves)
         if (streams_k_out(m.B, m.Mv, m.N, m.H, m.d, m.H * m.d, m.Rcap, m.threshold, m.lse) != m.want && ++bad)
             printf("B=%d Mv=%d N=%d Rcap=%d threshold=%d lse=%d: K rows out\n", m.B, m.Mv, m.N, m.Rcap, m.threshold, m.lse);
-    if (own < 10000 || behind < 1000) { ++bad; printf("too few single tiles looked at\n"); }
-    printf("%ld plans of single tiles, %ld with statistics behind the scores\n", own, behind);
+    if (own < 10000 || behind < 1000 || rows < 10000 || by_mask < 1000) { ++bad; printf("too few single tiles looked at\n"); }
+    printf("%ld plans of single tiles, %ld with statistics behind the scores, %ld with all text rows of a tile, %ld so by the mask\n", own, behind, rows, by_mask);
     printf("%ld plans, %ld runs, %ld wrong\n", plans, runs, bad);
     return bad != 0;
 }

@@ -77,7 +77,7 @@ def test_more_than_64_samples(N, with_lse):
 
 
 # Most of the calls above are small enough for single tiles.  Those below take the persistent form with its pieces: one image
-# with many heads, and batches beyond two rounds of tiles, with one text block per group and with two.
+# with many heads, and images of more than 8192 slots, with one text block per group and with two.
 @pytest.mark.parametrize("with_lse", [False, True])
 @pytest.mark.parametrize("valid", [1, 128, 144, 256])
 @pytest.mark.parametrize("H", [96, 128])
@@ -85,11 +85,22 @@ def test_few_valid_slots_of_one_image_in_pieces(H, valid, with_lse):
     check(H, [valid], 20, None, with_lse, pieces=True)
 
 
+def few_of_many(B, N, H, with_lse, side, pieces):
+    rng = np.random.default_rng(B * N)
+    valid = [int(v) for v in rng.choice([1, 2, 31, 64, 128, 130], size=B)]
+    valid[B // 2] = side * side
+    txt = [0 if b % 9 == 4 else int(rng.integers(1, N + 1)) for b in range(B)]
+    check(H, valid, N, txt, with_lse, side, pieces)
+
+
 @pytest.mark.parametrize("B,N,H", [(60, 20, 3), (60, 32, 12), (32, 60, 2), (32, 64, 9)])
 @pytest.mark.parametrize("with_lse", [False, True])
 def test_few_units_of_many_planned(B, N, H, with_lse):
-    rng = np.random.default_rng(B * N)
-    valid = [int(v) for v in rng.choice([1, 2, 31, 64, 128, 130], size=B)]
-    valid[B // 2] = 576
-    txt = [0 if b % 9 == 4 else int(rng.integers(1, N + 1)) for b in range(B)]
-    check(H, valid, N, txt, with_lse, pieces=True)
+    few_of_many(B, N, H, with_lse, 24, False)
+
+
+# more slots than the blocks that take all text rows of a key tile have room for
+@pytest.mark.parametrize("B,N,H", [(6, 20, 3), (5, 32, 12), (4, 60, 2), (5, 64, 9)])
+@pytest.mark.parametrize("with_lse", [False, True])
+def test_few_units_of_many_planned_in_pieces(B, N, H, with_lse):
+    few_of_many(B, N, H, with_lse, 91, True)

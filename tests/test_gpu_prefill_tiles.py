@@ -57,12 +57,12 @@ def test_single_tiles(B, Mv, N, H, d, head_major, mask, with_lse):
 
 
 # a key whose K row is no number in one head: its V is none either, and the maximum over scores that are none is 0, in both forms
-# of the sweep (30 images are 540 blocks of single tiles, beyond two rounds)
-@pytest.mark.parametrize("B", [1, 3, 30])
+# of the sweep (more than 8192 slots: the persistent one)
+@pytest.mark.parametrize("B,side", [(1, 24), (3, 24), (30, 24), (1, 91)])
 @pytest.mark.parametrize("with_lse", [False, True])
-def test_key_row_that_is_no_number(B, with_lse):
+def test_key_row_that_is_no_number(B, side, with_lse):
     from paper_2411_10803_amd import harness
-    cfg = wl.tiny(wl.CONFIGS[2], B=B, T=1, Hg=24, Wg=24, N=32, H=3, d=128, C=8)
+    cfg = wl.tiny(wl.CONFIGS[2], B=B, T=1, Hg=side, Wg=side, N=32, H=3, d=128, C=8)
     t = wl.prefill_inputs(cfg)
     Mv, scale = cfg.M, 1.0 / np.sqrt(128)
     lse = normalisers(t, Mv, np.ones((B, Mv), np.uint8), scale) if with_lse else None
