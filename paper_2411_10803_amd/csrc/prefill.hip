@@ -1983,17 +1983,10 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
     MD_LAUNCH("prefill_colscore", st, (prefill_colscore_kernel<NBW_, KT_, KS, M_, ST_>), s.col.P, 256, 0,          \
         w.qfrag, kp, w.cstat, w.rows, p, s.col, scale_log2e, w.apart)
     // 32 * (4 / NBW) * KT keys per unit = s.col.kb
-    // K by streaming loads, which leave the cache to the query fragments, or by plain ones.  Several text groups read K one after the other,
-    // so plain, unless the fragments are many (us per call, streaming / plain: 3 x 9000 keys, 300 rows, row normalisers 211 / 198, 8 x 2880,
-    // 200 rows 143 / 135, without 6 x 1152, 384 rows, 19 MB of fragments 142 / 140; 20 x 576, 200 rows, 37 MB 181 / 184).  One group: the last read of
-    // these rows, of which sweep 1 leaves nearly all in the Infinity Cache if they are no more than 105 MB (16 x 576, 128 rows 106.5 / 102.6, 14 x
-    // 900 110.8 / 108.3, 4 x 2880, 94 MB 83.5 / 84.1, 8 x 2880, 189 MB 126.1 / 127.0; with row normalisers 4 x 2000, 100 rows 53.1 / 54.6).
-    const double row_mb = (double)p.B * p.H * p.d * 2e-6;
-    const bool plain = s.ng > 1 ? row_mb * p.Npad < 28.0 : !row_lse && row_mb * p.Mv < 105.0;
     if (s.nbw == 1) MD_COLSCORE(1, 1, false, true);
     else if (s.nbw == 2) MD_COLSCORE(2, 1, false, true);
-    else if (s.ng == 1) { if (plain) MD_COLSCORE(4, 2, false, false); else MD_COLSCORE(4, 2, false, true); }
-    else { if (plain) MD_COLSCORE(4, 2, true, false); else MD_COLSCORE(4, 2, true, true); }
+    else if (s.ng == 1) { if (s.col_stream) MD_COLSCORE(4, 2, false, true); else MD_COLSCORE(4, 2, false, false); }
+    else { if (s.col_stream) MD_COLSCORE(4, 2, true, true); else MD_COLSCORE(4, 2, true, false); }
 #undef MD_COLSCORE
     const int fx = (p.Mv + 4 * kFixKeys - 1) / (4 * kFixKeys);          // four waves of kFixKeys keys per block
     // pieces that a tile has as a rule, by the length of the blocks' runs (one that has fewer reads in vain), and the rows of the

@@ -50,7 +50,7 @@ MD_PLAN_FN ColRun effective_run(int tiles, int H, ColPlan cp) {
 }
 
 // Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; bool rows, rows_lse, rows_stream; ColPlan col; int occ; };
+struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; bool rows, rows_lse, rows_stream, col_stream; ColPlan col; int occ; };
 
 // masked: the call has a validity mask.  (It decides about forms, not about sizes.)
 inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = false) {
@@ -213,6 +213,16 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     s.rs_stream = big_k && s.rs_waves == 4;           // (what the estimate picks for K of that size)
     s.rs_wide = s.ng > 1 || (s.nbw == 4 && d == 128 && s.rs_waves == 4);
     s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && deep_k;
+    // The persistent column sweep reads K by streaming loads, which leave the cache to the query fragments, unless it is likely to
+    // find K there.  One text group: where sweep 1 has read K with plain loads, or not at all.  Several groups read K one after
+    // the other: plain, unless the fragments are many (28 MB).
+    // us per call, streaming / plain, on three states in turn and on inputs just made: one group, 65 to 128 rows, 4 x 2880 keys at 3/4 88.3 /
+    // 85.9 and 100.7 / 99.3; 6 x 2000 (98 MB) 97.3 / 96.0 and 107.9 / 104.2; 8 x 2300 at 4/5 (151) 122.7 / 120.6 and
+    // 133.1 / 128.9; 8 x 2880 at 3/4 (189) 141.3 / 138.9 and 152.8 / 146.8; behind streaming loads 10 x 2880 (236) 202.9 / 199.8 and 207.1 /
+    // 213.0, 16 x 2600 (341) 268.6 / 263.1 and 271.5 / 275.8; with normalisers 6 x 2000 77.6 / 81.1 and 80.6 / 85.0, 8 x 2880 at 3/4
+    // 113.7 / 110.8 and 119.0 / 120.5, 16 x 2600 200.6 / 199.5 and 207.9 / 212.6.  Several: 3 x 9000, 300 rows, normalisers
+    // 211 / 198, 8 x 2880, 200 rows 143 / 135, without 6 x 1152, 384 rows, 19 MB of fragments 142 / 140; 20 x 576, 200 rows, 37 MB 181 / 184.
+    s.col_stream = s.ng > 1 ? (double)B * H * d * 2e-6 * 32 * s.nbt >= 28.0 : s.nbw < 4 || s.rs_stream;
     return s;
 }
 
@@ -221,6 +231,7 @@ inline ScorePlan with_normalisers(ScorePlan s) {
     s.nch = 1;
     s.rows = s.rows_lse;
     s.own = s.own_lse || s.rows;
+    s.col_stream |= s.ng == 1;
     return s;
 }
 

@@ -103,6 +103,16 @@ int main() {
     for (const auto& r : reads)
         if (plan_scores(r.B, r.Mv, r.N, r.H, r.d).rs_stream != r.want && ++bad)
             printf("B=%d Mv=%d N=%d H=%d d=%d: K of the row statistics\n", r.B, r.Mv, r.N, r.H, r.d);
+    // and for the column sweep: what sweep 1 leaves in the cache, K that several text groups share with few fragments
+    struct { int B, Mv, N, H, d; bool want, want_lse; } const again[] = {
+        {16, 576, 128, 32, 128, false, true}, {4, 2880, 120, 32, 128, false, true}, {8, 2880, 128, 32, 128, false, true}, {10, 2880, 100, 32, 128, true, true},
+        {24, 2880, 100, 32, 128, true, true}, {8, 2000, 100, 40, 64, false, true}, {1, 9000, 40, 32, 128, true, true}, {1, 9000, 20, 32, 128, true, true},
+        {3, 4608, 300, 32, 128, false, false}, {6, 1152, 384, 32, 128, false, false}, {20, 576, 200, 32, 128, true, true}};
+    for (const auto& r : again) {
+        const ScorePlan s = plan_scores(r.B, r.Mv, r.N, r.H, r.d);
+        if ((s.col_stream != r.want || with_normalisers(s).col_stream != r.want_lse) && ++bad)
+            printf("B=%d Mv=%d N=%d H=%d d=%d: K of the column sweep\n", r.B, r.Mv, r.N, r.H, r.d);
+    }
     // which calls write the kept K rows past the Infinity Cache: not those whose next reader finds them there
     struct { int B, Mv, N, H, d, Rcap; bool threshold, lse, want; } const moves[] = {
         {16, 576, 64, 32, 128, 192, false, false, true}, {16, 192, 64, 32, 128, 128, false, false, false},       // successive layers
