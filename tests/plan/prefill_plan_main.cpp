@@ -6,6 +6,7 @@
 // form, and it is taken where its kernels can.  And of the rules for the form that takes all text rows of a tile, for
 // the loads of K in the first sweep and for the stores of the kept K rows.
 #include <stdio.h>
+#include <stdlib.h>
 #include <initializer_list>
 #include <random>
 
@@ -13,7 +14,19 @@
 
 using namespace md;
 
-int main() {
+static const char* column_form(const ScorePlan& s) { return s.rows ? "rows" : s.own ? "tiles" : "persistent"; }
+
+// With arguments B Mv N H d masked: the form of that one call.
+int main(int argc, char** argv) {
+    if (argc == 7) {
+        int a[6];
+        for (int i = 0; i < 6; ++i) a[i] = atoi(argv[1 + i]);
+        const ScorePlan s = plan_scores(a[0], a[1], a[2], a[3], a[4], a[5] != 0);
+        printf("%s", column_form(s));
+        if (s.rs_wide) printf(" wide %d chunk%s", s.nch, s.nch == 1 ? "" : "s");
+        printf(", with normalisers %s\n", column_form(with_normalisers(s)));
+        return 0;
+    }
     long plans = 0, runs = 0, bad = 0;
     const int more_heads[] = {20, 24, 32, 40, 64, 96, 127, 128};
     for (int N : {1, 32, 33, 64, 65, 128, 129, 300, 1024})
@@ -63,6 +76,7 @@ int main() {
             if (s.rs_stream && (s.ng != 1 || s.rs_waves != 4 || s.rs_deep)) why = "streamed row statistics";
             if (m & 4 && s.nch != 1) why = "chunks with normalisers";
             if (s.rows && (!s.own || s.nbt > 2)) why = "all text rows of a tile";
+            if (s.own && !s.rows && s.nbt == 1) why = "one text block in single tiles";
             by_mask += m < 4 && (m & 2) && s.rows != plain.rows;
             rows += s.rows;
             if (!s.own) {
@@ -125,6 +139,7 @@ int main() {
     for (const auto& m : moves)
         if (streams_k_out(m.B, m.Mv, m.N, m.H, m.d, m.H * m.d, m.Rcap, m.threshold, m.lse) != m.want && ++bad)
             printf("B=%d Mv=%d N=%d Rcap=%d threshold=%d lse=%d: K rows out\n", m.B, m.Mv, m.N, m.Rcap, m.threshold, m.lse);
+    if (!streams_k_out(4, 3000, 20, 34, 128, 8, 1000, false, false) && ++bad) printf("K rows out of the head-major test\n");
     if (own < 10000 || behind < 1000 || rows < 10000 || by_mask < 1000) { ++bad; printf("too few single tiles looked at\n"); }
     printf("%ld plans of single tiles, %ld with statistics behind the scores, %ld with all text rows of a tile, %ld so by the mask\n", own, behind, rows, by_mask);
     printf("%ld plans, %ld runs, %ld wrong\n", plans, runs, bad);
