@@ -1889,11 +1889,11 @@ struct PrefillWorkspace {
     float2* partial; float* cstat; bf16x8* qfrag; float* apart; float* V; float* I; float* score; int32_t* src_row;
     SampleRows* rows;
     size_t bytes;
-    // V and I as the column sweep leaves them: one array each, or one per text block (ScorePlan::own) in the memory of the pieces,
-    // which that form does not write (a piece is at least 32 floats per key and text block)
+    // V and I as the column sweep leaves them: one array each, or one per text block (ScorePlan::own without ::rows, two to
+    // four text blocks) in the memory of the pieces, which that form does not write (a piece is at least 32 floats per key and text block)
     struct ScoreParts { float* V; float* I; int parts; };
     ScoreParts score_parts(const PrefillDims& p, const ScorePlan& s) const {
-        if (!s.own || s.nbt == 1 || s.rows) return ScoreParts{V, I, 1};
+        if (!s.own || s.rows) return ScoreParts{V, I, 1};
         return ScoreParts{apart, apart + (size_t)s.nbt * p.B * p.Mv, s.nbt};
     }
     float2* chunk_stats(const PrefillDims& p, const ScorePlan& s) const {

@@ -50,7 +50,17 @@ MD_PLAN_FN ColRun effective_run(int tiles, int H, ColPlan cp) {
 }
 
 // Launch shapes of the two sweeps; pure host arithmetic shared by the workspace size and the launch.
-struct ScorePlan { int nbt, nbw, ng, nch, rs_waves; bool rs_stream, rs_deep, rs_wide, own, own_lse, partial_in_pieces; int nch_ws; long own_blocks; bool rows, rows_lse, rows_stream, col_stream; ColPlan col; int occ; };
+struct ScorePlan {
+    int nbt, nbw, ng;                                 // text blocks of 32 rows; those of one group; groups
+    int nch, rs_waves;                                // sweep 1: key chunks per (sample, head, group), waves of a block
+    bool rs_stream, rs_deep, rs_wide;                 // streaming loads of K; three LDS slots; the wide form
+    bool own, own_lse, partial_in_pieces;             // sweep 2 by single tiles; so with normalisers; chunk statistics behind V and I
+    int nch_ws;                                       // chunks that the workspace has room for
+    long own_blocks;
+    bool rows, rows_lse, rows_stream, col_stream;     // single tiles with all text rows; so with normalisers; streaming loads of K
+    ColPlan col;
+    int occ;
+};
 
 // masked: the call has a validity mask.  (It decides about forms, not about sizes.)
 inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = false) {
@@ -75,53 +85,53 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     c.nkg = (Mv + c.kb - 1) / c.kb;
     c.nbw = s.nbw;
     c.U = (long)B * c.nkg * H * s.ng;
-    // blocks per CU: two where a block holds four text blocks (the second block covers the first one's waits),
-    // and with two text blocks when the runs stay long enough (20 units per CU); otherwise one (fewer, longer
-    // runs: fewer pieces, fewer prologues; measured faster there)
+    // Blocks per CU: two where a block holds four text blocks (the second one covers the first one's waits), and with two
+    // text blocks when the runs stay long enough (20 units per CU); otherwise one (fewer, longer runs: fewer pieces,
+    // fewer prologues; measured faster there).
     s.occ = s.nbw == 4 || (s.nbw == 2 && c.U >= 20L * kNumCU) ? 2 : 1;
-    // (two of them where a single text block would leave three quarters of the CUs idle.  Nearly all such calls take single tiles now
-    // and this only sizes their workspace; those of many heads still run so.  Measured on calls that have left: 1 x 576 keys 9.2 us for
-    // the sweep + 5.9 for its pieces with four, 7.2 + 6.6 with two; 4 x 576 with 100 text rows 12.9 + 5.6 and 13.4 + 7.1; and 2 x
-    // 1121 keys of 64, 32 heads, 28 text rows, with row normalisers: 28.7 and 29.1 for the call)
+    // Units per block, at least: four; two where a single text block would leave most CUs idle.
+    // us per call, four / two: 1 x 9000 keys, 28 text rows, 3 heads of 128 62.2 / 59.6, 2 x 9000, 1 head 66.3 / 62.8.  Of small images the
+    // persistent form only takes those of very many heads, which lose by the sum of the pieces (1 x 512 keys, 64 heads 36.9 / 36.7,
+    // 1 x 256, 127 heads 47.5 / 49.5); for all others this sizes the memory in which single tiles keep the statistics of their chunks.
     const long least = s.nbw == 1 && c.U < kNumCU ? 2 : 4;
     long P = (c.U + least - 1) / least;
     if (P > kNumCU * s.occ) P = kNumCU * s.occ;
     if (P < 1) P = 1;
     c.P = (int)P;
-    // pieces a key group can be cut into; sized for half the planned units (samples whose valid vision rows
-    // are a prefix of their slots bring fewer key groups), beyond that fewer blocks work
+    // Pieces a key group can be cut into: sized for half the planned units (samples whose valid vision rows are a prefix of
+    // their slots bring fewer key groups), beyond that fewer blocks work.
     c.Gmax = (int)((2L * H * c.P + c.U - 1) / c.U) + 1;
     if (c.Gmax > H) c.Gmax = H;
-    // Sweep 2 by blocks of one tile (32 keys, 32 text rows, all heads) where they are no more than two rounds, of one block per CU or,
-    // with heads of 64, of two: the blocks of the persistent form hand over their sums through memory and another launch, and
-    // leave most of the chip idle on small calls.  us per call, persistent / single tiles (up to 32 text rows before the form further
-    // down, which takes those now, was there): 1 x 576 keys, 32 text rows 33 / 28, 128 rows
-    // 39 / 28; 14 x 576, 32 rows 64 / 57 (252 blocks), 28 x 576 118 / 111 (504), 2 x 1246, 114 rows, 16 heads 41 / 35 (312); heads of 64, 12 x
-    // 300, 20 rows 28 / 20, 20 x 1000, 28 rows 84 / 72 (640).  Behind that the query fragments, read for every 32 keys, come to more:
-    // 4 x 4248, 25 rows 112 / 119 (532), 8 x 1955, 118 rows 144 / 183 (1984); heads of 64, 3 x 7055, 92 rows 125 / 134 (1989).  (Of
-    // 26 calls of 257 to 512 blocks 20 gain 2 to 15 %, none loses more than 1.5.)
+    // Sweep 2 by blocks of one tile (32 keys, 32 text rows, all heads): where they are no more than two rounds, of one block
+    // per CU or, with heads of 64, of two; with the caller's normalisers one round, as K has not been read before.  The blocks of the
+    // persistent form hand over their sums through memory and another launch, and leave most of the chip idle on small
+    // calls; behind two rounds the query fragments, read for every 32 keys, come to more.
+    // (Up to 64 text rows the form further down has taken these calls over where it may; it keeps the line of one text block.)
+    // us per call, persistent / single tiles: 1 x 576 keys, 32 text rows 33 / 28, 128 rows 39 / 28; 14 x 576, 32 rows 64 / 57 (252
+    // blocks), 28 x 576 118 / 111 (504), 2 x 1246, 114 rows, 16 heads 41 / 35 (312); heads of 64, 12 x 300, 20 rows 28 / 20,
+    // 20 x 1000, 28 rows 84 / 72 (640).  Beyond: 4 x 4248, 25 rows 112 / 119 (532), 8 x 1955, 118 rows 144 / 183 (1984); heads of 64,
+    // 3 x 7055, 92 rows 125 / 134 (1989).  With normalisers 23 x 181, 45 rows 50 / 54 (276).  (Of 26 calls of 257 to 512 blocks
+    // 20 gain 2 to 15 %, none loses more than 1.5.)
     const long own_round = d == 64 ? 2l * kNumCU : kNumCU;
     s.own_blocks = (long)B * ((Mv + 31) / 32) * s.nbt;
-    // A block takes in all heads one after the other on one CU, the persistent form spreads them: with many heads and few blocks that
-    // is the longer way, with heads of 64 from 1.4 times as many on.  us per call, persistent / single tiles, heads of 128: 1 x 576
-    // keys, 32 text rows (18 blocks), 56 heads 37.3 / 36.8, 64 37.2 / 38.0, 96 43.7 / 49.8, 128 49.3 / 58.9; 128 rows (72) 80 heads
-    // 50.6 / 47.8, 96 53.4 / 56.4; 6 x 576, 32 rows (108) 96 85.8 / 85.2, 128 105.8 / 108.4; with the caller's normalisers 1 x 576, 32
-    // rows 48 heads 31.1 / 31.0, 64 33.9 / 35.6; 4000 keys (125) 72 44.8 / 43.4, 80 47.9 / 49.1.  Heads of 64, 18 blocks: 80 34.7 / 33.7, 96
-    // 34.9 / 36.5; 72 blocks 112 44.3 / 43.0.
+    // And not of many heads on few tiles: a block takes in all heads one after the other on one CU, the persistent form
+    // spreads them.  Heads of 64 count for 1 / 1.4.
+    // us per call, persistent / single tiles, heads of 128: 1 x 576 keys, 32 text rows (18 blocks), 56 heads 37.3 / 36.8, 64 37.2 /
+    // 38.0, 96 43.7 / 49.8, 128 49.3 / 58.9; 128 rows (72) 80 heads 50.6 / 47.8, 96 53.4 / 56.4; 6 x 576, 32 rows (108) 96 85.8 /
+    // 85.2, 128 105.8 / 108.4; with normalisers 1 x 576, 32 rows 48 heads 31.1 / 31.0, 64 33.9 / 35.6; 4000 keys (125) 72 44.8 /
+    // 43.4, 80 47.9 / 49.1.  Heads of 64, 18 blocks: 80 34.7 / 33.7, 96 34.9 / 36.5; 72 blocks 112 44.3 / 43.0.
     const double heads = d == 64 ? H / 1.4 : H;
     s.own = s.nbt <= kOwnParts && Mv <= 8192 && s.own_blocks <= 2 * own_round && heads <= 54 + 0.4 * s.own_blocks;
-    // (with the caller's row normalisers, K has not been read before: one round, 23 x 181 keys, 45 text rows, 276 blocks 50 / 54)
     s.own_lse = s.own && s.own_blocks <= own_round && heads <= 46 + 0.22 * s.own_blocks;
     // Up to 64 text rows: blocks of 32 keys that take all text rows and heads (prefill_colrows_kernel).  K is read once and
     // there is one (V, I) pair per key, but a block is long, and the CUs that the last round of blocks leaves idle
     // are what the form can lose by.  (With a mask four fifths of the slots are taken to be valid: stage 1 leaves three quarters.)
     // idle: that part of a round, times its length in heads.
     //
-    // One text block: always; with the caller's normalisers, when K has not been read before and the persistent form is
-    // no longer bound by it alone, where idle is at most 20.  Two: where single tiles of one text block would have a second
-    // round, and idle is at most 20 with normalisers, else 16 in two rounds, 12 in three, 10 in four (the persistent
-    // form's part that does not shrink with K, its pieces, counts for less in more rounds).  Heads of 64 share a CU between two
-    // blocks, which evens the rounds out: they need only be beyond the two rounds of single tiles.
+    // One text block: always; with the caller's normalisers (no first sweep, whose merge of chunks this form takes over)
+    // where idle is at most 20.  Two: beyond one round of single tiles of one text block, where idle is at most 20 with
+    // normalisers, else 16 in two rounds, 12 in three, 10 in four.  The bounds are a fit to what follows.  Heads of 64 share a CU
+    // between two blocks, which evens the rounds out: they need only be beyond the two rounds of single tiles.
     //
     // us per call, persistent or single tiles / this form, 32 heads of 128 unless said otherwise:
     // one text block, 8 x 1085 keys (1.06 rounds) 60.1 / 60.4, 8 x 2918 (2.85) 126.7 / 120.8, 24 x 1600 at 4/5 192.6 / 181.3; with
@@ -142,24 +152,24 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
         s.rows_lse = heads <= 46 + 0.22 * tiles && (whole <= 1 || d == 64 || idle <= 20.0);
     }
     s.own |= s.rows;
-    // K that has not been read before, of a size that will not be in the Infinity Cache either (up to there plain loads: heads of 64, 16 x
-    // 1024 keys, 67 MB, 20 rows 41.8 streamed / 40.6; 16 x 576 of 128, 75 MB, 45.6 / 46.9, 4 x 2880, 94 MB, 57.3 / 62.4).  Behind a
-    // first sweep plain loads (24 x 1200, 236 MB, 60 rows 200.7 / 195.0, 16 x 1024 109.1 / 108.3)
+    // There, K by streaming loads where it has not been read before and is more than 70 MB.
+    // us per call, streaming / plain: with normalisers heads of 64, 16 x 1024 keys, 67 MB, 20 rows 41.8 / 40.6; 16 x 576 of 128, 75 MB,
+    // 45.6 / 46.9, 4 x 2880, 94 MB, 57.3 / 62.4.  Behind a first sweep 24 x 1200, 236 MB, 60 rows 200.7 / 195.0, 16 x 1024 109.1 / 108.3.
     s.rows_stream = k_mb > 70.0;
-    // sweep 1: blocks of four waves (two per CU) or of eight (one per CU; the chunks two small blocks would take meet in
-    // LDS), and the number of key chunks per (sample, head, text group), at least four 128-key units each.  Whole rounds
-    // of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's start
-    // (5), the keys it takes (ns per key, from alone on the chip to every place taken), the merge kernel for several chunks.
-    // Measured to within 20 % at 17 shapes; before -> after e.g. 13 x 1039 keys, 32 heads, 10 text rows: 36.6 -> 23.1,
-    // 6 x 1152 keys, 384 text rows: 250 -> 49 (in the wide form), 5 x 774 keys, 16 heads, 60 text rows: 14.5 -> 13.1.
+    // Sweep 1: blocks of four waves (two per CU) or of eight (one per CU; the chunks two small blocks would take meet in
+    // LDS), and the number of key chunks per (sample, head, text group), of at least four units of 128 keys.  Whole
+    // rounds of blocks are what a shape can lose most by, so both are picked by an estimate of the time in us: a block's
+    // start (5), the keys it takes (ns per key, from alone on the chip to every place taken), the merge of several chunks.
+    // Measured to within 20 % at 17 shapes; before -> after e.g. 13 x 1039 keys, 32 heads, 10 text rows 36.6 -> 23.1, 6 x 1152,
+    // 384 rows 250 -> 49 (in the wide form), 5 x 774, 16 heads, 60 rows 14.5 -> 13.1.
     const int units = (Mv + N + 127) / 128;
     const long n = (long)B * H * s.ng;
     // The wide form takes all calls with several text groups.  With one, K comes from HBM and bounds the sweep: there it only
     // takes the place of the blocks of four waves at d = 128 (13 x 1039 keys, 32 heads, 128 text rows 43 -> 40, 20 x 576, 40
-    // heads, 70 rows 53 -> 49), where it is one chunk as well of those of eight; heads of 64 have three smaller blocks per CU (8 x 2000,
-    // 128 rows 25 and 28).
-    // (three slots, rs_deep: with K of 160 MB at most; beyond it is alike, us per call with two / three: 8 x 2880 keys, 20 text rows, 189
-    // MB 102.1 / 102.3, 4 x 8000, 30 rows, 262 MB 134.6 / 134.9, and the workspace hangs on the estimate)
+    // heads, 70 rows 53 -> 49), where it is one chunk as well of those of eight; heads of 64 have three smaller blocks
+    // per CU (8 x 2000, 128 rows 25 and 28).
+    // Three slots (rs_deep) for K of up to 160 MB; beyond, two are as good (us per call, two / three: 8 x 2880 keys, 20 text rows, 189 MB
+    // 102.1 / 102.3, 4 x 8000, 30 rows, 262 MB 134.6 / 134.9), and the workspace hangs on the estimate.
     const bool deep_k = k_mb <= 160.0;
     auto pick = [&](double merge_us, int most, int least_units) {
         double best = 0;
@@ -191,20 +201,22 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
             }
     };
     pick(5.0, kMaxChunks, 4);
-    // Where the estimate is off: one wide block of four waves per (sample, head), one or two on a CU, is at least as fast as what it picks
-    // for 65 to 128 text rows when the heads of all samples nearly fill the CUs, the keys are many and K is small or it picks several
-    // chunks, which cost the merge too, and when the heads are more than two rounds of the CUs.  us per call, picked / wide: 6 x 2600 keys, 100 rows (192 heads
-    // in all) 107.2 / 103.5, 6 x 4000, 128 rows 147.3 / 139.3, 7 x 2880 (224) 132.5 / 126.9, 6 x 2880, 40 heads (240) 131.3 / 126.3, 17 x 500,
-    // 128 rows (544) 111.4 / 101.7, 24 x 1700 (768) 255 / 247; not 5 x 2600 (160) 93.8 / 95.2, 8 x 576, 128 rows 62.0 / 63.1, 9 x 1700 (288)
-    // 119.7 / 122.1.  Eight waves in one chunk (256 heads) stay where K is large: 8 x 2880, 128 rows 124.6 / 123.3 with K half in the
-    // Infinity Cache, and the sweep alone on new inputs, all of K from HBM, 57.2 / 63.7 (1800: 46.0 / 47.5, 1152: 25.6 / 23.7).
-    if (s.nbw == 4 && s.ng == 1 && d == 128 && !s.own && (n > 2 * kNumCU || (n > 176 && n <= kNumCU && (s.nch > 1 || k_mb <= 105.0) && Mv + N >= 1000))) { s.rs_waves = 4; s.nch = 1; }
+    // Where the estimate is off: one wide block of four waves per (sample, head) for 65 to 128 text rows when
+    // - the heads of all samples are more than two rounds of the CUs, or
+    // - they nearly fill the CUs, the keys are many, and K is small or the estimate picks several chunks, which cost the merge too.
+    // us per call, picked / wide: 17 x 500 keys, 128 rows (544 heads in all) 111.4 / 101.7, 24 x 1700 (768) 255 / 247; 6 x 2600, 100
+    // rows (192) 107.2 / 103.5, 6 x 4000, 128 rows 147.3 / 139.3, 7 x 2880 (224) 132.5 / 126.9, 6 x 2880, 40 heads (240) 131.3 / 126.3;
+    // not 5 x 2600 (160) 93.8 / 95.2, 8 x 576, 128 rows 62.0 / 63.1, 9 x 1700 (288) 119.7 / 122.1.  Eight waves in one chunk (256 heads)
+    // stay where K is large: 8 x 2880, 128 rows 124.6 / 123.3 with K half in the Infinity Cache, but the sweep alone on new
+    // inputs, all of K from HBM, 57.2 / 63.7 (1800: 46.0 / 47.5, 1152: 25.6 / 23.7).
+    const bool fills = n > 176 && n <= kNumCU && Mv + N >= 1000 && (s.nch > 1 || k_mb <= 105.0);
+    if (s.nbw == 4 && s.ng == 1 && d == 128 && !s.own && (n > 2 * kNumCU || fills)) { s.rs_waves = 4; s.nch = 1; }
     s.nch_ws = s.nch;
     s.partial_in_pieces = false;
     if (s.own) {
-        // single tiles: the merge of the chunks is part of sweep 2, and a chunk may be shorter (2 x 576 keys, 128 text rows 36 -> 32 us).  The
-        // workspace stays as it is: more chunks than the persistent form would take have their statistics in the memory of the
-        // pieces, behind V and I, as many as fit there.
+        // Single tiles: the merge of the chunks is part of sweep 2, and a chunk may be shorter (2 x 576 keys, 128 text rows 36 ->
+        // 32 us).  The workspace stays as it is: more chunks than the persistent form would take have their statistics in
+        // the memory of the pieces, behind V and I, as many as fit there.
         const long Npad = 32l * s.nbt, fit = ((long)s.col.Gmax * Mv * Npad - 2l * s.nbt * Mv) / (2l * H * Npad);
         const long most = fit > s.nch_ws ? fit : s.nch_ws;
         pick(1.0, most < kOwnChunks ? (int)most : kOwnChunks, s.nbw < 4 ? 1 : 2);
