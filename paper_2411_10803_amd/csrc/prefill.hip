@@ -1922,7 +1922,7 @@ PrefillWorkspace carve_prefill(void* base, int B, int Mv, int N, int H, int Rcap
 
 template <int KS>
 int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspace& w, hipStream_t st, const void* q_txt,
-                  const void* k, const uint8_t* vis_valid, const int32_t* txt_len, const float* row_lse, float scale_log2e) {
+                  const void* k, const uint8_t* vis_valid, const int32_t* txt_len, const float* row_lse, float scale_log2e, bool col_stream) {
     const uint16_t* qp = static_cast<const uint16_t*>(q_txt);
     const uint16_t* kp = static_cast<const uint16_t*>(k);
     float2* const partial = w.chunk_stats(p, s);
@@ -1985,8 +1985,8 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
     // 32 * (4 / NBW) * KT keys per unit = s.col.kb
     if (s.nbw == 1) MD_COLSCORE(1, 1, false, true);
     else if (s.nbw == 2) MD_COLSCORE(2, 1, false, true);
-    else if (s.ng == 1) { if (s.col_stream) MD_COLSCORE(4, 2, false, true); else MD_COLSCORE(4, 2, false, false); }
-    else { if (s.col_stream) MD_COLSCORE(4, 2, true, true); else MD_COLSCORE(4, 2, true, false); }
+    else if (s.ng == 1) { if (!col_stream) MD_COLSCORE(4, 2, false, false); else MD_COLSCORE(4, 2, false, true); }
+    else { if (!col_stream) MD_COLSCORE(4, 2, true, false); else MD_COLSCORE(4, 2, true, true); }
 #undef MD_COLSCORE
     const int fx = (p.Mv + 4 * kFixKeys - 1) / (4 * kFixKeys);          // four waves of kFixKeys keys per block
     // pieces that a tile has as a rule, by the length of the blocks' runs (one that has fewer reads in vain), and the rows of the
@@ -2085,8 +2085,9 @@ int prefill_filter_impl(
     hipStream_t st = static_cast<hipStream_t>(stream);
     const float sl2 = softmax_scale * kLog2e;
 
-    int rc = d == 128 ? launch_scores<8>(p, sp, w, st, q_txt, k, vis_valid, txt_len, row_lse, sl2)
-                      : launch_scores<4>(p, sp, w, st, q_txt, k, vis_valid, txt_len, row_lse, sl2);
+    const bool col_stream = streams_col_k(sp, B, Mv, H, d, Rcap, mode == MD_FILTER_THRESHOLD, row_lse != nullptr);
+    int rc = d == 128 ? launch_scores<8>(p, sp, w, st, q_txt, k, vis_valid, txt_len, row_lse, sl2, col_stream)
+                      : launch_scores<4>(p, sp, w, st, q_txt, k, vis_valid, txt_len, row_lse, sl2, col_stream);
     if (rc != MD_OK) return rc;
     int32_t* src_row = out_ids ? out_ids : w.src_row;     // the row map doubles as the optional out_ids
     const bool dense_io = is_dense(lkv, (long)L, H, d) && is_dense(lout, (long)Rcap + N, H, d);

@@ -57,7 +57,7 @@ struct ScorePlan {
     bool own, own_lse, partial_in_pieces;             // sweep 2 by single tiles; so with normalisers; chunk statistics behind V and I
     int nch_ws;                                       // chunks that the workspace has room for
     long own_blocks;
-    bool rows, rows_lse, rows_stream, col_stream;     // single tiles with all text rows; so with normalisers; streaming loads of K
+    bool rows, rows_lse, rows_stream;                 // single tiles with all text rows; so with normalisers; streaming loads of K there
     ColPlan col;
     int occ;
 };
@@ -225,16 +225,6 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     s.rs_stream = big_k && s.rs_waves == 4;           // (what the estimate picks for K of that size)
     s.rs_wide = s.ng > 1 || (s.nbw == 4 && d == 128 && s.rs_waves == 4);
     s.rs_deep = s.nbw == 1 && d == 128 && s.rs_waves == 4 && n * s.nch <= kNumCU && deep_k;
-    // The persistent column sweep reads K by streaming loads, which leave the cache to the query fragments, unless it is likely to
-    // find K there.  One text group: where sweep 1 has read K with plain loads, or not at all.  Several groups read K one after
-    // the other: plain, unless the fragments are many (28 MB).
-    // us per call, streaming / plain, on three states in turn and on inputs just made: one group, 65 to 128 rows, 4 x 2880 keys at 3/4 88.3 /
-    // 85.9 and 100.7 / 99.3; 6 x 2000 (98 MB) 97.3 / 96.0 and 107.9 / 104.2; 8 x 2300 at 4/5 (151) 122.7 / 120.6 and
-    // 133.1 / 128.9; 8 x 2880 at 3/4 (189) 141.3 / 138.9 and 152.8 / 146.8; behind streaming loads 10 x 2880 (236) 202.9 / 199.8 and 207.1 /
-    // 213.0, 16 x 2600 (341) 268.6 / 263.1 and 271.5 / 275.8; with normalisers 6 x 2000 77.6 / 81.1 and 80.6 / 85.0, 8 x 2880 at 3/4
-    // 113.7 / 110.8 and 119.0 / 120.5, 16 x 2600 200.6 / 199.5 and 207.9 / 212.6.  Several: 3 x 9000, 300 rows, normalisers
-    // 211 / 198, 8 x 2880, 200 rows 143 / 135, without 6 x 1152, 384 rows, 19 MB of fragments 142 / 140; 20 x 576, 200 rows, 37 MB 181 / 184.
-    s.col_stream = s.ng > 1 ? (double)B * H * d * 2e-6 * 32 * s.nbt >= 28.0 : s.nbw < 4 || s.rs_stream;
     return s;
 }
 
@@ -243,8 +233,30 @@ inline ScorePlan with_normalisers(ScorePlan s) {
     s.nch = 1;
     s.rows = s.rows_lse;
     s.own = s.own_lse || s.rows;
-    s.col_stream |= s.ng == 1;
     return s;
+}
+
+// Vision rows that a call keeps of a sample, as far as the host can know.  In threshold mode Rcap is no more than room: an eighth of the
+// slots is taken to be kept (of 576 tokens the printed rule keeps 64 on average).
+inline int rows_kept(int Mv, int Rcap, bool threshold) { return threshold && Rcap > Mv / 8 ? Mv / 8 : Rcap; }
+
+// Whether the persistent column sweep reads K by streaming loads, which leave the cache to the query fragments.
+//
+// Rule: unless K is likely to be found in the cache, or to be wanted there.  One text group of 65 to 128 rows: plain where sweep 1 has
+// read K with plain loads and more than an eighth of the rows is kept, which the copies read again.  Several groups read K one
+// after the other: plain, unless the fragments are many (28 MB).
+//
+// us per call, plain / streaming, on three states in turn and on inputs just made, 128 rows, all valid unless said otherwise: 4 x 2880
+// keys, a sixteenth kept 85.8 / 82.3 and 93.5 / 94.7, a ninth 90.1 / 87.0 and 96.9 / 98.4, a fifth 93.8 / 95.6 and 104.8 / 106.8;
+// 8 x 2880 at 3/4 117.2 / 115.6 and 124.2 / 124.3, 124.2 / 123.9 and 132.6 / 133.5, 138.1 / 140.5 and 145.8 / 149.6; 16 x 1600, 100 rows
+// 146.2 / 145.5 and 169.3 / 168.5, 156.3 / 157.3 and 178.1 / 179.0, 171.1 / 175.6 and 192.4 / 196.7.
+// Behind streaming loads, a fifth kept, 10 x 2880 (236 MB) 199.8 / 202.9 and 213.0 / 207.1, 16 x 2600 (341) 263.1 / 268.6 and 275.8 /
+// 271.5; with normalisers 6 x 2000 81.1 / 77.6 and 85.0 / 80.6, 8 x 2880 at 3/4 110.8 / 113.7 and 120.5 / 119.0, 16 x 2600 199.5 /
+// 200.6 and 212.6 / 207.9.  Several groups: 3 x 9000, 300 rows, normalisers 198 / 211, 8 x 2880, 200 rows 135 / 143, without 6 x 1152, 384
+// rows, 19 MB of fragments 140 / 142; 20 x 576, 200 rows, 37 MB 184 / 181.
+inline bool streams_col_k(const ScorePlan& s, int B, int Mv, int H, int d, int Rcap, bool threshold, bool row_lse) {
+    if (s.ng > 1) return (double)B * H * d * 2e-6 * 32 * s.nbt >= 28.0;
+    return s.nbw < 4 || row_lse || s.rs_stream || 8L * rows_kept(Mv, Rcap, threshold) <= Mv;
 }
 
 // Whether the kept K rows leave by streaming stores, as the kept rows of V and hidden always do.
@@ -252,8 +264,6 @@ inline ScorePlan with_normalisers(ScorePlan s) {
 // Rule: where there are more than 16 MB of them and the call's K, V and hidden, in and out, come to more than 200 MB,
 // so that the Infinity Cache (256 MB) would have to write them back before anything that is sure to come reads them;
 // with the caller's row normalisers only from 36 MB on, as one sweep of K less runs into the lines to be written back.
-// In threshold mode Rcap is no more than room: an eighth of the slots is taken to be kept (of 576 tokens the printed
-// rule keeps 64 on average).
 //
 // us per call on three states in turn, plain / streaming stores: 16 x 576 keys, 64 text rows, 192 kept (34 MB) 95.7 /
 // 88.8; 12 x 576 (25 MB, 264 MB in all) 66.4 / 61.5; 8 x 576 (17 MB, 176 MB) 49.7 / 49.4; 8 x 2880 at 3/4, 128 rows
@@ -267,7 +277,7 @@ inline ScorePlan with_normalisers(ScorePlan s) {
 // streamed (as here), 190.2 with all calls' streamed (24 x 576 -> 192 -> 64: 177.9, 176, 175.4).  Nothing in a call tells the
 // one use from the other.
 inline bool streams_k_out(int B, int Mv, int N, int H, int d, int C, int Rcap, bool threshold, bool row_lse) {
-    const int kept = threshold && Rcap > Mv / 8 ? Mv / 8 : Rcap;
+    const int kept = rows_kept(Mv, Rcap, threshold);
     const double out_mb = (double)B * (kept + N) * H * d * 2e-6;
     const double all_mb = (double)B * (Mv + kept + 2.0 * N) * (2.0 * H * d + C) * 2e-6;
     return out_mb > (row_lse ? 36.0 : 16.0) && all_mb > 200.0;

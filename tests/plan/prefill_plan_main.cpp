@@ -117,15 +117,18 @@ int main(int argc, char** argv) {
     for (const auto& r : reads)
         if (plan_scores(r.B, r.Mv, r.N, r.H, r.d).rs_stream != r.want && ++bad)
             printf("B=%d Mv=%d N=%d H=%d d=%d: K of the row statistics\n", r.B, r.Mv, r.N, r.H, r.d);
-    // and for the column sweep: what sweep 1 leaves in the cache, K that several text groups share with few fragments
-    struct { int B, Mv, N, H, d; bool want, want_lse; } const again[] = {
-        {16, 576, 128, 32, 128, false, true}, {4, 2880, 120, 32, 128, false, true}, {8, 2880, 128, 32, 128, false, true}, {10, 2880, 100, 32, 128, true, true},
-        {24, 2880, 100, 32, 128, true, true}, {8, 2000, 100, 40, 64, false, true}, {1, 9000, 40, 32, 128, true, true}, {1, 9000, 20, 32, 128, true, true},
-        {3, 4608, 300, 32, 128, false, false}, {6, 1152, 384, 32, 128, false, false}, {20, 576, 200, 32, 128, true, true}};
+    // and for the column sweep: where sweep 1 leaves K in the cache and the copies read much of it again, and where several
+    // text groups share it with few fragments
+    struct { int B, Mv, N, H, d, Rcap; bool threshold, want, want_lse; } const again[] = {
+        {16, 576, 128, 32, 128, 115, false, false, true}, {4, 2880, 120, 32, 128, 180, false, true, true}, {8, 2880, 128, 32, 128, 320, false, true, true},
+        {8, 2880, 128, 32, 128, 576, false, false, true}, {8, 2880, 128, 32, 128, 2880, true, true, true}, {10, 2880, 100, 32, 128, 576, false, true, true},
+        {8, 2000, 100, 40, 64, 251, false, false, true}, {1, 9000, 40, 32, 128, 3000, false, true, true}, {1, 9000, 20, 32, 128, 3000, false, true, true},
+        {3, 4608, 300, 32, 128, 4608, true, false, false}, {6, 1152, 384, 32, 128, 10, false, false, false}, {20, 576, 200, 32, 128, 192, false, true, true}};
     for (const auto& r : again) {
         const ScorePlan s = plan_scores(r.B, r.Mv, r.N, r.H, r.d);
-        if ((s.col_stream != r.want || with_normalisers(s).col_stream != r.want_lse) && ++bad)
-            printf("B=%d Mv=%d N=%d H=%d d=%d: K of the column sweep\n", r.B, r.Mv, r.N, r.H, r.d);
+        auto streams = [&](const ScorePlan& p, bool lse) { return streams_col_k(p, r.B, r.Mv, r.H, r.d, r.Rcap, r.threshold, lse); };
+        if ((streams(s, false) != r.want || streams(with_normalisers(s), true) != r.want_lse) && ++bad)
+            printf("B=%d Mv=%d N=%d H=%d d=%d Rcap=%d: K of the column sweep\n", r.B, r.Mv, r.N, r.H, r.d, r.Rcap);
     }
     // which calls write the kept K rows past the Infinity Cache: not those whose next reader finds them there
     struct { int B, Mv, N, H, d, Rcap; bool threshold, lse, want; } const moves[] = {
