@@ -1933,7 +1933,7 @@ int launch_scores(const PrefillDims& p, const ScorePlan& s, const PrefillWorkspa
         qp, kp, vis_valid, txt_len, p, scale_log2e, partial, w.cstat, w.qfrag, w.rows)
 #define MD_ROWSTATS(NBW_, TW_)                                                                                 \
         do {                                                                                                   \
-            if (NBW_ * TW_ == 4 && s.rs_stream) MD_ROWSTATS2(NBW_, TW_, (NBW_ * TW_ == 4), false);             \
+            if (KS == 8 && NBW_ * TW_ == 4 && s.rs_stream) MD_ROWSTATS2(NBW_, TW_, (KS == 8 && NBW_ * TW_ == 4), false); \
             else if (KS == 8 && NBW_ == 1 && TW_ == 4 && s.rs_deep) MD_ROWSTATS2(NBW_, TW_, false, (KS == 8 && NBW_ == 1 && TW_ == 4)); \
             else MD_ROWSTATS2(NBW_, TW_, false, false);                                                        \
         } while (0)

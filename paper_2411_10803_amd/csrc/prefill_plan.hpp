@@ -69,8 +69,8 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     s.nbw = s.nbt == 1 ? 1 : (s.nbt == 2 ? 2 : 4);    // text blocks per block, one per wave column
     s.ng = (s.nbt + s.nbw - 1) / s.nbw;               // text groups: each goes over K, side by side
     const double k_mb = (double)B * Mv * H * d * 2 / 1e6;
-    // Sweep 1 reads K with streaming loads where K outgrows the Infinity Cache and there is one text group, up to 64
-    // text rows from 300 MB on, else from 230.  Plain loads leave part of K to the second sweep, but on inputs that
+    // Sweep 1 reads K of heads of 128 with streaming loads where it outgrows the Infinity Cache and there is one text
+    // group, up to 64 text rows from 300 MB on, else from 230.  Plain loads leave part of K to the second sweep, but on inputs that
     // were just written they push the others' dirty lines out under the sweep.
     // us per call, plain / streaming, on three states in turn and on inputs just made: 100 to 128 rows 8 x 2880 keys of 40 heads
     // (236 MB) 176 / 187 and 218 / 192, 10 x 3000 (246) 178 / 185 and 220 / 193, 16 x 2880 (377) 253 / 263 and 313 /
@@ -78,7 +78,9 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     // 168 and 203 / 206, 12 x 2880 (283) 172 / 179 and 225 / 210, 14 x 2880 (330) 191 / 194 and 246 / 228, 16 x 2880 (377) 195 /
     // 193 and 250 / 237, 20 x 2800 (459) 270 / 269 and 327 / 307.  Several text groups go over K one after the other and
     // find it in the cache: 6 x 6000 (295), 384 rows 477 / 480 and 483 / 514, 10 x 3600 (295), 200 rows 325 / 345 and 357 / 382.
-    const bool big_k = s.ng == 1 && k_mb > (s.nbw <= 2 ? 300.0 : 230.0);
+    // (Not of heads of 64: K of that size is rare there, and more code in the object costs the other calls: 8 x 2880 keys at 3/4,
+    // 128 rows, 123.6 us, 125.0 with three more forms of the kernel, its own code being the same.)
+    const bool big_k = s.ng == 1 && d == 128 && k_mb > (s.nbw <= 2 ? 300.0 : 230.0);
     // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
     ColPlan& c = s.col;
     c.kb = s.nbw == 1 ? 128 : 64;

@@ -1,7 +1,7 @@
 """Calls of a size from which on memory is passed by the Infinity Cache.
 
-The row statistics of a K that outgrows the Infinity Cache, read by streaming loads: every form that has them (one, two and four text
-blocks, the wide one, heads of 64), with tiles that are not full, masks and prompts that leave text blocks empty.  The
+The row statistics of a K that outgrows the Infinity Cache, read by streaming loads: every form that has them (one and two text
+blocks, the wide one) and heads of 64, which do not, with tiles that are not full, masks and prompts that leave text blocks empty.  The
 column sweep of several text groups where their query fragments are 28 MB and more.  The copies of head-major rows where K is more than
 100 MB, with the K rows out by streaming stores and, with the caller's normalisers, by plain ones."""
 import pytest
