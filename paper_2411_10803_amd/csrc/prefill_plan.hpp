@@ -263,15 +263,19 @@ inline bool streams_col_k(const ScorePlan& s, int B, int Mv, int H, int d, int R
 
 // Whether the kept K rows leave by streaming stores, as the kept rows of V and hidden always do.
 //
-// Rule: where there are more than 16 MB of them and the call's K, V and hidden, in and out, come to more than 200 MB,
-// so that the Infinity Cache (256 MB) would have to write them back before anything that is sure to come reads them;
-// with the caller's row normalisers only from 36 MB on, as one sweep of K less runs into the lines to be written back.
+// Rule: where the call's K, V and hidden, in and out, come to more than 200 MB, so that the Infinity Cache (256 MB) would have to
+// write them back before anything that is sure to come reads them; with the caller's row normalisers only from 36 MB of K
+// rows out on, as one sweep of K less runs into the lines to be written back.
 //
-// us per call on three states in turn, plain / streaming stores: 16 x 576 keys, 64 text rows, 192 kept (34 MB) 95.7 /
-// 88.8; 12 x 576 (25 MB, 264 MB in all) 66.4 / 61.5; 8 x 576 (17 MB, 176 MB) 49.7 / 49.4; 8 x 2880 at 3/4, 128 rows
-// (29 MB) 127.8 / 124.2; 4 x 2880, 120 rows (14 MB) 88.9 / 89.7; by threshold, kept of 576 about 64: 16 samples 73.6 /
-// 70.8, 12 51.9 / 50.9, 4 29.6 / 30.1.  With normalisers 16 x 576, 128 kept (25 MB) 56.3 / 56.7, 192 kept (34 MB) 77.3 /
-// 77.1, 16 x 1152, 100 rows (38 MB) 108.4 / 103.5, 24 x 576 (50 MB) 104.9 / 98.8.
+// us per call, plain / streaming stores, on three states in turn and on inputs just made: 16 x 576 keys, 64 text rows, 192 kept (34 MB
+// out, 352 in all) 95.7 / 88.8; 24 x 516, 12 rows, 64 kept (15, 356) 75.6 / 70.9 and 80.5 / 80.9; 4 x 2880, 12 rows, 360 kept (12,
+// 321) 66.4 / 63.3 and 74.2 / 73.9, 128 rows, 320 kept (15, 340) 88.3 / 88.1 and 98.7 / 99.5; 16 x 1000, 20 rows, 64 kept (11, 434) 79.7 /
+// 74.4 and 86.1 / 86.7; 8 x 2880, 8 rows, 32 kept (3, 576) 90.6 / 87.8 and 104.7 / 105.1; 12 x 576, 64 rows, 72 kept (13, 229) 52.9 /
+// 52.7 and 59.3 / 59.0; 8 x 576 (17, 176) 49.7 / 49.4; heads of 64, 24 x 1000 (12, 281) 63.6 / 60.4 and 70.4 / 70.8.
+// By threshold 24 x 516, 12 rows 81.2 / 74.7 and 86.1 / 84.8, 14 x 576, 64 rows 63.3 / 59.1 and 68.9 / 68.5, 12 x 516 (178) 42.5 /
+// 42.8 and 46.0 / 46.2, 4 x 2880, 128 rows 97.2 / 92.7 and 102.0 / 104.6, 4 x 576 29.6 / 30.1.
+// With normalisers 16 x 576, 128 kept (25 MB) 56.3 / 56.7, 192 kept (34) 77.3 / 77.1, 16 x 1152, 100 rows (38) 108.4 / 103.5,
+// 24 x 576 (50) 104.9 / 98.8; by threshold 24 x 576, 20 rows 62.4 / 67.3 and 64.3 / 69.9, 14 x 576, 64 rows 54.0 / 49.3 and 56.8 / 58.0.
 // With 600 MB of other data read before each call, that time included, 16 x 576 255.0 / 252.8 and 8 x 2880 287.0 / 281.7.
 // Call after call on the same buffers the rows never leave the cache, and streaming them costs: 16 x 576 above 86.6 /
 // 88.8, with normalisers 8 x 2880, 128 rows (29 MB) 103.1 / 106.3 and 24 x 576 95.2 / 102.3.  So it does where the next
@@ -282,7 +286,7 @@ inline bool streams_k_out(int B, int Mv, int N, int H, int d, int C, int Rcap, b
     const int kept = rows_kept(Mv, Rcap, threshold);
     const double out_mb = (double)B * (kept + N) * H * d * 2e-6;
     const double all_mb = (double)B * (Mv + kept + 2.0 * N) * (2.0 * H * d + C) * 2e-6;
-    return out_mb > (row_lse ? 36.0 : 16.0) && all_mb > 200.0;
+    return all_mb > 200.0 && (!row_lse || out_mb > 36.0);
 }
 
 }  // namespace

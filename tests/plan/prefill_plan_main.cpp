@@ -136,7 +136,8 @@ int main(int argc, char** argv) {
         {16, 128, 64, 32, 128, 64, false, false, false}, {4, 4608, 64, 32, 128, 512, false, false, true},
         {8, 2880, 128, 32, 128, 320, false, false, true}, {8, 2880, 128, 32, 128, 320, false, true, false},      // 29 MB
         {24, 1600, 30, 32, 128, 400, false, true, true}, {8, 576, 64, 32, 128, 192, false, false, false},
-        {4, 576, 64, 32, 128, 576, true, false, false}, {12, 576, 64, 32, 128, 576, true, false, false},         // room for all, few kept
+        {4, 576, 64, 32, 128, 576, true, false, false}, {12, 516, 12, 32, 128, 516, true, false, false}, {24, 576, 20, 32, 128, 576, true, true, false},
+        {24, 516, 12, 32, 128, 516, true, false, true}, {4, 2880, 12, 32, 128, 360, false, false, true},         // few rows of large calls
         {16, 576, 64, 32, 128, 576, true, false, true}, {8, 2880, 64, 32, 128, 2880, true, false, true},
         {1, 1, 1, 1, 64, 1, true, true, false}, {1, 64, 1, 1, 64, 0, false, false, false}};
     for (const auto& m : moves)
