@@ -2093,7 +2093,8 @@ int prefill_filter_impl(
     const bool dense_io = is_dense(lkv, (long)L, H, d) && is_dense(lout, (long)Rcap + N, H, d);
     TextRows tr{static_cast<const u32x4*>(hidden), static_cast<const u32x4*>(k), static_cast<const u32x4*>(v),
                 static_cast<u32x4*>(hidden_out), static_cast<u32x4*>(k_out), static_cast<u32x4*>(v_out), 0, 0};
-    const bool stream_k = streams_k_out(B, Mv, N, H, d, C, Rcap, mode == MD_FILTER_THRESHOLD, row_lse != nullptr);
+    const bool k_streams = row_lse && (sp.rows ? sp.rows_stream : !sp.own && col_stream);
+    const bool stream_k = streams_k_out(B, Mv, N, H, d, C, Rcap, mode == MD_FILTER_THRESHOLD, k_streams);
     tr.stream_k = stream_k ? 1 : 0;
     tr.enabled = (mode == MD_FILTER_BUDGET && dense_io && Mv <= 8192) ? 1 : 0;
     const int sel_blocks = B + (tr.enabled ? B * ((N + kTextRowsPerBlock - 1) / kTextRowsPerBlock) : 0);

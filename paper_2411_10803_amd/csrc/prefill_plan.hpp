@@ -238,34 +238,35 @@ inline ScorePlan with_normalisers(ScorePlan s) {
     return s;
 }
 
-// Vision rows that a call keeps of a sample, as far as the host can know.  In threshold mode Rcap is no more than room: an eighth of the
-// slots is taken to be kept (of 576 tokens the printed rule keeps 64 on average).
-inline int rows_kept(int Mv, int Rcap, bool threshold) { return threshold && Rcap > Mv / 8 ? Mv / 8 : Rcap; }
-
 // Whether the persistent column sweep reads K by streaming loads, which leave the cache to the query fragments.
 //
 // Rule: unless K is likely to be found in the cache, or to be wanted there.  One text group of 65 to 128 rows: plain where sweep 1 has
-// read K with plain loads and more than an eighth of the rows is kept, which the copies read again.  Several groups read K one
-// after the other: plain, unless the fragments are many (28 MB).
+// read K with plain loads, except for K of more than 85 MB of which no more than an eighth is kept (the copies read the kept rows
+// again; how many a threshold keeps is not known).  Several groups read K one after the other: plain, unless the fragments are
+// many (28 MB).
 //
 // us per call, plain / streaming, on three states in turn and on inputs just made, 128 rows, all valid unless said otherwise: 4 x 2880
 // keys, a sixteenth kept 85.8 / 82.3 and 93.5 / 94.7, a ninth 90.1 / 87.0 and 96.9 / 98.4, a fifth 93.8 / 95.6 and 104.8 / 106.8;
 // 8 x 2880 at 3/4 117.2 / 115.6 and 124.2 / 124.3, 124.2 / 123.9 and 132.6 / 133.5, 138.1 / 140.5 and 145.8 / 149.6; 16 x 1600, 100 rows
-// 146.2 / 145.5 and 169.3 / 168.5, 156.3 / 157.3 and 178.1 / 179.0, 171.1 / 175.6 and 192.4 / 196.7.
+// 146.2 / 145.5 and 169.3 / 168.5, 156.3 / 157.3 and 178.1 / 179.0, 171.1 / 175.6 and 192.4 / 196.7.  Smaller K, a tenth kept: 5 x 2000
+// (82 MB) 86.6 / 85.6 and 93.4 / 93.5, 16 x 700, 80 rows, 16 heads (46) 60.3 / 61.4 and 63.8 / 64.2, 2 x 3000, 70 rows (49) 58.3 / 59.9
+// and 62.8 / 63.0, 4 x 2880, 100 rows, 40 heads of 64 (59) 73.3 / 75.1 and 77.3 / 78.2.
 // Behind streaming loads, a fifth kept, 10 x 2880 (236 MB) 199.8 / 202.9 and 213.0 / 207.1, 16 x 2600 (341) 263.1 / 268.6 and 275.8 /
 // 271.5; with normalisers 6 x 2000 81.1 / 77.6 and 85.0 / 80.6, 8 x 2880 at 3/4 110.8 / 113.7 and 120.5 / 119.0, 16 x 2600 199.5 /
 // 200.6 and 212.6 / 207.9.  Several groups: 3 x 9000, 300 rows, normalisers 198 / 211, 8 x 2880, 200 rows 135 / 143, without 6 x 1152, 384
 // rows, 19 MB of fragments 140 / 142; 20 x 576, 200 rows, 37 MB 184 / 181.
 inline bool streams_col_k(const ScorePlan& s, int B, int Mv, int H, int d, int Rcap, bool threshold, bool row_lse) {
     if (s.ng > 1) return (double)B * H * d * 2e-6 * 32 * s.nbt >= 28.0;
-    return s.nbw < 4 || row_lse || s.rs_stream || 8L * rows_kept(Mv, Rcap, threshold) <= Mv;
+    return s.nbw < 4 || row_lse || s.rs_stream || (!threshold && 8L * Rcap <= Mv && (double)B * Mv * H * d * 2e-6 > 85.0);
 }
 
 // Whether the kept K rows leave by streaming stores, as the kept rows of V and hidden always do.
 //
 // Rule: where the call's K, V and hidden, in and out, come to more than 200 MB, so that the Infinity Cache (256 MB) would have to
-// write them back before anything that is sure to come reads them; with the caller's row normalisers only from 36 MB of K
-// rows out on, as one sweep of K less runs into the lines to be written back.
+// write them back before anything that is sure to come reads them; where the call reads K by streaming loads alone (with the caller's
+// row normalisers), only from 34 MB of K rows out on: such loads leave the lines in the cache.
+// In threshold mode Rcap is no more than room: a quarter of the slots is taken to be kept (the printed rule keeps 64 of 576 tokens
+// on average; long inputs that keep a third have 4 x 6907 keys, 110 rows, normalisers 166.8 / 157.1).
 //
 // us per call, plain / streaming stores, on three states in turn and on inputs just made: 16 x 576 keys, 64 text rows, 192 kept (34 MB
 // out, 352 in all) 95.7 / 88.8; 24 x 516, 12 rows, 64 kept (15, 356) 75.6 / 70.9 and 80.5 / 80.9; 4 x 2880, 12 rows, 360 kept (12,
@@ -274,19 +275,20 @@ inline bool streams_col_k(const ScorePlan& s, int B, int Mv, int H, int d, int R
 // 52.7 and 59.3 / 59.0; 8 x 576 (17, 176) 49.7 / 49.4; heads of 64, 24 x 1000 (12, 281) 63.6 / 60.4 and 70.4 / 70.8.
 // By threshold 24 x 516, 12 rows 81.2 / 74.7 and 86.1 / 84.8, 14 x 576, 64 rows 63.3 / 59.1 and 68.9 / 68.5, 12 x 516 (178) 42.5 /
 // 42.8 and 46.0 / 46.2, 4 x 2880, 128 rows 97.2 / 92.7 and 102.0 / 104.6, 4 x 576 29.6 / 30.1.
-// With normalisers 16 x 576, 128 kept (25 MB) 56.3 / 56.7, 192 kept (34) 77.3 / 77.1, 16 x 1152, 100 rows (38) 108.4 / 103.5,
-// 24 x 576 (50) 104.9 / 98.8; by threshold 24 x 576, 20 rows 62.4 / 67.3 and 64.3 / 69.9, 14 x 576, 64 rows 54.0 / 49.3 and 56.8 / 58.0.
+// With normalisers and streaming loads of K 16 x 576, 128 kept (25 MB) 56.3 / 56.7, 192 kept (34) 77.3 / 77.1, 16 x 1152, 100 rows (38)
+// 108.4 / 103.5, 24 x 576 (50) 104.9 / 98.8; by threshold 24 x 576, 20 rows (32) 62.4 / 67.3 and 64.3 / 69.9; with plain ones, by
+// threshold, 14 x 576, 64 rows 54.0 / 49.3 and 56.8 / 58.0, 4 x 2044, 216 rows 81.2 / 74.9, 8 x 1576, 340 rows, 16 heads 96.0 / 90.0.
 // With 600 MB of other data read before each call, that time included, 16 x 576 255.0 / 252.8 and 8 x 2880 287.0 / 281.7.
 // Call after call on the same buffers the rows never leave the cache, and streaming them costs: 16 x 576 above 86.6 /
 // 88.8, with normalisers 8 x 2880, 128 rows (29 MB) 103.1 / 106.3 and 24 x 576 95.2 / 102.3.  So it does where the next
 // layer's filter reads them at once: 16 x 576 -> 192 -> 128 -> 64 takes 183.5 us all plain, 188.5 with the first call's
 // streamed (as here), 190.2 with all calls' streamed (24 x 576 -> 192 -> 64: 177.9, 176, 175.4).  Nothing in a call tells the
 // one use from the other.
-inline bool streams_k_out(int B, int Mv, int N, int H, int d, int C, int Rcap, bool threshold, bool row_lse) {
-    const int kept = rows_kept(Mv, Rcap, threshold);
+inline bool streams_k_out(int B, int Mv, int N, int H, int d, int C, int Rcap, bool threshold, bool k_streams) {
+    const int kept = threshold && Rcap > Mv / 4 ? Mv / 4 : Rcap;
     const double out_mb = (double)B * (kept + N) * H * d * 2e-6;
     const double all_mb = (double)B * (Mv + kept + 2.0 * N) * (2.0 * H * d + C) * 2e-6;
-    return all_mb > 200.0 && (!row_lse || out_mb > 36.0);
+    return all_mb > 200.0 && (!k_streams || out_mb > 34.0);
 }
 
 }  // namespace

@@ -121,8 +121,8 @@ int main(int argc, char** argv) {
     // text groups share it with few fragments
     struct { int B, Mv, N, H, d, Rcap; bool threshold, want, want_lse; } const again[] = {
         {16, 576, 128, 32, 128, 115, false, false, true}, {4, 2880, 120, 32, 128, 180, false, true, true}, {8, 2880, 128, 32, 128, 320, false, true, true},
-        {8, 2880, 128, 32, 128, 576, false, false, true}, {8, 2880, 128, 32, 128, 2880, true, true, true}, {10, 2880, 100, 32, 128, 576, false, true, true},
-        {8, 2000, 100, 40, 64, 251, false, false, true}, {1, 9000, 40, 32, 128, 3000, false, true, true}, {1, 9000, 20, 32, 128, 3000, false, true, true},
+        {8, 2880, 128, 32, 128, 576, false, false, true}, {8, 2880, 128, 32, 128, 2880, true, false, true}, {10, 2880, 100, 32, 128, 576, false, true, true},
+        {8, 2000, 100, 40, 64, 200, false, false, true}, {8, 3000, 100, 40, 64, 300, false, true, true}, {1, 9000, 40, 32, 128, 3000, false, true, true}, {1, 9000, 20, 32, 128, 3000, false, true, true},
         {3, 4608, 300, 32, 128, 4608, true, false, false}, {6, 1152, 384, 32, 128, 10, false, false, false}, {20, 576, 200, 32, 128, 192, false, true, true}};
     for (const auto& r : again) {
         const ScorePlan s = plan_scores(r.B, r.Mv, r.N, r.H, r.d);
@@ -131,18 +131,19 @@ int main(int argc, char** argv) {
             printf("B=%d Mv=%d N=%d H=%d d=%d Rcap=%d: K of the column sweep\n", r.B, r.Mv, r.N, r.H, r.d, r.Rcap);
     }
     // which calls write the kept K rows past the Infinity Cache: not those whose next reader finds them there
-    struct { int B, Mv, N, H, d, Rcap; bool threshold, lse, want; } const moves[] = {
+    struct { int B, Mv, N, H, d, Rcap; bool threshold, k_streams, want; } const moves[] = {
         {16, 576, 64, 32, 128, 192, false, false, true}, {16, 192, 64, 32, 128, 128, false, false, false},       // successive layers
         {16, 128, 64, 32, 128, 64, false, false, false}, {4, 4608, 64, 32, 128, 512, false, false, true},
         {8, 2880, 128, 32, 128, 320, false, false, true}, {8, 2880, 128, 32, 128, 320, false, true, false},      // 29 MB
         {24, 1600, 30, 32, 128, 400, false, true, true}, {8, 576, 64, 32, 128, 192, false, false, false},
         {4, 576, 64, 32, 128, 576, true, false, false}, {12, 516, 12, 32, 128, 516, true, false, false}, {24, 576, 20, 32, 128, 576, true, true, false},
+        {4, 6907, 110, 32, 128, 6907, true, true, true}, {14, 576, 64, 32, 128, 128, false, false, true}, {16, 576, 64, 32, 128, 128, false, true, false},
         {24, 516, 12, 32, 128, 516, true, false, true}, {4, 2880, 12, 32, 128, 360, false, false, true},         // few rows of large calls
         {16, 576, 64, 32, 128, 576, true, false, true}, {8, 2880, 64, 32, 128, 2880, true, false, true},
         {1, 1, 1, 1, 64, 1, true, true, false}, {1, 64, 1, 1, 64, 0, false, false, false}};
     for (const auto& m : moves)
-        if (streams_k_out(m.B, m.Mv, m.N, m.H, m.d, m.H * m.d, m.Rcap, m.threshold, m.lse) != m.want && ++bad)
-            printf("B=%d Mv=%d N=%d Rcap=%d threshold=%d lse=%d: K rows out\n", m.B, m.Mv, m.N, m.Rcap, m.threshold, m.lse);
+        if (streams_k_out(m.B, m.Mv, m.N, m.H, m.d, m.H * m.d, m.Rcap, m.threshold, m.k_streams) != m.want && ++bad)
+            printf("B=%d Mv=%d N=%d Rcap=%d threshold=%d K streams=%d: K rows out\n", m.B, m.Mv, m.N, m.Rcap, m.threshold, m.k_streams);
     if (!streams_k_out(4, 3000, 20, 34, 128, 8, 1000, false, false) && ++bad) printf("K rows out of the head-major test\n");
     if (own < 10000 || behind < 1000 || rows < 10000 || by_mask < 1000) { ++bad; printf("too few single tiles looked at\n"); }
     printf("%ld plans of single tiles, %ld with statistics behind the scores, %ld with all text rows of a tile, %ld so by the mask\n", own, behind, rows, by_mask);
