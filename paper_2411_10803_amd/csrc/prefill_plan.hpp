@@ -70,17 +70,18 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     s.ng = (s.nbt + s.nbw - 1) / s.nbw;               // text groups: each goes over K, side by side
     const double k_mb = (double)B * Mv * H * d * 2 / 1e6;
     // Sweep 1 reads K of heads of 128 with streaming loads where it outgrows the Infinity Cache and there is one text
-    // group, up to 64 text rows from 300 MB on, else from 230.  Plain loads leave part of K to the second sweep, but on inputs that
-    // were just written they push the others' dirty lines out under the sweep.
+    // group: from 230 MB on with 65 to 128 text rows, from 300 with 33 to 64, from 450 with fewer.  Plain loads leave part of K
+    // to the second sweep, but on inputs that were just written they push the others' dirty lines out under the sweep.
     // us per call, plain / streaming, on three states in turn and on inputs just made: 100 to 128 rows 8 x 2880 keys of 40 heads
-    // (236 MB) 176 / 187 and 218 / 192, 10 x 3000 (246) 178 / 185 and 220 / 193, 16 x 2880 (377) 253 / 263 and 313 /
-    // 291, 24 x 2880 (566) 360 / 368 and 426 / 391; 20 to 60 rows 8 x 2880 (189) 120 / 125 and 143 / 139, 16 x 2000 (262) 155 /
-    // 168 and 203 / 206, 12 x 2880 (283) 172 / 179 and 225 / 210, 14 x 2880 (330) 191 / 194 and 246 / 228, 16 x 2880 (377) 195 /
-    // 193 and 250 / 237, 20 x 2800 (459) 270 / 269 and 327 / 307.  Several text groups go over K one after the other and
+    // (236 MB) 176 / 187 and 218 / 192, 10 x 3000 (246) 178 / 185 and 220 / 193, 12 x 2880 (283) 197 / 207 and 224 / 211,
+    // 16 x 2880 (377) 246 / 255 and 275 / 258, 24 x 2880 (566) 360 / 372 and 393 / 379; 40 to 60 rows 8 x 2880 (189) 120 / 125 and 143 /
+    // 139, 12 x 2880 (283) 172 / 179 and 225 / 210, 14 x 2880 (330) 191 / 194 and 246 / 228, 16 x 2880 (377) 218 / 228 and 249 / 233,
+    // 20 x 2800 (459) 287 / 285 and 314 / 305; 30 rows 24 x 1700 (334) 208 / 211 and 232 / 233, 24 x 2880 (566) 298 / 297 and 338 / 328,
+    // 10 rows 18 x 1883 at 3/5, 40 heads (347) 221 / 230 and 237 / 247.  Several text groups go over K one after the other and
     // find it in the cache: 6 x 6000 (295), 384 rows 477 / 480 and 483 / 514, 10 x 3600 (295), 200 rows 325 / 345 and 357 / 382.
     // (Not of heads of 64: K of that size is rare there, and more code in the object costs the other calls: 8 x 2880 keys at 3/4,
     // 128 rows, 123.6 us, 125.0 with three more forms of the kernel, its own code being the same.)
-    const bool big_k = s.ng == 1 && d == 128 && k_mb > (s.nbw <= 2 ? 300.0 : 230.0);
+    const bool big_k = s.ng == 1 && d == 128 && k_mb > (s.nbw == 1 ? 450.0 : s.nbw == 2 ? 300.0 : 230.0);
     // sweep 2: a persistent grid; units of (kb keys, one head), at least four per block
     ColPlan& c = s.col;
     c.kb = s.nbw == 1 ? 128 : 64;

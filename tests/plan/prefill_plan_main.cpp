@@ -112,7 +112,7 @@ int main(int argc, char** argv) {
     // which calls read K for the row statistics past the Infinity Cache: heads of 128, one text group and K well beyond the cache
     struct { int B, Mv, N, H, d; bool want; } const reads[] = {
         {24, 2880, 100, 32, 128, true}, {10, 3000, 100, 32, 128, true}, {8, 2880, 128, 32, 128, false}, {7, 9172, 113, 28, 64, false},
-        {20, 2800, 40, 32, 128, true}, {12, 2880, 60, 32, 128, false}, {2, 18500, 32, 32, 128, true}, {2, 18700, 64, 32, 128, true},
+        {20, 2800, 40, 32, 128, true}, {12, 2880, 60, 32, 128, false}, {2, 18500, 32, 32, 128, false}, {3, 18500, 32, 32, 128, true}, {18, 1883, 10, 40, 128, false}, {2, 18700, 64, 32, 128, true},
         {8, 9161, 30, 33, 64, false}, {8, 9200, 48, 32, 64, false}, {6, 6000, 384, 32, 128, false}, {1, 1, 1, 1, 64, false}};
     for (const auto& r : reads)
         if (plan_scores(r.B, r.Mv, r.N, r.H, r.d).rs_stream != r.want && ++bad)
