@@ -2128,8 +2128,8 @@ int prefill_filter_impl(
     } else {
         // Streaming where K, V and hidden together outgrow the Infinity Cache, so that the rows left in it are not written
         // back under the next sweep (21 x 1163 keys, 40 heads of 64, 125 MB: compact + next row statistics 56.9 -> 53.8 us);
-        // smaller calls find their rows in L2, which streaming loads pass by (12 x 634, 32 heads of 64, 31 MB: 8.2 -> 6.0).  K out with
-        // them as above, but not with row normalisers (head-major, 24 x 1200, 60 rows 184 -> 181, with them 140 -> 143)
+        // smaller calls find their rows in L2, which streaming loads pass by (12 x 634, 32 heads of 64, 31 MB: 8.2 -> 6.0).  K out as
+        // streams_k_out says, but not with row normalisers (head-major, 24 x 1200, 60 rows 184 -> 181, with them 140 -> 143)
 #define MD_COMPACT_STRIDED(ST_, SK_)                                                                           \
         MD_LAUNCH("prefill_compact", st, (prefill_compact_strided_kernel<ST_, SK_>), gc, 256, 0, p, src_row,       \
             static_cast<const u32x4*>(hidden), static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),   \
