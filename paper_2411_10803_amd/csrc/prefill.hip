@@ -1326,12 +1326,11 @@ __global__ __launch_bounds__(512) void prefill_colrows_kernel(
     const bool work = tile < (int)((long)tiles * (xcd + 1) >> 3);      // block-uniform
     // keys behind the last valid one, or without text rows (in the end: no block waits for this before its tile)
     auto others = [&]() {
-        const uint32_t n = (uint32_t)p.B * (uint32_t)p.Mv;             // (at most 2^28)
-        for (uint32_t e = blockIdx.x * 512 + threadIdx.x; e < n; e += gridDim.x * 512) {
-            const uint32_t s = e / (uint32_t)p.Mv;
-            const SampleRows r = rows[s];
-            if (r.text_blocks == 0 || (int)(e - s * p.Mv) >= 32 * key_groups(r.vision, 32)) { Vout[e] = 0.f; Iout[e] = 0.f; }
-        }
+        const long e = (long)blockIdx.x * 512 + threadIdx.x;           // (16 threads for each slot are there)
+        if (e >= (long)p.B * p.Mv) return;
+        const long s = index_div(e, p.Mv);
+        const SampleRows r = rows[s];
+        if (r.text_blocks == 0 || (int)(e - s * p.Mv) >= 32 * key_groups(r.vision, 32)) { Vout[e] = 0.f; Iout[e] = 0.f; }
     };
     if (masked) {
         if (!work) { others(); return; }

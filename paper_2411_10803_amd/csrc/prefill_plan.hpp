@@ -135,6 +135,9 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     // where idle is at most 20.  Two: beyond one round of single tiles of one text block, where idle is at most 20 with
     // normalisers, else 16 in two rounds, 12 in three, 10 in four.  The bounds are a fit to what follows.  Heads of 64 share a CU
     // between two blocks, which evens the rounds out: they need only be beyond the two rounds of single tiles.
+    // With fewer than 16 heads a block's start and end count for more than what it saves in many rounds: 6.5 rounds at most, 4.5 with
+    // fewer than four heads and two text blocks; any number with heads of 64 and one text block, up to 1024 samples (every block
+    // looks through all of them).
     //
     // us per call, persistent or single tiles / this form, 32 heads of 128 unless said otherwise:
     // one text block, 8 x 1085 keys (1.06 rounds) 60.1 / 60.4, 8 x 2918 (2.85) 126.7 / 120.8, 24 x 1600 at 4/5 192.6 / 181.3; with
@@ -144,15 +147,21 @@ inline ScorePlan plan_scores(int B, int Mv, int N, int H, int d, bool masked = f
     // 122.9; 8 heads, 3.4 rounds 76.4 / 70.6; with normalisers 1.2 rounds 61.7 / 64.7, 1.6 73.1 / 70.9, 2.06 86.1 / 90.8, 3.4 127.7 /
     // 124.5, 16 heads 2.06 57.9 / 58.1, 3.4 76.9 / 74.5; 4 x 1000 at 4/5 (128 tiles) 40.6 / 44.4;
     // heads of 64, two text blocks, 16 x 576 44.3 / 45.6, 24 x 900 89.9 / 84.4, 4 x 7000 at 4/5 97.0 / 88.8, 12 heads 60 x 576 66.1 / 60.9; with
-    // normalisers 16 x 576 45.8 / 39.8, 24 x 1600 105.6 / 101.7.
+    // normalisers 16 x 576 45.8 / 39.8, 24 x 1600 105.6 / 101.7;
+    // few heads, one text block, 4 heads of 128: 80 x 576 (5.6 rounds) 56.3 / 48.3, 40 x 1600 at 4/5 (6.3) 63.5 / 58.5, 200 x 576 at 4/5 (11)
+    // 108.5 / 114.4, 24 x 8000 (23) 152 / 159; 12 heads 40 x 1600 119 / 115, 24 x 8000 360 / 365; one head 40 x 1600 50.3 / 47.4, 64 x 8000
+    // 185 / 246; two text blocks, 4 heads 40 x 1600 69.8 / 67.6, 64 x 2000 at 4/5 107 / 118, one head 4 x 8000 (3.9) 52.9 / 51.2, 96 x
+    // 576 at 4/5 (5.4) 55.2 / 58.4; heads of 64, one text block, 4 heads 64 x 8000 at 4/5 234 / 211, 2048 x 128 439 / 437.
     const long tiles = (long)B * ((Mv + 31) / 32);
     const double rounds = (masked ? 0.8 : 1.0) * tiles / kNumCU;
     const long whole = (long)rounds + (rounds > (long)rounds ? 1 : 0);
     const double idle = (whole - rounds) * H;
+    const double most = s.nbt == 1 || H >= 4 ? 6.5 : 4.5;
+    const bool enough = H >= 16 || rounds <= most || (d == 64 && s.nbt == 1 && B <= 1024);
     s.rows = s.rows_lse = false;
     if (Mv <= 8192 && (s.nbt == 1 || (s.nbt == 2 && tiles > kNumCU / 2))) {
-        s.rows = heads <= 54 + 0.4 * tiles && (s.nbt == 1 || whole <= 1 || (d == 64 ? !s.own : idle <= 4.0 + 24.0 / whole));
-        s.rows_lse = heads <= 46 + 0.22 * tiles && (whole <= 1 || d == 64 || idle <= 20.0);
+        s.rows = enough && heads <= 54 + 0.4 * tiles && (s.nbt == 1 || whole <= 1 || (d == 64 ? !s.own : idle <= 4.0 + 24.0 / whole));
+        s.rows_lse = enough && heads <= 46 + 0.22 * tiles && (whole <= 1 || d == 64 || idle <= 20.0);
     }
     s.own |= s.rows;
     // There, K by streaming loads where it has not been read before and is more than 70 MB.

@@ -103,7 +103,9 @@ int main(int argc, char** argv) {
         {8, 2662, 20, 32, 128, false, true, true}, {8, 1843, 60, 32, 128, false, true, true}, {8, 2355, 60, 32, 128, false, false, false},
         {8, 3235, 60, 32, 128, false, false, false}, {24, 1600, 60, 32, 128, true, true, true}, {16, 2600, 60, 16, 128, true, false, true},
         {8, 2355, 60, 16, 128, false, true, true}, {16, 576, 60, 32, 64, false, false, true}, {4, 7000, 60, 32, 64, true, true, true},
-        {4, 1000, 60, 32, 128, true, false, false}, {5, 8193, 20, 12, 64, true, false, false}, {1, 576, 20, 96, 64, false, false, false}};
+        {4, 1000, 60, 32, 128, true, false, false}, {5, 8193, 20, 12, 64, true, false, false}, {1, 576, 20, 96, 64, false, false, false},
+        {40, 1600, 20, 1, 128, true, true, true}, {200, 576, 20, 4, 128, true, false, false}, {64, 8000, 20, 4, 64, true, true, true},
+        {2048, 128, 20, 4, 64, true, false, false}, {96, 576, 60, 2, 128, true, false, false}, {40, 1600, 60, 4, 128, true, true, true}};
     for (const auto& f : forms) {
         const ScorePlan s = plan_scores(f.B, f.Mv, f.N, f.H, f.d, f.masked);
         if ((s.rows != f.rows || with_normalisers(s).rows != f.rows_lse) && ++bad)
